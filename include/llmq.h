@@ -27,8 +27,9 @@
  *     anything is launched and leave all outputs untouched.  LLMQ_ERR_DEVICE reports a launch failure.
  *   - Results are bitwise deterministic: same inputs, same bytes (Section 3 "Reproducibility").  The
  *     only atomic used is an integer max (fused output absmax), whose result does not depend on order.
- *   - Dimensions may be any positive value.  Shapes whose dimensions are multiples of 256 (GEMM) or of
- *     16 rows x 8 columns (quantize) take the tuned kernels; everything else takes slower generic ones.
+ *   - Dimensions may be any positive value.  Contractions run fastest when their dimensions are multiples of 128 and
+ *     the quantizers on multiples of 128 rows x 256 columns; contractions of other shapes take the same tile kernels
+ *     with guarded edges (fastest with a contraction length, or T-major row pitch, that is a multiple of 16).
  */
 #ifndef LLMQ_H
 #define LLMQ_H
@@ -149,8 +150,9 @@ int llmq_fp8_gemm_tn(const uint8_t* A, int fmtA, const uint8_t* B, int fmtB,
  * copies the forward pass made:
  *   dX[m,k] = sum_n dYq[m,n] Wq[n,k]   : A = dYq [M,N],            B = Wq [N,K] T-major, T = N
  *   dW[n,k] = sum_m dYq[m,n] Xq[m,k]   : A = dYq [M,N] T-major,    B = Xq [M,K] T-major, T = M
- * Tuned for B in E4M3 with R, C multiples of 128, T a multiple of 128 and T-major operands below 2 GiB; other
- * cases take a slow generic kernel.  In the tuned kernel (and likewise in the generic one) every product lands in the same accumulator
+ * Tuned for B in E4M3 and T-major operands below 2 GiB (dimensions that are no multiples of 128 with guarded edges);
+ * T-major B in E5M2, ragged shapes with only A T-major, contractions (and T-major widths) below 16 and dimensions of
+ * millions take a slow generic kernel.  In the tuned kernel (and likewise in the generic one) every product lands in the same accumulator
  * position as with transposed copies, so the result is bit-identical to llmq_fp8_gemm_tn on those copies
  * whenever both calls run the same kind of kernel, which is the case for what the linear calls below launch
  * on operands below 2 GiB.  Arguments otherwise as above.
@@ -196,7 +198,7 @@ int llmq_fp8_gemm_with_scratch(const uint8_t* A, int fmtA, int a_t_major, const 
  * A [R,T], B [C,T] BF16 with the contraction index contiguous, binary32 accumulation on the matrix cores
  * (v_mfma_f32_16x16x32_bf16 in the same tile kernel), one RNE rounding.  Error per element is bounded by
  * 2^-8 |c| + T 2^-24 sum_t |A[r,t] B[cc,t]|.  Shapes with R, C multiples of 128 and T a multiple of 64
- * take the tuned kernel, others a slow generic one.
+ * are fastest, others take the same kernel with guarded edges (a slow generic one below T = 8).
  */
 int llmq_bf16_gemm_tn(const void* A_bf16, const void* B_bf16, int64_t R, int64_t C, int64_t T,
                       void* c_bf16, int accumulate, void* stream);

@@ -17,6 +17,10 @@ TILE_SOURCES = ["gemm_tiles_e4m3_e4m3.hip", "gemm_tiles_e5m2_e4m3.hip", "gemm_ti
                 "gemm_tiles_e4m3_e4m3_abt.hip", "gemm_tiles_e4m3_e4m3_bt.hip", "gemm_tiles_e4m3_e4m3_at.hip",
                 "gemm_tiles_e5m2_e4m3_abt.hip", "gemm_tiles_e5m2_e4m3_bt.hip", "gemm_tiles_e5m2_e4m3_at.hip",
                 "gemm_tiles_bf16_bf16.hip"]
+# the same for ragged shapes
+TILE_SOURCES += ["gemm_edge_%s.hip" % kind for kind in
+                 ("e4m3_e4m3", "e5m2_e4m3", "e4m3_e5m2", "e5m2_e5m2", "bf16_bf16",
+                  "e4m3_e4m3_bt", "e5m2_e4m3_bt", "e4m3_e4m3_abt", "e5m2_e4m3_abt")]
 SOURCES = TILE_SOURCES + ["gemm.hip", "gemm_tmajor.hip", "api.hip", "amax.hip", "quantize.hip", "swiglu.hip", "rmsnorm.hip", "calibrate.hip"]
 # Sources that hold tile kernels (see check_accumulator_reads).
 CHECKED_SOURCES = set(TILE_SOURCES) | {"gemm.hip"}

@@ -64,14 +64,17 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(
         acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, acc, FB, FA, 0, 0, 0, 0);
     }
     // lane holds row r0 + lane % 16, columns c0 + 4 * (lane / 16) + 0..3
-    const float inv_a = 1.0f / *d_sA, inv_b = 1.0f / *d_sB;
+    // de-scaled as the tile kernels do it, so that the same sums give the same bytes whichever kernel ran
+    const float inv_a = 1.0f / *d_sA, inv_b = 1.0f / *d_sB, inv_ab = inv_a * inv_b;
+    const bool one_mul = inv_ab >= 1.17549435e-38f && inv_ab <= 3.402823466e+38f;
+    const float m1 = one_mul ? inv_ab : inv_a, m2 = one_mul ? 1.0f : inv_b;
     unsigned mag = 0;
     const int64_t r = r0 + (lane & 15);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int64_t c = c0 + (lane >> 4) * 4 + e;
         if (r < R && c < Cn) {
-            float y = acc[e] * inv_a * inv_b;
+            float y = acc[e] * m1 * m2;
             uint16_t* dst = C + r * Cn + c;
             if (accumulate) y += __uint_as_float((unsigned)*dst << 16);
             __bf16 o = (__bf16)y;
@@ -142,6 +145,33 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
     return best;
 }
 
+// Tile and kind of a ragged problem, by the same model with the tiles rounded up.
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b) {
+    EdgeChoice best{0, 0, 0};
+    // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
+    // bytes in every row of an operand
+    if (T >= (1ll << 23) || C >= (1ll << 22) || T < 16 || (ta && R < 16) || (tb && C < 16)) return best;
+    const bool aligned_a = ta ? R % 16 == 0 : slabs_a || T % 16 == 0, aligned_b = tb ? C % 16 == 0 : slabs_b || T % 16 == 0;
+    best.edge = aligned_a && aligned_b ? kEdge : kEdgeUnaligned;
+    if (const char* force = tuning_env("LLMQ_GEMM_EDGE_TILE")) {
+        const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
+        if ((ni == 2 || ni == 4) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
+    }
+    double best_cost = 0;
+    for (int ni = 4; ni >= 2; ni -= 2)
+        for (int nj = 4; nj >= 2; nj -= 2) {
+            const int64_t tiles = ((R + 64 * ni - 1) / (64 * ni)) * ((C + 64 * nj - 1) / (64 * nj));
+            if (tiles >= (1ll << 30)) continue;
+            const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;
+            const int64_t slots = resident_slots(num_cus, ni, nj);
+            const int64_t rounds = (tiles + slots - 1) / slots;
+            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : (ni == nj ? 1.0 : 0.77);
+            const double cost = (double)rounds * per_cu * ni * nj / e;
+            if (best.ni == 0 || cost < best_cost * 0.97) { best.ni = ni; best.nj = nj; best_cost = cost; }
+        }
+    return best;
+}
+
 template <int FA, int FB>
 static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T,
                        const float* sA, const float* sB, void* c, int accumulate, unsigned* amax,
@@ -150,6 +180,7 @@ static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C,
     const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);
     const bool fits = (!slabs_a || (T + 256) * R < lim) && (!slabs_b || (T + 256) * C < lim);
     if (fits && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b)) return;
+    if (fits && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b)) return;
     if constexpr (FA == kFmtBf16) {
         const int64_t n = R * C;
         int64_t blocks = (n + 255) / 256;
@@ -232,7 +263,7 @@ int launch_gemm_phase_stamps(const uint8_t* A, const uint8_t* B, int64_t R, int6
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGemmThreads), 0, stream, A, B, reinterpret_cast<uint16_t*>(c_bf16),
                            (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c, touch_ahead(), band, next_stride, (int)T, (int)T,
-                           BK, BK, share_a, share_b, plan);
+                           BK, BK, share_a, share_b, plan, (int)R, 0);
     };
     if (ieee_maximum) launch(gemm_tile_kernel<0, 0, 4, 4, false, GemmPhaseTuning<true>>);
     else launch(gemm_tile_kernel<0, 0, 4, 4, false, GemmPhaseTuning<false>>);

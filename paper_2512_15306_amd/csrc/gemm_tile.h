@@ -25,8 +25,9 @@
 //   - workgroup ids are dealt round-robin to the 8 XCDs by the hardware, so ids are remapped to give
 //     each XCD (own L2) a contiguous range of tiles, walked in bands 4 tile-rows high;
 //   - the host picks NI x NJ per problem so that the tiles fill the 256 CUs in whole rounds.
-// Generic kernel: any shape, one wavefront per 16x16 outputs, guarded loads; slow, for tests and
-// odd sizes.
+// Ragged shapes take the same kernel with guarded edges (EDGE below).
+// Generic kernel: any shape, one wavefront per 16x16 outputs, guarded loads; slow, for contractions shorter than 16
+// bytes and the operand mixes no tile kernel is built for.
 //
 // An operand may also be given "T-major", [T, rows] with the contraction index running down the rows (the
 // untransposed quantized tensor where the backward pass contracts over what is the row index of the
@@ -264,12 +265,46 @@ struct SlabShape {
 // kernels rather than branches of one: the accumulators fill the accumulator file, and code that reaches them from
 // two sides (loaded sums or MFMA results) made the register allocator spill them around the K loop.
 constexpr int kWholeTiles = 0, kSharePieces = 1, kShareFixup = 2;
-template <int FA, int FB, int NI, int NJ, bool ACCUM, class V = GemmTuning, bool TA = false, bool TB = false, int MODE = kWholeTiles>
+// EDGE: what the shape may be.  kNoEdge: every dimension a multiple of its tile, nothing is guarded.  kEdge and
+// kEdgeUnaligned: any R, Cn and T; tiles reach over the edge of the output and the last K step over the end of the
+// contraction.  What they fetch there:
+//   kEdge           every 16-byte chunk of an operand is aligned (row pitch a multiple of 16 bytes) and goes straight to
+//                   LDS as in the unguarded kernel.  Chunks behind the operand are out of the buffer's range and arrive
+//                   as zeros; chunks behind the end of a row (last K step of a row-wise operand) get an offset that is.
+//   kEdgeUnaligned  any row pitch.  The chunks go through registers: loaded (unaligned) a whole K step before they are
+//                   written to LDS, at offsets cut to the last 16 bytes of the operand, so no load leaves it.  The last
+//                   slab is then written a second time with guarded loads (fix_last_slab) that leave zeros behind the
+//                   end of the contraction.
+// Rows of a slab behind the operand's last row hold zeros or bytes of other rows; they only reach outputs that do not
+// exist, which are neither stored nor counted in the absmax.  Measured with R, C, T = 8100, 7168, 5120 (kEdge, E4M3):
+// 3.98 ms with one wavefront per 16 x 16 outputs and no LDS -> 0.238 ms (8192 rows without guards: 0.215);  7168,
+// 5120, 8100 (kEdgeUnaligned, the weight gradient on transposed copies): 44.1 -> 0.380 ms, bound by the unaligned
+// loads, which the L1 serves at half the rate.  Both take the old values of C, if any, by a run-time
+// flag (ACCUM is set: the binary32 staging of the epilogue serves both).
+constexpr int kNoEdge = 0, kEdge = 1, kEdgeUnaligned = 2;
+typedef v4u v4u_any __attribute__((aligned(1)));            // a 16-byte vector at any address
+
+// The 16 bytes at p of which only the first `valid` exist (none if valid <= 0); zeros in the place of the others.  Reads
+// bytes in front of p instead of those that do not exist: at least 16 bytes lie in front of the end.
+__device__ inline v4u load16_upto(const uint8_t* p, int64_t valid) {
+    if (valid >= 16) return *reinterpret_cast<const v4u_any*>(p);
+    if (valid <= 0) return v4u{0, 0, 0, 0};
+    const v4u v = *reinterpret_cast<const v4u_any*>(p + valid - 16);
+    const int drop = 8 * (16 - (int)valid);                 // bits to shift out at the bottom: 8 .. 120
+    uint64_t lo = ((uint64_t)v[1] << 32) | v[0], hi = ((uint64_t)v[3] << 32) | v[2];
+    if (drop >= 64) { lo = hi >> (drop - 64); hi = 0; }
+    else { lo = (lo >> drop) | (hi << (64 - drop)); hi >>= drop; }
+    return v4u{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
+}
+
+template <int FA, int FB, int NI, int NJ, bool ACCUM, class V = GemmTuning, bool TA = false, bool TB = false, int MODE = kWholeTiles, int EDGE = kNoEdge>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ C,
     int Cn, int T, const float* __restrict__ d_sA, const float* __restrict__ d_sB,
     unsigned* __restrict__ amax_bits, int tiles_r, int tiles_c, int touch_ahead, int band_rows, int next_stride,
-    int ldA, int ldB, int ks_a, int ks_b, int share_a, int share_b, const SplitPlan plan) {
+    int ldA, int ldB, int ks_a, int ks_b, int share_a, int share_b, const SplitPlan plan, int Rn, int accumulate) {
+    static_assert(EDGE == kNoEdge || (MODE == kWholeTiles && ACCUM), "ragged shapes: whole tiles, old values by run-time flag");
+    constexpr bool UA = EDGE == kEdgeUnaligned;
     static_assert(!(TA || TB) || (FA != kFmtBf16 && FB != kFmtBf16), "the transposing reads move single bytes");
     // Bytes from one K step of an operand to the next: 128 rows of a T-major operand, else what the host says
     // (128 for rows of T contiguous bytes; rows x 128 when the operand is stored slab by slab, see OperandLayout).
@@ -293,7 +328,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     // What this workgroup computes (uniform over the workgroup): the tile at position `pos` of the walk, K steps
     // [kb, kb + nk), written as a whole tile (slot < 0) or as one piece of a shared tile.  In the fix-up launch
     // slot is the first slot of the tile's pieces and nk their number.
-    int pos, kb = 0, nk = T / BK, slot = -1;
+    int pos, kb = 0, nk = EDGE ? (T + BK - 1) / BK : T / BK, slot = -1;
     constexpr bool SPLIT = MODE != kWholeTiles, fixup = MODE == kShareFixup;
     if constexpr (!SPLIT) {
         pos = walk_position(blockIdx.x, plan.n_whole);
@@ -343,10 +378,17 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     // at a multiple of 16 rows).  T-major operand: an instruction moves 1 KB = 64 units of consecutive LDS
     // rows (64 NX bytes each); wave w moves slab rows [32 w, 32 w + 32), again 2 NX instructions, whose
     // lane pattern repeats every kPeriod instructions (kPeriodRows slab rows).
+    // Bytes of an operand from the tile's first byte on that the tile may read: to the end of the last row of the tile
+    // that exists (row-wise; the slab form, with rows x 128 bytes between K steps, ends with its last piece).
+    auto bytes_of_rows = [&](int rows_left, int tile_rows, int ld, int ks) -> unsigned {
+        const int rows = EDGE && rows_left < tile_rows ? rows_left : tile_rows;
+        if (EDGE && ks == BK) return (unsigned)((size_t)(rows - 1) * ld + T);
+        return (unsigned)((size_t)(T / BK - 1) * ks + (size_t)(rows - 1) * ld + BK);
+    };
     const __amdgpu_buffer_rsrc_t rsA = TA ? make_rsrc(A + (size_t)tr * BM, (unsigned)((size_t)T * ldA - (size_t)tr * BM))
-                                          : make_rsrc(A + (size_t)tr * BM * ldA, (unsigned)((size_t)(T / BK - 1) * ksA + (size_t)(BM - 1) * ldA + BK));
+                                          : make_rsrc(A + (size_t)tr * BM * ldA, bytes_of_rows(Rn - tr * BM, BM, ldA, ksA));
     const __amdgpu_buffer_rsrc_t rsB = TB ? make_rsrc(B + (size_t)tc * BN, (unsigned)((size_t)T * ldB - (size_t)tc * BN))
-                                          : make_rsrc(B + (size_t)tc * BN * ldB, (unsigned)((size_t)(T / BK - 1) * ksB + (size_t)(BN - 1) * ldB + BK));
+                                          : make_rsrc(B + (size_t)tc * BN * ldB, bytes_of_rows(Cn - tc * BN, BN, ldB, ksB));
     const int ld_row = lane >> 3;                                   // row inside the group of 8
     auto rows_voff = [&](int m, int ld) {                           // rows 8 m + ld_row of a row-wise operand, `ld` bytes apart
         return ld_row * ld + (((lane & 7) ^ row_swizzle(8 * m + ld_row)) << 4);
@@ -362,6 +404,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         ld_voffA[m] = TA ? (m < SA::kPeriod ? tmajor_voff(SA{}, m, ldA) : 0) : rows_voff(m & 1, ldA);
         ld_voffB[m] = TB ? (m < SB::kPeriod ? tmajor_voff(SB{}, m, ldB) : 0) : rows_voff(m & 1, ldB);
     }
+    // The offsets for the last K step of a row-wise operand whose rows end inside it (T % 16 == 0: a chunk exists or not)
+    const int tail = EDGE == kEdge ? T % BK : 0;
+    int tail_voffA[2], tail_voffB[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const bool beyond = tail != 0 && (((lane & 7) ^ row_swizzle(8 * m + ld_row)) << 4) >= tail;
+        tail_voffA[m] = beyond ? kOutOfRange : ld_voffA[m];
+        tail_voffB[m] = beyond ? kOutOfRange : ld_voffB[m];
+    }
     const int ld_soffA = TA ? wave * 32 * ldA : wave * 16 * NI * ldA, ld_soffB = TB ? wave * 32 * ldB : wave * 16 * NJ * ldB;
     // The direct-to-LDS loads of one slab pair: pieces 0 .. 2 NI - 1 fill the wave's share of the A slab, the
     // next 2 NJ that of the B slab.  step: K step of the slab, or a negative value for "no slab"
@@ -370,16 +421,27 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         baseA = step < 0 ? kOutOfRange : ld_soffA + step * ksA;
         baseB = step < 0 ? kOutOfRange : ld_soffB + step * ksB;
     };
+    int now_voffA[2], now_voffB[2];                                 // kEdge: of the step that is being fetched
+    auto voffs_of_step = [&](int step) {
+        if constexpr (EDGE == kEdge) {
+            const bool last = step == nk - 1;
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                now_voffA[m] = last ? tail_voffA[m] : ld_voffA[m];
+                now_voffB[m] = last ? tail_voffB[m] : ld_voffB[m];
+            }
+        }
+    };
     auto issue_load = [&](uint8_t* slabA, uint8_t* slabB, int baseA, int baseB, auto piece) {
         constexpr int p = decltype(piece)::value;
         if constexpr (p < 2 * NI) {
             constexpr int j = p;
-            const int voff = TA ? ld_voffA[j % SA::kPeriod] : ld_voffA[j & 1];
+            const int voff = TA ? ld_voffA[j % SA::kPeriod] : EDGE == kEdge ? now_voffA[j & 1] : ld_voffA[j & 1];
             const int soff = TA ? (j / SA::kPeriod) * SA::kPeriodRows * ldA : j * 8 * ldA;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void*)(slabA + wave * 16 * NI * BK + j * 8 * BK), 16, voff, baseA + soff, 0, 0);
         } else {
             constexpr int j = p - 2 * NI;
-            const int voff = TB ? ld_voffB[j % SB::kPeriod] : ld_voffB[j & 1];
+            const int voff = TB ? ld_voffB[j % SB::kPeriod] : EDGE == kEdge ? now_voffB[j & 1] : ld_voffB[j & 1];
             const int soff = TB ? (j / SB::kPeriod) * SB::kPeriodRows * ldB : j * 8 * ldB;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void*)(slabB + wave * 16 * NJ * BK + j * 8 * BK), 16, voff, baseB + soff, 0, 0);
         }
@@ -388,7 +450,57 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     auto issue_loads = [&](uint8_t* slabA, uint8_t* slabB, int step) {
         int baseA, baseB;
         load_base(step, baseA, baseB);
+        voffs_of_step(step);
         static_for<kLoadsPerStep>([&](auto piece) { issue_load(slabA, slabB, baseA, baseB, piece); });
+    };
+    // kEdgeUnaligned: the same pieces through registers.
+    const uint8_t* uaA = TA ? A + (size_t)tr * BM : A + (size_t)tr * BM * ldA;
+    const uint8_t* uaB = TB ? B + (size_t)tc * BN : B + (size_t)tc * BN * ldB;
+    auto last16 = [&](int64_t bytes) -> unsigned { return bytes - 16 < 0x7FFFFFF0ll ? (unsigned)(bytes - 16) : 0x7FFFFFF0u; };
+    const unsigned endA = UA ? last16((int64_t)Rn * T - (uaA - A)) : 0, endB = UA ? last16((int64_t)Cn * T - (uaB - B)) : 0;
+    v4u staged[UA ? kLoadsPerStep : 1];
+    auto fetch = [&](int step, auto piece) {                        // any step: offsets are cut to the operand's end
+        constexpr int p = decltype(piece)::value;
+        if constexpr (p < 2 * NI) {
+            const unsigned s = ld_soffA + step * ksA + (TA ? (p / SA::kPeriod) * SA::kPeriodRows * ldA : p * 8 * ldA);
+            const unsigned off = (TA ? ld_voffA[p % SA::kPeriod] : ld_voffA[p & 1]) + s;
+            staged[p] = *reinterpret_cast<const v4u_any*>(uaA + (off < endA ? off : endA));
+        } else {
+            constexpr int j = p - 2 * NI;
+            const unsigned s = ld_soffB + step * ksB + (TB ? (j / SB::kPeriod) * SB::kPeriodRows * ldB : j * 8 * ldB);
+            const unsigned off = (TB ? ld_voffB[j % SB::kPeriod] : ld_voffB[j & 1]) + s;
+            staged[p] = *reinterpret_cast<const v4u_any*>(uaB + (off < endB ? off : endB));
+        }
+    };
+    auto put = [&](uint8_t* slabA, uint8_t* slabB, const v4u& v, auto piece) {
+        constexpr int p = decltype(piece)::value;
+        uint8_t* dst = p < 2 * NI ? slabA + wave * 16 * NI * BK + p * 8 * BK : slabB + wave * 16 * NJ * BK + (p - 2 * NI) * 8 * BK;
+        *reinterpret_cast<v4u*>(dst + lane * 16) = v;
+    };
+    auto fix_piece = [&](auto shape, bool tmajor, const uint8_t* base, int64_t first, int rows, int ld, int ks, int lds_row0, int j, auto period) -> v4u {
+        typedef decltype(shape) S;
+        const int step = nk - 1;
+        if (tmajor) {
+            const int unit = 64 * (j % decltype(period)::value) + lane, row = unit / S::kUnits, col = unit % S::kUnits;
+            const int64_t k = (int64_t)step * BK + 32 * wave + (j / decltype(period)::value) * S::kPeriodRows + row;
+            const int64_t c = first + ((col ^ S::swizzle_of_row(row + 32 * wave)) << 4);
+            if (k >= T || c >= rows) return v4u{0, 0, 0, 0};
+            return load16_upto(base + k * ld + c, (int64_t)T * ld - k * ld - c);
+        }
+        const int kin = ((lane & 7) ^ row_swizzle(8 * (j & 1) + ld_row)) << 4;
+        const int64_t r = first + lds_row0 + 8 * j + ld_row;
+        if (r >= rows) return v4u{0, 0, 0, 0};
+        return load16_upto(base + r * ld + (int64_t)step * ks + kin, (int64_t)T - step * BK - kin);
+    };
+    auto fix_last_slab = [&](uint8_t* slabA, uint8_t* slabB) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int j = 0; j < 2 * NI; ++j)
+            *reinterpret_cast<v4u*>(slabA + wave * 16 * NI * BK + j * 8 * BK + lane * 16) =
+                fix_piece(SA{}, TA, A, (int64_t)tr * BM, Rn, ldA, ksA, wave * 16 * NI, j, IntTag<SA::kPeriod>{});
+#pragma unroll 1
+        for (int j = 0; j < 2 * NJ; ++j)
+            *reinterpret_cast<v4u*>(slabB + wave * 16 * NJ * BK + j * 8 * BK + lane * 16) =
+                fix_piece(SB{}, TB, B, (int64_t)tc * BN, Cn, ldB, ksB, wave * 16 * NJ, j, IntTag<SB::kPeriod>{});
     };
     // The wave tile as 16 x 16 blocks: MI x MJ of them, handled in halves of HI block rows / HJ block columns.
     constexpr int MI = 2 * NI, MJ = 2 * NJ, HI = NI, HJ = NJ;
@@ -464,7 +576,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     // each slab: a workgroup touches the lines [g * n / share, (g + 1) * n / share) of the n lines of its A slab,
     // g = tile column mod share_a, and likewise of its B slab with the tile row and share_b (the host picks the
     // shares); each wave takes a quarter of that.
-    constexpr bool kTouch = V::kTouch;
+    constexpr bool kTouch = V::kTouch && !UA;
     // (T-major operand: the slab is 128 memory rows of kLines lines each, shared out the same way.)
     constexpr int kLinesOfA = TA ? BK * SA::kLines : BM, kLinesOfB = TB ? BK * SB::kLines : BN;
     const int per_wave_a = (kLinesOfA + share_a * 4 - 1) / (share_a * 4), per_wave_b = (kLinesOfB + share_b * 4 - 1) / (share_b * 4);
@@ -493,8 +605,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     auto readsB_of_slot = [&](uint8_t* slab, auto first_block, auto& f, auto m) {
         pieces_of_slot(IntTag<kReadsB>{}, IntTag<kDsSpan>{}, m, [&](auto piece) { read_pieceB(slab, first_block, f, piece); });
     };
-    auto loads_of_slot = [&](uint8_t* slabA, uint8_t* slabB, int baseA, int baseB, auto m) {
-        pieces_of_slot(IntTag<kLoadsPerStep>{}, IntTag<kVmSpan>{}, m, [&](auto piece) { issue_load(slabA, slabB, baseA, baseB, piece); });
+    auto loads_of_slot = [&](uint8_t* slabA, uint8_t* slabB, int baseA, int baseB, int fetch_step, auto m) {
+        pieces_of_slot(IntTag<kLoadsPerStep>{}, IntTag<kVmSpan>{}, m, [&](auto piece) {
+            if constexpr (UA) {
+                put(slabA, slabB, staged[decltype(piece)::value], piece);
+                fetch(fetch_step, piece);
+            } else {
+                issue_load(slabA, slabB, baseA, baseB, piece);
+            }
+        });
     };
     auto read_fragsA = [&](uint8_t* slab, auto first_block, auto& f) {
         static_for<kReadsA>([&](auto piece) { read_pieceA(slab, first_block, f, piece); });
@@ -514,7 +633,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     //   quarter 3: MFMAs (aX, bH) | read aY of the next slab, which is the next step's aX
     // Loads that would start beyond the last slab are pointed outside the buffer range instead:
     // the hardware then fetches nothing (LDS receives zeros), and that stage is never used.
-    auto k_step = [&](uint8_t* curA, uint8_t* curB, uint8_t* nxtA, uint8_t* nxtB, int kt, int parity, auto x_is_high) {
+    auto k_step = [&](uint8_t* curA, uint8_t* curB, uint8_t* nxtA, uint8_t* nxtB, int kt, int parity, auto x_is_high) __attribute__((always_inline)) {
         constexpr bool XH = decltype(x_is_high)::value;
         constexpr int X0 = XH ? HI : 0, Y0 = XH ? 0 : HI;
         auto& aX = *(XH ? &aH : &aL);
@@ -523,19 +642,25 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         mma_quadrant<FA, FB, Y0, 0, false>(acc, aY, bL, [&](auto m) { readsB_of_slot(curB, IntTag<HJ>{}, bH, m); });
         // the direct-to-LDS loads of the previous step must have landed; its two touch loads, issued
         // after them, may still be in flight
-        if constexpr (kTouch) wait_vmcnt<2>(); else wait_vmcnt<0>();
+        // (kEdgeUnaligned: the slab was written by ordinary LDS stores, which the barrier orders)
+        if constexpr (UA) {} else if constexpr (kTouch) wait_vmcnt<2>(); else wait_vmcnt<0>();
         lds_barrier();
         __builtin_amdgcn_sched_barrier(0);
         int baseA, baseB;
         load_base(kt + 2 < nk ? kb + kt + 2 : -1, baseA, baseB);
+        voffs_of_step(kt + 2);
+        const int fetch_step = kt + 3 < nk ? kt + 3 : nk - 1;        // kEdgeUnaligned: the loads run a step ahead of the LDS writes
         mma_quadrant<FA, FB, Y0, HJ, true>(acc, aY, bH, [&](auto m) {
             readsB_of_slot(nxtB, IntTag<0>{}, bL, m);     // past the last slab this reads bytes that are never used
-            loads_of_slot(curA, curB, baseA, baseB, m);
+            loads_of_slot(curA, curB, baseA, baseB, fetch_step, m);
         });
         mma_quadrant<FA, FB, X0, HJ, false>(acc, aX, bH, [&](auto m) {
             readsA_of_slot(nxtA, IntTag<Y0>{}, aY, m);
-            loads_of_slot(curA, curB, baseA, baseB, IntTag<kSlots + decltype(m)::value>{});
+            loads_of_slot(curA, curB, baseA, baseB, fetch_step, IntTag<kSlots + decltype(m)::value>{});
         });
+        if constexpr (UA) {
+            if (kt + 2 == nk - 1) fix_last_slab(curA, curB);         // this thread's own chunks once more
+        }
         if constexpr (kTouch) {
             const int kp = kt + 2 + touch_ahead;
             const bool on = touch_ahead > 0 && kp < nk;
@@ -548,14 +673,24 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
 
     if constexpr (!fixup) {
     // both stages are requested at once; only the first has to have landed before the first fragments
+    if constexpr (UA) {
+        static_for<kLoadsPerStep>([&](auto piece) { fetch(0, piece); });
+        static_for<kLoadsPerStep>([&](auto piece) { put(ldsA0, ldsB0, staged[decltype(piece)::value], piece); });
+        static_for<kLoadsPerStep>([&](auto piece) { fetch(nk > 1 ? 1 : 0, piece); });
+        static_for<kLoadsPerStep>([&](auto piece) { put(ldsA1, ldsB1, staged[decltype(piece)::value], piece); });
+        if (nk == 1) fix_last_slab(ldsA0, ldsB0);
+        if (nk == 2) fix_last_slab(ldsA1, ldsB1);
+        static_for<kLoadsPerStep>([&](auto piece) { fetch(nk > 2 ? 2 : nk - 1, piece); });
+    } else {
     issue_loads(ldsA0, ldsB0, kb);
     issue_loads(ldsA1, ldsB1, nk > 1 ? kb + 1 : -1);
+    }
     if constexpr (kTouch) {                       // keep "two touch loads are the newest" true from the start
         const bool on = touch_ahead > 0 && 2 < nk;
         touchA[1] = __builtin_amdgcn_raw_buffer_load_b32(rsA, touch_voffA, on ? (kb + 2) * ksA : kOutOfRange, 0);
         touchB[1] = __builtin_amdgcn_raw_buffer_load_b32(rsB, touch_voffB, on ? (kb + 2) * ksB : kOutOfRange, 0);
     }
-    wait_vmcnt<kLoadsPerStep + (kTouch ? 2 : 0)>();
+    if constexpr (!UA) wait_vmcnt<kLoadsPerStep + (kTouch ? 2 : 0)>();
     lds_barrier();
     read_fragsA(ldsA0, IntTag<0>{}, aL);
     read_fragsB(ldsB0, IntTag<0>{}, bL);
@@ -669,11 +804,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     const float inv_ab = inv_a * inv_b;
     const bool one_mul = inv_ab >= 1.17549435e-38f && inv_ab <= 3.402823466e+38f;
     const float m1 = one_mul ? inv_ab : inv_a;
+    const float m2 = EDGE != kNoEdge && one_mul ? 1.0f : inv_b;     // EDGE: one body, whose second factor is exact if not needed
     // The output absmax is taken in fp32 before rounding: rounding to BF16 is monotonic, so the BF16
     // rounding of the largest |y| is the largest rounded magnitude.  The maximum is the IEEE 754-2019 one
     // (v_maximum3_f32, two elements per instruction): a NaN output makes the absmax NaN, as it does for the
     // absmax kernel run over the stored tensor.
     float maxabs = 0.0f;
+    unsigned edge_mag = 0;                       // EDGE: packed magnitudes of the BF16 values that are stored
     auto track4 = [&](const v4f& y) {
         if constexpr (V::kIeeeMaximum) {
             maxabs = __builtin_elementwise_maximum(__builtin_elementwise_maximum(maxabs, __builtin_fabsf(y[0])), __builtin_fabsf(y[1]));
@@ -692,11 +829,78 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             y[e] = block[e] * m1;
-            if constexpr (decltype(two_mul)::value) y[e] *= inv_b;
+            if constexpr (decltype(two_mul)::value) y[e] *= m2;
         }
         return y;
     };
-    if constexpr (!ACCUM) {
+    if constexpr (EDGE != kNoEdge) {
+        // The staging of the accumulating epilogue below, with or without old values.  Widths that are multiples of 8
+        // move 16 bytes per lane through a buffer that ends with the output's last row (pieces beside the output get an
+        // offset outside it); other widths go element by element, neighbouring lanes on neighbouring columns.
+        constexpr int kSlots = 4 * NJ, kPitch = 32 * kSlots;
+        uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
+        static_assert(32 * kPitch <= kSlabA && 32 * kPitch <= kSlabB - 16, "32 staged rows fit the start of any slab");
+        const int row0 = tr * BM + wr * 32 * NI, col0 = tc * BN + wc * 32 * NJ;
+        const int rows_left = Rn - row0, cols_left = Cn - col0;              // of this wave's quadrant; may be <= 0
+        uint16_t* cbase = C + (size_t)row0 * Cn + col0;
+        const int here = rows_left < 32 * NI ? rows_left : 32 * NI;
+        const __amdgpu_buffer_rsrc_t rsC = make_rsrc(cbase, here > 0 && cols_left > 0 ? (unsigned)(((size_t)(here - 1) * Cn + cols_left) * 2) : 0u);
+        const int piece0 = fr_q >> 1, unit_off = (fr_q & 1) * (16 * kSlots);
+        const bool vector = Cn % 8 == 0;
+        // the piece a lane moves first; the others of 32 rows lie kRowStep rows further down each
+        constexpr int kRowStep = kWave / kSlots, kPiecesPerLane = 32 * kSlots / kWave;
+        const int pr = lane / kSlots, sl = lane % kSlots;
+        const unsigned voff = 8 * sl < cols_left ? (unsigned)(pr * Cn + 8 * sl) * 2 : kOutOfRange;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii) {
+                const int row = 16 * ii + fr_row;
+                uint8_t* srow = stage + row * kPitch + unit_off;
+#pragma unroll
+                for (int j = 0; j < MJ; ++j)
+                    *reinterpret_cast<v4f*>(srow + (((2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (vector) {
+#pragma unroll
+                for (int k = 0; k < kPiecesPerLane; ++k) {
+                    const int r = pr + k * kRowStep;
+                    const uint8_t* src = stage + r * kPitch + (((sl + r) % kSlots) << 4);
+                    v4f y0 = *reinterpret_cast<const v4f*>(src), y1 = *reinterpret_cast<const v4f*>(src + 16 * kSlots);
+                    const unsigned off = voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2;
+                    if (accumulate) {
+                        const v4u old = __builtin_amdgcn_raw_buffer_load_b128(rsC, off, 0, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const unsigned o = old[e >> 1], o1 = old[2 + (e >> 1)];
+                            y0[e] += __uint_as_float((e & 1) ? o & 0xFFFF0000u : o << 16);
+                            y1[e] += __uint_as_float((e & 1) ? o1 & 0xFFFF0000u : o1 << 16);
+                        }
+                    }
+                    const v2u w0 = __builtin_bit_cast(v2u, __builtin_convertvector(y0, bf16x4)), w1 = __builtin_bit_cast(v2u, __builtin_convertvector(y1, bf16x4));
+                    const v4u out = {w0[0], w0[1], w1[0], w1[1]};
+                    if (i * 32 + r < rows_left && 8 * sl < cols_left) {
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) edge_mag = pk_max_mag(edge_mag, out[w]);
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(out, rsC, off, 0, 0);
+                }
+            } else {
+                const int n_rows = rows_left - i * 32 < 32 ? rows_left - i * 32 : 32, n_cols = cols_left < 32 * NJ ? cols_left : 32 * NJ;
+                for (int r = 0; r < n_rows; ++r)
+                    for (int c = lane; c < n_cols; c += kWave) {
+                        float y = *reinterpret_cast<const float*>(stage + r * kPitch + ((((c >> 3) + r) % kSlots) << 4) + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4);
+                        uint16_t* dst = cbase + (size_t)(i * 32 + r) * Cn + c;
+                        if (accumulate) y += __uint_as_float((unsigned)*dst << 16);
+                        const unsigned bits = __builtin_bit_cast(uint16_t, (__bf16)y);
+                        *dst = (uint16_t)bits;
+                        edge_mag = pk_max_mag(edge_mag, bits);
+                    }
+            }
+        }
+    } else if constexpr (!ACCUM) {
         constexpr int kSlots = 4 * NJ;                                       // 16-byte slots per staged row
         constexpr int kPitch = 16 * kSlots;
         uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
@@ -809,13 +1013,16 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         if constexpr (V::kProfile) stamp(4);
     }
     };
-    if (one_mul) {
+    if constexpr (EDGE != kNoEdge) {
+        write_out(BoolTag<true>{});
+    } else if (one_mul) {
         write_out(BoolTag<false>{});
     } else {
         write_out(BoolTag<true>{});
     }
     if constexpr (kTouch) asm volatile("" ::"v"(next_touch[0] ^ next_touch[1] ^ next_touch[2] ^ next_touch[3]));
     unsigned mag = (unsigned)__builtin_bit_cast(uint16_t, (__bf16)maxabs);   // non-negative: magnitude bits
+    if constexpr (EDGE != kNoEdge) mag = (edge_mag & 0xFFFFu) > (edge_mag >> 16) ? (edge_mag & 0xFFFFu) : (edge_mag >> 16);
     if (amax_bits) {
         mag = wave_max_u32(mag);
         if (lane == 0) s_amax[wave] = mag;
@@ -984,7 +1191,7 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     auto launch = [&](auto kernel, int blocks, const SplitPlan& pl) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kGemmThreads), 0, stream,
                            A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c,
-                           touch, band, next_stride, ldA, ldB, ksA, ksB, share_a, share_b, pl);
+                           touch, band, next_stride, ldA, ldB, ksA, ksB, share_a, share_b, pl, (int)R, accumulate);
     };
     // The pieces first (all CUs start and end them together), their sums next, the whole rounds last.
     if constexpr (split_supported(NI, NJ) && FA != kFmtBf16 && !TA && !TB) {
@@ -999,6 +1206,61 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmTuning, TA, TB>, grid, plan);
 }
 
+
+// ---- ragged shapes (EDGE instantiations)
+struct EdgeChoice {
+    int ni, nj;       // 0, 0: the generic kernel
+    int edge;         // kEdge or kEdgeUnaligned
+};
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b);
+
+template <int FA, int FB, int NI, int NJ, bool TA, bool TB, int EDGE>
+static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
+                        void* c, int accumulate, unsigned* amax, hipStream_t stream, bool slabs_a, bool slabs_b) {
+    const int ldA = TA ? (int)R : slabs_a ? BK : (int)T, ldB = TB ? (int)C : slabs_b ? BK : (int)T;
+    const int ksA = slabs_a ? (int)(R * BK) : BK, ksB = slabs_b ? (int)(C * BK) : BK;
+    const int tiles_r = (int)((R + 64 * NI - 1) / (64 * NI)), tiles_c = (int)((C + 64 * NJ - 1) / (64 * NJ));
+    SplitPlan plan{};
+    plan.n_whole = tiles_r * tiles_c;
+    const int grid = ((plan.n_whole + kXcds - 1) / kXcds) * kXcds;
+    const int touch = (NI == 2 && NJ == 2) ? touch_ahead_pair() : touch_ahead();
+    const int band = band_rows();
+    const int share_b = band < tiles_r ? band : tiles_r, share_a = 4 < tiles_c ? 4 : tiles_c;
+    // (no requests for the next workgroup's first slabs: they would need the same guards as the loads)
+    hipLaunchKernelGGL((gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB, kWholeTiles, EDGE>), dim3(grid), dim3(kGemmThreads), 0, stream,
+                       A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c, touch, band, 0,
+                       ldA, ldB, ksA, ksB, share_a, share_b, plan, (int)R, accumulate);
+}
+
+#define LLMQ_EDGE_LAUNCH_PARAMS                                                                                   \
+    const uint8_t *A, const uint8_t *B, int64_t R, int64_t C, int64_t T, const float *sA, const float *sB, void *c, \
+        int accumulate, unsigned *amax, hipStream_t stream, int num_cus, bool slabs_a, bool slabs_b
+// false: no tile kernel takes the shape.  Instantiated in gemm_edge_*.hip.
+template <int FA, int FB, bool TA, bool TB>
+bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
+    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b);
+#define LLMQ_EDGE_CASE(I, J)                                                                                        \
+    case I * 8 + J:                                                                                                 \
+        if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); \
+        else launch_edge<FA, FB, I, J, TA, TB, kEdgeUnaligned>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b);         \
+        return true;
+    switch (ec.ni * 8 + ec.nj) {
+        LLMQ_EDGE_CASE(4, 4) LLMQ_EDGE_CASE(4, 2) LLMQ_EDGE_CASE(2, 4) LLMQ_EDGE_CASE(2, 2)
+        default: break;
+    }
+#undef LLMQ_EDGE_CASE
+    return false;
+}
+extern template bool launch_edge_tile<0, 0, false, false>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<1, 0, false, false>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<0, 1, false, false>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<1, 1, false, false>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<kFmtBf16, kFmtBf16, false, false>(LLMQ_EDGE_LAUNCH_PARAMS);
+// T-major operands: the pairs the linear calls use
+extern template bool launch_edge_tile<0, 0, false, true>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<0, 0, true, true>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<1, 0, false, true>(LLMQ_EDGE_LAUNCH_PARAMS);
+extern template bool launch_edge_tile<1, 0, true, true>(LLMQ_EDGE_LAUNCH_PARAMS);
 
 // Dispatch on the tile chosen for the problem; false if none divides it.  One translation unit per operand kinds and
 // layout instantiates this (gemm_tiles_*.hip: each holds the kernels of all tile shapes for its case, and the files

@@ -22,6 +22,13 @@ static bool launch_layout(bool ta, bool tb, const uint8_t* A, const uint8_t* B, 
     return launch_chosen_tile<FA, FB, true, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, false, slabs_b);
 }
 
+template <int FA, int FB>
+static bool launch_edge_layout(bool ta, const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
+                               void* c, int accumulate, unsigned* amax, hipStream_t stream, int num_cus, bool slabs_a) {
+    if (ta) return launch_edge_tile<FA, FB, true, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, false, false);
+    return launch_edge_tile<FA, FB, false, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, false);
+}
+
 int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, int fmtB, int layout_b, int64_t R, int64_t C,
                     int64_t T, const float* d_scaleA, const float* d_scaleB, void* c_bf16, int accumulate,
                     float* d_amax_c, bool amax_is_zeroed, hipStream_t stream, int num_cus, GemmScratch scratch) {
@@ -41,6 +48,11 @@ int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, 
     if (fits && fmtB == 0) {
         if (fmtA == 0) done = launch_layout<0, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b);
         else done = launch_layout<1, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b);
+    }
+    if (!done && fits && fmtB == 0 && tb) {
+        // ragged shapes, in the pairs the linear calls use (A T-major alone completes the set of whole tiles only)
+        if (fmtA == 0) done = launch_edge_layout<0, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a);
+        else done = launch_edge_layout<1, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a);
     }
     if (!done) launch_gemm_generic(A, fmtA, layout_a, B, fmtB, layout_b, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream);
     return hipGetLastError() == hipSuccess ? 0 : -6;

@@ -1,0 +1,104 @@
+"""GPU parity of the tile kernels on ragged shapes (any rows, columns and contraction length, any row pitch) against
+the fp64 oracle, at the edges of their tiles; nothing outside the output may be written."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_15306_amd import llmq, synth
+from gpu_common import DEV, GEMM_TOL, bf16_to_f64, assert_gemm_close, f32_bits, gpu_amax
+from test_gpu_gemm import _rand_codes, _scales
+from test_gpu_gemm_bf16 import _check, _rand
+
+pytestmark = pytest.mark.gpu
+
+TILES = ["4x4", "4x2", "2x4", "2x2"]
+# (R, C, T): just below, at and above tile edges; T with whole 16-byte chunks (0, 1 and several K steps, with and without
+# a tail) and without; widths that are multiples of 8 and odd ones
+SHAPES = [(1, 8, 16), (127, 130, 112), (257, 264, 128), (300, 17, 144), (255, 513, 272), (130, 256, 400),
+          (1, 1, 17), (33, 40, 31), (129, 255, 127), (256, 136, 129), (270, 260, 250), (513, 24, 393), (40, 300, 1001)]
+GUARD = 512      # sentinel elements before and after the output
+
+
+def _guarded(R, C, init=None):
+    buf = torch.full((R * C + 2 * GUARD,), -77.0, dtype=torch.bfloat16, device=DEV)
+    c = buf[GUARD:GUARD + R * C].view(R, C)
+    c.copy_(torch.full((R, C), float("nan"), dtype=torch.bfloat16) if init is None else init)
+    return buf, c
+
+
+def _untouched(buf, R, C):
+    return bool((buf[:GUARD] == -77.0).all() and (buf[GUARD + R * C:] == -77.0).all())
+
+
+def _operand(codes, layout):
+    t = torch.from_numpy(np.ascontiguousarray(codes.T) if layout else codes)
+    return t.to(DEV)
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("R,C,T", SHAPES)
+def test_ragged_fp8(R, C, T, tile, monkeypatch):
+    monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+    layouts = [(False, False), (False, True), (True, True)]
+    fa = (R + T) % 2
+    A, B = _rand_codes((R, T), fa, 7 * R + T), _rand_codes((C, T), 0, 5 * C + T + 1)
+    y, S = oracle.gemm_tn(A, fa, B, 0, 3.7, 0.61)
+    c0 = _rand((R, C), 5, 30.0)
+    first = None
+    for ta, tb in layouts:
+        print("edge R=%d C=%d T=%d tile=%s ta=%d tb=%d" % (R, C, T, tile, ta, tb), flush=True)
+        dsa, dsb = _scales(3.7, 0.61)
+        am = torch.full((1,), -1.0, dtype=torch.float32, device=DEV)
+        buf, c = _guarded(R, C)
+        llmq.llmq_fp8_gemm(_operand(A, ta), fa, ta, _operand(B, tb), 0, tb, dsa, dsb, c, False, am)
+        assert_gemm_close(c, y, S, "edge")
+        assert _untouched(buf, R, C)
+        assert f32_bits(am) == f32_bits(gpu_amax(c.reshape(-1).clone(), 0, want_scale=False)[0])
+        buf, acc = _guarded(R, C, c0)
+        llmq.llmq_fp8_gemm(_operand(A, ta), fa, ta, _operand(B, tb), 0, tb, dsa, dsb, acc, True, am)
+        want = bf16_to_f64(c0) + y
+        assert np.all(np.abs(bf16_to_f64(acc) - want) <= GEMM_TOL * S + 2.0 ** -8 * np.abs(want))
+        assert _untouched(buf, R, C)
+        assert f32_bits(am) == f32_bits(gpu_amax(acc.reshape(-1).clone(), 0, want_scale=False)[0])
+        if first is None:
+            first = c.clone()
+        assert torch.equal(first.view(torch.int16), c.view(torch.int16))      # same sums in every layout
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("R,C,T", [(257, 264, 136), (130, 8, 8), (40, 300, 500), (255, 129, 63), (300, 520, 257)])
+def test_ragged_bf16(R, C, T, tile, monkeypatch):
+    monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+    print("edge bf16 R=%d C=%d T=%d tile=%s" % (R, C, T, tile), flush=True)
+    A, B, prev = _rand((R, T), 100 + R + T), _rand((C, T), 200 + C + T, 0.05), _rand((R, C), 300 + R, 0.5)
+    y, S = oracle.gemm_bf16_tn(synth.bf16_bits(A), synth.bf16_bits(B))
+    for p in (None, prev):
+        buf, c = _guarded(R, C, p)
+        llmq.llmq_bf16_gemm_tn(A.to(DEV), B.to(DEV), c, accumulate=p is not None)
+        _check(c, y, S, T, "edge", prev=None if p is None else bf16_to_f64(p))
+        assert _untouched(buf, R, C)
+
+
+@pytest.mark.parametrize("fa,T", [(0, 272), (1, 272), (0, 275), (1, 275)])
+def test_values_beyond_the_operands_do_not_reach_the_results(fa, T):
+    """NaN and Inf codes lie directly behind the operands in memory; one NaN row inside stays one NaN row."""
+    R, C = 130, 72
+    nan, inf = (0x7F, 0x7F) if fa == 0 else (0x7E, 0x7C)
+    A, B = _rand_codes((R, T), fa, 3), _rand_codes((C, T), 0, 4)
+    A[5, T - 1] = nan
+    bufA = torch.full((R * T + 4096,), inf, dtype=torch.uint8, device=DEV)
+    bufB = torch.full((C * T + 4096,), 0x7F, dtype=torch.uint8, device=DEV)
+    a, b = bufA[:R * T].view(R, T), bufB[:C * T].view(C, T)
+    a.copy_(torch.from_numpy(A))
+    b.copy_(torch.from_numpy(B))
+    dsa, dsb = _scales(1.5, 0.8)
+    am = torch.zeros(1, dtype=torch.float32, device=DEV)
+    c = torch.zeros((R, C), dtype=torch.bfloat16, device=DEV)
+    llmq.llmq_fp8_gemm_tn(a, fa, b, 0, dsa, dsb, c, False, am)
+    bad = torch.isnan(c).all(dim=1)
+    assert bad[5] and int(bad.sum()) == 1 and torch.isfinite(c[torch.arange(R, device=DEV) != 5]).all()
+    assert f32_bits(am) == 0x7FC00000
+    a[5, T - 1] = 0x38
+    llmq.llmq_fp8_gemm_tn(a, fa, b, 0, dsa, dsb, c, False, am)
+    assert torch.isfinite(c).all() and am.item() == c.float().abs().max().item()

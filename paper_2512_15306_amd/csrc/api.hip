@@ -92,12 +92,12 @@ int check_swiglu_shape(int64_t M, int64_t I) {
 // stores the scale in d_scale (saving the launch of the second stage).
 int quantize_operand(const void* t, int64_t rows, int64_t cols, float* d_scale, int fmt, uint8_t* q, uint8_t* q_t,
                      bool jit, unsigned* partial, unsigned* zero, hipStream_t s, bool qt_slabs) {
-    if (!jit) return llmq::launch_quantize(t, rows, cols, d_scale, fmt, q, q_t, zero, s, qt_slabs);
+    if (!jit) return llmq::launch_quantize(t, rows, cols, d_scale, fmt, q, q_t, zero, s, qt_slabs, true);
     int n_partial = 0;
     int st = llmq::launch_amax_partial(t, (size_t)rows * (size_t)cols, partial, &n_partial, s, num_cus());
     if (st) return st;
     const llmq::ScaleSource src{nullptr, partial, n_partial, fmt == LLMQ_E4M3 ? 448.0f : 57344.0f, d_scale};
-    return llmq::launch_quantize_from(t, rows, cols, src, fmt, q, q_t, zero, s, qt_slabs);
+    return llmq::launch_quantize_from(t, rows, cols, src, fmt, q, q_t, zero, s, qt_slabs, true);
 }
 
 // Under LLMQ_SLAB_COPIES the transposed copy of a tensor [rows, cols] is stored in slabs of 128 contraction bytes
@@ -155,7 +155,7 @@ int llmq_quantize_fp8(const void* x_bf16, int64_t rows, int64_t cols, const floa
     if (!dim_ok(rows) || !dim_ok(cols) || rows * cols >= kMaxElems) return LLMQ_ERR_SHAPE;
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(x_bf16, 16) || !aligned(q, 16) || !aligned(q_t, 16) || !aligned(d_scale, 4)) return LLMQ_ERR_ALIGN;
-    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream));
+    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream), false, false);
 }
 
 int llmq_quantize_fp8_slabs(const void* x_bf16, int64_t rows, int64_t cols, const float* d_scale, int fmt,
@@ -166,7 +166,7 @@ int llmq_quantize_fp8_slabs(const void* x_bf16, int64_t rows, int64_t cols, cons
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(x_bf16, 16) || !aligned(q, 16) || !aligned(q_t, 16) || !aligned(d_scale, 4)) return LLMQ_ERR_ALIGN;
     if (!llmq::quantize_can_write_slabs(rows, cols)) return LLMQ_ERR_SHAPE;
-    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream), true);
+    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream), true, false);
 }
 
 int llmq_fp8_gemm_tn(const uint8_t* A, int fmtA, const uint8_t* B, int fmtB, int64_t R, int64_t C, int64_t T,

@@ -55,6 +55,10 @@ __device__ inline unsigned pk_max_mag(unsigned acc, unsigned w) {
     return __builtin_bit_cast(unsigned, __builtin_elementwise_max(a, b));
 }
 
+__device__ inline unsigned pk_max_u16(unsigned a, unsigned b) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(v2us, a), __builtin_bit_cast(v2us, b)));
+}
+
 // Maximum over a workgroup of THREADS lanes; s_part holds one word per wavefront.
 template <int THREADS>
 __device__ inline unsigned block_max_u32(unsigned m, unsigned* s_part) {
@@ -107,6 +111,13 @@ __host__ __device__ inline void band_walk(unsigned id, unsigned grid_rows, unsig
     const unsigned in_band = id - band_first * grid_rows;
     brow = in_band / band_width;
     bcol = band_first + in_band % band_width;
+}
+
+// A store, with the streaming hint if STREAM
+template <bool STREAM, class T>
+__device__ inline void store_hinted(const T& v, T* p) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // ---- FP8 cast helpers (used by the quantize kernel and by the producers that emit FP8 directly) ----
@@ -204,6 +215,139 @@ __device__ inline void tile_write_transposed(const uint8_t* s_t, uint8_t* dt, in
         const int c = p >> 3, ch = p & 7;
         const v4u v = *reinterpret_cast<const v4u*>(s_t + c * kTilePitch + ch * 16);
         *reinterpret_cast<v4u*>(dt + (int64_t)c * row_stride + ch * 16) = v;
+    }
+}
+
+// ---- The same at the edges of ragged tensors: any number of rows and columns, rows starting at any address ----
+//
+// A patch that lies inside the tensor moves in the same 16- and 8-byte vectors, only without the alignment (the
+// hardware takes them at any address); a patch over the edge moves what exists element by element, zeros for the rest.
+typedef v4u v4u_at2 __attribute__((aligned(2)));
+typedef v4u v4u_at1 __attribute__((aligned(1)));
+typedef v2u v2u_at1 __attribute__((aligned(1)));
+
+// Eight BF16 values of which the first `valid` exist.
+__device__ inline v4u load8_upto(const uint16_t* p, int64_t valid) {
+    if (valid >= 8) return *reinterpret_cast<const v4u_at2*>(p);
+    v4u v = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+        if (e < valid) v[e >> 1] |= (unsigned)p[e] << (16 * (e & 1));
+    return v;
+}
+__device__ inline void store8_upto(uint16_t* p, const v4u& v, int64_t valid) {
+    if (valid >= 8) { *reinterpret_cast<v4u_at2*>(p) = v; return; }
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+        if (e < valid) p[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+}
+__device__ inline void store8_codes_upto(uint8_t* p, unsigned lo, unsigned hi, int64_t valid) {
+    if (valid >= 8) { *reinterpret_cast<v2u_at1*>(p) = v2u{lo, hi}; return; }
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+        if (e < valid) p[e] = (uint8_t)((e < 4 ? lo : hi) >> (8 * (e & 3)));
+}
+
+// Rows of a patch of BF16 values [rows_left, cols_left] at src, `ld` elements apart; PR rows x 8 columns
+template <int PR>
+__device__ inline void load_patch_upto(v4u (&in)[PR], const uint16_t* src, int64_t ld, int64_t rows_left, int64_t cols_left) {
+    if (rows_left >= PR && cols_left >= 8) {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(src + (int64_t)i * ld));
+    } else {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) in[i] = load8_upto(src + (int64_t)i * ld, i < rows_left ? cols_left : 0);
+    }
+}
+template <int PR>
+__device__ inline void store_patch_upto(const v4u (&out)[PR], uint16_t* dst, int64_t ld, int64_t rows_left, int64_t cols_left) {
+    if (rows_left >= PR && cols_left >= 8) {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) *reinterpret_cast<v4u_at2*>(dst + (int64_t)i * ld) = out[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < PR; ++i)
+            if (i < rows_left) store8_upto(dst + (int64_t)i * ld, out[i], cols_left);
+    }
+}
+template <int PR>
+__device__ inline void store_codes_upto(const unsigned (&w)[PR][2], uint8_t* dst, int64_t ld, int64_t rows_left, int64_t cols_left) {
+    if (rows_left >= PR && cols_left >= 8) {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) *reinterpret_cast<v2u_at1*>(dst + (int64_t)i * ld) = v2u{w[i][0], w[i][1]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < PR; ++i)
+            if (i < rows_left) store8_codes_upto(dst + (int64_t)i * ld, w[i][0], w[i][1], cols_left);
+    }
+}
+
+// ---- The 64-row x 128-column tile of the same kernels for tensors of few tiles ----
+//
+// A tensor of a few dozen 128 x 256 tiles leaves most of the chip idle and the rest waiting: a lane's sixteen rows are
+// read, converted and written by a handful of waves per CU.  Here a lane owns 4 rows x 8 columns and four times as many
+// workgroups share the tensor; a wave is 4 lanes stacked x 16 side by side (256-byte runs of the input, whole lines of
+// codes), the four waves are stacked.  Guarded edges, any alignment; the transposed copy leaves in 64-byte pieces.
+constexpr int kSmallRows = 64, kSmallCols = 128, kSmallPatch = 4;
+constexpr int kSmallPitch = kSmallRows + 16, kSmallLdsBytes = kSmallCols * kSmallPitch;
+
+// Rows that do not start at a cache line share lines with the tiles beside them, so neighbours belong on one XCD (own L2;
+// the hardware deals workgroup ids round-robin to them): each XCD then walks a contiguous range of tiles, eight tile columns
+// wide and down the rows.  Where rows do start at lines, plain launch order along the columns is better.  Quantize
+// kernel, launch order / XCD ranges in bands of 2 / 8 / all columns: 8112 x 5128 elements 45.7 / 39.9 / 37.7 / 37.5 us,
+// 1777 x 20000 40.3 / 33.5 / 33.6 / 38.9, 9001 x 3001 32.4 / 31.3 / 30.8 / 31.3, 16000 x 9000 202 / 202 / 174 / 173;  rows of
+// whole lines: 3584 x 21440 69 / 78 / 73 / 85, 8100 x 7168 53.6 / 55.1 / 58.0 / 59.8.
+constexpr unsigned kSmallXcds = 8, kSmallBand = 8;
+struct SmallGrid { unsigned rows, cols, blocks; bool xcd_ranges; };          // tiles, and workgroups of the launch
+inline SmallGrid small_grid(int64_t rows, int64_t cols) {
+    SmallGrid g;
+    g.rows = (unsigned)((rows + kSmallRows - 1) / kSmallRows);
+    g.cols = (unsigned)((cols + kSmallCols - 1) / kSmallCols);
+    g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
+    g.xcd_ranges = cols % 64 != 0;
+    return g;
+}
+// This workgroup's tile; false for the padding ids (id 0 always has one)
+__device__ inline bool small_tile(const SmallGrid& g, unsigned& brow, unsigned& bcol) {
+    const unsigned id = blockIdx.x;
+    const unsigned pos = g.xcd_ranges ? (id % kSmallXcds) * (g.blocks / kSmallXcds) + id / kSmallXcds : id;
+    if (pos >= g.rows * g.cols) return false;
+    const unsigned band = g.xcd_ranges && kSmallBand < g.cols ? kSmallBand : g.cols;
+    band_walk(pos, g.rows, g.cols, band, brow, bcol);
+    return true;
+}
+
+__device__ inline void small_patch_origin(int& tr, int& tc) {
+    const int lane = threadIdx.x & (kWave - 1);
+    tr = (threadIdx.x / kWave) * 16 + (lane & 3) * kSmallPatch;
+    tc = (lane >> 2) * 8;
+}
+
+__device__ inline void small_stage_transposed(const unsigned (&w)[kSmallPatch][2], int tr, int tc, uint8_t* s_t) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const unsigned blk[4] = {w[0][k], w[1][k], w[2][k], w[3][k]};
+        unsigned o[4];
+        transpose4x4_bytes(blk, o);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) *reinterpret_cast<unsigned*>(s_t + (tc + 4 * k + c) * kSmallPitch + tr) = o[c];
+    }
+}
+
+// dt = where row 0 of the tile starts in transposed row 0 of the tile; transposed rows row_stride bytes apart
+__device__ inline void small_write_transposed_upto(const uint8_t* s_t, uint8_t* dt, int64_t row_stride, int64_t rows_left, int64_t cols_left) {
+#pragma unroll
+    for (int m = 0; m < kSmallCols * (kSmallRows / 16) / kTileThreads; ++m) {
+        const int p = threadIdx.x + m * kTileThreads;
+        const int c = p >> 2, ch = p & 3;
+        if (c >= cols_left) continue;
+        uint8_t* dst = dt + (int64_t)c * row_stride + ch * 16;
+        const int64_t valid = rows_left - ch * 16;
+        if (valid >= 16) {
+            *reinterpret_cast<v4u_at1*>(dst) = *reinterpret_cast<const v4u*>(s_t + c * kSmallPitch + ch * 16);
+        } else {
+            for (int e = 0; e < valid; ++e) dst[e] = s_t[c * kSmallPitch + ch * 16 + e];
+        }
     }
 }
 

@@ -16,10 +16,29 @@ inline const char* tuning_env(const char* name) {
 }
 
 // The workgroup tile of the kernels that write FP8 codes in both layouts (quantize, and the SwiGLU and RMSNorm
-// kernels that emit FP8 directly): tensors made of whole tiles take the tile kernels, and only those can write
-// the transposed copy in slabs.
+// kernels that emit FP8 directly); only tensors made of whole tiles have a transposed copy in slabs.
 constexpr int kTileRows = 128, kTileCols = 256;
 inline bool tile_shape_ok(int64_t rows, int64_t cols) { return rows % kTileRows == 0 && cols % kTileCols == 0; }
+
+// Such a tensor takes the tile kernels from `min_tiles` tiles on, below that the 64 x 128 tile, of which there are four
+// times as many.  Quantize kernel, 64 x 128 against 128 x 256: 256 x 512 elements (4 tiles) 4.6 / 6.7 us, 2048 x 3072 (192)
+// 6.8 / 7.6, 4096 x 3072 (384) 12.7 / 12.3, 16384 x 5120 60.6 / 56.8: one tile per CU.
+// LLMQ_QUANT_TILE=0 / 1 (tests): always the one or, for shapes made of them, always the other.
+inline bool takes_large_tile(int64_t rows, int64_t cols, int64_t min_tiles = 256) {
+    if (!tile_shape_ok(rows, cols)) return false;
+    if (const char* e = tuning_env("LLMQ_QUANT_TILE")) return atoi(e) != 0;
+    return (rows / kTileRows) * (cols / kTileCols) >= min_tiles;
+}
+
+// Large results are stored with the streaming hint, so that they do not push out of the 256 MB memory-side cache what is
+// still to be read.  Plain / streaming, every pass on other buffers: SwiGLU backward 8192 x 18944 (592 MiB of results)
+// 283 / 267 us, forward 8192 x 18944 (296 MiB) 170 / 162, codes 8192 x 18944 197 / 187 (the row-major copy; the transposed
+// one leaves in pieces of lines and stays plain); RMSNorm 16384 x 5120 (320 MiB) 134 / 127; codes in both layouts of
+// 8192 x 7168 elements (112 MiB) 45.4 / 42.3, 4096 x 8192 (64 MiB) 26.1 / 26.2.  What the next kernel reads should stay in
+// that cache when it fits: with results of 128 MiB streamed an MLP sub-block (4096 x 3072 x 8192) takes 1021 instead of 1013
+// us.  Hence 144 MiB; 96 for the quantize calls of their own (a weight's codes are read much later); inside the linear
+// calls, whose contraction reads the codes at once, codes are never streamed (no difference up to 32B-class layers).
+inline bool streams_out(int64_t result_bytes, int limit_mib = 144) { return result_bytes > ((int64_t)limit_mib << 20); }
 
 // Each returns 0 or LLMQ_ERR_DEVICE (-6).  Arguments are validated by the callers in api.hip.
 constexpr int kAmaxMaxPartials = 1024;      // the absmax workspace holds one 32-bit word per block
@@ -41,8 +60,9 @@ int launch_scale_from_amax(const float* d_amax, int fmt, float* d_scale, hipStre
 // qt_slabs: the transposed copy is written in slabs of 128 contraction bytes (kLayoutSlabs of the contraction that
 // reads it: [cols, rows] with rows the contraction index), which only the tile kernel does: ask
 // quantize_can_write_slabs() first (else -2).
+// read_next: the launch that follows reads the codes (see streams_out).
 int launch_quantize(const void* x, int64_t rows, int64_t cols, const float* d_scale, int fmt,
-                    uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs = false);
+                    uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs, bool read_next);
 bool quantize_can_write_slabs(int64_t rows, int64_t cols);
 // Where a quantizing kernel gets its scale from: a scale on the device, or the per-workgroup results of
 // the first stage of an absmax reduction over the same tensor, in which case every workgroup finishes the
@@ -58,7 +78,7 @@ struct ScaleSource {
 
 // The same with the scale taken from a ScaleSource (a given scale, or the first-stage results of an absmax).
 int launch_quantize_from(const void* x, int64_t rows, int64_t cols, const ScaleSource& src, int fmt,
-                         uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs = false);
+                         uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs, bool read_next);
 // First stage of the absmax only: one BF16 magnitude pattern per workgroup into partial; returns the number
 // of workgroups (<= kAmaxMaxPartials) through n_partial.
 int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus);

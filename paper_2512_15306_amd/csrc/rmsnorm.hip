@@ -6,13 +6,13 @@
 //   res'[m,c] = bf16( res[m,c] + x[m,c] ),  rstd[m] = 1 / sqrt( mean_c res'[m,c]^2 + eps ),
 //   y[m,c]    = bf16( (res'[m,c] * rstd[m]) * w[c] )
 //
-// Forward kernel: one wavefront per row, the row stays in registers between the reduction and the
-// normalisation (one pass over HBM: 4 B read, 2 + 2 B written per element; 2 B less without the
+// Forward kernels: one wavefront per row, or a workgroup on two rows at a time; the row stays in registers between the
+// reduction and the normalisation (one pass over HBM: 4 B read, 2 + 2 B written per element; 2 B less without the
 // addition), sum of squares in binary32 with a butterfly over the lanes, absmax of y as a packed
 // integer max of the rounded bits, one partial absmax per workgroup for the second-stage kernel.
-// Recompute kernel: rstd and the scale are inputs, so the operation is element-wise; it has the
-// lane geometry of the quantize kernel (16 rows x 8 columns per lane) and reuses its register
-// transpose to write the FP8 codes in both layouts (2 B read, 1 + 1 B written per element).
+// Recompute kernels: rstd and the scale are inputs, so the operation is element-wise; they have the
+// lane geometry of the quantize kernels and reuse their transposes to write the FP8 codes in both layouts (2 B read,
+// 1 + 1 B written per element).
 #include <stdlib.h>
 
 #include "llmq_device.h"
@@ -21,14 +21,15 @@
 #pragma clang fp contract(off)
 
 namespace llmq {
+template <int N> struct IntTag { static constexpr int value = N; };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr int kRnThreads = 256;
 constexpr int kRnRowsPerBlock = kRnThreads / kWave;        // one wavefront per row
-constexpr int kRnMaxVec = 16;                               // 16-byte vectors per lane kept in registers
-constexpr int kRnMaxC = kRnMaxVec * kWave * 8;              // 8192 columns
+constexpr int kRnVec = 4;                                   // one wavefront per row: 16-byte vectors per lane
+constexpr int64_t kRnRowC = kRnVec * kWave * 8;             // 2048 columns
 
 __device__ inline unsigned rn_pack(float lo, float hi) {
     v2f v = {lo, hi};
@@ -59,8 +60,23 @@ __device__ inline v4u normalize8(const v4u& r, float rstd, const v4u& w) {
     return o;
 }
 
-// C % 8 == 0, C <= 8192.  x == nullptr: no addition (res is normalised as it is, res_out is not written).
-template <bool HAS_X>
+// Vector idx of a row of C elements; EDGE: of any C, at any even address
+template <bool EDGE>
+__device__ inline v4u rn_load(const uint16_t* row, int idx, int C) {
+    if constexpr (!EDGE) return __builtin_nontemporal_load(reinterpret_cast<const v4u*>(row) + idx);
+    if (8 * idx + 8 <= C) return __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(row + 8 * idx));
+    return load8_upto(row + 8 * idx, C - 8 * idx);
+}
+template <bool EDGE, bool STREAM = false>
+__device__ inline void rn_store(uint16_t* row, int idx, int C, const v4u& v) {
+    if constexpr (!EDGE) store_hinted<STREAM>(v, reinterpret_cast<v4u*>(row) + idx);
+    else store8_upto(row + 8 * idx, v, C - 8 * idx);
+}
+
+// Rows of up to 2048 columns in registers, one wavefront each.  EDGE: any C (the rows start at any even address, the last
+// vector of a row may be a part of one); else C % 8 == 0.  HAS_X false: no addition (res is normalised as it is, res_out is not
+// written).
+template <bool HAS_X, bool EDGE>
 __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
     const uint16_t* res, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     int64_t M, int C, float eps, uint16_t* res_out, uint16_t* __restrict__ y,
@@ -70,19 +86,21 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int64_t row = (int64_t)blockIdx.x * kRnRowsPerBlock + wave;
-    const int nvec = C / 8;
+    const int nvec = EDGE ? (C + 7) / 8 : C / 8;
     unsigned mag = 0;
+    auto load = [&](const uint16_t* base, int idx) { return rn_load<EDGE>(base, idx, C); };
+    auto store = [&](uint16_t* base, int idx, const v4u& v) { rn_store<EDGE>(base, idx, C, v); };
     if (row < M) {
-        const v4u* pr = reinterpret_cast<const v4u*>(res + row * C);
-        const v4u* px = HAS_X ? reinterpret_cast<const v4u*>(x + row * C) : nullptr;
-        v4u r[kRnMaxVec];
+        const uint16_t* pr = res + row * C;
+        const uint16_t* px = HAS_X ? x + row * C : nullptr;
+        v4u r[kRnVec];
 #pragma unroll
-        for (int k = 0; k < kRnMaxVec; ++k) {
+        for (int k = 0; k < kRnVec; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
-                r[k] = __builtin_nontemporal_load(pr + idx);
+                r[k] = load(pr, idx);
                 if constexpr (HAS_X) {
-                    const v4u xv = __builtin_nontemporal_load(px + idx);
+                    const v4u xv = load(px, idx);
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[k][j] = rn_pack(rn_lo(r[k][j]) + rn_lo(xv[j]), rn_hi(r[k][j]) + rn_hi(xv[j]));
@@ -91,10 +109,10 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
         }
         float ss = 0.0f;
 #pragma unroll
-        for (int k = 0; k < kRnMaxVec; ++k) {
+        for (int k = 0; k < kRnVec; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
-                if constexpr (HAS_X) *reinterpret_cast<v4u*>(res_out + row * C + (int64_t)idx * 8) = r[k];
+                if constexpr (HAS_X) store(res_out + row * C, idx, r[k]);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const float a = rn_lo(r[k][j]), b = rn_hi(r[k][j]);
@@ -108,26 +126,122 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
         const float rstd = 1.0f / __builtin_sqrtf(ms + eps);
         if (lane == 0) rstd_out[row] = rstd;
         unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;
-        const v4u* pw = reinterpret_cast<const v4u*>(w);
 #pragma unroll
-        for (int k = 0; k < kRnMaxVec; ++k) {
+        for (int k = 0; k < kRnVec; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
-                const v4u o = normalize8(r[k], rstd, pw[idx]);
-                *reinterpret_cast<v4u*>(y + row * C + (int64_t)idx * 8) = o;
+                v4u wv;
+                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
+                else wv = reinterpret_cast<const v4u*>(w)[idx];
+                const v4u o = normalize8(r[k], rstd, wv);
+                store(y + row * C, idx, o);
                 m0 = pk_max_mag(m0, o[0]);
                 m1 = pk_max_mag(m1, o[1]);
                 m2 = pk_max_mag(m2, o[2]);
                 m3 = pk_max_mag(m3, o[3]);
             }
         }
+        // (the zeros behind the end of a row give 0, or NaN where rstd is not finite and the row's own results are NaN)
         mag = fold_pairs(m0, m1, m2, m3);
     }
     mag = block_max_u32<kRnThreads>(mag, s_part);
     if (threadIdx.x == 0) partial[blockIdx.x] = mag;
 }
 
-// Any C: one wavefront per row, element-wise strided loops; the row is read again for the second pass
+// Wider rows: the four rows of a workgroup are read by all of its lanes (VPL vectors per lane and row, two rows at a time),
+// so that a lane holds a few vectors of each row instead of a whole row's share, which leaves room for more waves, and
+// reads the norm's weight once for both.  The row sums of the four waves meet in LDS, in a fixed order.  Measured against
+// one wave per row with up to 16 vectors per lane, with the addition: 16384 x 5120 137 -> 130 us (5.2 TB/s), 8192 x 3584
+// 52 -> 46, 4096 x 7680 59 -> 51, 279 x 7680 21 -> 14; all four rows at a time took 134, 48, 63 and 14.
+template <bool HAS_X, bool EDGE, int VPL, bool STREAM>
+__global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
+    const uint16_t* res, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+    int64_t M, int C, float eps, uint16_t* res_out, uint16_t* __restrict__ y,
+    float* __restrict__ rstd_out, unsigned* __restrict__ partial) {
+    constexpr int kWaves = kRnThreads / kWave, ROWS = VPL <= 4 ? 2 : 1;
+    __shared__ unsigned s_part[kWaves];
+    __shared__ float s_sum[kRnRowsPerBlock][kWaves];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int nvec = EDGE ? (C + 7) / 8 : C / 8;
+    unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;
+#pragma unroll 1
+    for (int p = 0; p < kRnRowsPerBlock; p += ROWS) {
+        const int64_t row = (int64_t)blockIdx.x * kRnRowsPerBlock + p;
+        if (row >= M) break;                                 // the same for the whole workgroup
+        v4u r[ROWS][VPL], xv[ROWS][HAS_X ? VPL : 1];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) {
+                const int idx = k * kRnThreads + threadIdx.x;
+                r[i][k] = v4u{0, 0, 0, 0};
+                if (row + i < M && idx < nvec) {
+                    r[i][k] = rn_load<EDGE>(res + (row + i) * C, idx, C);
+                    if constexpr (HAS_X) xv[i][k] = rn_load<EDGE>(x + (row + i) * C, idx, C);
+                }
+            }
+        float ss[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            ss[i] = 0.0f;
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) {
+                const int idx = k * kRnThreads + threadIdx.x;
+                if (row + i < M && idx < nvec) {
+                    if constexpr (HAS_X) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            r[i][k][j] = rn_pack(rn_lo(r[i][k][j]) + rn_lo(xv[i][k][j]), rn_hi(r[i][k][j]) + rn_hi(xv[i][k][j]));
+                        rn_store<EDGE, STREAM>(res_out + (row + i) * C, idx, C, r[i][k]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float a = rn_lo(r[i][k][j]), b = rn_hi(r[i][k][j]);
+                        ss[i] = __builtin_fmaf(a, a, ss[i]);
+                        ss[i] = __builtin_fmaf(b, b, ss[i]);
+                    }
+                }
+            }
+            ss[i] = wave_sum_f32(ss[i]);
+            if (lane == 0) s_sum[p + i][wave] = ss[i];
+        }
+        __syncthreads();
+        float rstd[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            float t = s_sum[p + i][0];
+#pragma unroll
+            for (int v = 1; v < kWaves; ++v) t += s_sum[p + i][v];
+            const float ms = t / (float)C;
+            rstd[i] = 1.0f / __builtin_sqrtf(ms + eps);
+            if (threadIdx.x == 0 && row + i < M) rstd_out[row + i] = rstd[i];
+        }
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) {
+            const int idx = k * kRnThreads + threadIdx.x;
+            if (idx < nvec) {
+                v4u wv;
+                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
+                else wv = reinterpret_cast<const v4u*>(w)[idx];
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i)
+                    if (row + i < M) {
+                        const v4u o = normalize8(r[i][k], rstd[i], wv);
+                        rn_store<EDGE, STREAM>(y + (row + i) * C, idx, C, o);
+                        m0 = pk_max_mag(m0, o[0]);
+                        m1 = pk_max_mag(m1, o[1]);
+                        m2 = pk_max_mag(m2, o[2]);
+                        m3 = pk_max_mag(m3, o[3]);
+                    }
+            }
+        }
+    }
+    const unsigned mag = block_max_u32<kRnThreads>(fold_pairs(m0, m1, m2, m3), s_part);
+    if (threadIdx.x == 0) partial[blockIdx.x] = mag;
+}
+
+// More than 16384 columns: one wavefront per row, element-wise strided loops; the row is read again for the second pass
 // (from res_out when the addition was done).
 __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_generic_kernel(
     const uint16_t* res, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
@@ -165,17 +279,16 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_generic_kernel(
     if (threadIdx.x == 0) partial[blockIdx.x] = mag;
 }
 
-// Recompute path: rstd [M] and the scale are given.  Lane = PR rows x 8 columns (PR = 16 with the
-// transposed copy, else 4); M % PR == 0, C % 8 == 0.
+// Recompute path: rstd [M] and the scale are given, no transposed copy.  Lane = 4 rows x 8 columns; M % 4 == 0, C % 8 == 0.
 constexpr int kRnLanesR = 8;
 constexpr int kRnBlockCols = 8 * (kWave / kRnLanesR) * (kRnThreads / kWave);
 
-template <int PR, int QFMT, bool TRANSPOSE, bool WRITE_Y>
+template <int QFMT, bool WRITE_Y>
 __global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_patch_kernel(
     const uint16_t* __restrict__ res, const uint16_t* __restrict__ w, const float* __restrict__ rstd,
-    int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
-    uint8_t* __restrict__ qt, uint16_t* __restrict__ y, unsigned grid_cols) {
-    static_assert(!TRANSPOSE || PR == 16, "the register transpose works on 16 x 8 patches");
+    int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q, uint16_t* __restrict__ y,
+    unsigned grid_cols) {
+    constexpr int PR = 4;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const unsigned brow = blockIdx.x / grid_cols, bcol = blockIdx.x % grid_cols;     // walk along the columns
@@ -187,54 +300,25 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_patch_kernel(
 #pragma unroll
     for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * C));
     const v4u wv = *reinterpret_cast<const v4u*>(w + c0);
-    float rs[PR];
-#pragma unroll
-    for (int i = 0; i < PR / 4; ++i) {
-        const v4f t = *reinterpret_cast<const v4f*>(rstd + r0 + 4 * i);
-        rs[4 * i] = t[0]; rs[4 * i + 1] = t[1]; rs[4 * i + 2] = t[2]; rs[4 * i + 3] = t[3];
-    }
+    const v4f rs = *reinterpret_cast<const v4f*>(rstd + r0);
     const float s = *d_qscale;
-    unsigned wq[PR][2];
+    uint8_t* dq = q + r0 * C + c0;
 #pragma unroll
     for (int i = 0; i < PR; ++i) {
         const v4u o = normalize8(in[i], rs[i], wv);
         if constexpr (WRITE_Y) *reinterpret_cast<v4u*>(y + (r0 + i) * C + c0) = o;
-        quantize8<QFMT>(o, s, wq[i][0], wq[i][1]);
-    }
-    uint8_t* dq = q + r0 * C + c0;
-#pragma unroll
-    for (int i = 0; i < PR; ++i) {
-        v2u v = {wq[i][0], wq[i][1]};
-        *reinterpret_cast<v2u*>(dq + (int64_t)i * C) = v;
-    }
-    if constexpr (TRANSPOSE) {
-        uint8_t* dt = qt + c0 * M + r0;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            unsigned col[4][4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                unsigned blk[4] = {wq[4 * t][k], wq[4 * t + 1][k], wq[4 * t + 2][k], wq[4 * t + 3][k]};
-                unsigned ot[4];
-                transpose4x4_bytes(blk, ot);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) col[c][t] = ot[c];
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                v4u v = {col[c][0], col[c][1], col[c][2], col[c][3]};
-                *reinterpret_cast<v4u*>(dt + (int64_t)(4 * k + c) * M) = v;
-            }
-        }
+        unsigned lo, hi;
+        quantize8<QFMT>(o, s, lo, hi);
+        *reinterpret_cast<v2u*>(dq + (int64_t)i * C) = v2u{lo, hi};
     }
 }
 
-// The same for tensors made of whole 128 x 256 tiles: lane geometry and LDS transpose of the quantize kernel's tile
+// With the transposed copy, tensors made of whole 128 x 256 tiles: lane geometry and LDS transpose of the quantize kernel's tile
 // variant (full 128-byte lines on every stream; the transposed copy optionally in slabs).
-template <int QFMT, bool WRITE_Y>
+template <int QFMT, bool WRITE_Y, bool STREAM>
 __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_tile_kernel(
     const uint16_t* __restrict__ res, const uint16_t* __restrict__ w, const float* __restrict__ rstd,
-    int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
+    int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
     uint8_t* __restrict__ qt, uint16_t* __restrict__ y, unsigned grid_cols, int64_t qt_row_stride,
     int64_t qt_band_stride) {
     __shared__ __attribute__((aligned(16))) uint8_t s_t[kTileLdsBytes];
@@ -264,28 +348,44 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_tile_kernel(
     }
     uint8_t* dq = q + r0 * C + c0;
 #pragma unroll
-    for (int i = 0; i < kPatchRows; ++i) *reinterpret_cast<v2u*>(dq + (int64_t)i * C) = v2u{wq[i][0], wq[i][1]};
+    for (int i = 0; i < kPatchRows; ++i) store_hinted<STREAM>(v2u{wq[i][0], wq[i][1]}, reinterpret_cast<v2u*>(dq + (int64_t)i * C));
     tile_stage_transposed(wq, tr, tc, s_t);
     __syncthreads();
     tile_write_transposed(s_t, qt + (int64_t)bcol * kTileCols * qt_row_stride + (int64_t)brow * qt_band_stride, qt_row_stride);
 }
 
-template <int QFMT>
-__global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_generic_kernel(
+// Ragged shapes and tensors of few tiles: the 64 x 128 tile; y (if not NULL), q and the transposed copy (TRANSPOSE).
+template <int QFMT, bool TRANSPOSE>
+__global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     const uint16_t* __restrict__ res, const uint16_t* __restrict__ w, const float* __restrict__ rstd,
     int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
-    uint8_t* __restrict__ qt, uint16_t* __restrict__ y) {
-    const int64_t n = M * C;
+    uint8_t* __restrict__ qt, uint16_t* __restrict__ y, const SmallGrid grid, int64_t qt_row_stride, int64_t qt_band_stride) {
+    __shared__ __attribute__((aligned(16))) uint8_t s_t[TRANSPOSE ? kSmallLdsBytes : 16];
+    unsigned brow, bcol;
+    if (!small_tile(grid, brow, bcol)) return;
+    int tr, tc;
+    small_patch_origin(tr, tc);
+    const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
+    const int64_t rows_left = M - r0, cols_left = C - c0;
+    v4u in[kSmallPatch];
+    load_patch_upto(in, res + r0 * C + c0, C, rows_left, cols_left);
+    const v4u wv = load8_upto(w + c0, cols_left);
+    float rs[kSmallPatch];
+#pragma unroll
+    for (int i = 0; i < kSmallPatch; ++i) rs[i] = i < rows_left ? rstd[r0 + i] : 0.0f;
     const float s = *d_qscale;
-    for (int64_t idx = (int64_t)blockIdx.x * kRnThreads + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * kRnThreads) {
-        const int64_t m = idx / C, c = idx - m * C;
-        const float t = __uint_as_float((unsigned)res[idx] << 16) * rstd[m];
-        const unsigned bits = rn_pack(t * __uint_as_float((unsigned)w[c] << 16), 0.0f) & 0xFFFFu;
-        if (y) y[idx] = (uint16_t)bits;
-        const float p = __uint_as_float(bits << 16) * s;
-        const unsigned code = cvt_pair<QFMT>(p, p, 0u, false) & 0xFFu;
-        q[idx] = (uint8_t)code;
-        if (qt) qt[c * M + m] = (uint8_t)code;
+    unsigned wq[kSmallPatch][2];
+#pragma unroll
+    for (int i = 0; i < kSmallPatch; ++i) {
+        in[i] = normalize8(in[i], rs[i], wv);
+        quantize8<QFMT>(in[i], s, wq[i][0], wq[i][1]);
+    }
+    if (y) store_patch_upto(in, y + r0 * C + c0, C, rows_left, cols_left);
+    store_codes_upto(wq, q + r0 * C + c0, C, rows_left, cols_left);
+    if constexpr (TRANSPOSE) {
+        small_stage_transposed(wq, tr, tc, s_t);
+        __syncthreads();
+        small_write_transposed_upto(s_t, qt + C0 * qt_row_stride + (R0 / kTileRows) * qt_band_stride + R0 % kTileRows, qt_row_stride, M - R0, C - C0);
     }
 }
 
@@ -300,9 +400,26 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     uint16_t* res_out = reinterpret_cast<uint16_t*>(res_out_);
     uint16_t* y = reinterpret_cast<uint16_t*>(y_);
     const dim3 grid((unsigned)rmsnorm_blocks(M)), block(kRnThreads);
-    if (C % 8 == 0 && C <= kRnMaxC) {
-        if (x) hipLaunchKernelGGL((rmsnorm_row_kernel<true>), grid, block, 0, stream, res, x, w, M, (int)C, eps, res_out, y, rstd, partial);
-        else hipLaunchKernelGGL((rmsnorm_row_kernel<false>), grid, block, 0, stream, res, x, w, M, (int)C, eps, res_out, y, rstd, partial);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, res, x, w, M, (int)C, eps, res_out, y, rstd, partial); };
+    const bool edge = C % 8 != 0;
+    auto rows = [&](auto vpl) {
+        constexpr int V = decltype(vpl)::value;
+        const bool out = !edge && streams_out((x ? 4 : 2) * M * C);
+        if (x) { if (edge) launch(rmsnorm_rows_kernel<true, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<true, false, V, true>); else launch(rmsnorm_rows_kernel<true, false, V, false>); }
+        else { if (edge) launch(rmsnorm_rows_kernel<false, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<false, false, V, true>); else launch(rmsnorm_rows_kernel<false, false, V, false>); }
+    };
+    // A wave per row as long as a row is at most four vectors per lane; from there on the workgroup reads its rows together.
+    if (C <= kRnRowC) {
+        if (x) { if (edge) launch(rmsnorm_row_kernel<true, true>); else launch(rmsnorm_row_kernel<true, false>); }
+        else { if (edge) launch(rmsnorm_row_kernel<false, true>); else launch(rmsnorm_row_kernel<false, false>); }
+    } else if (C <= 2 * kRnThreads * 8) {
+        rows(IntTag<2>{});
+    } else if (C <= 3 * kRnThreads * 8) {
+        rows(IntTag<3>{});
+    } else if (C <= 4 * kRnThreads * 8) {
+        rows(IntTag<4>{});
+    } else if (C <= 8 * kRnThreads * 8) {
+        rows(IntTag<8>{});
     } else {
         hipLaunchKernelGGL(rmsnorm_row_generic_kernel, grid, block, 0, stream, res, x, w, M, C, eps, res_out, y, rstd, partial);
     }
@@ -310,34 +427,25 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     return launch_amax_final(partial, (int)rmsnorm_blocks(M), fmt, d_amax, d_scale, stream);
 }
 
-static bool use_tile_kernel() {       // LLMQ_FUSED_TILE=0 (tuning override): patch kernels also for whole tiles
-    if (const char* e = tuning_env("LLMQ_FUSED_TILE")) return atoi(e) != 0;
-    return true;
-}
-
 template <int QFMT>
 static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rstd, int64_t M, int64_t C,
                          const float* d_qscale, uint8_t* q, uint8_t* q_t, uint16_t* y, hipStream_t stream,
                          bool qt_slabs) {
-    const dim3 block(kRnThreads);
-    const unsigned gc = (unsigned)((C + kRnBlockCols - 1) / kRnBlockCols);
-    if (q_t && tile_shape_ok(M, C) && (qt_slabs || use_tile_kernel())) {
+    const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
+    if (q_t && takes_large_tile(M, C, 2304)) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
-        const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
-        if (y) hipLaunchKernelGGL((rmsnorm_apply_fp8_tile_kernel<QFMT, true>), dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride);
-        else hipLaunchKernelGGL((rmsnorm_apply_fp8_tile_kernel<QFMT, false>), dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride);
-    } else if (q_t && M % 16 == 0 && C % 8 == 0) {
-        const dim3 grid((unsigned)((M + 16 * kRnLanesR - 1) / (16 * kRnLanesR)) * gc);
-        if (y) hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<16, QFMT, true, true>), grid, block, 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, gc);
-        else hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<16, QFMT, true, false>), grid, block, 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, gc);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
+        if (streams_out(2 * M * C)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }
+        else { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, false>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, false>); }
     } else if (!q_t && M % 4 == 0 && C % 8 == 0) {
+        const unsigned gc = (unsigned)((C + kRnBlockCols - 1) / kRnBlockCols);
         const dim3 grid((unsigned)((M + 4 * kRnLanesR - 1) / (4 * kRnLanesR)) * gc);
-        if (y) hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<4, QFMT, false, true>), grid, block, 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, gc);
-        else hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<4, QFMT, false, false>), grid, block, 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, gc);
+        if (y) hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<QFMT, true>), grid, dim3(kRnThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, y, gc);
+        else hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<QFMT, false>), grid, dim3(kRnThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, y, gc);
     } else {
-        int64_t blocks = (M * C + kRnThreads - 1) / kRnThreads;
-        if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL((rmsnorm_apply_fp8_generic_kernel<QFMT>), dim3((unsigned)blocks), block, 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y);
+        const SmallGrid g = small_grid(M, C);
+        if (q_t) hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, true>), dim3(g.blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
+        else hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, false>), dim3(g.blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
     }
 }
 

@@ -1,0 +1,108 @@
+"""GPU parity of the element-wise kernels at the edges of their tiles (64 x 128 and 128 x 256), vectors and row widths,
+byte for byte against the oracle; nothing behind an output may be written."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_15306_amd import llmq, synth
+from gpu_common import DEV, f32_bits, np_f32_bits
+from test_gpu_rmsnorm import EPS, RSTD_TOL, _case as rms_case
+from test_gpu_swiglu import _case as swiglu_case
+
+pytestmark = pytest.mark.gpu
+PAD = 256
+
+
+def _out(n, dtype, fill):
+    """n elements followed by PAD sentinels"""
+    return torch.full((n + PAD,), fill, dtype=dtype, device=DEV)
+
+
+def _whole(buf, n, fill):
+    assert bool((buf[n:] == fill).all()), "written behind the end"
+    return buf[:n]
+
+
+SHAPES = [(1, 1), (1, 7), (3, 9), (63, 127), (64, 128), (65, 129), (66, 136), (129, 257), (200, 250), (127, 513), (16, 264), (300, 1001)]
+FORCED = [(128, 256), (256, 512), (384, 256)]            # whole tiles: both tile kernels, plain and slabs
+
+
+def _slabs(qt, rows, cols):
+    return qt.reshape(cols, rows // 128, 128).transpose(1, 0, 2).reshape(-1)
+
+
+@pytest.mark.parametrize("rows,cols,tile", [s + (None,) for s in SHAPES] + [s + (t,) for s in FORCED for t in "01"])
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_codes_of_every_producer(rows, cols, tile, fmt, monkeypatch):
+    if tile is not None:
+        monkeypatch.setenv("LLMQ_QUANT_TILE", tile)
+    print("codes rows=%d cols=%d tile=%s fmt=%d" % (rows, cols, tile, fmt), flush=True)
+    n = rows * cols
+    gu, _ = swiglu_case(rows, cols, 31 + rows + cols)
+    res, _, w = rms_case(rows, cols, 37 + rows + cols)
+    h = oracle.swiglu_fwd(synth.bf16_bits(gu))
+    rstd = oracle.rms_rstd(synth.bf16_bits(res), EPS).astype(np.float32)
+    y = oracle.rmsnorm_apply(synth.bf16_bits(res), synth.bf16_bits(w), rstd)
+    x_d, gu_d, w_d, rstd_d = res.to(DEV), gu.to(DEV), w.to(DEV), torch.from_numpy(rstd).to(DEV)
+    for bits, plain, slabs in (
+            (synth.bf16_bits(res), lambda s, q, qt: llmq.llmq_quantize_fp8(x_d, s, fmt, q, qt), lambda s, q, qt: llmq.llmq_quantize_fp8_slabs(x_d, s, fmt, q, qt)),
+            (h, lambda s, q, qt: llmq.llmq_swiglu_fwd_fp8(gu_d, s, fmt, q, qt, None), lambda s, q, qt: llmq.llmq_swiglu_fwd_fp8_slabs(gu_d, s, fmt, q, qt, None)),
+            (y, lambda s, q, qt: llmq.llmq_rmsnorm_apply_fp8(x_d, w_d, rstd_d, s, fmt, q, qt, None), lambda s, q, qt: llmq.llmq_rmsnorm_apply_fp8_slabs(x_d, w_d, rstd_d, s, fmt, q, qt, None))):
+        sc = oracle.scale(oracle.amax_bf16(bits), fmt)
+        if not np.isfinite(sc) or sc == 0:
+            continue
+        want_q, want_qt = oracle.quantize(bits.reshape(rows, cols), sc, fmt)
+        s_d = torch.tensor([float(sc)], dtype=torch.float32, device=DEV)
+        calls = [(plain, want_qt.reshape(-1)), (plain, None)] + ([(slabs, _slabs(want_qt, rows, cols))] if tile is not None else [])
+        for call, want in calls:
+            q, qt = _out(n, torch.uint8, 0xAA), _out(n, torch.uint8, 0xAA)
+            call(s_d, q[:n], None if want is None else qt[:n])
+            assert np.array_equal(_whole(q, n, 0xAA).cpu().numpy(), want_q.reshape(-1))
+            if want is not None:
+                assert np.array_equal(_whole(qt, n, 0xAA).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("M,I", [(1, 1), (3, 9), (5, 511), (4, 512), (7, 513), (130, 1001), (2, 1030)])
+def test_swiglu_forward_and_backward_of_ragged_shapes(M, I):
+    gu, dh = swiglu_case(M, I, 3 * M + I)
+    gu[0, 0] = -90.0                          # below the range of the short sigmoid, and far below
+    if I > 8:
+        gu[M - 1, I - 1] = -300.0
+        gu[0, 8] = -86.5
+    gu_d, dh_d, n = gu.to(DEV), dh.to(DEV), M * I
+    ws = torch.full((llmq.llmq_swiglu_workspace_bytes(M, I) + PAD,), 0xFF, dtype=torch.uint8, device=DEV)
+    f = torch.zeros(4, dtype=torch.float32, device=DEV)
+    h, dgu = _out(n, torch.bfloat16, -7.0), _out(2 * n, torch.bfloat16, -7.0)
+    wsv = ws[:ws.numel() - PAD]
+    llmq.llmq_swiglu_fwd(gu_d, h[:n], 0, f[0:1], f[1:2], wsv)
+    llmq.llmq_swiglu_bwd(dh_d, gu_d, dgu[:2 * n], 1, f[2:3], f[3:4], wsv)
+    want_h, want_d = oracle.swiglu_fwd(synth.bf16_bits(gu)), oracle.swiglu_bwd(synth.bf16_bits(dh), synth.bf16_bits(gu))
+    assert np.array_equal(synth.bf16_bits(_whole(h, n, -7.0)), want_h.reshape(-1))
+    assert np.array_equal(synth.bf16_bits(_whole(dgu, 2 * n, -7.0)), want_d.reshape(-1))
+    assert f32_bits(f[0:1]) == np_f32_bits(oracle.amax_bf16(want_h)) and f32_bits(f[2:3]) == np_f32_bits(oracle.amax_bf16(want_d))
+    assert bool((ws[-PAD:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("M", [1, 4, 7])
+@pytest.mark.parametrize("C", [1, 511, 512, 2047, 2048, 2049, 4096, 4097, 6144, 6145, 8191, 8192, 8200, 12289, 16384, 16385])
+@pytest.mark.parametrize("with_x", [True, False])
+def test_rmsnorm_forward_at_the_edges_of_its_widths(M, C, with_x):
+    res, x, w = rms_case(M, C, M + C)
+    x = x if with_x else None
+    n = M * C
+    ro, y, rstd = _out(n, torch.bfloat16, -7.0), _out(n, torch.bfloat16, -7.0), _out(M, torch.float32, -7.0)
+    f = torch.zeros(2, dtype=torch.float32, device=DEV)
+    ws = torch.full((llmq.llmq_rmsnorm_workspace_bytes(M) + PAD,), 0xFF, dtype=torch.uint8, device=DEV)
+    llmq.llmq_rmsnorm_fwd(res.to(DEV), None if x is None else x.to(DEV), w.to(DEV), EPS, ro[:n] if with_x else None, y[:n], rstd[:M], 0,
+                          f[0:1], f[1:2], ws[:ws.numel() - PAD])
+    new = oracle.residual_add(synth.bf16_bits(res), synth.bf16_bits(x)) if with_x else synth.bf16_bits(res)
+    if with_x:
+        assert np.array_equal(synth.bf16_bits(_whole(ro, n, -7.0)), new.reshape(-1))
+    want = oracle.rms_rstd(new, EPS)
+    got = _whole(rstd, M, -7.0).cpu().numpy()
+    assert np.all(np.abs(got - want) <= RSTD_TOL * want)
+    want_y = oracle.rmsnorm_apply(new, synth.bf16_bits(w), got)          # the formula with the statistic the kernel found
+    assert np.array_equal(synth.bf16_bits(_whole(y, n, -7.0)), want_y.reshape(-1))
+    assert f32_bits(f[0:1]) == np_f32_bits(oracle.amax_bf16(want_y))
+    assert bool((ws[-PAD:] == 0xFF).all())

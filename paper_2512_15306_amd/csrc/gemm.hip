@@ -125,6 +125,12 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
         const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
         if (ni >= 2 && ni <= 4 && nj >= 2 && nj <= 4 && R % (64 * ni) == 0 && C % (64 * nj) == 0) return TileChoice{ni, nj};
     }
+    // At most one 128 x 128 tile per CU: that tile, with four LDS stages, whatever the model says about larger ones (1024 x
+    // 3072 x 3072: 14.6 us against 18.0 with 192 x 128 tiles; 128 x 9984 x 13184: 68 against 98).  Contractions long enough
+    // for sharing out tiles keep the model's choice when there is scratch for it.
+    if (R % 128 == 0 && C % 128 == 0 && (scratch_bytes == 0 || T / BK < 64) &&
+        (R / 128) * (C / 128) <= resident_slots(num_cus, 2, 2) / 2)
+        return TileChoice{2, 2};
     double best_cost = 0;
     for (int ni = 4; ni >= 2; --ni)
         for (int nj = 4; nj >= 2; --nj) {
@@ -157,6 +163,7 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
         const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
         if ((ni == 2 || ni == 4) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
     }
+    if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
     double best_cost = 0;
     for (int ni = 4; ni >= 2; ni -= 2)
         for (int nj = 4; nj >= 2; nj -= 2) {

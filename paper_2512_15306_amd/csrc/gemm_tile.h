@@ -120,6 +120,8 @@ struct GemmTuning {
     // Scheduling fences between the 32-row blocks of the epilogue: without them the compiler hoists every
     // de-scale multiply to the front and parks the products in accumulator registers.
     static constexpr bool kEpilogueFence = true;
+    // LDS stages: how many K steps are resident or on their way (see GemmDeepTuning).
+    static constexpr int kStages = 2;
     // Phase stamps (llmq_calibrate_gemm_phases): a tuning struct with kProfile = true also provides
     //   static __device__ void record(float* buf, int block, int slot, long long value)
     // and wave 0 of every workgroup stamps the cycle counter and the 100 MHz clock at the start (slots 0, 8),
@@ -130,6 +132,17 @@ struct GemmTuning {
     // The fused output absmax with the IEEE 754-2019 maximum (v_maximum3_f32: two elements per instruction, NaN
     // propagates) or, for comparison in the phase stamps only, with maxNum (v_max_f32 per element, NaN dropped).
     static constexpr bool kIeeeMaximum = true;
+};
+
+// For problems of at most one 128 x 128 tile per CU.  Alone on its CU, a workgroup of that size with two stages waits for its
+// loads in every K step: a slab is requested one step before it is needed, and a step (16 MFMAs per wave) is shorter than
+// the way from the L2 or beyond.  Four stages (128 KB of LDS) request it three steps ahead; the sums keep their order.
+// R x C x T = 512 x 4096 x 4096 23.2 -> 15.8 us, 128 x 13184 x 9984 77 -> 54, 1777 x 960 x 2880 21.6 -> 16.0, 4096 x 1024 x 4096
+// 25.1 -> 19.2; with more tiles than CUs two workgroups of two stages cover each other better (1777 x 2880 x 960, 322 tiles:
+// 14.9 against 17.2).
+struct GemmDeepTuning : GemmTuning {
+    static constexpr bool kTouch = false;
+    static constexpr int kStages = 4;
 };
 
 template <bool B>
@@ -148,6 +161,14 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The same where direct-to-LDS loads of later stages stay in flight: the fences above would wait for all of them (they
+// write LDS).  LDS reads are waited for by hand, the statements keep memory accesses on their side of the barrier.
+__device__ inline void lds_barrier_in_flight() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // Operand kinds of the tuned kernel: 0 = E4M3, 1 = E5M2 (one byte per element, any mix), 2 = BF16 (both
@@ -317,10 +338,20 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     // One array per stage and operand: distinct LDS objects let the compiler see that the
     // direct-to-LDS loads of one stage do not alias the fragment reads of the other, so it does
     // not make the reads wait for the loads in flight.
-    __shared__ __attribute__((aligned(1024))) uint8_t ldsA0[kSlabA];
-    __shared__ __attribute__((aligned(1024))) uint8_t ldsB0[kSlabB];
-    __shared__ __attribute__((aligned(1024))) uint8_t ldsA1[kSlabA];
-    __shared__ __attribute__((aligned(1024))) uint8_t ldsB1[kSlabB];
+    // With four stages there would be more of them than the compiler tells apart, so there it is one per stage.
+    constexpr int ST = V::kStages;
+    static_assert(ST == 2 || (ST == 4 && !V::kTouch && !UA && MODE == kWholeTiles), "four stages: direct-to-LDS loads without touch loads");
+    constexpr int kPair = ST == 2 ? 16 : kSlabA + kSlabB, kOneA = ST == 2 ? kSlabA : 16, kOneB = ST == 2 ? kSlabB : 16;
+    __shared__ __attribute__((aligned(1024))) uint8_t s_a0[kOneA];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_b0[kOneB];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_a1[kOneA];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_b1[kOneB];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_p0[kPair];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_p1[kPair];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_p2[kPair];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_p3[kPair];
+    uint8_t *const ldsA0 = ST == 2 ? s_a0 : s_p0, *const ldsB0 = ST == 2 ? s_b0 : s_p0 + kSlabA;
+    uint8_t *const ldsA1 = ST == 2 ? s_a1 : s_p1, *const ldsB1 = ST == 2 ? s_b1 : s_p1 + kSlabA;
     // Four words for the workgroup's output absmax.  The epilogue stages 2048 NJ bytes per wave at the start
     // of the slabs (8192 NJ bytes in the case of this one), so the end of the last slab is free by then; the
     // kernel's LDS is exactly its slabs.
@@ -643,12 +674,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         // the direct-to-LDS loads of the previous step must have landed; its two touch loads, issued
         // after them, may still be in flight
         // (kEdgeUnaligned: the slab was written by ordinary LDS stores, which the barrier orders)
-        if constexpr (UA) {} else if constexpr (kTouch) wait_vmcnt<2>(); else wait_vmcnt<0>();
-        lds_barrier();
+        if constexpr (UA) {} else if constexpr (kTouch) wait_vmcnt<2>(); else wait_vmcnt<(ST - 2) * kLoadsPerStep>();
+        if constexpr (ST == 2) lds_barrier(); else lds_barrier_in_flight();
         __builtin_amdgcn_sched_barrier(0);
         int baseA, baseB;
-        load_base(kt + 2 < nk ? kb + kt + 2 : -1, baseA, baseB);
-        voffs_of_step(kt + 2);
+        load_base(kt + ST < nk ? kb + kt + ST : -1, baseA, baseB);
+        voffs_of_step(kt + ST);
         const int fetch_step = kt + 3 < nk ? kt + 3 : nk - 1;        // kEdgeUnaligned: the loads run a step ahead of the LDS writes
         mma_quadrant<FA, FB, Y0, HJ, true>(acc, aY, bH, [&](auto m) {
             readsB_of_slot(nxtB, IntTag<0>{}, bL, m);     // past the last slab this reads bytes that are never used
@@ -684,23 +715,39 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     } else {
     issue_loads(ldsA0, ldsB0, kb);
     issue_loads(ldsA1, ldsB1, nk > 1 ? kb + 1 : -1);
+    if constexpr (ST == 4) {
+        issue_loads(s_p2, s_p2 + kSlabA, nk > 2 ? kb + 2 : -1);
+        issue_loads(s_p3, s_p3 + kSlabA, nk > 3 ? kb + 3 : -1);
+    }
     }
     if constexpr (kTouch) {                       // keep "two touch loads are the newest" true from the start
         const bool on = touch_ahead > 0 && 2 < nk;
         touchA[1] = __builtin_amdgcn_raw_buffer_load_b32(rsA, touch_voffA, on ? (kb + 2) * ksA : kOutOfRange, 0);
         touchB[1] = __builtin_amdgcn_raw_buffer_load_b32(rsB, touch_voffB, on ? (kb + 2) * ksB : kOutOfRange, 0);
     }
-    if constexpr (!UA) wait_vmcnt<kLoadsPerStep + (kTouch ? 2 : 0)>();
-    lds_barrier();
+    if constexpr (!UA) wait_vmcnt<(ST - 1) * kLoadsPerStep + (kTouch ? 2 : 0)>();
+    if constexpr (ST == 2) lds_barrier(); else lds_barrier_in_flight();
     read_fragsA(ldsA0, IntTag<0>{}, aL);
     read_fragsB(ldsB0, IntTag<0>{}, bL);
     stamp(1);
     int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
-        k_step(ldsA1, ldsB1, ldsA0, ldsB0, kt + 1, 1, BoolTag<true>{});
+    if constexpr (ST == 2) {
+        for (; kt + 1 < nk; kt += 2) {
+            k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
+            k_step(ldsA1, ldsB1, ldsA0, ldsB0, kt + 1, 1, BoolTag<true>{});
+        }
+        if (kt < nk) k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
+    } else {
+        for (; kt + 3 < nk; kt += 4) {
+            k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
+            k_step(ldsA1, ldsB1, s_p2, s_p2 + kSlabA, kt + 1, 1, BoolTag<true>{});
+            k_step(s_p2, s_p2 + kSlabA, s_p3, s_p3 + kSlabA, kt + 2, 0, BoolTag<false>{});
+            k_step(s_p3, s_p3 + kSlabA, ldsA0, ldsB0, kt + 3, 1, BoolTag<true>{});
+        }
+        if (kt < nk) k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
+        if (kt + 1 < nk) k_step(ldsA1, ldsB1, s_p2, s_p2 + kSlabA, kt + 1, 1, BoolTag<true>{});
+        if (kt + 2 < nk) k_step(s_p2, s_p2 + kSlabA, s_p3, s_p3 + kSlabA, kt + 2, 0, BoolTag<false>{});
     }
-    if (kt < nk) k_step(ldsA0, ldsB0, ldsA1, ldsB1, kt, 0, BoolTag<false>{});
     // The last block updates must have left the matrix pipeline before ordinary instructions read the accumulators
     // (the compiler cannot count these wait states for a written-out MFMA).
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
@@ -1082,6 +1129,13 @@ inline int resident_slots(int num_cus, int ni, int nj) {
     return (num_cus / kXcds) * kXcds * ((ni == 2 && nj == 2) ? 2 : 1);
 }
 
+// Whether a problem of nt 2 x 2 tiles takes four LDS stages: one workgroup per CU then has the CU's LDS to itself.
+// LLMQ_GEMM_DEEP=0 / 1 overrides it for tests.
+inline bool deep_stages(int nt, int slots) {
+    if (const char* e = tuning_env("LLMQ_GEMM_DEEP")) return atoi(e) != 0;
+    return nt <= slots / 2;
+}
+
 // The tile shape whose kernels exist in the tile-sharing form (for contraction-contiguous operands only): the
 // largest one, which is what problems big enough to have a ragged last round worth sharing get.
 constexpr bool split_supported(int ni, int nj) { return ni == 4 && nj == 4; }
@@ -1202,6 +1256,13 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
         }
     }
     if (sc.n_whole == 0) return;
+    if constexpr (NI == 2 && NJ == 2) {
+        if (deep_stages(nt, slots)) {
+            if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB>, grid, plan);
+            else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmDeepTuning, TA, TB>, grid, plan);
+            return;
+        }
+    }
     if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB>, grid, plan);
     else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmTuning, TA, TB>, grid, plan);
 }
@@ -1216,7 +1277,7 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
 
 template <int FA, int FB, int NI, int NJ, bool TA, bool TB, int EDGE>
 static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
-                        void* c, int accumulate, unsigned* amax, hipStream_t stream, bool slabs_a, bool slabs_b) {
+                        void* c, int accumulate, unsigned* amax, hipStream_t stream, int num_cus, bool slabs_a, bool slabs_b) {
     const int ldA = TA ? (int)R : slabs_a ? BK : (int)T, ldB = TB ? (int)C : slabs_b ? BK : (int)T;
     const int ksA = slabs_a ? (int)(R * BK) : BK, ksB = slabs_b ? (int)(C * BK) : BK;
     const int tiles_r = (int)((R + 64 * NI - 1) / (64 * NI)), tiles_c = (int)((C + 64 * NJ - 1) / (64 * NJ));
@@ -1227,9 +1288,18 @@ static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     const int band = band_rows();
     const int share_b = band < tiles_r ? band : tiles_r, share_a = 4 < tiles_c ? 4 : tiles_c;
     // (no requests for the next workgroup's first slabs: they would need the same guards as the loads)
-    hipLaunchKernelGGL((gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB, kWholeTiles, EDGE>), dim3(grid), dim3(kGemmThreads), 0, stream,
-                       A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c, touch, band, 0,
-                       ldA, ldB, ksA, ksB, share_a, share_b, plan, (int)R, accumulate);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGemmThreads), 0, stream,
+                           A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c, touch, band, 0,
+                           ldA, ldB, ksA, ksB, share_a, share_b, plan, (int)R, accumulate);
+    };
+    if constexpr (NI == 2 && NJ == 2 && EDGE == kEdge) {
+        if (deep_stages(plan.n_whole, resident_slots(num_cus, NI, NJ))) {
+            launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB, kWholeTiles, EDGE>);
+            return;
+        }
+    }
+    launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB, kWholeTiles, EDGE>);
 }
 
 #define LLMQ_EDGE_LAUNCH_PARAMS                                                                                   \
@@ -1241,8 +1311,8 @@ bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
     const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b);
 #define LLMQ_EDGE_CASE(I, J)                                                                                        \
     case I * 8 + J:                                                                                                 \
-        if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); \
-        else launch_edge<FA, FB, I, J, TA, TB, kEdgeUnaligned>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b);         \
+        if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); \
+        else launch_edge<FA, FB, I, J, TA, TB, kEdgeUnaligned>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b);         \
         return true;
     switch (ec.ni * 8 + ec.nj) {
         LLMQ_EDGE_CASE(4, 4) LLMQ_EDGE_CASE(4, 2) LLMQ_EDGE_CASE(2, 4) LLMQ_EDGE_CASE(2, 2)

@@ -45,15 +45,29 @@ static unsigned* static_scratch_of_current_device() {
 constexpr int kAmaxThreads = 256;
 constexpr int kAmaxUnroll = 8;          // 16-byte loads in flight per lane
 
-// partial[b] = largest BF16 magnitude pattern (15 bits) seen by block b
-__global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(
-    const v4u* __restrict__ x, size_t n_vec, const uint16_t* __restrict__ tail, int n_tail,
-    unsigned* __restrict__ partial) {
+// One tensor of a first-stage launch: its vectors and trailing elements, where its partial results go and how many
+// workgroups it has.
+struct AmaxTensor {
+    const v4u* x;
+    size_t n_vec;
+    const uint16_t* tail;
+    int n_tail;
+    unsigned* partial;
+    unsigned blocks;
+};
+
+// partial[b] = largest BF16 magnitude pattern (15 bits) seen by block b.  A launch takes one tensor (second.blocks == 0) or
+// two, whose workgroups run side by side: the forward pass of a small layer is made of launches.
+__global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(const AmaxTensor first, const AmaxTensor second) {
     __shared__ unsigned s_part[kAmaxThreads / kWave];
+    const bool is_first = blockIdx.x < first.blocks;
+    const unsigned block = is_first ? blockIdx.x : blockIdx.x - first.blocks, blocks = is_first ? first.blocks : second.blocks;
+    const v4u* __restrict__ x = is_first ? first.x : second.x;
+    const size_t n_vec = is_first ? first.n_vec : second.n_vec;
     unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;      // packed pairs of 15-bit magnitudes
     const size_t chunk = (size_t)kAmaxThreads * kAmaxUnroll;
     const size_t n_full = n_vec / chunk;
-    for (size_t c = blockIdx.x; c < n_full; c += gridDim.x) {
+    for (size_t c = block; c < n_full; c += blocks) {
         const v4u* p = x + c * chunk + threadIdx.x;
         v4u r[kAmaxUnroll];
 #pragma unroll
@@ -66,7 +80,7 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(
             m3 = pk_max_mag(m3, r[j][3]);
         }
     }
-    if (blockIdx.x == gridDim.x - 1) {            // the partial chunk and the n % 8 trailing elements
+    if (block == blocks - 1) {                    // the partial chunk and the n % 8 trailing elements
         for (size_t i = n_full * chunk + threadIdx.x; i < n_vec; i += kAmaxThreads) {
             v4u r = x[i];
             m0 = pk_max_mag(m0, r[0]);
@@ -74,12 +88,13 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(
             m2 = pk_max_mag(m2, r[2]);
             m3 = pk_max_mag(m3, r[3]);
         }
-        if ((int)threadIdx.x < n_tail) m0 = pk_max_mag(m0, (unsigned)tail[threadIdx.x]);
+        const uint16_t* tail = is_first ? first.tail : second.tail;
+        if ((int)threadIdx.x < (is_first ? first.n_tail : second.n_tail)) m0 = pk_max_mag(m0, (unsigned)tail[threadIdx.x]);
     }
     m0 = pk_max_mag(pk_max_mag(m0, m1), pk_max_mag(m2, m3));
     unsigned m = (m0 & 0xFFFFu) > (m0 >> 16) ? (m0 & 0xFFFFu) : (m0 >> 16);
     m = block_max_u32<kAmaxThreads>(m, s_part);
-    if (threadIdx.x == 0) partial[blockIdx.x] = m;
+    if (threadIdx.x == 0) (is_first ? first.partial : second.partial)[block] = m;
 }
 
 // amax = max over the partial results (NaN made canonical), scale = scale_of_amax(amax, FMAX)
@@ -177,9 +192,8 @@ int launch_amax_static(const void* x, size_t n, int fmt, float* d_amax, float* d
     return launch_amax(x, n, fmt, d_amax, d_scale, scratch, stream, num_cus);
 }
 
-int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus) {
+static AmaxTensor amax_tensor(const void* x, size_t n, unsigned* partial, int num_cus) {
     const size_t n_vec = n / 8;
-    const int n_tail = (int)(n % 8);
     const size_t chunk = (size_t)kAmaxThreads * kAmaxUnroll;
     const size_t chunks = n_vec / chunk;
     size_t max_blocks = (size_t)num_cus * 4;
@@ -189,10 +203,22 @@ int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_parti
     const size_t trips = (chunks + max_blocks - 1) / max_blocks;
     size_t blocks = trips > 0 ? (chunks + trips - 1) / trips : 1;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(amax_partial_kernel, dim3((unsigned)blocks), dim3(kAmaxThreads), 0, stream,
-                       reinterpret_cast<const v4u*>(x), n_vec,
-                       reinterpret_cast<const uint16_t*>(x) + n_vec * 8, n_tail, partial);
-    *n_partial = (int)blocks;
+    return AmaxTensor{reinterpret_cast<const v4u*>(x), n_vec, reinterpret_cast<const uint16_t*>(x) + n_vec * 8, (int)(n % 8), partial, (unsigned)blocks};
+}
+
+int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus) {
+    const AmaxTensor t = amax_tensor(x, n, partial, num_cus);
+    hipLaunchKernelGGL(amax_partial_kernel, dim3(t.blocks), dim3(kAmaxThreads), 0, stream, t, AmaxTensor{});
+    *n_partial = (int)t.blocks;
+    return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+int launch_amax_partial_pair(const void* x, size_t n, unsigned* partial, int* n_partial, const void* x2, size_t n2, unsigned* partial2,
+                             int* n_partial2, hipStream_t stream, int num_cus) {
+    const AmaxTensor t = amax_tensor(x, n, partial, num_cus), t2 = amax_tensor(x2, n2, partial2, num_cus);
+    hipLaunchKernelGGL(amax_partial_kernel, dim3(t.blocks + t2.blocks), dim3(kAmaxThreads), 0, stream, t, t2);
+    *n_partial = (int)t.blocks;
+    *n_partial2 = (int)t2.blocks;
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

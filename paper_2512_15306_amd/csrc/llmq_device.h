@@ -307,9 +307,8 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     g.xcd_ranges = cols % 64 != 0;
     return g;
 }
-// This workgroup's tile; false for the padding ids (id 0 always has one)
-__device__ inline bool small_tile(const SmallGrid& g, unsigned& brow, unsigned& bcol) {
-    const unsigned id = blockIdx.x;
+// The tile of workgroup id; false for the padding ids (id 0 always has one)
+__device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsigned& brow, unsigned& bcol) {
     const unsigned pos = g.xcd_ranges ? (id % kSmallXcds) * (g.blocks / kSmallXcds) + id / kSmallXcds : id;
     if (pos >= g.rows * g.cols) return false;
     const unsigned band = g.xcd_ranges && kSmallBand < g.cols ? kSmallBand : g.cols;

@@ -55,15 +55,6 @@ int launch_amax_final(const unsigned* partial, int n_partial, int fmt, float* d_
 int launch_gemm_bf16_tn(const void* A, const void* B, int64_t R, int64_t C, int64_t T, void* c_bf16,
                         int accumulate, hipStream_t stream, int num_cus);
 int launch_scale_from_amax(const float* d_amax, int fmt, float* d_scale, hipStream_t stream);
-// zero_word: if not NULL, one 32-bit word the kernel also clears (the absmax accumulator of the GEMM
-// that follows in the same call, which saves a launch).
-// qt_slabs: the transposed copy is written in slabs of 128 contraction bytes (kLayoutSlabs of the contraction that
-// reads it: [cols, rows] with rows the contraction index), which only the tile kernel does: ask
-// quantize_can_write_slabs() first (else -2).
-// read_next: the launch that follows reads the codes (see streams_out).
-int launch_quantize(const void* x, int64_t rows, int64_t cols, const float* d_scale, int fmt,
-                    uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs, bool read_next);
-bool quantize_can_write_slabs(int64_t rows, int64_t cols);
 // Where a quantizing kernel gets its scale from: a scale on the device, or the per-workgroup results of
 // the first stage of an absmax reduction over the same tensor, in which case every workgroup finishes the
 // reduction itself (at most 1024 words) and the first one also stores the scale: the second-stage launch of
@@ -76,12 +67,29 @@ struct ScaleSource {
     float* d_scale_out;          // written (by one workgroup) when partial != nullptr
 };
 
-// The same with the scale taken from a ScaleSource (a given scale, or the first-stage results of an absmax).
-int launch_quantize_from(const void* x, int64_t rows, int64_t cols, const ScaleSource& src, int fmt,
-                         uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs, bool read_next);
+// One tensor to quantize.
+//   zero_word: if not NULL, one 32-bit word the kernel also clears (the absmax accumulator of the GEMM
+//     that follows in the same call, which saves a launch).
+//   qt_slabs: the transposed copy is written in slabs of 128 contraction bytes (kLayoutSlabs of the contraction that
+//     reads it: [cols, rows] with rows the contraction index); ask quantize_can_write_slabs() first (else -2).
+struct QuantJob {
+    const void* x;
+    int64_t rows, cols;
+    ScaleSource scale;
+    uint8_t *q, *q_t;            // q_t may be NULL
+    unsigned* zero_word;
+    bool qt_slabs;
+};
+// One tensor, or two of the same format (second != NULL) in one launch where they take the same kernel.
+// read_next: the launch that follows reads the codes (see streams_out).
+int launch_quantize(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream);
+bool quantize_can_write_slabs(int64_t rows, int64_t cols);
 // First stage of the absmax only: one BF16 magnitude pattern per workgroup into partial; returns the number
 // of workgroups (<= kAmaxMaxPartials) through n_partial.
 int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus);
+// The same for two tensors in one launch.
+int launch_amax_partial_pair(const void* x, size_t n, unsigned* partial, int* n_partial, const void* x2, size_t n2, unsigned* partial2,
+                             int* n_partial2, hipStream_t stream, int num_cus);
 // Caller-owned device scratch for the binary32 pieces of output tiles whose contraction is shared among
 // several workgroups (a ragged last round of tiles); {nullptr, 0}: every tile is computed by one workgroup.
 struct GemmScratch {

@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     uint8_t* __restrict__ qt, uint16_t* __restrict__ y, const SmallGrid grid, int64_t qt_row_stride, int64_t qt_band_stride) {
     __shared__ __attribute__((aligned(16))) uint8_t s_t[TRANSPOSE ? kSmallLdsBytes : 16];
     unsigned brow, bcol;
-    if (!small_tile(grid, brow, bcol)) return;
+    if (!small_tile(grid, blockIdx.x, brow, bcol)) return;
     int tr, tc;
     small_patch_origin(tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;

@@ -115,7 +115,7 @@ __global__ void gemm_amax_reset_kernel(unsigned* amax_bits) {
 // model: every CU works through its share of the tiles, a tile costs NI * NJ MFMA blocks per K step
 // divided by the measured efficiency of that shape relative to 4 x 4 (smaller tiles read more LDS
 // and L2 bytes per MFMA; 2 x 2 tiles fit two workgroups per CU, which hide each other's stalls).
-TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes) {
+TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes, bool bf16) {
     static const float eff[5][5] = {{0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}, {0, 0, 0.90f, 0.74f, 0.77f},
                                     {0, 0, 0.74f, 0.70f, 0.83f}, {0, 0, 0.77f, 0.83f, 1.00f}};
     TileChoice best{0, 0};
@@ -142,7 +142,9 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
             const int64_t rounds = (tiles + slots - 1) / slots;
             // two resident 2 x 2 workgroups overlap each other's prologue and epilogue, which pays most
             // when the contraction is short
-            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : eff[ni][nj];
+            // (BF16 moves twice the bytes per product, which costs 128 x 128 tiles more and the 2 : 1 ones less: 4096 x 5120 x 3072
+            // takes 122 us on 256 x 128 tiles, 128 on 256 x 256 and 133 on 128 x 128, which FP8's numbers would choose)
+            const double e = per_cu == 2 ? (bf16 ? 0.66 : T <= 3072 ? 0.90 : 0.80) : bf16 && ni * nj == 8 ? 0.80 : eff[ni][nj];
             // a ragged last round may be shared out among all CUs (choose_split): the model's gain scales the cost
             const SplitChoice sc = choose_split((int)tiles, (int)(T / BK), (int)slots, ni, nj, scratch_bytes);
             const double cost = (double)rounds * per_cu * ni * nj / e * (sc.cost_us / sc.whole_cost_us);

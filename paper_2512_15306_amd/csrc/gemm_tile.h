@@ -1094,7 +1094,8 @@ struct TileChoice {
     int ni, nj;       // 0, 0: no tuned tile divides the problem, use the generic kernel
 };
 // scratch_bytes: what the launch may use for the pieces of shared tiles (0: every tile is computed whole)
-TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes);
+// bf16: operands in BF16 (T in bytes)
+TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes, bool bf16 = false);
 
 // Distance of the L2 touch loads in K steps beyond the slab the direct-to-LDS loads are fetching (measured with
 // bands 4 high on the block configurations: 1 is 0.5-0.8 % faster than 2, 3 and 4 lose 1.5 % and 4 %);
@@ -1340,7 +1341,7 @@ extern template bool launch_edge_tile<1, 0, true, true>(LLMQ_EDGE_LAUNCH_PARAMS)
         int accumulate, unsigned *amax, hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a, bool slabs_b
 template <int FA, int FB, bool TA, bool TB>
 bool launch_chosen_tile(LLMQ_TILE_LAUNCH_PARAMS) {
-    const TileChoice tc = choose_tile(R, C, T, num_cus, (scratch.ptr && !TA && !TB && FA != kFmtBf16) ? scratch.bytes : 0);
+    const TileChoice tc = choose_tile(R, C, T, num_cus, (scratch.ptr && !TA && !TB && FA != kFmtBf16) ? scratch.bytes : 0, FA == kFmtBf16);
 #define LLMQ_TILE_CASE(I, J)                                                                              \
     case I * 8 + J:                                                                                       \
         launch_tile<FA, FB, I, J, TA, TB>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b); \

@@ -106,22 +106,29 @@ struct Operand {
 // 333, where two launches' tails are saved.)
 int quantize_operands(const Operand& a, const Operand* b, int fmt, hipStream_t s) {
     const float fmax = fmt == LLMQ_E4M3 ? 448.0f : 57344.0f;
-    int n_a = 0, n_b = 0, st = 0;
     auto elements = [](const Operand& o) { return (size_t)o.rows * (size_t)o.cols; };
-    if (a.jit && b && b->jit) {
+    auto source = [&](const Operand& o, int n_partial) {
+        return o.jit ? llmq::ScaleSource{nullptr, o.partial, n_partial, fmax, o.d_scale} : llmq::ScaleSource{o.d_scale, nullptr, 0, fmax, nullptr};
+    };
+    auto one = [&](const Operand& o) {
+        int n = 0;
+        const int st = o.jit ? llmq::launch_amax_partial(o.t, elements(o), o.partial, &n, s, num_cus()) : 0;
+        return st ? st : llmq::launch_quantize_from(o.t, o.rows, o.cols, source(o, n), fmt, o.q, o.q_t, o.zero, s, o.qt_slabs);
+    };
+    if (!b || !llmq::launch_amax_partial_pair || !llmq::launch_quantize_pair) {
+        const int st = one(a);
+        return st || !b ? st : one(*b);
+    }
+    int n_a = 0, n_b = 0, st = 0;
+    if (a.jit && b->jit) {
         st = llmq::launch_amax_partial_pair(a.t, elements(a), a.partial, &n_a, b->t, elements(*b), b->partial, &n_b, s, num_cus());
     } else {
         if (a.jit) st = llmq::launch_amax_partial(a.t, elements(a), a.partial, &n_a, s, num_cus());
-        if (!st && b && b->jit) st = llmq::launch_amax_partial(b->t, elements(*b), b->partial, &n_b, s, num_cus());
+        if (!st && b->jit) st = llmq::launch_amax_partial(b->t, elements(*b), b->partial, &n_b, s, num_cus());
     }
     if (st) return st;
-    auto job = [&](const Operand& o, int n_partial) {
-        const llmq::ScaleSource src = o.jit ? llmq::ScaleSource{nullptr, o.partial, n_partial, fmax, o.d_scale}
-                                            : llmq::ScaleSource{o.d_scale, nullptr, 0, fmax, nullptr};
-        return llmq::QuantJob{o.t, o.rows, o.cols, src, o.q, o.q_t, o.zero, o.qt_slabs};
-    };
-    const llmq::QuantJob ja = job(a, n_a), jb = b ? job(*b, n_b) : llmq::QuantJob{};
-    return llmq::launch_quantize(ja, b ? &jb : nullptr, fmt, true, s);
+    auto job = [&](const Operand& o, int n) { return llmq::QuantJob{o.t, o.rows, o.cols, source(o, n), o.q, o.q_t, o.zero, o.qt_slabs}; };
+    return llmq::launch_quantize_pair(job(a, n_a), job(*b, n_b), fmt, s);
 }
 
 // What a linear call has to quantize: one operand in fmt_a, one in E4M3, either may be NULL.
@@ -130,12 +137,6 @@ int quantize_mixed(const Operand* a, int fmt_a, const Operand* b, hipStream_t s)
     int st = a ? quantize_operands(*a, nullptr, fmt_a, s) : 0;
     if (!st && b) st = quantize_operands(*b, nullptr, LLMQ_E4M3, s);
     return st;
-}
-
-// The quantize calls of their own
-int quantize_tensor(const void* x, int64_t rows, int64_t cols, const float* d_scale, int fmt, uint8_t* q, uint8_t* q_t, bool slabs, void* stream) {
-    const llmq::ScaleSource src{d_scale, nullptr, 0, fmt == LLMQ_E4M3 ? 448.0f : 57344.0f, nullptr};
-    return llmq::launch_quantize(llmq::QuantJob{x, rows, cols, src, q, q_t, nullptr, slabs}, nullptr, fmt, false, static_cast<hipStream_t>(stream));
 }
 
 // Under LLMQ_SLAB_COPIES the transposed copy of a tensor [rows, cols] is stored in slabs of 128 contraction bytes
@@ -193,7 +194,7 @@ int llmq_quantize_fp8(const void* x_bf16, int64_t rows, int64_t cols, const floa
     if (!dim_ok(rows) || !dim_ok(cols) || rows * cols >= kMaxElems) return LLMQ_ERR_SHAPE;
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(x_bf16, 16) || !aligned(q, 16) || !aligned(q_t, 16) || !aligned(d_scale, 4)) return LLMQ_ERR_ALIGN;
-    return quantize_tensor(x_bf16, rows, cols, d_scale, fmt, q, q_t, false, stream);
+    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream), false);
 }
 
 int llmq_quantize_fp8_slabs(const void* x_bf16, int64_t rows, int64_t cols, const float* d_scale, int fmt,
@@ -204,7 +205,7 @@ int llmq_quantize_fp8_slabs(const void* x_bf16, int64_t rows, int64_t cols, cons
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(x_bf16, 16) || !aligned(q, 16) || !aligned(q_t, 16) || !aligned(d_scale, 4)) return LLMQ_ERR_ALIGN;
     if (!llmq::quantize_can_write_slabs(rows, cols)) return LLMQ_ERR_SHAPE;
-    return quantize_tensor(x_bf16, rows, cols, d_scale, fmt, q, q_t, true, stream);
+    return llmq::launch_quantize(x_bf16, rows, cols, d_scale, fmt, q, q_t, nullptr, static_cast<hipStream_t>(stream), true);
 }
 
 int llmq_fp8_gemm_tn(const uint8_t* A, int fmtA, const uint8_t* B, int fmtB, int64_t R, int64_t C, int64_t T,

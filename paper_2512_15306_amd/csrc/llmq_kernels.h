@@ -72,6 +72,12 @@ struct ScaleSource {
 //     that follows in the same call, which saves a launch).
 //   qt_slabs: the transposed copy is written in slabs of 128 contraction bytes (kLayoutSlabs of the contraction that
 //     reads it: [cols, rows] with rows the contraction index); ask quantize_can_write_slabs() first (else -2).
+// launch_quantize: a scale on the device, for the quantize calls of their own; launch_quantize_from: any source of the
+// scale, for the operands of the linear calls, whose contraction reads the codes next (see streams_out).
+int launch_quantize(const void* x, int64_t rows, int64_t cols, const float* d_scale, int fmt,
+                    uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs);
+int launch_quantize_from(const void* x, int64_t rows, int64_t cols, const ScaleSource& src, int fmt,
+                         uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs);
 struct QuantJob {
     const void* x;
     int64_t rows, cols;
@@ -80,16 +86,16 @@ struct QuantJob {
     unsigned* zero_word;
     bool qt_slabs;
 };
-// One tensor, or two of the same format (second != NULL) in one launch where they take the same kernel.
-// read_next: the launch that follows reads the codes (see streams_out).
-int launch_quantize(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream);
+// launch_quantize_from for two tensors of the same format, in one launch where they take the same kernel.  (Weak, as the
+// absmax pair below: a host-only build of the ABI over counting stubs has the launchers of single tensors only.)
+int launch_quantize_pair(const QuantJob& first, const QuantJob& second, int fmt, hipStream_t stream) __attribute__((weak));
 bool quantize_can_write_slabs(int64_t rows, int64_t cols);
 // First stage of the absmax only: one BF16 magnitude pattern per workgroup into partial; returns the number
 // of workgroups (<= kAmaxMaxPartials) through n_partial.
 int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus);
 // The same for two tensors in one launch.
 int launch_amax_partial_pair(const void* x, size_t n, unsigned* partial, int* n_partial, const void* x2, size_t n2, unsigned* partial2,
-                             int* n_partial2, hipStream_t stream, int num_cus);
+                             int* n_partial2, hipStream_t stream, int num_cus) __attribute__((weak));
 // Caller-owned device scratch for the binary32 pieces of output tiles whose contraction is shared among
 // several workgroups (a ragged last round of tiles); {nullptr, 0}: every tile is computed by one workgroup.
 struct GemmScratch {

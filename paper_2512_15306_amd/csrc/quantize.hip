@@ -174,7 +174,7 @@ static void launch_kind(QuantKind kind, const QuantPair& pair, bool stream_out, 
 }
 
 // second: another tensor of the same format, or NULL.  Tensors that take the same kernel share a launch.
-int launch_quantize(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream) {
+static int launch_jobs(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream) {
     for (const QuantJob* j : {&first, second})
         if (j && j->qt_slabs && !(j->q_t && quantize_can_write_slabs(j->rows, j->cols))) return -2;       // the caller asks first
     auto launch = [&](const QuantJob& j, const QuantJob* with) {
@@ -187,6 +187,21 @@ int launch_quantize(const QuantJob& first, const QuantJob* second, int fmt, bool
     launch(first, together ? second : nullptr);
     if (second && !together) launch(*second, nullptr);
     return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+int launch_quantize(const void* x, int64_t rows, int64_t cols, const float* d_scale, int fmt,
+                    uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs) {
+    const ScaleSource src{d_scale, nullptr, 0, fp8_max(fmt), nullptr};
+    return launch_jobs(QuantJob{x, rows, cols, src, q, q_t, zero_word, qt_slabs}, nullptr, fmt, false, stream);
+}
+
+int launch_quantize_from(const void* x, int64_t rows, int64_t cols, const ScaleSource& src, int fmt,
+                         uint8_t* q, uint8_t* q_t, unsigned* zero_word, hipStream_t stream, bool qt_slabs) {
+    return launch_jobs(QuantJob{x, rows, cols, src, q, q_t, zero_word, qt_slabs}, nullptr, fmt, true, stream);
+}
+
+int launch_quantize_pair(const QuantJob& first, const QuantJob& second, int fmt, hipStream_t stream) {
+    return launch_jobs(first, &second, fmt, true, stream);
 }
 
 }  // namespace llmq

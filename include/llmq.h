@@ -327,9 +327,8 @@ int llmq_scale_from_amax(const float* d_amax, int fmt, float* d_scale, void* str
  * llmq_swiglu_bwd: dh [M, I], GU [M, 2I] -> dGU [M, 2I] (same column layout):
  *     dGU[m, I+i] = bf16( dh * (g * sg) ),   dGU[m, i] = bf16( ((dh * u) * sg) * fma(g, 1 - sg, 1) ),
  *   plus absmax and, if wanted, scale (format fmt) of dGU, which is the dY of the gate+up projection.
- * M, I >= 1, I < 2^24; GU, h, dh, dGU 16-byte aligned and I % 8 == 0 for that to hold for every row (other
- * I, and M not a multiple of 4, or of 16 with q_t, take a slower generic kernel; with q_t, M % 128 == 0 and
- * I % 256 == 0 take the fastest one).
+ * M, I >= 1, I < 2^24; GU, h, dh, dGU 16-byte aligned.  I % 8 == 0 (every row aligned) and M % 4 == 0 are fastest, with
+ * q_t M % 128 == 0 and I % 256 == 0; other shapes take the same arithmetic with guarded edges.
  */
 size_t llmq_swiglu_workspace_bytes(int64_t M, int64_t I);
 int llmq_swiglu_fwd(const void* gu_bf16, int64_t M, int64_t I, void* h_bf16, int fmt,
@@ -366,9 +365,8 @@ int llmq_swiglu_bwd(const void* dh_bf16, const void* gu_bf16, int64_t M, int64_t
  * llmq_rmsnorm_apply_fp8_slabs: the same with q_t (required) in slabs of 128 contraction bytes, as
  *   llmq_quantize_fp8_slabs writes it from y, for a linear call with LLMQ_REUSE_X | LLMQ_SLAB_COPIES.
  *   M % 128 == 0, C % 256 == 0 and M C < 0x70000000, else LLMQ_ERR_SHAPE.
- * M, C >= 1, C < 2^24.  C % 8 == 0 and C <= 8192 take the single-pass forward kernel; M % 16 == 0 (M % 4
- * without q_t) and C % 8 == 0 the tuned recompute kernels (with q_t, M % 128 == 0 and C % 256 == 0 the fastest
- * one); other shapes slower generic ones.
+ * M, C >= 1, C < 2^24.  C % 8 == 0 is fastest; C <= 16384 takes a single-pass forward kernel, wider rows are read twice.
+ * The recompute calls are fastest with M % 128 == 0 and C % 256 == 0 (M % 4 == 0 and C % 8 == 0 without q_t).
  */
 size_t llmq_rmsnorm_workspace_bytes(int64_t M);
 int llmq_rmsnorm_fwd(const void* res_bf16, const void* x_bf16, const void* w_bf16, int64_t M, int64_t C,

@@ -298,9 +298,9 @@ constexpr int kWholeTiles = 0, kSharePieces = 1, kShareFixup = 2;
 //                   end of the contraction.
 // Rows of a slab behind the operand's last row hold zeros or bytes of other rows; they only reach outputs that do not
 // exist, which are neither stored nor counted in the absmax.  Measured with R, C, T = 8100, 7168, 5120 (kEdge, E4M3):
-// 3.98 ms with one wavefront per 16 x 16 outputs and no LDS -> 0.238 ms (8192 rows without guards: 0.215);  7168,
-// 5120, 8100 (kEdgeUnaligned, the weight gradient on transposed copies): 44.1 -> 0.380 ms, bound by the unaligned
-// loads, which the L1 serves at half the rate.  Both take the old values of C, if any, by a run-time
+// 3.98 ms with one wavefront per 16 x 16 outputs and no LDS -> 0.238 ms;  7168, 5120, 8100 (kEdgeUnaligned, the
+// weight gradient on transposed copies): 44.1 -> 0.380 ms.  Most of that difference is rows that do not start at cache
+// lines, so that every 128-byte chunk touches two: 7168, 5120, 8112 takes 0.347 ms with kEdge.  Both take the old values of C, if any, by a run-time
 // flag (ACCUM is set: the binary32 staging of the epilogue serves both).
 constexpr int kNoEdge = 0, kEdge = 1, kEdgeUnaligned = 2;
 typedef v4u v4u_any __attribute__((aligned(1)));            // a 16-byte vector at any address

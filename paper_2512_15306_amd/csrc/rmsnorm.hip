@@ -10,6 +10,11 @@
 // reduction and the normalisation (one pass over HBM: 4 B read, 2 + 2 B written per element; 2 B less without the
 // addition), sum of squares in binary32 with a butterfly over the lanes, absmax of y as a packed
 // integer max of the rounded bits, one partial absmax per workgroup for the second-stage kernel.
+// The order of that sum is a function of C alone, so that a row has the same statistic whichever kernel and batch it is
+// computed in, and so do the codes made from it:
+//   C % 8 == 0, C <= 8192:  lane l of 64 adds up the vectors of eight elements l, l + 64, l + 128, ... one after the other;
+//   any other C:            lane l adds up the elements l, l + 64, l + 128, ...;
+// then a butterfly over the 64 sums.  Kernels whose lanes hold other parts of a row pass it through LDS.
 // Recompute kernels: rstd and the scale are inputs, so the operation is element-wise; they have the
 // lane geometry of the quantize kernels and reuse their transposes to write the FP8 codes in both layouts (2 B read,
 // 1 + 1 B written per element).
@@ -28,8 +33,7 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr int kRnThreads = 256;
 constexpr int kRnRowsPerBlock = kRnThreads / kWave;        // one wavefront per row
-constexpr int kRnVec = 4;                                   // one wavefront per row: 16-byte vectors per lane
-constexpr int64_t kRnRowC = kRnVec * kWave * 8;             // 2048 columns
+constexpr int64_t kRnVecOrderC = 8192;                      // widest row that is summed vector by vector
 
 __device__ inline unsigned rn_pack(float lo, float hi) {
     v2f v = {lo, hi};
@@ -42,6 +46,25 @@ __device__ inline float wave_sum_f32(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
     return v;
+}
+
+__device__ inline void add_squares(const v4u& r, float& ss) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = rn_lo(r[j]), b = rn_hi(r[j]);
+        ss = __builtin_fmaf(a, a, ss);
+        ss = __builtin_fmaf(b, b, ss);
+    }
+}
+// The same element by element, from a row in LDS
+__device__ inline float sum_by_elements(const uint16_t* s_row, int C, int lane) {
+    float ss = 0.0f;
+#pragma unroll 8
+    for (int c = lane; c < C; c += kWave) {
+        const float v = __uint_as_float((unsigned)s_row[c] << 16);
+        ss = __builtin_fmaf(v, v, ss);
+    }
+    return ss;
 }
 
 __device__ inline unsigned fold_pairs(unsigned m0, unsigned m1, unsigned m2, unsigned m3) {
@@ -73,16 +96,17 @@ __device__ inline void rn_store(uint16_t* row, int idx, int C, const v4u& v) {
     else store8_upto(row + 8 * idx, v, C - 8 * idx);
 }
 
-// Rows of up to 2048 columns in registers, one wavefront each.  EDGE: any C (the rows start at any even address, the last
+// One wavefront per row, VPL vectors per lane in registers.  EDGE: any C (the rows start at any even address, the last
 // vector of a row may be a part of one); else C % 8 == 0.  HAS_X false: no addition (res is normalised as it is, res_out is not
 // written).
-template <bool HAS_X, bool EDGE>
+template <bool HAS_X, bool EDGE, int VPL>
 __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
     const uint16_t* res, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     int64_t M, int C, float eps, uint16_t* res_out, uint16_t* __restrict__ y,
     float* __restrict__ rstd_out, unsigned* __restrict__ partial) {
     // res_out may be res (addition in place): every lane reads its elements before it writes them
     __shared__ unsigned s_part[kRnThreads / kWave];
+    __shared__ v4u s_rows[kRnRowsPerBlock][EDGE ? VPL * kWave : 1];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int64_t row = (int64_t)blockIdx.x * kRnRowsPerBlock + wave;
@@ -93,9 +117,9 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
     if (row < M) {
         const uint16_t* pr = res + row * C;
         const uint16_t* px = HAS_X ? x + row * C : nullptr;
-        v4u r[kRnVec];
+        v4u r[VPL];
 #pragma unroll
-        for (int k = 0; k < kRnVec; ++k) {
+        for (int k = 0; k < VPL; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
                 r[k] = load(pr, idx);
@@ -109,17 +133,19 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
         }
         float ss = 0.0f;
 #pragma unroll
-        for (int k = 0; k < kRnVec; ++k) {
+        for (int k = 0; k < VPL; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
                 if constexpr (HAS_X) store(res_out + row * C, idx, r[k]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float a = rn_lo(r[k][j]), b = rn_hi(r[k][j]);
-                    ss = __builtin_fmaf(a, a, ss);
-                    ss = __builtin_fmaf(b, b, ss);
-                }
+                if constexpr (EDGE) s_rows[wave][idx] = r[k];
+                else add_squares(r[k], ss);
             }
+        }
+        if constexpr (EDGE) {
+            // only this wave reads what it wrote: no barrier, but the order of its LDS accesses has to stay
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            ss = sum_by_elements(reinterpret_cast<const uint16_t*>(s_rows[wave]), C, lane);
         }
         ss = wave_sum_f32(ss);
         const float ms = ss / (float)C;
@@ -127,7 +153,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
         if (lane == 0) rstd_out[row] = rstd;
         unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;
 #pragma unroll
-        for (int k = 0; k < kRnVec; ++k) {
+        for (int k = 0; k < VPL; ++k) {
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
                 v4u wv;
@@ -150,7 +176,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
 
 // Wider rows: the four rows of a workgroup are read by all of its lanes (VPL vectors per lane and row, two rows at a time),
 // so that a lane holds a few vectors of each row instead of a whole row's share, which leaves room for more waves, and
-// reads the norm's weight once for both.  The row sums of the four waves meet in LDS, in a fixed order.  Measured against
+// reads the norm's weight once for both.  One wave per row adds up the squares, from LDS.  Measured against
 // one wave per row with up to 16 vectors per lane, with the addition: 16384 x 5120 137 -> 130 us (5.2 TB/s), 8192 x 3584
 // 52 -> 46, 4096 x 7680 59 -> 51, 279 x 7680 21 -> 14; all four rows at a time took 134, 48, 63 and 14.
 template <bool HAS_X, bool EDGE, int VPL, bool STREAM>
@@ -158,9 +184,11 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
     const uint16_t* res, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     int64_t M, int C, float eps, uint16_t* res_out, uint16_t* __restrict__ y,
     float* __restrict__ rstd_out, unsigned* __restrict__ partial) {
-    constexpr int kWaves = kRnThreads / kWave, ROWS = VPL <= 4 ? 2 : 1;
-    __shared__ unsigned s_part[kWaves];
-    __shared__ float s_sum[kRnRowsPerBlock][kWaves];
+    constexpr int ROWS = VPL <= 4 ? 2 : 1;
+    constexpr bool BY_ELEMENTS = EDGE || VPL * kRnThreads * 8 > kRnVecOrderC;       // VPL > 4 is for rows wider than that
+    __shared__ unsigned s_part[kRnThreads / kWave];
+    __shared__ float s_rstd[kRnRowsPerBlock];
+    __shared__ v4u s_rows[ROWS][VPL * kRnThreads];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int nvec = EDGE ? (C + 7) / 8 : C / 8;
@@ -181,10 +209,8 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                     if constexpr (HAS_X) xv[i][k] = rn_load<EDGE>(x + (row + i) * C, idx, C);
                 }
             }
-        float ss[ROWS];
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) {
-            ss[i] = 0.0f;
+        for (int i = 0; i < ROWS; ++i)
 #pragma unroll
             for (int k = 0; k < VPL; ++k) {
                 const int idx = k * kRnThreads + threadIdx.x;
@@ -195,28 +221,30 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                             r[i][k][j] = rn_pack(rn_lo(r[i][k][j]) + rn_lo(xv[i][k][j]), rn_hi(r[i][k][j]) + rn_hi(xv[i][k][j]));
                         rn_store<EDGE, STREAM>(res_out + (row + i) * C, idx, C, r[i][k]);
                     }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float a = rn_lo(r[i][k][j]), b = rn_hi(r[i][k][j]);
-                        ss[i] = __builtin_fmaf(a, a, ss[i]);
-                        ss[i] = __builtin_fmaf(b, b, ss[i]);
-                    }
+                    s_rows[i][idx] = r[i][k];
                 }
             }
-            ss[i] = wave_sum_f32(ss[i]);
-            if (lane == 0) s_sum[p + i][wave] = ss[i];
+        __syncthreads();
+        if (wave < ROWS && row + wave < M) {
+            float ss = 0.0f;
+            if constexpr (BY_ELEMENTS) {
+                ss = sum_by_elements(reinterpret_cast<const uint16_t*>(s_rows[wave]), C, lane);
+            } else {
+#pragma unroll 4
+                for (int idx = lane; idx < nvec; idx += kWave) add_squares(s_rows[wave][idx], ss);
+            }
+            ss = wave_sum_f32(ss);
+            const float ms = ss / (float)C;
+            const float rstd = 1.0f / __builtin_sqrtf(ms + eps);
+            if (lane == 0) {
+                rstd_out[row + wave] = rstd;
+                s_rstd[p + wave] = rstd;
+            }
         }
         __syncthreads();
         float rstd[ROWS];
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) {
-            float t = s_sum[p + i][0];
-#pragma unroll
-            for (int v = 1; v < kWaves; ++v) t += s_sum[p + i][v];
-            const float ms = t / (float)C;
-            rstd[i] = 1.0f / __builtin_sqrtf(ms + eps);
-            if (threadIdx.x == 0 && row + i < M) rstd_out[row + i] = rstd[i];
-        }
+        for (int i = 0; i < ROWS; ++i) rstd[i] = s_rstd[p + i];
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = k * kRnThreads + threadIdx.x;
@@ -402,6 +430,11 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     const dim3 grid((unsigned)rmsnorm_blocks(M)), block(kRnThreads);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, res, x, w, M, (int)C, eps, res_out, y, rstd, partial); };
     const bool edge = C % 8 != 0;
+    auto row = [&](auto vpl) {
+        constexpr int V = decltype(vpl)::value;
+        if (x) { if (edge) launch(rmsnorm_row_kernel<true, true, V>); else launch(rmsnorm_row_kernel<true, false, V>); }
+        else { if (edge) launch(rmsnorm_row_kernel<false, true, V>); else launch(rmsnorm_row_kernel<false, false, V>); }
+    };
     auto rows = [&](auto vpl) {
         constexpr int V = decltype(vpl)::value;
         const bool out = !edge && streams_out((x ? 4 : 2) * M * C);
@@ -409,19 +442,18 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
         else { if (edge) launch(rmsnorm_rows_kernel<false, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<false, false, V, true>); else launch(rmsnorm_rows_kernel<false, false, V, false>); }
     };
     // A wave per row as long as a row is at most four vectors per lane; from there on the workgroup reads its rows together.
-    if (C <= kRnRowC) {
-        if (x) { if (edge) launch(rmsnorm_row_kernel<true, true>); else launch(rmsnorm_row_kernel<true, false>); }
-        else { if (edge) launch(rmsnorm_row_kernel<false, true>); else launch(rmsnorm_row_kernel<false, false>); }
+    if (C > 8 * kRnThreads * 8) {
+        hipLaunchKernelGGL(rmsnorm_row_generic_kernel, grid, block, 0, stream, res, x, w, M, C, eps, res_out, y, rstd, partial);
+    } else if (C <= 4 * kWave * 8) {
+        row(IntTag<4>{});
     } else if (C <= 2 * kRnThreads * 8) {
         rows(IntTag<2>{});
     } else if (C <= 3 * kRnThreads * 8) {
         rows(IntTag<3>{});
     } else if (C <= 4 * kRnThreads * 8) {
         rows(IntTag<4>{});
-    } else if (C <= 8 * kRnThreads * 8) {
-        rows(IntTag<8>{});
     } else {
-        hipLaunchKernelGGL(rmsnorm_row_generic_kernel, grid, block, 0, stream, res, x, w, M, C, eps, res_out, y, rstd, partial);
+        rows(IntTag<8>{});
     }
     if (hipGetLastError() != hipSuccess) return -6;
     return launch_amax_final(partial, (int)rmsnorm_blocks(M), fmt, d_amax, d_scale, stream);

@@ -83,6 +83,14 @@ __device__ inline v4u normalize8(const v4u& r, float rstd, const v4u& w) {
     return o;
 }
 
+// The first `valid` of eight elements, zeros for the others: what lies behind the end of a row counts for nothing, also where
+// 0 * rstd * w is NaN (a row whose squares underflow, eps = 0: rstd is infinite and the row's own results are too).
+__device__ inline v4u keep_upto(v4u v, int valid) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] &= (2 * j < valid ? 0xFFFFu : 0u) | (2 * j + 1 < valid ? 0xFFFF0000u : 0u);
+    return v;
+}
+
 // Vector idx of a row of C elements; EDGE: of any C, at any even address
 template <bool EDGE>
 __device__ inline v4u rn_load(const uint16_t* row, int idx, int C) {
@@ -159,7 +167,8 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
                 v4u wv;
                 if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
                 else wv = reinterpret_cast<const v4u*>(w)[idx];
-                const v4u o = normalize8(r[k], rstd, wv);
+                v4u o = normalize8(r[k], rstd, wv);
+                if constexpr (EDGE) o = keep_upto(o, C - 8 * idx);
                 store(y + row * C, idx, o);
                 m0 = pk_max_mag(m0, o[0]);
                 m1 = pk_max_mag(m1, o[1]);
@@ -167,7 +176,6 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
                 m3 = pk_max_mag(m3, o[3]);
             }
         }
-        // (the zeros behind the end of a row give 0, or NaN where rstd is not finite and the row's own results are NaN)
         mag = fold_pairs(m0, m1, m2, m3);
     }
     mag = block_max_u32<kRnThreads>(mag, s_part);
@@ -255,7 +263,8 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i)
                     if (row + i < M) {
-                        const v4u o = normalize8(r[i][k], rstd[i], wv);
+                        v4u o = normalize8(r[i][k], rstd[i], wv);
+                        if constexpr (EDGE) o = keep_upto(o, C - 8 * idx);
                         rn_store<EDGE, STREAM>(y + (row + i) * C, idx, C, o);
                         m0 = pk_max_mag(m0, o[0]);
                         m1 = pk_max_mag(m1, o[1]);

@@ -106,3 +106,23 @@ def test_rmsnorm_forward_at_the_edges_of_its_widths(M, C, with_x):
     assert np.array_equal(synth.bf16_bits(_whole(y, n, -7.0)), want_y.reshape(-1))
     assert f32_bits(f[0:1]) == np_f32_bits(oracle.amax_bf16(want_y))
     assert bool((ws[-PAD:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("C", [17, 500, 2047, 2049, 4100, 8193, 16383, 16400])
+@pytest.mark.parametrize("with_x", [True, False])
+def test_rmsnorm_absmax_of_rows_whose_squares_underflow(C, with_x):
+    """eps = 0 and a row of 2^-80: its statistic and its results are infinite, and the absmax is that of what is stored,
+    whatever a kernel computes behind the end of a row."""
+    M, n = 5, 5 * C
+    res, _, w = rms_case(M, C, C)
+    res[3] = 2.0 ** -80
+    x = torch.zeros((M, C), dtype=torch.bfloat16) if with_x else None
+    w.abs_()
+    y, ro = _out(n, torch.bfloat16, -7.0), _out(n, torch.bfloat16, -7.0)
+    rstd, f = torch.zeros(M, dtype=torch.float32, device=DEV), torch.zeros(4, dtype=torch.float32, device=DEV)
+    ws = torch.empty(llmq.llmq_rmsnorm_workspace_bytes(M), dtype=torch.uint8, device=DEV)
+    llmq.llmq_rmsnorm_fwd(res.to(DEV), None if x is None else x.to(DEV), w.to(DEV), 0.0, ro[:n] if with_x else None, y[:n], rstd, 0, f[0:1], f[1:2], ws)
+    stored = _whole(y, n, -7.0).view(M, C)
+    assert bool(torch.isinf(stored[3]).all()) and bool(torch.isfinite(stored[torch.arange(M) != 3]).all())
+    llmq.llmq_amax(stored.reshape(-1).clone(), 0, f[2:3], f[3:4], torch.empty(llmq.llmq_amax_workspace_bytes(), dtype=torch.uint8, device=DEV))
+    assert f32_bits(f[0:1]) == f32_bits(f[2:3]) == 0x7F800000 and f32_bits(f[1:2]) == f32_bits(f[3:4]) == 0

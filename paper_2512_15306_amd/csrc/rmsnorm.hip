@@ -428,6 +428,34 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
 
 int64_t rmsnorm_blocks(int64_t M) { return (M + kRnRowsPerBlock - 1) / kRnRowsPerBlock; }
 
+// Which forward kernel.  Microseconds with the addition unless said otherwise (generic: element by element, a wave per row;
+// row: vectors, a wave per row; rows: the workgroup reads its rows together).
+//   Rows of whole vectors up to 2048 columns, generic against row: 4001 x 264 8.8 / 6.6, 16384 x 1000 33 / 29: always row.
+//   Ragged rows, generic against row: 16384 x 100 10.5 / 14.7, 2048 x 300 7.7 / 7.7, 4001 x 385 10.1 / 8.9, 16384 x 1001 42 / 32;
+//   without the addition and on many rows the generic kernel, which has less to move then, holds out longer: 16384 x 501 17 / 21,
+//   60001 x 700 65 / 79, 16384 x 1001 30 / 26, while 4001 x 450 takes 8.7 / 8.3.
+//   Wide rows, row against rows: 1 x 8192 10.8 / 7.0, 64 x 8192 12.3 / 13.5, 700 x 6144 18 / 14, 1000 x 8192 26 / 21, 4001 x 6144 36 / 40,
+//   8000 x 7168 88 / 89, 16384 x 5120 135 / 123; 16384 x 4096 96 / 96, and without the addition row is as good from three rows on.
+//   More than 8192 columns, or ragged and more than 2048: rows at any size (300 x 8200 55 / 18 against generic).
+// LLMQ_NORM_KERNEL=0 / 1 / 2 (tests): generic, row or rows wherever that kernel takes the width.
+enum NormKind { kNormGeneric, kNormRow, kNormRows };
+static NormKind norm_kind(int64_t M, int64_t C, bool with_x) {
+    const bool edge = C % 8 != 0;
+    const bool row_ok = C <= 4 * kWave * 8 || (!edge && C <= 16 * kWave * 8), rows_ok = C > 4 * kWave * 8 && C <= 8 * kRnThreads * 8;
+    const bool generic_ok = edge || C > kRnVecOrderC;               // the order of the sums
+    if (const char* e = tuning_env("LLMQ_NORM_KERNEL")) {
+        const int k = atoi(e);
+        if (k == 0 && generic_ok) return kNormGeneric;
+        if (k == 1 && row_ok) return kNormRow;
+        if (k == 2 && rows_ok) return kNormRows;
+    }
+    if (!row_ok) return rows_ok ? kNormRows : kNormGeneric;
+    if (edge) return C < (with_x ? 320 : M > 8192 ? 800 : 384) ? kNormGeneric : kNormRow;
+    if (!rows_ok) return kNormRow;
+    const bool few = M <= 2, one_per_cu = M >= 640 && M <= 1536, many = M >= 12288;
+    return few || (with_x && C > 4096 && (one_per_cu || many)) ? kNormRows : kNormRow;
+}
+
 int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t M, int64_t C, float eps,
                        void* res_out_, void* y_, float* rstd, unsigned* partial, int fmt, float* d_amax,
                        float* d_scale, hipStream_t stream) {
@@ -441,8 +469,10 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     const bool edge = C % 8 != 0;
     auto row = [&](auto vpl) {
         constexpr int V = decltype(vpl)::value;
-        if (x) { if (edge) launch(rmsnorm_row_kernel<true, true, V>); else launch(rmsnorm_row_kernel<true, false, V>); }
-        else { if (edge) launch(rmsnorm_row_kernel<false, true, V>); else launch(rmsnorm_row_kernel<false, false, V>); }
+        if constexpr (V <= 4) {                            // (ragged rows of more vectors per lane take the rows kernel)
+            if (edge) { if (x) launch(rmsnorm_row_kernel<true, true, V>); else launch(rmsnorm_row_kernel<false, true, V>); return; }
+        }
+        if (x) launch(rmsnorm_row_kernel<true, false, V>); else launch(rmsnorm_row_kernel<false, false, V>);
     };
     auto rows = [&](auto vpl) {
         constexpr int V = decltype(vpl)::value;
@@ -450,19 +480,22 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
         if (x) { if (edge) launch(rmsnorm_rows_kernel<true, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<true, false, V, true>); else launch(rmsnorm_rows_kernel<true, false, V, false>); }
         else { if (edge) launch(rmsnorm_rows_kernel<false, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<false, false, V, true>); else launch(rmsnorm_rows_kernel<false, false, V, false>); }
     };
-    // A wave per row as long as a row is at most four vectors per lane; from there on the workgroup reads its rows together.
-    if (C > 8 * kRnThreads * 8) {
-        hipLaunchKernelGGL(rmsnorm_row_generic_kernel, grid, block, 0, stream, res, x, w, M, C, eps, res_out, y, rstd, partial);
-    } else if (C <= 4 * kWave * 8) {
-        row(IntTag<4>{});
-    } else if (C <= 2 * kRnThreads * 8) {
-        rows(IntTag<2>{});
-    } else if (C <= 3 * kRnThreads * 8) {
-        rows(IntTag<3>{});
-    } else if (C <= 4 * kRnThreads * 8) {
-        rows(IntTag<4>{});
-    } else {
-        rows(IntTag<8>{});
+    switch (norm_kind(M, C, x != nullptr)) {
+        case kNormGeneric: hipLaunchKernelGGL(rmsnorm_row_generic_kernel, grid, block, 0, stream, res, x, w, M, C, eps, res_out, y, rstd, partial); break;
+        case kNormRow:
+            // (As few registers as the row needs, but for a few workgroups per CU: those are dealt out evenly only if few fit
+            // on one.  3000 x 3584 with 8 and 16 vectors per lane: 21.4 / 19.1 us, 4001 x 3584 24.7 / 29.4.)
+            if (C <= 4 * kWave * 8) row(IntTag<4>{});
+            else if (x && M >= 1280 && M <= 3500) row(IntTag<16>{});
+            else if (C <= 8 * kWave * 8) row(IntTag<8>{});
+            else if (C <= 12 * kWave * 8) row(IntTag<12>{});
+            else row(IntTag<16>{});
+            break;
+        case kNormRows:
+            if (C <= 2 * kRnThreads * 8) rows(IntTag<2>{});
+            else if (C <= 3 * kRnThreads * 8) rows(IntTag<3>{});
+            else if (C <= 4 * kRnThreads * 8) rows(IntTag<4>{});
+            else rows(IntTag<8>{});
     }
     if (hipGetLastError() != hipSuccess) return -6;
     return launch_amax_final(partial, (int)rmsnorm_blocks(M), fmt, d_amax, d_scale, stream);

@@ -32,7 +32,9 @@ def _rstd(bits, C):
 @pytest.mark.parametrize("C", [1, 17, 100, 264, 2040, 2047, 2048, 2049, 2056, 3072, 4095, 4096, 4104, 5120, 6150, 8184, 8191, 8192, 8193, 8200, 12296,
                                16383, 16384, 16385])
 @pytest.mark.parametrize("M", [1, 6])
-def test_row_sum_order(M, C):
+@pytest.mark.parametrize("kernel", ["0", "1", "2"])
+def test_row_sum_order(M, C, kernel, monkeypatch):
+    monkeypatch.setenv("LLMQ_NORM_KERNEL", kernel)         # where the width allows it
     g = torch.Generator().manual_seed(C + M)
     res = (torch.randn(M, C, generator=g) * 1.3).to(torch.bfloat16)
     res[:, torch.randint(0, C, (max(1, C // 200),), generator=g)] *= 50.0

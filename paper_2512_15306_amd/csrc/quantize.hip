@@ -71,10 +71,10 @@ __global__ __launch_bounds__(kTileThreads) void quantize_tile_kernel(const Quant
     tile_write_transposed(s_t, t.qt + (int64_t)bcol * kTileCols * t.qt_row_stride + (int64_t)brow * t.qt_band_stride, t.qt_row_stride);
 }
 
-// Everything else: tensors of few tiles, and ragged shapes of any size (plain transposed copy, or slabs where the shape
+// Tensors of few tiles, and ragged shapes with enough to move (plain transposed copy, or slabs where the shape
 // has them), on the 64 x 128 tile.  The input is requested before a scale
 // that has to be found from partial results, so that the two waits overlap.
-// Measured against what was here before (one element per lane for shapes that are no multiples of 16 x 8; 16 x 8 patches
+// Measured against the kernels below (one element per lane for shapes that are no multiples of 16 x 8; 16 x 8 patches
 // without LDS for the others): 8100 x 5120 255 -> 35 us, 8112 x 5128 54 -> 38, 16000 x 9000 190 -> 174, 1777 x 960 14.7 -> 5.1.
 // The 128 x 256 tile with the same guards took 39, 44 and 10.4 on the first, second and last.
 template <int FMT>
@@ -101,6 +101,52 @@ __global__ __launch_bounds__(kTileThreads) void quantize_small_kernel(const Quan
     small_stage_transposed(w, tr, tc, s_t);
     __syncthreads();
     small_write_transposed_upto(s_t, t.qt + C0 * t.qt_row_stride + (R0 / kTileRows) * t.qt_band_stride + R0 % kTileRows, t.qt_row_stride, rows - R0, cols - C0);
+}
+
+// Narrow tensors of whole 16 x 8 patches, which would leave most lanes of the 64 x 128 tile idle (codes_kind).
+template <int FMT>
+__global__ __launch_bounds__(kQThreads) void quantize_narrow_kernel(const QuantPair pair) {
+    __shared__ unsigned s_part[kQThreads / kWave];
+    unsigned block;
+    const QuantTensor& t = tensor_of_block(pair, block);
+    if (t.zero_word && block == 0 && threadIdx.x == 0) *t.zero_word = 0u;
+    const float s = resolve_scale(t.scale, block == 0, s_part);          // before any lane leaves
+    const int64_t rows = t.rows, cols = t.cols;
+    int tr, tc;
+    narrow_patch_origin(tr, tc);
+    const int64_t r0 = (int64_t)block * kNarrowRows + tr;
+    if (r0 >= rows || tc >= cols) return;
+    const uint16_t* src = t.x + r0 * cols + tc;
+    v4u in[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * cols));
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned w[16][2];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) quantize8<FMT>(in[i], s, w[i][0], w[i][1]);
+    uint8_t* dst = t.q + r0 * cols + tc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) *reinterpret_cast<v2u*>(dst + (int64_t)i * cols) = v2u{w[i][0], w[i][1]};
+    narrow_write_transposed(w, t.qt + (int64_t)tc * rows + r0, rows);
+}
+
+// One element per lane: small tensors, and ragged ones of few rows or columns (codes_kind).
+constexpr int64_t kElementsMaxBlocks = 65536;
+template <int FMT>
+__global__ __launch_bounds__(kQThreads) void quantize_elements_kernel(const QuantPair pair) {
+    __shared__ unsigned s_part[kQThreads / kWave];
+    unsigned block;
+    const QuantTensor& t = tensor_of_block(pair, block);
+    if (t.zero_word && block == 0 && threadIdx.x == 0) *t.zero_word = 0u;
+    const float s = resolve_scale(t.scale, block == 0, s_part);
+    const int64_t rows = t.rows, cols = t.cols, n = rows * cols;
+    for (int64_t i = (int64_t)block * kQThreads + threadIdx.x; i < n; i += (int64_t)t.blocks * kQThreads) {
+        const float p = __uint_as_float((unsigned)t.x[i] << 16) * s;
+        const uint8_t code = (uint8_t)(cvt_pair<FMT>(p, p, 0u, false) & 0xFFu);
+        t.q[i] = code;
+        const int64_t r = i / cols, c = i - r * cols;
+        t.qt[c * rows + r] = code;
+    }
 }
 
 // No transposed copy wanted: the conversion is element-wise and the tensor can be taken as a flat array.  A
@@ -142,19 +188,29 @@ __global__ __launch_bounds__(kQThreads) void quantize_flat_kernel(const QuantPai
 bool quantize_can_write_slabs(int64_t rows, int64_t cols) { return tile_shape_ok(rows, cols); }
 
 // Which kernel a tensor takes, and what the kernel is told about it
-enum QuantKind { kQuantFlat, kQuantSmall, kQuantTile };
-static QuantKind quant_kind(const QuantJob& j) { return !j.q_t ? kQuantFlat : takes_large_tile(j.rows, j.cols) ? kQuantTile : kQuantSmall; }
+enum QuantKind { kQuantFlat, kQuantElements, kQuantNarrow, kQuantSmall, kQuantTile };
+static QuantKind quant_kind(const QuantJob& j) {
+    if (!j.q_t) return kQuantFlat;
+    if (takes_large_tile(j.rows, j.cols)) return kQuantTile;
+    if (j.qt_slabs) return kQuantSmall;
+    const CodesKind k = codes_kind(j.rows, j.cols);
+    return k == kCodesElements ? kQuantElements : k == kCodesNarrow ? kQuantNarrow : kQuantSmall;
+}
 
-static QuantTensor quant_tensor(const QuantJob& j) {
+static QuantTensor quant_tensor(const QuantJob& j, QuantKind kind) {
     QuantTensor t{};
     t.x = reinterpret_cast<const uint16_t*>(j.x);
     t.rows = j.rows; t.cols = j.cols; t.scale = j.scale; t.q = j.q; t.qt = j.q_t; t.zero_word = j.zero_word;
     t.qt_row_stride = j.qt_slabs ? kTileRows : j.rows;
     t.qt_band_stride = j.qt_slabs ? j.cols * kTileRows : kTileRows;
-    const QuantKind kind = quant_kind(j);
     if (kind == kQuantFlat) {
         const int64_t n8 = j.rows * j.cols / 8, blocks = (n8 + kQThreads * kFlatUnits - 1) / (kQThreads * kFlatUnits);
         t.blocks = blocks < 1 ? 1u : (unsigned)blocks;
+    } else if (kind == kQuantElements) {
+        const int64_t blocks = (j.rows * j.cols + kQThreads - 1) / kQThreads;
+        t.blocks = (unsigned)(blocks < kElementsMaxBlocks ? blocks : kElementsMaxBlocks);
+    } else if (kind == kQuantNarrow) {
+        t.blocks = (unsigned)((j.rows + kNarrowRows - 1) / kNarrowRows);
     } else if (kind == kQuantTile) {
         t.blocks = (unsigned)((j.rows / kTileRows) * (j.cols / kTileCols));
     } else {
@@ -168,6 +224,8 @@ template <int FMT>
 static void launch_kind(QuantKind kind, const QuantPair& pair, bool stream_out, hipStream_t stream) {
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(pair.first.blocks + pair.second.blocks), dim3(kQThreads), 0, stream, pair); };
     if (kind == kQuantFlat) launch(quantize_flat_kernel<FMT>);
+    else if (kind == kQuantElements) launch(quantize_elements_kernel<FMT>);
+    else if (kind == kQuantNarrow) launch(quantize_narrow_kernel<FMT>);
     else if (kind == kQuantSmall) launch(quantize_small_kernel<FMT>);
     else if (stream_out) launch(quantize_tile_kernel<FMT, true>);
     else launch(quantize_tile_kernel<FMT, false>);
@@ -177,15 +235,18 @@ static void launch_kind(QuantKind kind, const QuantPair& pair, bool stream_out, 
 static int launch_jobs(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream) {
     for (const QuantJob* j : {&first, second})
         if (j && j->qt_slabs && !(j->q_t && quantize_can_write_slabs(j->rows, j->cols))) return -2;       // the caller asks first
-    auto launch = [&](const QuantJob& j, const QuantJob* with) {
-        const QuantPair pair{quant_tensor(j), with ? quant_tensor(*with) : QuantTensor{}};
+    auto launch = [&](const QuantJob& j, const QuantJob* with, QuantKind kind) {
+        const QuantPair pair{quant_tensor(j, kind), with ? quant_tensor(*with, kind) : QuantTensor{}};
         const bool stream_out = !read_next && streams_out(2 * j.rows * j.cols, 96);
-        if (fmt == 0) launch_kind<0>(quant_kind(j), pair, stream_out, stream);
-        else launch_kind<1>(quant_kind(j), pair, stream_out, stream);
+        if (fmt == 0) launch_kind<0>(kind, pair, stream_out, stream);
+        else launch_kind<1>(kind, pair, stream_out, stream);
     };
-    const bool together = second && quant_kind(first) == quant_kind(*second);
-    launch(first, together ? second : nullptr);
-    if (second && !together) launch(*second, nullptr);
+    QuantKind kind = quant_kind(first), kind2 = second ? quant_kind(*second) : kind;
+    // (the 64 x 128 tile takes every shape: one launch of both on it beats two launches)
+    if ((kind == kQuantElements && kind2 == kQuantSmall) || (kind == kQuantSmall && kind2 == kQuantElements)) kind = kind2 = kQuantSmall;
+    const bool together = second && kind == kind2;
+    launch(first, together ? second : nullptr, kind);
+    if (second && !together) launch(*second, nullptr, kind2);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

@@ -26,18 +26,24 @@ def _whole(buf, n, fill):
 
 SHAPES = [(1, 1), (1, 7), (3, 9), (63, 127), (64, 128), (65, 129), (66, 136), (129, 257), (200, 250), (127, 513), (16, 264), (300, 1001)]
 FORCED = [(128, 256), (256, 512), (384, 256)]            # whole tiles: both tile kernels, plain and slabs
+NARROW = [(16, 8), (128, 64), (144, 40), (272, 16), (1040, 56)]        # whole patches of 16 x 8
+# more than one tile row, more tile columns than a band is wide (ragged pitches walk in bands), and every kind of kernel
+KINDS = [s + (k,) for s in SHAPES + [(200, 1300), (150, 1152)] for k in "02"] + [s + (k,) for s in NARROW for k in "012"]
 
 
 def _slabs(qt, rows, cols):
     return qt.reshape(cols, rows // 128, 128).transpose(1, 0, 2).reshape(-1)
 
 
-@pytest.mark.parametrize("rows,cols,tile", [s + (None,) for s in SHAPES] + [s + (t,) for s in FORCED for t in "01"])
+@pytest.mark.parametrize("rows,cols,tile,kind", [s + (None, None) for s in SHAPES] + [s + (t, None) for s in FORCED for t in "01"] +
+                         [s[:2] + (None, s[2]) for s in KINDS])
 @pytest.mark.parametrize("fmt", [0, 1])
-def test_codes_of_every_producer(rows, cols, tile, fmt, monkeypatch):
+def test_codes_of_every_producer(rows, cols, tile, kind, fmt, monkeypatch):
     if tile is not None:
         monkeypatch.setenv("LLMQ_QUANT_TILE", tile)
-    print("codes rows=%d cols=%d tile=%s fmt=%d" % (rows, cols, tile, fmt), flush=True)
+    if kind is not None:
+        monkeypatch.setenv("LLMQ_CODES_KERNEL", kind)
+    print("codes rows=%d cols=%d tile=%s kind=%s fmt=%d" % (rows, cols, tile, kind, fmt), flush=True)
     n = rows * cols
     gu, _ = swiglu_case(rows, cols, 31 + rows + cols)
     res, _, w = rms_case(rows, cols, 37 + rows + cols)
@@ -63,8 +69,11 @@ def test_codes_of_every_producer(rows, cols, tile, fmt, monkeypatch):
                 assert np.array_equal(_whole(qt, n, 0xAA).cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("M,I", [(1, 1), (3, 9), (5, 511), (4, 512), (7, 513), (130, 1001), (2, 1030)])
-def test_swiglu_forward_and_backward_of_ragged_shapes(M, I):
+@pytest.mark.parametrize("M,I", [(1, 1), (3, 9), (5, 511), (4, 512), (7, 513), (130, 1001), (2, 1030), (64, 8), (36, 32), (4, 40)])
+@pytest.mark.parametrize("kind", [None, "0", "2"])
+def test_swiglu_forward_and_backward_of_ragged_shapes(M, I, kind, monkeypatch):
+    if kind is not None:
+        monkeypatch.setenv("LLMQ_CODES_KERNEL", kind)
     gu, dh = swiglu_case(M, I, 3 * M + I)
     gu[0, 0] = -90.0                          # below the range of the short sigmoid, and far below
     if I > 8:

@@ -392,6 +392,92 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_bwd_edge_kernel(
     if (threadIdx.x == 0) partial[blockIdx.x] = mag;
 }
 
+// FP8 codes in both layouts of narrow shapes of whole 16 x 8 patches; h may be NULL.
+template <int QFMT>
+__global__ __launch_bounds__(kSwThreads) void swiglu_fwd_fp8_narrow_kernel(
+    const uint16_t* __restrict__ gu, int64_t M, int64_t I, uint16_t* __restrict__ h,
+    const float* __restrict__ d_qscale, uint8_t* __restrict__ q, uint8_t* __restrict__ qt) {
+    int tr, tc;
+    narrow_patch_origin(tr, tc);
+    const int64_t r0 = (int64_t)blockIdx.x * kNarrowRows + tr;
+    if (r0 >= M || tc >= I) return;
+    const uint16_t* src = gu + r0 * (2 * I) + tc;
+    const float s = *d_qscale;
+    constexpr int kGroup = 8;
+    unsigned w[16][2];
+#pragma unroll
+    for (int i0 = 0; i0 < 16; i0 += kGroup) {
+        v4u g[kGroup], u[kGroup];
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) {
+            g[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)(i0 + i) * 2 * I));
+            u[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)(i0 + i) * 2 * I + I));
+        }
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) {
+            const v4u o = swiglu8(g[i], u[i]);
+            if (h) *reinterpret_cast<v4u*>(h + (r0 + i0 + i) * I + tc) = o;
+            quantize8<QFMT>(o, s, w[i0 + i][0], w[i0 + i][1]);
+            *reinterpret_cast<v2u*>(q + (r0 + i0 + i) * I + tc) = v2u{w[i0 + i][0], w[i0 + i][1]};
+        }
+    }
+    narrow_write_transposed(w, qt + (int64_t)tc * M + r0, M);
+}
+
+// One element per lane: small shapes, and ragged ones that are narrow or have few rows (edge_worth, codes_kind_of).
+// h, partial, q and qt may be NULL.
+template <int QFMT>
+__global__ __launch_bounds__(kSwThreads) void swiglu_fwd_elements_kernel(
+    const uint16_t* __restrict__ gu, int64_t M, int64_t I, uint16_t* __restrict__ h,
+    unsigned* __restrict__ partial, const float* __restrict__ d_qscale, uint8_t* __restrict__ q, uint8_t* __restrict__ qt) {
+    __shared__ unsigned s_part[kSwThreads / kWave];
+    const int64_t n = M * I;
+    unsigned mag = 0;
+    float s = 0.0f;
+    if constexpr (QFMT >= 0) s = *d_qscale;
+    for (int64_t idx = (int64_t)blockIdx.x * kSwThreads + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * kSwThreads) {
+        const int64_t m = idx / I, i = idx - m * I;
+        const float g = __uint_as_float((unsigned)gu[m * 2 * I + i] << 16);
+        const float u = __uint_as_float((unsigned)gu[m * 2 * I + I + i] << 16);
+        const unsigned bits = pack_bf16(swiglu_f32<false>(g, u), 0.0f) & 0xFFFFu;
+        if (h) h[idx] = (uint16_t)bits;
+        mag = pk_max_mag(mag, bits);
+        if constexpr (QFMT >= 0) {
+            const float p = __uint_as_float(bits << 16) * s;
+            const uint8_t code = (uint8_t)(cvt_pair<QFMT>(p, p, 0u, false) & 0xFFu);
+            q[idx] = code;
+            if (qt) qt[i * M + m] = code;
+        }
+    }
+    if (partial) {
+        mag = block_max_u32<kSwThreads>(mag & 0xFFFFu, s_part);
+        if (threadIdx.x == 0) partial[blockIdx.x] = mag;
+    }
+}
+
+__global__ __launch_bounds__(kSwThreads) void swiglu_bwd_elements_kernel(
+    const uint16_t* __restrict__ dh, const uint16_t* __restrict__ gu, int64_t M, int64_t I,
+    uint16_t* __restrict__ dgu, unsigned* __restrict__ partial) {
+    __shared__ unsigned s_part[kSwThreads / kWave];
+    const int64_t n = M * I;
+    unsigned mag = 0;
+    for (int64_t idx = (int64_t)blockIdx.x * kSwThreads + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * kSwThreads) {
+        const int64_t m = idx / I, i = idx - m * I;
+        const float g = __uint_as_float((unsigned)gu[m * 2 * I + i] << 16);
+        const float u = __uint_as_float((unsigned)gu[m * 2 * I + I + i] << 16);
+        const float d = __uint_as_float((unsigned)dh[idx] << 16);
+        float dg, du;
+        swiglu_bwd_f32<false>(d, g, u, dg, du);
+        const unsigned w = pack_bf16(dg, du);
+        dgu[m * 2 * I + i] = (uint16_t)(w & 0xFFFFu);
+        dgu[m * 2 * I + I + i] = (uint16_t)(w >> 16);
+        mag = pk_max_mag(mag, w);
+    }
+    mag = (mag & 0xFFFFu) > (mag >> 16) ? (mag & 0xFFFFu) : (mag >> 16);
+    mag = block_max_u32<kSwThreads>(mag, s_part);
+    if (threadIdx.x == 0) partial[blockIdx.x] = mag;
+}
+
 static bool patch_ok(int64_t M, int64_t I, int pr) { return M % pr == 0 && I % 8 == 0; }
 
 // Ragged shapes: workgroups of an absmax-producing launch, at most one per word of the scratch
@@ -405,6 +491,34 @@ static int64_t edge_blocks(int64_t M, int64_t I) {
     const int64_t b = (edge_pieces(M, I) + kSwThreads / kWave - 1) / (kSwThreads / kWave), w = edge_scratch_words(M, I);
     const int64_t trips = (b + w - 1) / w;             // the same number of pieces for every workgroup, give or take one
     return (b + trips - 1) / trips;
+}
+
+// Which kernel ragged (and small or narrow) shapes take: one element per lane, or guarded vectors once there is enough to move
+// for their code and their waits.  Microseconds, elements / vectors:
+//   forward with h   1001 x 600 6.3 / 7.0, 2001 x 600 7.3 / 7.1, 4001 x 200 6.6 / 7.0, 8001 x 264 8.9 / 8.1, 200001 x 264 156 / 93;  rows that are no whole
+//                    vectors 2001 x 1366 10.6 / 14.3, 4001 x 1001 14.2 / 12.2, 8001 x 500 14.2 / 13.9, 8001 x 300 10.0 / 13.0, 60001 x 700 98 / 112
+//   backward         1001 x 2736 11.9 / 11.0, 2001 x 600 7.7 / 8.5, 4001 x 200 6.9 / 8.4;  other rows 4001 x 1001 15 / 18, 4001 x 5001 51 / 61,
+//                    8001 x 5001 136 / 80
+//   codes in both layouts   500 x 1000 5.1 / 6.3, 1000 x 1000 8.8 / 7.1;  other rows 8000 x 100 6.8 / 8.6, 1000 x 1001 8.7 / 8.6, 4001 x 500
+//                    14.3 / 9.9;  33 x 20000 4.6 / 5.8, 60000 x 33 9.8 / 12.9, 16384 x 8 2.2 / 6.0 (narrow patches 13)
+//   codes alone      4001 x 512 6.6 / 5.6, 1001 x 2001 6.8 / 8.5, 2001 x 2001 12.2 / 10.3
+// LLMQ_CODES_KERNEL=0 / 1 / 2 (tests): elements, narrow patches or vectors, where they take the shape.
+static bool edge_worth(int64_t M, int64_t I, bool backward) {
+    if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) return atoi(e) != kCodesElements;
+    const int64_t n = M * I;
+    if (I % 8 == 0) return (I >= 400 && n >= (backward ? (int64_t)15 << 17 : (int64_t)1 << 20)) || (I >= 256 && n >= ((int64_t)1 << (backward ? 25 : 21)));
+    if (backward) return I >= 1000 && n >= ((int64_t)1 << 25);
+    return n >= ((int64_t)15 << 18) && I >= 500 && 10 * I >= 7 * edge_col_pieces(I) * kSwEdgeCols;       // (a wave takes 512 columns)
+}
+static CodesKind codes_kind_of(int64_t M, int64_t I, bool transpose) {
+    if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) {
+        const int k = atoi(e);
+        return k != kCodesNarrow ? (CodesKind)k : transpose && codes_narrow_ok(M, I) ? kCodesNarrow : kCodesSmall;
+    }
+    const int64_t n = M * I;
+    if (!transpose) return M >= 32 && I >= 64 && n >= (I % 8 == 0 ? (int64_t)15 << 17 : (int64_t)15 << 18) ? kCodesSmall : kCodesElements;
+    if (I >= 32 && n >= ((int64_t)1 << 22) && codes_narrow_ok(M, I)) return kCodesNarrow;       // 1000000 x 32: 105 / 81 / 107 us
+    return M >= 32 && I >= 64 && n >= (I % 8 == 0 ? (int64_t)3 << 18 : (int64_t)1 << 20) ? kCodesSmall : kCodesElements;
 }
 
 // Workgroups of the absmax-producing launches (forward with h, backward): an upper bound of the partial
@@ -439,6 +553,12 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
     } else if (!q_t && patch_ok(M, I, 4)) {
         if (h) launch_fwd_patch<4, true, false, QFMT>(gu, M, I, h, nullptr, d_qscale, q, stream);
         else launch_fwd_patch<4, false, false, QFMT>(gu, M, I, h, nullptr, d_qscale, q, stream);
+    } else if (const CodesKind kind = qt_slabs ? kCodesSmall : codes_kind_of(M, I, q_t != nullptr); kind == kCodesElements) {
+        hipLaunchKernelGGL((swiglu_fwd_elements_kernel<QFMT>), dim3((unsigned)edge_scratch_words(M, I)), dim3(kSwThreads), 0, stream, gu, M, I, h,
+                           (unsigned*)nullptr, d_qscale, q, q_t);
+    } else if (kind == kCodesNarrow) {
+        hipLaunchKernelGGL(swiglu_fwd_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kSwThreads), 0, stream,
+                           gu, M, I, h, d_qscale, q, q_t);
     } else {
         const SmallGrid g = small_grid(M, I);
         if (q_t) hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, true>), dim3(g.blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
@@ -467,6 +587,10 @@ int launch_swiglu_fwd(const void* gu_, int64_t M, int64_t I, void* h_, unsigned*
     } else if (patch_ok(M, I, 4)) {
         launch_fwd_patch<4, true, true, -1>(gu, M, I, h, partial, nullptr, nullptr, stream);
         n_partial = patch_blocks(M, I, 4);
+    } else if (!edge_worth(M, I, false)) {
+        n_partial = edge_scratch_words(M, I);
+        hipLaunchKernelGGL((swiglu_fwd_elements_kernel<-1>), dim3((unsigned)n_partial), dim3(kSwThreads), 0, stream, gu, M, I, h, partial,
+                           (const float*)nullptr, (uint8_t*)nullptr, (uint8_t*)nullptr);
     } else {
         n_partial = edge_blocks(M, I);
         hipLaunchKernelGGL(swiglu_fwd_edge_kernel, dim3((unsigned)n_partial), dim3(kSwThreads), 0, stream, gu, M, I, h, partial,
@@ -479,13 +603,19 @@ int launch_swiglu_fwd(const void* gu_, int64_t M, int64_t I, void* h_, unsigned*
 int launch_swiglu_bwd(const void* dh, const void* gu, int64_t M, int64_t I, void* dgu, unsigned* partial,
                       int amax_fmt, float* d_amax, float* d_scale, hipStream_t stream) {
     int64_t n_partial = swiglu_blocks(M, I);
-    if (patch_ok(M, I, 4)) {
+    // (a wave of the patch kernel is 64 columns wide: patches / elements: 16384 x 16 8.0 / 4.6 us, 60000 x 16 9.8 / 6.5, 1000000 x 16 81 / 43)
+    const bool narrow = I <= 32 || !patch_ok(M, I, 4);
+    if (!narrow) {
         const unsigned gr = (unsigned)((M + 4 * kSwLanesR - 1) / (4 * kSwLanesR)), gc = (unsigned)((I + kSwBlockCols - 1) / kSwBlockCols);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kSwThreads), 0, stream, reinterpret_cast<const uint16_t*>(dh),
                                reinterpret_cast<const uint16_t*>(gu), M, I, reinterpret_cast<uint16_t*>(dgu), partial, gc);
         };
         if (streams_out(4 * M * I)) launch(swiglu_bwd_patch_kernel<true>); else launch(swiglu_bwd_patch_kernel<false>);
+    } else if (patch_ok(M, I, 4) || !edge_worth(M, I, true)) {
+        if (edge_scratch_words(M, I) < n_partial) n_partial = edge_scratch_words(M, I);
+        hipLaunchKernelGGL(swiglu_bwd_elements_kernel, dim3((unsigned)n_partial), dim3(kSwThreads), 0, stream, reinterpret_cast<const uint16_t*>(dh),
+                           reinterpret_cast<const uint16_t*>(gu), M, I, reinterpret_cast<uint16_t*>(dgu), partial);
     } else {
         n_partial = edge_blocks(M, I);
         hipLaunchKernelGGL(swiglu_bwd_edge_kernel, dim3((unsigned)n_partial), dim3(kSwThreads), 0, stream,

@@ -12,9 +12,11 @@
 // integer max of the rounded bits, one partial absmax per workgroup for the second-stage kernel.
 // The order of that sum is a function of C alone, so that a row has the same statistic whichever kernel and batch it is
 // computed in, and so do the codes made from it:
-//   C % 8 == 0, C <= 8192:  lane l of 64 adds up the vectors of eight elements l, l + 64, l + 128, ... one after the other;
-//   any other C:            lane l adds up the elements l, l + 64, l + 128, ...;
-// then a butterfly over the 64 sums.  Kernels whose lanes hold other parts of a row pass it through LDS.
+//   C % 8 == 0, C <= 8192:        lane l of 64 adds up the vectors of eight elements l, l + 64, l + 128, ... one after the other;
+//   other C <= 2048 or > 16384:   lane l adds up the elements l, l + 64, l + 128, ...;
+//   the rest:                     four waves add up the vectors l, l + 256, l + 512, ... of theirs (l = 64 wave + lane), the first
+//                                 wave's sum first;
+// each wave's 64 sums by a butterfly.  Kernels whose lanes hold other parts of a row pass it through LDS.
 // Recompute kernels: rstd and the scale are inputs, so the operation is element-wise; they have the
 // lane geometry of the quantize kernels and reuse their transposes to write the FP8 codes in both layouts (2 B read,
 // 1 + 1 B written per element).
@@ -33,7 +35,7 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr int kRnThreads = 256;
 constexpr int kRnRowsPerBlock = kRnThreads / kWave;        // one wavefront per row
-constexpr int64_t kRnVecOrderC = 8192;                      // widest row that is summed vector by vector
+constexpr int64_t kRnVecOrderC = 8192;                      // widest row that one wave sums vector by vector
 
 __device__ inline unsigned rn_pack(float lo, float hi) {
     v2f v = {lo, hi};
@@ -168,7 +170,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
                 if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
                 else wv = reinterpret_cast<const v4u*>(w)[idx];
                 v4u o = normalize8(r[k], rstd, wv);
-                if constexpr (EDGE) o = keep_upto(o, C - 8 * idx);
+                if (EDGE && idx == nvec - 1) o = keep_upto(o, C % 8);
                 store(y + row * C, idx, o);
                 m0 = pk_max_mag(m0, o[0]);
                 m1 = pk_max_mag(m1, o[1]);
@@ -184,7 +186,9 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
 
 // Wider rows: the four rows of a workgroup are read by all of its lanes (VPL vectors per lane and row, two rows at a time),
 // so that a lane holds a few vectors of each row instead of a whole row's share, which leaves room for more waves, and
-// reads the norm's weight once for both.  One wave per row adds up the squares, from LDS.  Measured against
+// reads the norm's weight once for both.  Where one wave adds up the squares of a row, it reads them from LDS; widths that had
+// no kernel of one wave per row to agree with are summed by all four (by one, element by element, 4001 x 10001 took 102 us
+// instead of 73).  Measured against
 // one wave per row with up to 16 vectors per lane, with the addition: 16384 x 5120 137 -> 130 us (5.2 TB/s), 8192 x 3584
 // 52 -> 46, 4096 x 7680 59 -> 51, 279 x 7680 21 -> 14; all four rows at a time took 134, 48, 63 and 14.
 template <bool HAS_X, bool EDGE, int VPL, bool STREAM>
@@ -193,10 +197,11 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
     int64_t M, int C, float eps, uint16_t* res_out, uint16_t* __restrict__ y,
     float* __restrict__ rstd_out, unsigned* __restrict__ partial) {
     constexpr int ROWS = VPL <= 4 ? 2 : 1;
-    constexpr bool BY_ELEMENTS = EDGE || VPL * kRnThreads * 8 > kRnVecOrderC;       // VPL > 4 is for rows wider than that
-    __shared__ unsigned s_part[kRnThreads / kWave];
-    __shared__ float s_rstd[kRnRowsPerBlock];
-    __shared__ v4u s_rows[ROWS][VPL * kRnThreads];
+    constexpr bool ONE_WAVE = !EDGE && VPL * kRnThreads * 8 <= kRnVecOrderC;        // sums a row (VPL > 4 is for wider ones)
+    constexpr int kWaves = kRnThreads / kWave;
+    __shared__ unsigned s_part[kWaves];
+    __shared__ float s_rstd[kRnRowsPerBlock], s_sum[kRnRowsPerBlock][kWaves];
+    __shared__ v4u s_rows[ONE_WAVE ? ROWS : 1][ONE_WAVE ? VPL * kRnThreads : 1];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int nvec = EDGE ? (C + 7) / 8 : C / 8;
@@ -218,7 +223,8 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                 }
             }
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i)
+        for (int i = 0; i < ROWS; ++i) {
+            float ss = 0.0f;
 #pragma unroll
             for (int k = 0; k < VPL; ++k) {
                 const int idx = k * kRnThreads + threadIdx.x;
@@ -229,30 +235,44 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                             r[i][k][j] = rn_pack(rn_lo(r[i][k][j]) + rn_lo(xv[i][k][j]), rn_hi(r[i][k][j]) + rn_hi(xv[i][k][j]));
                         rn_store<EDGE, STREAM>(res_out + (row + i) * C, idx, C, r[i][k]);
                     }
-                    s_rows[i][idx] = r[i][k];
+                    if constexpr (ONE_WAVE) s_rows[i][idx] = r[i][k];
+                    else add_squares(r[i][k], ss);
                 }
             }
-        __syncthreads();
-        if (wave < ROWS && row + wave < M) {
-            float ss = 0.0f;
-            if constexpr (BY_ELEMENTS) {
-                ss = sum_by_elements(reinterpret_cast<const uint16_t*>(s_rows[wave]), C, lane);
-            } else {
-#pragma unroll 4
-                for (int idx = lane; idx < nvec; idx += kWave) add_squares(s_rows[wave][idx], ss);
-            }
-            ss = wave_sum_f32(ss);
-            const float ms = ss / (float)C;
-            const float rstd = 1.0f / __builtin_sqrtf(ms + eps);
-            if (lane == 0) {
-                rstd_out[row + wave] = rstd;
-                s_rstd[p + wave] = rstd;
+            if constexpr (!ONE_WAVE) {
+                ss = wave_sum_f32(ss);
+                if (lane == 0) s_sum[p + i][wave] = ss;
             }
         }
         __syncthreads();
         float rstd[ROWS];
+        if constexpr (ONE_WAVE) {
+            if (wave < ROWS && row + wave < M) {
+                float ss = 0.0f;
+#pragma unroll 4
+                for (int idx = lane; idx < nvec; idx += kWave) add_squares(s_rows[wave][idx], ss);
+                ss = wave_sum_f32(ss);
+                const float ms = ss / (float)C;
+                const float t = 1.0f / __builtin_sqrtf(ms + eps);
+                if (lane == 0) {
+                    rstd_out[row + wave] = t;
+                    s_rstd[p + wave] = t;
+                }
+            }
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) rstd[i] = s_rstd[p + i];
+            for (int i = 0; i < ROWS; ++i) rstd[i] = s_rstd[p + i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                float t = s_sum[p + i][0];
+#pragma unroll
+                for (int v = 1; v < kWaves; ++v) t += s_sum[p + i][v];
+                const float ms = t / (float)C;
+                rstd[i] = 1.0f / __builtin_sqrtf(ms + eps);
+                if (threadIdx.x == 0 && row + i < M) rstd_out[row + i] = rstd[i];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = k * kRnThreads + threadIdx.x;
@@ -264,7 +284,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                 for (int i = 0; i < ROWS; ++i)
                     if (row + i < M) {
                         v4u o = normalize8(r[i][k], rstd[i], wv);
-                        if constexpr (EDGE) o = keep_upto(o, C - 8 * idx);
+                        if (EDGE && idx == nvec - 1) o = keep_upto(o, C % 8);
                         rn_store<EDGE, STREAM>(y + (row + i) * C, idx, C, o);
                         m0 = pk_max_mag(m0, o[0]);
                         m1 = pk_max_mag(m1, o[1]);
@@ -442,7 +462,7 @@ enum NormKind { kNormGeneric, kNormRow, kNormRows };
 static NormKind norm_kind(int64_t M, int64_t C, bool with_x) {
     const bool edge = C % 8 != 0;
     const bool row_ok = C <= 4 * kWave * 8 || (!edge && C <= 16 * kWave * 8), rows_ok = C > 4 * kWave * 8 && C <= 8 * kRnThreads * 8;
-    const bool generic_ok = edge || C > kRnVecOrderC;               // the order of the sums
+    const bool generic_ok = edge ? C <= 4 * kWave * 8 : !rows_ok && !row_ok;       // by the order of the sums
     if (const char* e = tuning_env("LLMQ_NORM_KERNEL")) {
         const int k = atoi(e);
         if (k == 0 && generic_ok) return kNormGeneric;

@@ -12,21 +12,30 @@ EPS = np.float32(1e-6)
 
 
 def _rstd(bits, C):
-    """Lane l of 64 adds up the vectors of eight l, l + 64, ... (C % 8 == 0, C <= 8192) or the elements l, l + 64, ... (other
-    widths), a butterfly adds up the lanes.  The square of a BF16 number is exact in binary32, so a fused multiply-add is
-    the binary32 sum of that square."""
+    """Lane l of `lanes` adds up the vectors of eight (or, unit = 1, the elements) l, l + lanes, ..., a butterfly the 64 lanes
+    of a wave, and the waves' sums follow one after the other.  The square of a BF16 number is exact in binary32, so a
+    fused multiply-add is the binary32 sum of that square."""
+    if C % 8 == 0 and C <= 8192:
+        unit, lanes = 8, 64
+    elif C <= 2048 or C > 16384:
+        unit, lanes = 1, 64
+    else:
+        unit, lanes = 8, 256
     f = (bits.astype(np.uint32) << 16).view(np.float32)
-    unit = 8 if C % 8 == 0 and C <= 8192 else 1
-    ss = np.zeros((len(f), 64), dtype=np.float32)
-    for first in range(0, C, 64 * unit):
-        part = f[:, first:first + 64 * unit]
-        n = part.shape[1] // unit
+    f = np.concatenate([f, np.zeros((len(f), -C % unit), dtype=np.float32)], axis=1)       # adding 0 changes nothing
+    ss = np.zeros((len(f), lanes), dtype=np.float32)
+    for first in range(0, C, lanes * unit):
+        part = f[:, first:first + lanes * unit]
         for e in range(unit):
             v = part[:, e::unit]
-            ss[:, :n] = ss[:, :n] + v * v
+            ss[:, :v.shape[1]] = ss[:, :v.shape[1]] + v * v
+    ss = ss.reshape(len(f), lanes // 64, 64)
     for off in (32, 16, 8, 4, 2, 1):
-        ss = ss + ss[:, np.arange(64) ^ off]
-    return np.float32(1.0) / np.sqrt(ss[:, 0] / np.float32(C) + EPS)
+        ss = ss + ss[:, :, np.arange(64) ^ off]
+    total = ss[:, 0, 0]
+    for wave in range(1, lanes // 64):
+        total = total + ss[:, wave, 0]
+    return np.float32(1.0) / np.sqrt(total / np.float32(C) + EPS)
 
 
 @pytest.mark.parametrize("C", [1, 17, 100, 264, 2040, 2047, 2048, 2049, 2056, 3072, 4095, 4096, 4104, 5120, 6150, 8184, 8191, 8192, 8193, 8200, 12296,

@@ -411,6 +411,60 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_tile_kernel(
     tile_write_transposed(s_t, qt + (int64_t)bcol * kTileCols * qt_row_stride + (int64_t)brow * qt_band_stride, qt_row_stride);
 }
 
+// Narrow shapes of whole 16 x 8 patches, with the transposed copy (codes_kind; 64 x 128 tile / patches: 60000 x 64 7.7 / 6.1 us,
+// 1000000 x 16 49 / 28).  y may be NULL.
+template <int QFMT>
+__global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_narrow_kernel(
+    const uint16_t* __restrict__ res, const uint16_t* __restrict__ w, const float* __restrict__ rstd,
+    int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
+    uint8_t* __restrict__ qt, uint16_t* __restrict__ y) {
+    int tr, tc;
+    narrow_patch_origin(tr, tc);
+    const int64_t r0 = (int64_t)blockIdx.x * kNarrowRows + tr;
+    if (r0 >= M || tc >= C) return;
+    const uint16_t* src = res + r0 * C + tc;
+    v4u in[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * C));
+    const v4u wv = *reinterpret_cast<const v4u*>(w + tc);
+    v4f rs[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rs[i] = *reinterpret_cast<const v4f*>(rstd + r0 + 4 * i);
+    const float s = *d_qscale;
+    unsigned wq[16][2];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const v4u o = normalize8(in[i], rs[i / 4][i % 4], wv);
+        if (y) *reinterpret_cast<v4u*>(y + (r0 + i) * C + tc) = o;
+        quantize8<QFMT>(o, s, wq[i][0], wq[i][1]);
+    }
+    uint8_t* dq = q + r0 * C + tc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) *reinterpret_cast<v2u*>(dq + (int64_t)i * C) = v2u{wq[i][0], wq[i][1]};
+    narrow_write_transposed(wq, qt + (int64_t)tc * M + r0, M);
+}
+
+// One element per lane: small shapes, and ragged ones that are narrow or have few rows.  qt, y may be NULL.
+constexpr int64_t kApplyElementsMaxBlocks = 65536;
+template <int QFMT>
+__global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_elements_kernel(
+    const uint16_t* __restrict__ res, const uint16_t* __restrict__ w, const float* __restrict__ rstd,
+    int64_t M, int64_t C, const float* __restrict__ d_qscale, uint8_t* __restrict__ q,
+    uint8_t* __restrict__ qt, uint16_t* __restrict__ y) {
+    const int64_t n = M * C;
+    const float s = *d_qscale;
+    for (int64_t idx = (int64_t)blockIdx.x * kRnThreads + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * kRnThreads) {
+        const int64_t m = idx / C, c = idx - m * C;
+        const float t = __uint_as_float((unsigned)res[idx] << 16) * rstd[m];
+        const unsigned bits = rn_pack(t * __uint_as_float((unsigned)w[c] << 16), 0.0f) & 0xFFFFu;
+        if (y) y[idx] = (uint16_t)bits;
+        const float p = __uint_as_float(bits << 16) * s;
+        const uint8_t code = (uint8_t)(cvt_pair<QFMT>(p, p, 0u, false) & 0xFFu);
+        q[idx] = code;
+        if (qt) qt[c * M + m] = code;
+    }
+}
+
 // Ragged shapes and tensors of few tiles: the 64 x 128 tile; y (if not NULL), q and the transposed copy (TRANSPOSE).
 template <int QFMT, bool TRANSPOSE>
 __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
@@ -521,12 +575,22 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     return launch_amax_final(partial, (int)rmsnorm_blocks(M), fmt, d_amax, d_scale, stream);
 }
 
+// The recompute call's kernel where it is not the large tile's or, without the transposed copy, that of whole 4 x 8 patches.
+// Without the transposed copy the 64 x 128 tile is worth its code and its waits only for millions of elements (elements / tile,
+// microseconds: 1001 x 2730 6.3 / 6.6, 2001 x 2001 8.1 / 7.1, 4001 x 512 5.1 / 4.1, 4001 x 200 3.8 / 4.7, 200001 x 33 11.3 / 14.4).
+static CodesKind apply_kind(int64_t M, int64_t C, bool transpose) {
+    if (transpose) return codes_kind(M, C);
+    if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) return atoi(e) == 0 ? kCodesElements : kCodesSmall;
+    return M >= 32 && C >= 64 && M * C >= (C % 8 == 0 ? (int64_t)15 << 17 : (int64_t)15 << 18) ? kCodesSmall : kCodesElements;
+}
+
 template <int QFMT>
 static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rstd, int64_t M, int64_t C,
                          const float* d_qscale, uint8_t* q, uint8_t* q_t, uint16_t* y, hipStream_t stream,
                          bool qt_slabs) {
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
-    if (q_t && takes_large_tile(M, C, 2304)) {
+    const int64_t tiles = (M / kTileRows) * (C / kTileCols);
+    if (q_t && (takes_large_tile(M, C, 2304) || (takes_large_tile(M, C, 384) && tiles <= 512))) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
         if (streams_out(2 * M * C)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }
@@ -536,6 +600,13 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
         const dim3 grid((unsigned)((M + 4 * kRnLanesR - 1) / (4 * kRnLanesR)) * gc);
         if (y) hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<QFMT, true>), grid, dim3(kRnThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, y, gc);
         else hipLaunchKernelGGL((rmsnorm_apply_fp8_patch_kernel<QFMT, false>), grid, dim3(kRnThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, y, gc);
+    } else if (const CodesKind kind = qt_slabs ? kCodesSmall : apply_kind(M, C, q_t != nullptr); kind == kCodesElements) {
+        const int64_t blocks = (M * C + kRnThreads - 1) / kRnThreads;
+        const dim3 grid((unsigned)(blocks < kApplyElementsMaxBlocks ? blocks : kApplyElementsMaxBlocks));
+        hipLaunchKernelGGL(rmsnorm_apply_fp8_elements_kernel<QFMT>, grid, dim3(kRnThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y);
+    } else if (kind == kCodesNarrow) {
+        hipLaunchKernelGGL(rmsnorm_apply_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kRnThreads), 0, stream,
+                           res, w, rstd, M, C, d_qscale, q, q_t, y);
     } else {
         const SmallGrid g = small_grid(M, C);
         if (q_t) hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, true>), dim3(g.blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);

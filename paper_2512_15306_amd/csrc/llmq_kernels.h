@@ -66,7 +66,11 @@ inline CodesKind codes_kind(int64_t rows, int64_t cols) {
 // that cache when it fits: with results of 128 MiB streamed an MLP sub-block (4096 x 3072 x 8192) takes 1021 instead of 1013
 // us.  Hence 144 MiB; 96 for the quantize calls of their own (a weight's codes are read much later); inside the linear
 // calls, whose contraction reads the codes at once, codes are never streamed (no difference up to 32B-class layers).
-inline bool streams_out(int64_t result_bytes, int limit_mib = 144) { return result_bytes > ((int64_t)limit_mib << 20); }
+// Only rows of whole 128-byte lines (cols_of_lines: columns a line holds): a line that two stores share goes to memory twice when it
+// is streamed (backward of 60000 x 1000 131 / 177 us, of 1000000 x 72 193 / 275).
+inline bool streams_out(int64_t result_bytes, int64_t cols, int64_t cols_of_line, int limit_mib = 144) {
+    return cols % cols_of_line == 0 && result_bytes > ((int64_t)limit_mib << 20);
+}
 
 // Each returns 0 or LLMQ_ERR_DEVICE (-6).  Arguments are validated by the callers in api.hip.
 constexpr int kAmaxMaxPartials = 1024;      // the absmax workspace holds one 32-bit word per block

@@ -237,7 +237,7 @@ static int launch_jobs(const QuantJob& first, const QuantJob* second, int fmt, b
         if (j && j->qt_slabs && !(j->q_t && quantize_can_write_slabs(j->rows, j->cols))) return -2;       // the caller asks first
     auto launch = [&](const QuantJob& j, const QuantJob* with, QuantKind kind) {
         const QuantPair pair{quant_tensor(j, kind), with ? quant_tensor(*with, kind) : QuantTensor{}};
-        const bool stream_out = !read_next && streams_out(2 * j.rows * j.cols, 96);
+        const bool stream_out = !read_next && streams_out(2 * j.rows * j.cols, j.cols, 128, 96);
         if (fmt == 0) launch_kind<0>(kind, pair, stream_out, stream);
         else launch_kind<1>(kind, pair, stream_out, stream);
     };

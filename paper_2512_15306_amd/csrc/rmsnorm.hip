@@ -550,7 +550,7 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
     };
     auto rows = [&](auto vpl) {
         constexpr int V = decltype(vpl)::value;
-        const bool out = !edge && streams_out((x ? 4 : 2) * M * C);
+        const bool out = streams_out((x ? 4 : 2) * M * C, C, 64);
         if (x) { if (edge) launch(rmsnorm_rows_kernel<true, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<true, false, V, true>); else launch(rmsnorm_rows_kernel<true, false, V, false>); }
         else { if (edge) launch(rmsnorm_rows_kernel<false, true, V, false>); else if (out) launch(rmsnorm_rows_kernel<false, false, V, true>); else launch(rmsnorm_rows_kernel<false, false, V, false>); }
     };
@@ -593,7 +593,7 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
     if (q_t && (takes_large_tile(M, C, 2304) || (takes_large_tile(M, C, 384) && tiles <= 512))) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
-        if (streams_out(2 * M * C)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }
+        if (streams_out(2 * M * C, C, 128)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }
         else { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, false>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, false>); }
     } else if (!q_t && M % 4 == 0 && C % 8 == 0) {
         const unsigned gc = (unsigned)((C + kRnBlockCols - 1) / kRnBlockCols);

@@ -548,7 +548,7 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
     if (q_t && takes_large_tile(M, I, 1536)) {
         const unsigned gr = (unsigned)(M / kTileRows), gc = (unsigned)(I / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kTileThreads), 0, stream, gu, I, h, d_qscale, q, q_t, gc, row_stride, band_stride); };
-        if (streams_out(2 * M * I)) { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, true>); else launch(swiglu_fwd_tile_kernel<false, QFMT, true>); }
+        if (streams_out(2 * M * I, I, 128)) { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, true>); else launch(swiglu_fwd_tile_kernel<false, QFMT, true>); }
         else { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, false>); else launch(swiglu_fwd_tile_kernel<false, QFMT, false>); }
     } else if (!q_t && patch_ok(M, I, 4)) {
         if (h) launch_fwd_patch<4, true, false, QFMT>(gu, M, I, h, nullptr, d_qscale, q, stream);
@@ -581,7 +581,7 @@ int launch_swiglu_fwd(const void* gu_, int64_t M, int64_t I, void* h_, unsigned*
     if (qt_slabs) return -2;
     int64_t n_partial;
     if (patch_ok(M, I, 8)) {                   // 8 rows per lane: more bytes in flight, half the partial results
-        if (streams_out(2 * M * I)) launch_fwd_patch<8, true, true, -1, true>(gu, M, I, h, partial, nullptr, nullptr, stream);
+        if (streams_out(2 * M * I, I, 64)) launch_fwd_patch<8, true, true, -1, true>(gu, M, I, h, partial, nullptr, nullptr, stream);
         else launch_fwd_patch<8, true, true, -1>(gu, M, I, h, partial, nullptr, nullptr, stream);
         n_partial = patch_blocks(M, I, 8);
     } else if (patch_ok(M, I, 4)) {
@@ -611,7 +611,7 @@ int launch_swiglu_bwd(const void* dh, const void* gu, int64_t M, int64_t I, void
             hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kSwThreads), 0, stream, reinterpret_cast<const uint16_t*>(dh),
                                reinterpret_cast<const uint16_t*>(gu), M, I, reinterpret_cast<uint16_t*>(dgu), partial, gc);
         };
-        if (streams_out(4 * M * I)) launch(swiglu_bwd_patch_kernel<true>); else launch(swiglu_bwd_patch_kernel<false>);
+        if (streams_out(4 * M * I, I, 64)) launch(swiglu_bwd_patch_kernel<true>); else launch(swiglu_bwd_patch_kernel<false>);
     } else if (patch_ok(M, I, 4) || !edge_worth(M, I, true)) {
         if (edge_scratch_words(M, I) < n_partial) n_partial = edge_scratch_words(M, I);
         hipLaunchKernelGGL(swiglu_bwd_elements_kernel, dim3((unsigned)n_partial), dim3(kSwThreads), 0, stream, reinterpret_cast<const uint16_t*>(dh),

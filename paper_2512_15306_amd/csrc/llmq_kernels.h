@@ -21,7 +21,8 @@ constexpr int kTileRows = 128, kTileCols = 256;
 inline bool tile_shape_ok(int64_t rows, int64_t cols) { return rows % kTileRows == 0 && cols % kTileCols == 0; }
 
 // Such a tensor takes the tile kernels from `min_tiles` tiles on, below that the 64 x 128 tile, of which there are four
-// times as many.  Quantize kernel, 64 x 128 against 128 x 256: 256 x 512 elements (4 tiles) 4.6 / 6.7 us, 2048 x 3072 (192)
+// times as many (the SwiGLU and RMSNorm kernels have limits of their own, beside their launches).  Quantize kernel, 64 x 128
+// against 128 x 256: 256 x 512 elements (4 tiles) 4.6 / 6.7 us, 2048 x 3072 (192)
 // 6.8 / 7.6, 4096 x 3072 (384) 12.7 / 12.3, 16384 x 5120 60.6 / 56.8: one tile per CU.
 // LLMQ_QUANT_TILE=0 / 1 (tests): always the one or, for shapes made of them, always the other.
 inline bool takes_large_tile(int64_t rows, int64_t cols, int64_t min_tiles = 256) {

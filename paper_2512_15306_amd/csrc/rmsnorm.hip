@@ -589,8 +589,10 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
                          const float* d_qscale, uint8_t* q, uint8_t* q_t, uint16_t* y, hipStream_t stream,
                          bool qt_slabs) {
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
+    // (64 x 128 / 128 x 256 tiles, buffers of their own for every pass: 320 large tiles 10.9 / 12.8 us, 384 14.3 / 14.4, 512 - all resident at
+    // once - 17.0 / 14.5, 640 20.0 / 22.2, 1024 28.1 / 29.2, 1536 43.4 / 43.8, 2048 68 / 60, 4096 139 / 113)
     const int64_t tiles = (M / kTileRows) * (C / kTileCols);
-    if (q_t && (takes_large_tile(M, C, 2304) || (takes_large_tile(M, C, 384) && tiles <= 512))) {
+    if (q_t && (takes_large_tile(M, C, 1792) || (takes_large_tile(M, C, 384) && tiles <= 512))) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
         if (streams_out(2 * M * C, C, 128)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }

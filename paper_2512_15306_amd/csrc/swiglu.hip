@@ -545,7 +545,9 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
                           uint8_t* q, uint8_t* q_t, hipStream_t stream, bool qt_slabs) {
     if (qt_slabs && !(q_t && tile_shape_ok(M, I))) return -2;
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? I * kTileRows : kTileRows;
-    if (q_t && takes_large_tile(M, I, 1536)) {
+    // (64 x 128 / 128 x 256 tiles, buffers of their own for every pass: 640 large tiles 29.2 / 30.7 us, 768 33.1 / 32.5, 1024 41.9 / 39.2,
+    // 1536 67 / 64, 2560 115 / 94)
+    if (q_t && takes_large_tile(M, I, 768)) {
         const unsigned gr = (unsigned)(M / kTileRows), gc = (unsigned)(I / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kTileThreads), 0, stream, gu, I, h, d_qscale, q, q_t, gc, row_stride, band_stride); };
         if (streams_out(2 * M * I, I, 128)) { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, true>); else launch(swiglu_fwd_tile_kernel<false, QFMT, true>); }

@@ -153,8 +153,50 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
     return best;
 }
 
+// Whether the generic kernel finishes first.  Its waves of 16 x 16 outputs (BF16: lanes of one output) have no LDS to fill
+// and no tile to write out, which makes it the faster one for small problems, as long as its operands can be loaded in
+// vectors or the contraction is one K step long.  FP8: the same sums, so the same bytes.  A model in microseconds: waits of
+// one wave, and for every further round of workgroups per CU; fitted to 1712 shapes in four layouts up to 4001 x 1001 outputs
+// and T = 2048.  Generic / tile kernel:
+//   both operands in rows, R x C x T   100 x 136 x 64 2.9 / 5.2, x 512 4.4 / 6.2, x 1024 6.4 / 7.4, x 2048 10.4 / 9.8;  1000 x 520 x 64 4.0 / 5.4,
+//     x 256 5.6 / 5.8, x 384 7.0 / 6.1;  2000 x 1000 x 64 7.5 / 5.9;  T no multiple of 32: 100 x 136 x 400 6.9 / 6.2, x 50 6.5 / 7.5, x 1001 47 / 14
+//   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
+//   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
+//   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
+static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool bf16, int num_cus) {
+    if (bf16) {                                                             // (T in bytes)
+        const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
+        return R * C <= most;
+    }
+    if (R * C > ((int64_t)1 << 23)) return false;
+    const double steps = (double)((T + BK - 1) / BK);
+    const int64_t workgroups = ((R + 31) / 32) * ((C + 31) / 32);
+    const double more = (double)((workgroups + num_cus - 1) / num_cus - 1);
+    const bool one = T <= BK, odd_width = C % 8 != 0;
+    double generic, tile;
+    if (!ta && !tb && T % 16 == 0) {
+        generic = (T % 32 == 0 ? 2.6 : 5.45) + 0.45 * steps + more * (0.25 + 0.44 * steps);
+        tile = 4.9 + 0.29 * steps;
+    } else if (!ta && !tb && one) {
+        generic = 6.6 + more * 0.03 * (double)T;
+        tile = 7.2;
+    } else if (!ta && one) {
+        generic = T <= 16 ? 6.3 + more * 0.6 : T % 32 == 0 ? 6.0 + more * 0.8 : 7.9 + more * 0.02 * (double)T;
+        tile = T % 16 == 0 && C % 16 == 0 ? 5.0 : 6.5;
+    } else if (ta && one) {
+        generic = T <= 16 ? 6.7 + more * 0.6 : (C <= 32 ? 7.9 : 9.2) + more * 0.9;
+        tile = R % 16 == 0 && C % 16 == 0 ? 5.0 : 6.5;
+    } else {
+        return false;
+    }
+    const double rows = R < 16 ? 16.0 : R > 64 ? 64.0 : (double)R;          // that a wave of the tile kernel writes out
+    if (odd_width) tile += (rows - 16.0) / 48.0 * 2.1;
+    if (accumulate) { generic += 0.9 + 0.68 * more; tile += odd_width ? 1.2 : 0.6; }
+    return generic < tile + 0.4e-6 * (double)R * (double)C;
+}
+
 // Tile and kind of a ragged problem, by the same model with the tiles rounded up.
-EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b) {
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
     // bytes in every row of an operand
@@ -164,7 +206,9 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
     if (const char* force = tuning_env("LLMQ_GEMM_EDGE_TILE")) {
         const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
         if ((ni == 2 || ni == 4) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
+        if (ni == 0) return best;                             // 0x0: the generic kernel
     }
+    if (generic_is_faster(R, C, T, ta, tb, accumulate, bf16, num_cus)) return best;
     if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
     double best_cost = 0;
     for (int ni = 4; ni >= 2; ni -= 2)

@@ -911,6 +911,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
             if (vector) {
+                v4u old[kPiecesPerLane];                                     // all of them on their way before the first is needed
+                if (accumulate) {
+#pragma unroll
+                    for (int k = 0; k < kPiecesPerLane; ++k) old[k] = __builtin_amdgcn_raw_buffer_load_b128(rsC, voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2, 0, 0);
+                }
 #pragma unroll
                 for (int k = 0; k < kPiecesPerLane; ++k) {
                     const int r = pr + k * kRowStep;
@@ -918,10 +923,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     v4f y0 = *reinterpret_cast<const v4f*>(src), y1 = *reinterpret_cast<const v4f*>(src + 16 * kSlots);
                     const unsigned off = voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2;
                     if (accumulate) {
-                        const v4u old = __builtin_amdgcn_raw_buffer_load_b128(rsC, off, 0, 0);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const unsigned o = old[e >> 1], o1 = old[2 + (e >> 1)];
+                            const unsigned o = old[k][e >> 1], o1 = old[k][2 + (e >> 1)];
                             y0[e] += __uint_as_float((e & 1) ? o & 0xFFFF0000u : o << 16);
                             y1[e] += __uint_as_float((e & 1) ? o1 & 0xFFFF0000u : o1 << 16);
                         }
@@ -935,16 +939,38 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     __builtin_amdgcn_raw_buffer_store_b128(out, rsC, off, 0, 0);
                 }
             } else {
-                const int n_rows = rows_left - i * 32 < 32 ? rows_left - i * 32 : 32, n_cols = cols_left < 32 * NJ ? cols_left : 32 * NJ;
-                for (int r = 0; r < n_rows; ++r)
-                    for (int c = lane; c < n_cols; c += kWave) {
-                        float y = *reinterpret_cast<const float*>(stage + r * kPitch + ((((c >> 3) + r) % kSlots) << 4) + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4);
-                        uint16_t* dst = cbase + (size_t)(i * 32 + r) * Cn + c;
-                        if (accumulate) y += __uint_as_float((unsigned)*dst << 16);
-                        const unsigned bits = __builtin_bit_cast(uint16_t, (__bf16)y);
-                        *dst = (uint16_t)bits;
-                        edge_mag = pk_max_mag(edge_mag, bits);
+                // sixteen rows at a time: their old values are on their way together (row after row
+                // 300 x 300 x 64 took 24.7 us with accumulation and 8.9 without, this way 8.5 and 7.3; eight at a time 9.9 and 8.2)
+#pragma unroll
+                for (int cc = 0; cc < 32 * NJ; cc += kWave) {
+                    if (cc >= cols_left) break;
+                    const int c = cc + lane;
+                    const uint8_t* src = stage + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4;
+                    const unsigned coff = c < cols_left ? (unsigned)(i * 32 * Cn + c) * 2 : kOutOfRange;
+                    auto rows_from = [&](auto at_once, int r0) __attribute__((always_inline)) {
+                        constexpr int kRowsAtOnce = decltype(at_once)::value;
+                        float y[kRowsAtOnce];
+                        unsigned old[kRowsAtOnce];
+                        if (accumulate) {
+#pragma unroll
+                            for (int k = 0; k < kRowsAtOnce; ++k) old[k] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(rsC, coff + (unsigned)((r0 + k) * Cn) * 2, 0, 0) << 16;
+                        }
+#pragma unroll
+                        for (int k = 0; k < kRowsAtOnce; ++k) y[k] = *reinterpret_cast<const float*>(src + (r0 + k) * kPitch + ((((c >> 3) + r0 + k) % kSlots) << 4));
+#pragma unroll
+                        for (int k = 0; k < kRowsAtOnce; ++k) {
+                            if (accumulate) y[k] += __uint_as_float(old[k]);
+                            const unsigned short bits = __builtin_bit_cast(unsigned short, (__bf16)y[k]);
+                            if (i * 32 + r0 + k < rows_left && c < cols_left) edge_mag = pk_max_mag(edge_mag, (unsigned)bits);
+                            __builtin_amdgcn_raw_buffer_store_b16(bits, rsC, coff + (unsigned)((r0 + k) * Cn) * 2, 0, 0);
+                        }
+                    };
+#pragma unroll 1
+                    for (int r0 = 0; r0 < 32 && i * 32 + r0 < rows_left; r0 += 16) {
+                        if (rows_left - (i * 32 + r0) > 2) rows_from(IntTag<16>{}, r0);
+                        else rows_from(IntTag<2>{}, r0);                     // a single row (decoding) does not wait for sixteen
                     }
+                }
             }
         }
     } else if constexpr (!ACCUM) {
@@ -1274,7 +1300,7 @@ struct EdgeChoice {
     int ni, nj;       // 0, 0: the generic kernel
     int edge;         // kEdge or kEdgeUnaligned
 };
-EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b);
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool bf16);
 
 template <int FA, int FB, int NI, int NJ, bool TA, bool TB, int EDGE>
 static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
@@ -1309,7 +1335,7 @@ static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
 // false: no tile kernel takes the shape.  Instantiated in gemm_edge_*.hip.
 template <int FA, int FB, bool TA, bool TB>
 bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
-    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b);
+    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b, accumulate != 0, FA == kFmtBf16);
 #define LLMQ_EDGE_CASE(I, J)                                                                                        \
     case I * 8 + J:                                                                                                 \
         if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); \

@@ -66,6 +66,31 @@ def test_ragged_fp8(R, C, T, tile, monkeypatch):
         assert torch.equal(first.view(torch.int16), c.view(torch.int16))      # same sums in every layout
 
 
+@pytest.mark.parametrize("R,C,T", SHAPES + [(1, 1001, 384), (16, 17, 16), (130, 300, 48), (700, 520, 256), (40, 40, 2000), (2000, 136, 100)])
+def test_generic_and_tile_kernel_give_the_same_bytes(R, C, T, monkeypatch):
+    """Small problems take the generic kernel, by a rule on sizes, layouts and accumulation: nothing else may depend on it."""
+    fa = (R + C) % 2
+    A, B = _rand_codes((R, T), fa, 11 * R + T), _rand_codes((C, T), 0, 13 * C + T)
+    dsa, dsb = _scales(2.9, 0.37)
+    c0 = _rand((R, C), 6, 30.0)
+    for ta, tb in ((False, False), (False, True), (True, True)):
+        a, b, got = _operand(A, ta), _operand(B, tb), []
+        for tile in ("0x0", "2x2", None):
+            if tile is None:
+                monkeypatch.delenv("LLMQ_GEMM_EDGE_TILE")
+            else:
+                monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+            print("R=%d C=%d T=%d tile=%s ta=%d tb=%d" % (R, C, T, tile, ta, tb), flush=True)
+            am = torch.zeros(2, dtype=torch.float32, device=DEV)
+            (buf, c), (buf2, acc) = _guarded(R, C), _guarded(R, C, c0)
+            llmq.llmq_fp8_gemm(a, fa, ta, b, 0, tb, dsa, dsb, c, False, am[0:1])
+            llmq.llmq_fp8_gemm(a, fa, ta, b, 0, tb, dsa, dsb, acc, True, am[1:2])
+            assert _untouched(buf, R, C) and _untouched(buf2, R, C)
+            got.append((buf.view(torch.int16), buf2.view(torch.int16), am))
+        for other in got[1:]:
+            assert all(torch.equal(x, y) for x, y in zip(got[0], other))
+
+
 @pytest.mark.parametrize("tile", TILES)
 @pytest.mark.parametrize("R,C,T", [(257, 264, 136), (130, 8, 8), (40, 300, 500), (255, 129, 63), (300, 520, 257)])
 def test_ragged_bf16(R, C, T, tile, monkeypatch):

@@ -507,7 +507,7 @@ int64_t rmsnorm_blocks(int64_t M) { return (M + kRnRowsPerBlock - 1) / kRnRowsPe
 //   Rows of whole vectors up to 2048 columns, generic against row: 4001 x 264 8.8 / 6.6, 16384 x 1000 33 / 29: always row.
 //   Ragged rows, generic against row: 16384 x 100 10.5 / 14.7, 2048 x 300 7.7 / 7.7, 4001 x 385 10.1 / 8.9, 16384 x 1001 42 / 32;
 //   without the addition and on many rows the generic kernel, which has less to move then, holds out longer: 16384 x 501 17 / 21,
-//   60001 x 700 65 / 79, 16384 x 1001 30 / 26, while 4001 x 450 takes 8.7 / 8.3.
+//   60001 x 700 65 / 79, 8001 x 701 11.9 / 13.7, 16384 x 1001 30 / 26, while 4001 x 450 takes 8.7 / 8.3.
 //   Wide rows, row against rows: 1 x 8192 10.8 / 7.0, 64 x 8192 12.3 / 13.5, 700 x 6144 18 / 14, 1000 x 8192 26 / 21, 4001 x 6144 36 / 40,
 //   8000 x 7168 88 / 89, 16384 x 5120 135 / 123; 16384 x 4096 96 / 96, and without the addition row is as good from three rows on.
 //   More than 8192 columns, or ragged and more than 2048: rows at any size (300 x 8200 55 / 18 against generic).
@@ -524,7 +524,7 @@ static NormKind norm_kind(int64_t M, int64_t C, bool with_x) {
         if (k == 2 && rows_ok) return kNormRows;
     }
     if (!row_ok) return rows_ok ? kNormRows : kNormGeneric;
-    if (edge) return C < (with_x ? 320 : M > 8192 ? 800 : 384) ? kNormGeneric : kNormRow;
+    if (edge) return C < (with_x ? 320 : M >= 6000 ? 800 : 384) ? kNormGeneric : kNormRow;
     if (!rows_ok) return kNormRow;
     const bool few = M <= 2, one_per_cu = M >= 640 && M <= 1536, many = M >= 12288;
     return few || (with_x && C > 4096 && (one_per_cu || many)) ? kNormRows : kNormRow;

@@ -214,7 +214,7 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
     for (int ni = 4; ni >= 2; ni -= 2)
         for (int nj = 4; nj >= 2; nj -= 2) {
             const int64_t tiles = ((R + 64 * ni - 1) / (64 * ni)) * ((C + 64 * nj - 1) / (64 * nj));
-            if (tiles >= (1ll << 30)) continue;
+            if (tiles > kMaxWorkgroups) continue;
             const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;
             const int64_t slots = resident_slots(num_cus, ni, nj);
             const int64_t rounds = (tiles + slots - 1) / slots;

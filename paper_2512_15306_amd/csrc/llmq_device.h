@@ -327,14 +327,25 @@ constexpr int kSmallPitch = kSmallRows + 16, kSmallLdsBytes = kSmallCols * kSmal
 // 1777 x 20000 40.3 / 33.5 / 33.6 / 38.9, 9001 x 3001 32.4 / 31.3 / 30.8 / 31.3, 16000 x 9000 202 / 202 / 174 / 173;  rows of
 // whole lines: 3584 x 21440 69 / 78 / 73 / 85, 8100 x 7168 53.6 / 55.1 / 58.0 / 59.8.
 constexpr unsigned kSmallXcds = 8, kSmallBand = 8;
-struct SmallGrid { unsigned rows, cols, blocks; bool xcd_ranges; };          // tiles, and workgroups of the launch
+struct SmallGrid {
+    unsigned rows, cols, blocks;            // tiles (at most 2^28: tensors have at most 2^40 elements and 2^31 rows), workgroups in all
+    unsigned first;                         // first workgroup of this launch
+    bool xcd_ranges;
+};
 inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     SmallGrid g;
     g.rows = (unsigned)((rows + kSmallRows - 1) / kSmallRows);
     g.cols = (unsigned)((cols + kSmallCols - 1) / kSmallCols);
     g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
+    g.first = 0;
     g.xcd_ranges = cols % 64 != 0;
     return g;
+}
+// launch(grid, workgroups of this launch), once or as often as the launch limit asks for
+template <class F>
+inline void small_launches(SmallGrid g, F launch) {
+    const unsigned most = max_workgroups();
+    for (; g.first < g.blocks; g.first += most) launch(g, g.blocks - g.first < most ? g.blocks - g.first : most);
 }
 // The tile of workgroup id; false for the padding ids (id 0 always has one)
 __device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsigned& brow, unsigned& bcol) {

@@ -15,6 +15,14 @@ inline const char* tuning_env(const char* name) {
     return enabled ? getenv(name) : nullptr;
 }
 
+// Workgroups of 256 lanes that one launch may have (fewer than 2^32 lanes, whole rounds of the 8 XCDs); what needs more is
+// launched in pieces.  LLMQ_MAX_WORKGROUPS=n (tests): a smaller limit, a multiple of 8.
+constexpr unsigned kMaxWorkgroups = (1u << 24) - 8;
+inline unsigned max_workgroups() {
+    if (const char* e = tuning_env("LLMQ_MAX_WORKGROUPS")) return (unsigned)atoi(e);
+    return kMaxWorkgroups;
+}
+
 // The workgroup tile of the kernels that write FP8 codes in both layouts (quantize, and the SwiGLU and RMSNorm
 // kernels that emit FP8 directly); only tensors made of whole tiles have a transposed copy in slabs.
 constexpr int kTileRows = 128, kTileCols = 256;

@@ -26,12 +26,12 @@ struct QuantTensor {
     // (qt_row_stride, qt_band_stride) = (rows, 128) for the transposed tensor as such, (128, cols x 128) in slabs
     int64_t qt_row_stride, qt_band_stride;
     SmallGrid grid;                              // 64 x 128 tiles
-    unsigned blocks;
+    unsigned first_block, blocks;                // of this launch
 };
 struct QuantPair { QuantTensor first, second; };
 __device__ inline const QuantTensor& tensor_of_block(const QuantPair& p, unsigned& block) {
-    if (blockIdx.x < p.first.blocks) { block = blockIdx.x; return p.first; }
-    block = blockIdx.x - p.first.blocks;
+    if (blockIdx.x < p.first.blocks) { block = p.first.first_block + blockIdx.x; return p.first; }
+    block = p.second.first_block + (blockIdx.x - p.first.blocks);
     return p.second;
 }
 
@@ -235,18 +235,29 @@ static void launch_kind(QuantKind kind, const QuantPair& pair, bool stream_out, 
 static int launch_jobs(const QuantJob& first, const QuantJob* second, int fmt, bool read_next, hipStream_t stream) {
     for (const QuantJob* j : {&first, second})
         if (j && j->qt_slabs && !(j->q_t && quantize_can_write_slabs(j->rows, j->cols))) return -2;       // the caller asks first
-    auto launch = [&](const QuantJob& j, const QuantJob* with, QuantKind kind) {
-        const QuantPair pair{quant_tensor(j, kind), with ? quant_tensor(*with, kind) : QuantTensor{}};
-        const bool stream_out = !read_next && streams_out(2 * j.rows * j.cols, j.cols, 128, 96);
+    const unsigned most = max_workgroups();
+    auto launch = [&](const QuantTensor& t, const QuantTensor& with, QuantKind kind) {
+        const QuantPair pair{t, with};
+        const bool stream_out = !read_next && streams_out(2 * t.rows * t.cols, t.cols, 128, 96);
         if (fmt == 0) launch_kind<0>(kind, pair, stream_out, stream);
         else launch_kind<1>(kind, pair, stream_out, stream);
+    };
+    auto launch_one = [&](QuantTensor t, QuantKind kind) {                       // in pieces, if it has to be
+        for (unsigned blocks = t.blocks; t.first_block < blocks; t.first_block += most) {
+            t.blocks = blocks - t.first_block < most ? blocks - t.first_block : most;
+            launch(t, QuantTensor{}, kind);
+        }
     };
     QuantKind kind = quant_kind(first), kind2 = second ? quant_kind(*second) : kind;
     // (the 64 x 128 tile takes every shape: one launch of both on it beats two launches)
     if ((kind == kQuantElements && kind2 == kQuantSmall) || (kind == kQuantSmall && kind2 == kQuantElements)) kind = kind2 = kQuantSmall;
-    const bool together = second && kind == kind2;
-    launch(first, together ? second : nullptr, kind);
-    if (second && !together) launch(*second, nullptr, kind2);
+    const QuantTensor t = quant_tensor(first, kind), t2 = second ? quant_tensor(*second, kind2) : QuantTensor{};
+    if (second && kind == kind2 && t.blocks < most && t2.blocks < most - t.blocks) {
+        launch(t, t2, kind);
+    } else {
+        launch_one(t, kind);
+        if (second) launch_one(t2, kind2);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     uint8_t* __restrict__ qt, uint16_t* __restrict__ y, const SmallGrid grid, int64_t qt_row_stride, int64_t qt_band_stride) {
     __shared__ __attribute__((aligned(16))) uint8_t s_t[TRANSPOSE ? kSmallLdsBytes : 16];
     unsigned brow, bcol;
-    if (!small_tile(grid, blockIdx.x, brow, bcol)) return;
+    if (!small_tile(grid, grid.first + blockIdx.x, brow, bcol)) return;
     int tr, tc;
     small_patch_origin(tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
@@ -610,9 +610,10 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
         hipLaunchKernelGGL(rmsnorm_apply_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kRnThreads), 0, stream,
                            res, w, rstd, M, C, d_qscale, q, q_t, y);
     } else {
-        const SmallGrid g = small_grid(M, C);
-        if (q_t) hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, true>), dim3(g.blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
-        else hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, false>), dim3(g.blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
+        small_launches(small_grid(M, C), [&](const SmallGrid& g, unsigned blocks) {
+            if (q_t) hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, true>), dim3(blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
+            else hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, false>), dim3(blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
+        });
     }
 }
 

@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_fp8_small_kernel(
     int64_t qt_row_stride, int64_t qt_band_stride) {
     __shared__ __attribute__((aligned(16))) uint8_t s_t[TRANSPOSE ? kSmallLdsBytes : 16];
     unsigned brow, bcol;
-    if (!small_tile(grid, blockIdx.x, brow, bcol)) return;
+    if (!small_tile(grid, grid.first + blockIdx.x, brow, bcol)) return;
     int tr, tc;
     small_patch_origin(tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
@@ -562,9 +562,10 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
         hipLaunchKernelGGL(swiglu_fwd_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kSwThreads), 0, stream,
                            gu, M, I, h, d_qscale, q, q_t);
     } else {
-        const SmallGrid g = small_grid(M, I);
-        if (q_t) hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, true>), dim3(g.blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
-        else hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, false>), dim3(g.blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
+        small_launches(small_grid(M, I), [&](const SmallGrid& g, unsigned blocks) {
+            if (q_t) hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, true>), dim3(blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
+            else hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, false>), dim3(blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
+        });
     }
     return 0;
 }

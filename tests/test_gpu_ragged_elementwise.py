@@ -69,6 +69,27 @@ def test_codes_of_every_producer(rows, cols, tile, kind, fmt, monkeypatch):
                 assert np.array_equal(_whole(qt, n, 0xAA).cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("rows,cols", [(200, 1300), (129, 257), (300, 1001)])
+def test_launches_in_pieces(rows, cols, monkeypatch):
+    """More workgroups than a launch may have (a limit of 8 stands for that of the hardware): the same bytes."""
+    monkeypatch.setenv("LLMQ_CODES_KERNEL", "2")
+    monkeypatch.setenv("LLMQ_MAX_WORKGROUPS", "8")
+    for fmt in (0, 1):
+        test_codes_of_every_producer(rows, cols, None, None, fmt, monkeypatch)
+    M, K, N = rows, cols, rows + 24
+    g = torch.Generator().manual_seed(rows)
+    x, w = (torch.randn(s, generator=g).to(torch.bfloat16).to(DEV) for s in ((M, K), (N, K)))
+    got = []
+    for most in ("8", None):
+        if most is None:
+            monkeypatch.delenv("LLMQ_MAX_WORKGROUPS")
+        ws = torch.zeros(llmq.llmq_fp8_linear_workspace_bytes(M, N, K), dtype=torch.uint8, device=DEV)
+        y, s, a = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV), torch.zeros(2, device=DEV), torch.full((1,), 7.0, device=DEV)
+        llmq.llmq_fp8_linear_fwd(x, w, M, N, K, s[0:1], s[1:2], y, a, ws, llmq.JIT_X | llmq.JIT_W)
+        got.append((ws, y.view(torch.int16), s, a))
+    assert all(torch.equal(p, q) for p, q in zip(*got))
+
+
 @pytest.mark.parametrize("M,I", [(1, 1), (3, 9), (5, 511), (4, 512), (7, 513), (130, 1001), (2, 1030), (64, 8), (36, 32), (4, 40)])
 @pytest.mark.parametrize("kind", [None, "0", "2"])
 def test_swiglu_forward_and_backward_of_ragged_shapes(M, I, kind, monkeypatch):

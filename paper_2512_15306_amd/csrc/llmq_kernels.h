@@ -127,16 +127,15 @@ struct QuantJob {
     unsigned* zero_word;
     bool qt_slabs;
 };
-// launch_quantize_from for two tensors of the same format, in one launch where they take the same kernel.  (Weak, as the
-// absmax pair below: a host-only build of the ABI over counting stubs has the launchers of single tensors only.)
-int launch_quantize_pair(const QuantJob& first, const QuantJob& second, int fmt, hipStream_t stream) __attribute__((weak));
+// launch_quantize_from for two tensors of the same format, in one launch where they take the same kernel.
+int launch_quantize_pair(const QuantJob& first, const QuantJob& second, int fmt, hipStream_t stream);
 bool quantize_can_write_slabs(int64_t rows, int64_t cols);
 // First stage of the absmax only: one BF16 magnitude pattern per workgroup into partial; returns the number
 // of workgroups (<= kAmaxMaxPartials) through n_partial.
 int launch_amax_partial(const void* x, size_t n, unsigned* partial, int* n_partial, hipStream_t stream, int num_cus);
 // The same for two tensors in one launch.
 int launch_amax_partial_pair(const void* x, size_t n, unsigned* partial, int* n_partial, const void* x2, size_t n2, unsigned* partial2,
-                             int* n_partial2, hipStream_t stream, int num_cus) __attribute__((weak));
+                             int* n_partial2, hipStream_t stream, int num_cus);
 // Caller-owned device scratch for the binary32 pieces of output tiles whose contraction is shared among
 // several workgroups (a ragged last round of tiles); {nullptr, 0}: every tile is computed by one workgroup.
 struct GemmScratch {

@@ -348,7 +348,7 @@ inline void small_launches(SmallGrid g, F launch) {
     for (; g.first < g.blocks; g.first += most) launch(g, g.blocks - g.first < most ? g.blocks - g.first : most);
 }
 // The tile of workgroup id; false for the padding ids (id 0 always has one)
-__device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsigned& brow, unsigned& bcol) {
+__host__ __device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsigned& brow, unsigned& bcol) {
     const unsigned pos = g.xcd_ranges ? (id % kSmallXcds) * (g.blocks / kSmallXcds) + id / kSmallXcds : id;
     if (pos >= g.rows * g.cols) return false;
     const unsigned band = g.xcd_ranges && kSmallBand < g.cols ? kSmallBand : g.cols;

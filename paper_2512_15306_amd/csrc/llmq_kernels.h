@@ -77,7 +77,9 @@ inline CodesKind codes_kind(int64_t rows, int64_t cols) {
 // calls, whose contraction reads the codes at once, codes are never streamed (no difference up to 32B-class layers).
 // Only rows of whole 128-byte lines (cols_of_lines: columns a line holds): a line that two stores share goes to memory twice when it
 // is streamed (backward of 60000 x 1000 131 / 177 us, of 1000000 x 72 193 / 275).
+// LLMQ_STREAM=0 / 1 (tests): never, or for rows of whole lines always.
 inline bool streams_out(int64_t result_bytes, int64_t cols, int64_t cols_of_line, int limit_mib = 144) {
+    if (const char* e = tuning_env("LLMQ_STREAM")) return atoi(e) != 0 && cols % cols_of_line == 0;
     return cols % cols_of_line == 0 && result_bytes > ((int64_t)limit_mib << 20);
 }
 

@@ -1,6 +1,7 @@
 // Host-side brute force over the index arithmetic of the tile kernel's launches, under the sanitizers: the walk
 // of the workgroup ids over the tiles, the planner that shares a ragged last round of tiles among the compute
-// units, and the walk of the quantize kernel's workgroups over the blocks of its tensor.  Every tile, and every K step of every shared tile, must be computed exactly once, and every partial
+// units, the walk of the quantize kernel's workgroups over the blocks of its tensor, and that of the 64 x 128-tile kernels'
+// workgroups over their tiles.  Every tile, and every K step of every shared tile, must be computed exactly once, and every partial
 // result must have a slot of its own inside the scratch the plan asks for.
 #include <stdio.h>
 #include <stdlib.h>
@@ -64,6 +65,35 @@ static void check_bands(unsigned gr, unsigned gc, unsigned band) {
             seen[(size_t)br * gc + bc] = 1;
         }
     }
+}
+
+// The 64 x 128-tile kernels: every tile once, whatever the launches are cut into; no id but the padding ones without a tile, id 0
+// with one (it stores the scale); on ragged pitches each XCD's ids (congruent modulo 8) on one contiguous range of the walk.
+static void check_small(int64_t rows, int64_t cols) {
+    const SmallGrid g = small_grid(rows, cols);
+    CHECK(g.rows == (unsigned)((rows + 63) / 64) && g.cols == (unsigned)((cols + 127) / 128) && g.first == 0, "%lld x %lld", (long long)rows, (long long)cols);
+    CHECK(g.blocks % 8 == 0 && g.blocks >= g.rows * g.cols && g.blocks < g.rows * g.cols + 8, "%lld x %lld: %u workgroups", (long long)rows, (long long)cols, g.blocks);
+    std::vector<int> seen((size_t)g.rows * g.cols, 0), in_launches(g.blocks, 0);
+    small_launches(g, [&](const SmallGrid& part, unsigned n) {
+        for (unsigned b = 0; b < n; ++b) {
+            const unsigned id = part.first + b;
+            CHECK(id < g.blocks, "id %u of %u", id, g.blocks);
+            if (id < g.blocks) ++in_launches[id];
+        }
+    });
+    unsigned padding = 0;
+    for (unsigned id = 0; id < g.blocks; ++id) {
+        CHECK(in_launches[id] == 1, "%lld x %lld: id %u launched %d times", (long long)rows, (long long)cols, id, in_launches[id]);
+        unsigned br = ~0u, bc = ~0u;
+        if (!small_tile(g, id, br, bc)) { ++padding; CHECK(id != 0, "id 0 without a tile"); continue; }
+        CHECK(br < g.rows && bc < g.cols, "%lld x %lld id %u -> (%u, %u)", (long long)rows, (long long)cols, id, br, bc);
+        if (br < g.rows && bc < g.cols) ++seen[(size_t)br * g.cols + bc];
+        unsigned br2, bc2;
+        if (g.xcd_ranges && id + 8 < g.blocks && small_tile(g, id + 8, br2, bc2))          // the next of this XCD: a neighbour in the band or its next row
+            CHECK((br2 == br && bc2 == bc + 1) || br2 == br + 1 || br2 == 0, "%lld x %lld: ids %u, %u -> (%u, %u), (%u, %u)", (long long)rows, (long long)cols, id, id + 8, br, bc, br2, bc2);
+    }
+    CHECK(padding == g.blocks - g.rows * g.cols, "%lld x %lld: %u ids without a tile", (long long)rows, (long long)cols, padding);
+    for (size_t t = 0; t < seen.size(); ++t) CHECK(seen[t] == 1, "%lld x %lld: tile %zu taken %d times", (long long)rows, (long long)cols, t, seen[t]);
 }
 
 // Replays what the three launches of a contraction do with the plan, as the kernel's prologue does.
@@ -142,6 +172,13 @@ int main() {
         check_bands(3 * 4096 + 1, 7, b);
         check_bands(1u << 20, 2, b);               // 2^27 rows
     }
+    for (const char* most : {(const char*)nullptr, "8", "64"}) {
+        if (most) setenv("LLMQ_MAX_WORKGROUPS", most, 1);
+        else unsetenv("LLMQ_MAX_WORKGROUPS");
+        for (int64_t r : {1, 64, 65, 130, 640, 1025, 5000})
+            for (int64_t c : {1, 24, 128, 129, 192, 1000, 1024, 1152, 1300, 4097, 9000}) check_small(r, c);
+    }
+    unsetenv("LLMQ_MAX_WORKGROUPS");
     const char* modes[] = {nullptr, "1", "a2", "a3", "a5", "a16", "0"};
     const int nks[] = {1, 2, 7, 8, 15, 16, 28, 40, 63, 64, 65, 108, 128, 216, 432};
     const int slot_counts[] = {256, 64, 8};

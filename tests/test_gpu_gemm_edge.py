@@ -127,3 +127,58 @@ def test_values_beyond_the_operands_do_not_reach_the_results(fa, T):
     a[5, T - 1] = 0x38
     llmq.llmq_fp8_gemm_tn(a, fa, b, 0, dsa, dsb, c, False, am)
     assert torch.isfinite(c).all() and am.item() == c.float().abs().max().item()
+
+
+@pytest.mark.parametrize("fa", [0, 1])
+@pytest.mark.parametrize("T", [16, 40, 100, 129, 250, 272, 400])
+def test_values_beyond_t_major_operands_do_not_reach_the_results(fa, T):
+    """The same with the contraction running down the rows: what lies behind the last row and, T no multiple of a K step,
+    where the rows of that step would be; widths with and without whole 16-byte chunks."""
+    nan, inf = (0x7F, 0x7F) if fa == 0 else (0x7E, 0x7C)
+    for R, C in ((144, 80), (130, 72)):
+        A, B = _rand_codes((R, T), fa, 3), _rand_codes((C, T), 0, 4)
+        bufA = torch.full((R * T + 65536,), inf, dtype=torch.uint8, device=DEV)
+        bufB = torch.full((C * T + 65536,), 0x7F, dtype=torch.uint8, device=DEV)
+        dsa, dsb = _scales(1.5, 0.8)
+        y, S = oracle.gemm_tn(A, fa, B, 0, 1.5, 0.8)
+        for ta in (False, True):
+            a, b = (bufA[:R * T].view(T, R) if ta else bufA[:R * T].view(R, T)), bufB[:C * T].view(T, C)
+            a.copy_(_operand(A, ta))
+            b.copy_(_operand(B, True))
+            for tile in ("2x2", "4x4", "0x0"):
+                with pytest.MonkeyPatch.context() as mp:
+                    mp.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+                    print("beyond T-major: fa=%d R=%d C=%d T=%d ta=%d tile=%s" % (fa, R, C, T, ta, tile), flush=True)
+                    am, c = torch.zeros(1, dtype=torch.float32, device=DEV), torch.zeros((R, C), dtype=torch.bfloat16, device=DEV)
+                    llmq.llmq_fp8_gemm(a, fa, ta, b, 0, True, dsa, dsb, c, False, am)
+                    assert_gemm_close(c, y, S, "beyond")
+                    assert am.item() == c.float().abs().max().item()
+
+
+@pytest.mark.parametrize("T", [272, 1001, 4112, 3999])
+def test_more_tiles_than_compute_units(T, monkeypatch):
+    """Many tiles, bands and rounds, long and short contractions, aligned and unaligned: the tile the library picks, all tiles
+    forced, a second run and every layout give the same bytes; sampled rows and columns against the oracle."""
+    R, C = 3001, 2888
+    A, B = _rand_codes((R, T), 0, T), _rand_codes((C, T), 0, T + 1)
+    dsa, dsb = _scales(1.7, 0.9)
+    rows, cols = np.r_[0:R:397, R - 1], np.r_[0:C:351, C - 1]
+    y, S = oracle.gemm_tn(np.ascontiguousarray(A[rows]), 0, np.ascontiguousarray(B[cols]), 0, 1.7, 0.9)
+    first = None
+    for ta, tb in ((False, False), (False, True), (True, True)):
+        a, b = _operand(A, ta), _operand(B, tb)
+        for tile in (None, None) + tuple(TILES if not ta else ()):
+            if tile is None:
+                monkeypatch.delenv("LLMQ_GEMM_EDGE_TILE", raising=False)
+            else:
+                monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+            print("large T=%d tile=%s ta=%d tb=%d" % (T, tile, ta, tb), flush=True)
+            am = torch.zeros(1, dtype=torch.float32, device=DEV)
+            buf, c = _guarded(R, C)
+            llmq.llmq_fp8_gemm(a, 0, ta, b, 0, tb, dsa, dsb, c, False, am)
+            assert _untouched(buf, R, C)
+            assert am.item() == c.float().abs().max().item()
+            if first is None:
+                first = c.clone().view(torch.int16)
+                assert_gemm_close(c[torch.from_numpy(rows).to(DEV)][:, torch.from_numpy(cols).to(DEV)], y, S, "large")
+            assert torch.equal(first, c.view(torch.int16))

@@ -7,7 +7,7 @@ import torch
 import oracle
 from paper_2512_15306_amd import llmq, synth
 from gpu_common import DEV, f32_bits, np_f32_bits
-from test_gpu_rmsnorm import EPS, RSTD_TOL, _case as rms_case
+from test_gpu_rmsnorm import EPS, RSTD_TOL, _case as rms_case, gpu_rmsnorm_fwd
 from test_gpu_swiglu import _case as swiglu_case
 
 pytestmark = pytest.mark.gpu
@@ -67,6 +67,27 @@ def test_codes_of_every_producer(rows, cols, tile, kind, fmt, monkeypatch):
             assert np.array_equal(_whole(q, n, 0xAA).cpu().numpy(), want_q.reshape(-1))
             if want is not None:
                 assert np.array_equal(_whole(qt, n, 0xAA).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("stream", ["0", "1"])
+def test_streamed_results(stream, monkeypatch):
+    """Results of rows of whole lines are streamed from 96 or 144 MiB on: every such kernel on small shapes, against the oracle."""
+    monkeypatch.setenv("LLMQ_STREAM", stream)
+    for rows, cols in FORCED:
+        for fmt in (0, 1):
+            test_codes_of_every_producer(rows, cols, "1", None, fmt, monkeypatch)
+    for M, I in ((8, 64), (16, 576), (4, 128), (36, 320)):                      # eight and four rows per lane
+        test_swiglu_forward_and_backward_of_ragged_shapes(M, I, None, monkeypatch)
+    monkeypatch.setenv("LLMQ_NORM_KERNEL", "2")
+    for M in (1, 6):
+        for C in (2112, 4096, 5120, 8192, 8256, 16384):
+            for with_x in (True, False):
+                test_rmsnorm_forward_at_the_edges_of_its_widths(M, C, with_x)
+    for C in (2112, 8192, 16384):
+        res, x, w = rms_case(7, C, C)
+        out = gpu_rmsnorm_fwd(res, x, w, 0)
+        in_place = gpu_rmsnorm_fwd(res, x, w, 0, in_place=True)
+        assert all(torch.equal(a, b) for a, b in zip(out, in_place))
 
 
 @pytest.mark.parametrize("rows,cols", [(200, 1300), (129, 257), (300, 1001)])

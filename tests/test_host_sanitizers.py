@@ -1,8 +1,8 @@
 """Host code under AddressSanitizer and UndefinedBehaviorSanitizer, on the CPU: the C oracle on small, ragged
 and degenerate inputs, the C ABI's argument checks and launch sequencing (csrc/api.hip compiled for the
 host only, kernel launchers replaced by counting stubs), and the index arithmetic of the GEMM launches (the
-walk of the workgroup ids over the tiles and the planner that shares a ragged last round of tiles, replayed by
-brute force).  GPU code is not instrumented: device sanitizers are
+walk of the workgroup ids over the tiles, also of the element-wise kernels, and the planner that shares a ragged last
+round of tiles, replayed by brute force).  GPU code is not instrumented: device sanitizers are
 not available on the test machines."""
 import os
 import shutil

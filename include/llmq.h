@@ -152,7 +152,7 @@ int llmq_fp8_gemm_tn(const uint8_t* A, int fmtA, const uint8_t* B, int fmtB,
  *   dW[n,k] = sum_m dYq[m,n] Xq[m,k]   : A = dYq [M,N] T-major,    B = Xq [M,K] T-major, T = M
  * Tuned for B in E4M3 and T-major operands below 2 GiB (dimensions that are no multiples of 128 with guarded edges);
  * T-major B in E5M2, ragged shapes with only A T-major, contractions (and T-major widths) below 16 and dimensions of
- * millions take a slow generic kernel.  In the tuned kernel (and likewise in the generic one) every product lands in the same accumulator
+ * millions take a slow generic kernel, ragged problems so small that it is the faster one too.  In the tuned kernel (and likewise in the generic one) every product lands in the same accumulator
  * position as with transposed copies, so the result is bit-identical to llmq_fp8_gemm_tn on those copies
  * whenever both calls run the same kind of kernel, which is the case for what the linear calls below launch
  * on operands below 2 GiB.  Arguments otherwise as above.
@@ -198,7 +198,8 @@ int llmq_fp8_gemm_with_scratch(const uint8_t* A, int fmtA, int a_t_major, const 
  * A [R,T], B [C,T] BF16 with the contraction index contiguous, binary32 accumulation on the matrix cores
  * (v_mfma_f32_16x16x32_bf16 in the same tile kernel), one RNE rounding.  Error per element is bounded by
  * 2^-8 |c| + T 2^-24 sum_t |A[r,t] B[cc,t]|.  Shapes with R, C multiples of 128 and T a multiple of 64
- * are fastest, others take the same kernel with guarded edges (a slow generic one below T = 8).
+ * are fastest, others take the same kernel with guarded edges (a generic one below T = 8 and for small problems, with its
+ * sums in another order).
  */
 int llmq_bf16_gemm_tn(const void* A_bf16, const void* B_bf16, int64_t R, int64_t C, int64_t T,
                       void* c_bf16, int accumulate, void* stream);
@@ -354,8 +355,8 @@ int llmq_swiglu_bwd(const void* dh_bf16, const void* gu_bf16, int64_t M, int64_t
  * llmq_rmsnorm_fwd: x may be NULL (no addition: res is normalised as it is and res_out is ignored);
  *   otherwise res_out receives res' and may be the same buffer as res (in place).  Writes y, rstd (kept for
  *   the backward pass / recomputation), d_amax_y = max |y| and, if not NULL, d_scale_y for format fmt, both
- *   bit-identical to llmq_amax of y.  The row sum runs in binary32 in an order of the kernel's choosing, so
- *   rstd is reproducible run to run but only equal to the exact value within 2^-20 relative; y then is the
+ *   bit-identical to llmq_amax of y.  The row sum runs in binary32 in an order that depends on C alone, so
+ *   rstd is reproducible from run to run and batch to batch but only equal to the exact value within 2^-20 relative; y then is the
  *   formula above evaluated with that rstd.  ws: at least llmq_rmsnorm_workspace_bytes(M) bytes, 16-byte
  *   aligned, contents irrelevant (per-workgroup partial absmax; no atomics).
  * llmq_rmsnorm_apply_fp8: the recompute path.  res (the stored stream), w, rstd and the scale of y are
@@ -365,7 +366,7 @@ int llmq_swiglu_bwd(const void* dh_bf16, const void* gu_bf16, int64_t M, int64_t
  * llmq_rmsnorm_apply_fp8_slabs: the same with q_t (required) in slabs of 128 contraction bytes, as
  *   llmq_quantize_fp8_slabs writes it from y, for a linear call with LLMQ_REUSE_X | LLMQ_SLAB_COPIES.
  *   M % 128 == 0, C % 256 == 0 and M C < 0x70000000, else LLMQ_ERR_SHAPE.
- * M, C >= 1, C < 2^24.  C % 8 == 0 is fastest; C <= 16384 takes a single-pass forward kernel, wider rows are read twice.
+ * M, C >= 1, C < 2^24.  C % 8 == 0 is fastest; rows of C <= 16384 are read once, wider and narrow ragged ones twice.
  * The recompute calls are fastest with M % 128 == 0 and C % 256 == 0 (M % 4 == 0 and C % 8 == 0 without q_t).
  */
 size_t llmq_rmsnorm_workspace_bytes(int64_t M);

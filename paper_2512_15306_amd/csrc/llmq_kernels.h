@@ -68,7 +68,8 @@ inline CodesKind codes_kind(int64_t rows, int64_t cols) {
 }
 
 // Large results are stored with the streaming hint, so that they do not push out of the 256 MB memory-side cache what is
-// still to be read.  Plain / streaming, every pass on other buffers: SwiGLU backward 8192 x 18944 (592 MiB of results)
+// still to be read.  Plain / streaming, passes over three sets of buffers in turn, and the same over one set (a first pass over
+// buffers never touched before gains nothing: norm and recompute of 16384 x 5120 208 / 214): SwiGLU backward 8192 x 18944 (592 MiB of results)
 // 283 / 267 us, forward 8192 x 18944 (296 MiB) 170 / 162, codes 8192 x 18944 197 / 187 (the row-major copy; the transposed
 // one leaves in pieces of lines and stays plain); RMSNorm 16384 x 5120 (320 MiB) 134 / 127; codes in both layouts of
 // 8192 x 7168 elements (112 MiB) 45.4 / 42.3, 4096 x 8192 (64 MiB) 26.1 / 26.2.  What the next kernel reads should stay in

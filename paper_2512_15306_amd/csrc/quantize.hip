@@ -35,7 +35,7 @@ __device__ inline const QuantTensor& tensor_of_block(const QuantPair& p, unsigne
     return p.second;
 }
 
-// Tensors whose rows are a multiple of 128 and whose columns a multiple of 256 (every benchmark tensor): full 128-byte
+// Tensors of at least 256 whole 128 x 256 tiles (the benchmark's tensors but for its smallest configuration's): full 128-byte
 // lines on all three streams.  A lane owns a 16 x 8 patch, a wave is
 // 4 lanes stacked x 16 side by side, and the transposed copy cannot be written that way from registers (4 stacked
 // lanes hold 64 contiguous bytes of a transposed row), so the transposed patches go through LDS (the tile_*

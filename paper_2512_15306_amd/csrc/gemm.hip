@@ -165,7 +165,7 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
 //   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
 //   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
 //   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
-static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool bf16, int num_cus) {
+static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus) {
     if (bf16) {                                                             // (T in bytes)
         const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
         return R * C <= most;
@@ -177,7 +177,7 @@ static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
     const bool one = T <= BK, odd_width = C % 8 != 0;
     double generic, tile;
     if (!ta && !tb && T % 16 == 0) {
-        generic = (T % 32 == 0 ? 2.6 : 5.45) + 0.45 * steps + more * (0.25 + 0.44 * steps);
+        generic = (T % 32 == 0 ? 2.5 : 5.4) + 0.5 * steps + more * (0.25 + 0.44 * steps);
         tile = 4.9 + 0.29 * steps;
     } else if (!ta && !tb && one) {
         generic = 6.6 + more * 0.03 * (double)T;
@@ -194,13 +194,16 @@ static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
     const double rows = R < 16 ? 16.0 : R > 64 ? 64.0 : (double)R;          // that a wave of the tile kernel writes out
     if (odd_width) tile += (rows - 16.0) / 48.0 * 2.1;
     if (accumulate) { generic += 0.9 + 0.68 * more; tile += odd_width ? 1.2 : 0.6; }
+    // every wave of the generic kernel raises the same word, and atomics on one address follow each other at 9.5 ns (forward call
+    // of 300 x 256 -> 1024, 1216 waves: 25 us with it, 13.5 with the tile kernel)
+    if (with_amax) generic += 0.0095 * (double)(((R + 15) / 16) * ((C + 15) / 16));
     return generic < tile + 0.4e-6 * (double)R * (double)C;
 }
 
 // Tile and kind of a ragged problem, by the same model with the tiles rounded up.  Against the best of the four tiles, forced, over
 // 28 shapes from 1000^3 to 9000^2 x 1000: 0.7 % behind on average with aligned rows, 2.6 % with unaligned ones and 1.4 % with both
 // operands T-major; no other efficiencies of this model do better on the first two.
-EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool bf16) {
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
     // bytes in every row of an operand
@@ -212,7 +215,7 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
         if ((ni == 2 || ni == 4) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
         if (ni == 0) return best;                             // 0x0: the generic kernel
     }
-    if (generic_is_faster(R, C, T, ta, tb, accumulate, bf16, num_cus)) return best;
+    if (generic_is_faster(R, C, T, ta, tb, accumulate, with_amax, bf16, num_cus)) return best;
     if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
     double best_cost = 0;
     for (int ni = 4; ni >= 2; ni -= 2)

@@ -1301,7 +1301,7 @@ struct EdgeChoice {
     int ni, nj;       // 0, 0: the generic kernel
     int edge;         // kEdge or kEdgeUnaligned
 };
-EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool bf16);
+EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16);
 
 template <int FA, int FB, int NI, int NJ, bool TA, bool TB, int EDGE>
 static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
@@ -1336,7 +1336,7 @@ static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
 // false: no tile kernel takes the shape.  Instantiated in gemm_edge_*.hip.
 template <int FA, int FB, bool TA, bool TB>
 bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
-    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b, accumulate != 0, FA == kFmtBf16);
+    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16);
 #define LLMQ_EDGE_CASE(I, J)                                                                                        \
     case I * 8 + J:                                                                                                 \
         if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); \

@@ -26,12 +26,12 @@ struct QuantTensor {
     // (qt_row_stride, qt_band_stride) = (rows, 128) for the transposed tensor as such, (128, cols x 128) in slabs
     int64_t qt_row_stride, qt_band_stride;
     SmallGrid grid;                              // 64 x 128 tiles
-    unsigned first_block, blocks;                // of this launch
+    unsigned blocks, first_block;                // of this launch (only the 64 x 128 tile and the flat kernel may need several)
 };
 struct QuantPair { QuantTensor first, second; };
 __device__ inline const QuantTensor& tensor_of_block(const QuantPair& p, unsigned& block) {
-    if (blockIdx.x < p.first.blocks) { block = p.first.first_block + blockIdx.x; return p.first; }
-    block = p.second.first_block + (blockIdx.x - p.first.blocks);
+    if (blockIdx.x < p.first.blocks) { block = blockIdx.x; return p.first; }
+    block = blockIdx.x - p.first.blocks;
     return p.second;
 }
 
@@ -83,6 +83,7 @@ __global__ __launch_bounds__(kTileThreads) void quantize_small_kernel(const Quan
     __shared__ __attribute__((aligned(16))) uint8_t s_t[kSmallLdsBytes];
     unsigned block, brow, bcol;
     const QuantTensor& t = tensor_of_block(pair, block);
+    block += t.first_block;
     if (t.zero_word && block == 0 && threadIdx.x == 0) *t.zero_word = 0u;
     if (!small_tile(t.grid, block, brow, bcol)) return;
     const int64_t rows = t.rows, cols = t.cols;
@@ -160,6 +161,7 @@ __global__ __launch_bounds__(kQThreads) void quantize_flat_kernel(const QuantPai
     __shared__ unsigned s_part[kQThreads / kWave];
     unsigned block;
     const QuantTensor& t = tensor_of_block(pair, block);
+    block += t.first_block;
     if (t.zero_word && block == 0 && threadIdx.x == 0) *t.zero_word = 0u;
     const float s = resolve_scale(t.scale, block == 0, s_part);
     const int64_t n = t.rows * t.cols, n8 = n / 8;

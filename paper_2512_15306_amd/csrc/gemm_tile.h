@@ -911,9 +911,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     *reinterpret_cast<v4f*>(srow + (((2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (vector) {
-                v4u old[kPiecesPerLane];                                     // all of them on their way before the first is needed
-                if (accumulate) {
+            auto pieces = [&](auto with_old) __attribute__((always_inline)) {
+                constexpr bool OLD = decltype(with_old)::value;
+                v4u old[OLD ? kPiecesPerLane : 1];                           // all of them on their way before the first is needed
+                if constexpr (OLD) {
 #pragma unroll
                     for (int k = 0; k < kPiecesPerLane; ++k) old[k] = __builtin_amdgcn_raw_buffer_load_b128(rsC, voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2, 0, 0);
                 }
@@ -923,7 +924,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     const uint8_t* src = stage + r * kPitch + (((sl + r) % kSlots) << 4);
                     v4f y0 = *reinterpret_cast<const v4f*>(src), y1 = *reinterpret_cast<const v4f*>(src + 16 * kSlots);
                     const unsigned off = voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2;
-                    if (accumulate) {
+                    if constexpr (OLD) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const unsigned o = old[k][e >> 1], o1 = old[k][2 + (e >> 1)];
@@ -939,6 +940,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     }
                     __builtin_amdgcn_raw_buffer_store_b128(out, rsC, off, 0, 0);
                 }
+            };
+            if (vector) {
+                if (accumulate) pieces(BoolTag<true>{});
+                else pieces(BoolTag<false>{});
             } else {
                 // sixteen rows at a time: their old values are on their way together (row after row
                 // 300 x 300 x 64 took 24.7 us with accumulation and 8.9 without, this way 8.5 and 7.3; eight at a time 9.9 and 8.2)

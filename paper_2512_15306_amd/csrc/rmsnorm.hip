@@ -508,8 +508,14 @@ int64_t rmsnorm_blocks(int64_t M) { return (M + kRnRowsPerBlock - 1) / kRnRowsPe
 //   Ragged rows, generic against row: 16384 x 100 10.5 / 14.7, 2048 x 300 7.7 / 7.7, 4001 x 385 10.1 / 8.9, 16384 x 1001 42 / 32;
 //   without the addition and on many rows the generic kernel, which has less to move then, holds out longer: 16384 x 501 17 / 21,
 //   60001 x 700 65 / 79, 8001 x 701 11.9 / 13.7, 16384 x 1001 30 / 26, while 4001 x 450 takes 8.7 / 8.3.
-//   Wide rows, row against rows: 1 x 8192 10.8 / 7.0, 64 x 8192 12.3 / 13.5, 700 x 6144 18 / 14, 1000 x 8192 26 / 21, 4001 x 6144 36 / 40,
-//   8000 x 7168 88 / 89, 16384 x 5120 135 / 123; 16384 x 4096 96 / 96, and without the addition row is as good from three rows on.
+//   Wide rows, row against rows; "cold" with buffers of its own for every pass, "warm" with the same ones:
+//     cold 126 x 2304 9.8 / 9.2, 126 x 3072 11.1 / 9.6, 126 x 3584 12.3 / 9.9, 126 x 7168 18.4 / 14.4, 640 x 5120 17.0 / 13.8,
+//     1536 x 8192 30.5 / 27.2, 2048 x 4096 18.9 / 18.8, 3000 x 5120 27.6 / 30.5, 4096 x 3584 25.7 / 28.6, 8000 x 7168 95.6 / 90.6,
+//     16384 x 4096 110 / 94; warm 126 x 2304 7.0 / 8.4, 126 x 3072 7.5 / 8.8, 126 x 3584 8.1 / 9.1, 126 x 7168 11.6 / 12.9,
+//     640 x 5120 11.4 / 12.0, 1536 x 8192 31.5 / 26.3, 3000 x 5120 27.3 / 28.3, 16384 x 5120 134 / 124.  The line is where rows gains
+//     at least twice as much cold as it loses warm, or gains in both.  One or two rows are faster with rows at any width, 1 x 8192 9.9 / 6.2.
+//     Without the addition a wave has half as much to wait for, and row is faster from three rows on: cold 126 x 7168 8.8 / 10.6,
+//     3000 x 5120 15.0 / 18.4, 16384 x 7168 90.9 / 86.9, warm 81.8 / 86.0.
 //   More than 8192 columns, or ragged and more than 2048: rows at any size (300 x 8200 55 / 18 against generic).
 // LLMQ_NORM_KERNEL=0 / 1 / 2 (tests): generic, row or rows wherever that kernel takes the width.
 enum NormKind { kNormGeneric, kNormRow, kNormRows };
@@ -526,8 +532,7 @@ static NormKind norm_kind(int64_t M, int64_t C, bool with_x) {
     if (!row_ok) return rows_ok ? kNormRows : kNormGeneric;
     if (edge) return C < (with_x ? 320 : M >= 6000 ? 800 : 384) ? kNormGeneric : kNormRow;
     if (!rows_ok) return kNormRow;
-    const bool few = M <= 2, one_per_cu = M >= 640 && M <= 1536, many = M >= 12288;
-    return few || (with_x && C > 4096 && (one_per_cu || many)) ? kNormRows : kNormRow;
+    return M <= 2 || (with_x && C > 3072 && (M < 2560 || M >= 12288)) ? kNormRows : kNormRow;
 }
 
 int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t M, int64_t C, float eps,

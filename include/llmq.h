@@ -285,7 +285,8 @@ int llmq_fp8_linear_dgrad(const void* dY, const void* W, int64_t M, int64_t N, i
 
 /*
  * Weight gradient: dW[N,K] = dY[M,N]^T X[M,K] (accumulate != 0: dW += ..., in BF16).  Contraction over M on
- * dYq_t and Xq_t (on dYq and Xq read T-major under LLMQ_NO_TRANSPOSE).
+ * dYq_t and Xq_t, or on dYq and Xq read T-major (under LLMQ_NO_TRANSPOSE, and for values of M that are no multiples of 64
+ * wherever that is faster): an operand whose REUSE flag is set has both of its copies in the workspace.
  */
 int llmq_fp8_linear_wgrad(const void* dY, const void* X, int64_t M, int64_t N, int64_t K,
                           float* d_scale_dy, float* d_scale_x, int fmt_dy,

@@ -305,3 +305,22 @@ def test_step_without_transposed_copies_replays_from_a_graph():
         torch.cuda.synchronize()
         g.replay()
         assert same(ref, snapshot()), "graph replay %d differs" % rep
+
+
+@pytest.mark.parametrize("fmt_dy,accumulate", [(0, True), (1, False)])
+@pytest.mark.parametrize("M,N,K", [(16, 48, 64), (17, 256, 144), (127, 300, 304), (129, 300, 301), (200, 24, 40), (301, 15, 64), (1777, 320, 192),
+                                   (4064, 1024, 16), (4016, 1024, 64), (4048, 784, 256), (4032, 784, 256)])
+def test_ragged_weight_gradient_reads_either_copy(M, N, K, fmt_dy, accumulate):
+    """Token counts on either side of the lines between the transposed and the row-major copies: the weight gradient of the
+    linear call has the bytes of the contraction of the transposed copies, which are in the workspace either way."""
+    g = torch.Generator(device=DEV).manual_seed(M * 7 + N + K)
+    x = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    dy = (torch.randn((M, N), generator=g, device=DEV) * 1e-3).to(torch.bfloat16)
+    ws = torch.empty(llmq.llmq_fp8_linear_workspace_bytes(M, N, K), dtype=torch.uint8, device=DEV)
+    offs = llmq.llmq_fp8_linear_workspace_offsets(M, N, K)
+    sx, sd = torch.zeros(1, device=DEV), torch.zeros(1, device=DEV)
+    dW = torch.randn((N, K), generator=g, device=DEV).to(torch.bfloat16)
+    want = dW.clone()
+    llmq.llmq_fp8_linear_wgrad(dy, x, M, N, K, sd, sx, fmt_dy, dW, accumulate, ws, llmq.JIT_DY | llmq.JIT_X)
+    llmq.llmq_fp8_gemm_tn(ws[offs[5]:offs[5] + N * M].view(N, M), fmt_dy, ws[offs[1]:offs[1] + K * M].view(K, M), 0, sd, sx, want, accumulate)
+    assert torch.equal(dW.view(torch.int16), want.view(torch.int16))

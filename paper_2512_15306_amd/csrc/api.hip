@@ -431,7 +431,7 @@ int llmq_swiglu_fwd_fp8_slabs(const void* gu_bf16, int64_t M, int64_t I, const f
     if (!gu_bf16 || !d_scale_h || !q || !q_t) return LLMQ_ERR_NULL;
     int st = check_swiglu_shape(M, I);
     if (st != LLMQ_OK) return st;
-    if (!llmq::tile_shape_ok(M, I) || M * I >= kMaxSlabElems) return LLMQ_ERR_SHAPE;
+    if (!llmq::slab_shape_ok(M, I) || M * I >= kMaxSlabElems) return LLMQ_ERR_SHAPE;
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(gu_bf16, 16) || !aligned(h_bf16, 16) || !aligned(q, 16) || !aligned(q_t, 16) || !aligned(d_scale_h, 4))
         return LLMQ_ERR_ALIGN;
@@ -492,7 +492,7 @@ int llmq_rmsnorm_apply_fp8_slabs(const void* res_bf16, const void* w_bf16, const
                                  void* stream) {
     if (!res_bf16 || !w_bf16 || !rstd || !d_scale_y || !q || !q_t) return LLMQ_ERR_NULL;
     if (!dim_ok(M) || !dim_ok(C) || C >= ((int64_t)1 << 24) || M * C >= kMaxElems) return LLMQ_ERR_SHAPE;
-    if (!llmq::tile_shape_ok(M, C) || M * C >= kMaxSlabElems) return LLMQ_ERR_SHAPE;
+    if (!llmq::slab_shape_ok(M, C) || M * C >= kMaxSlabElems) return LLMQ_ERR_SHAPE;
     if (!fmt_ok(fmt)) return LLMQ_ERR_FORMAT;
     if (!aligned(res_bf16, 16) || !aligned(w_bf16, 16) || !aligned(rstd, 16) || !aligned(d_scale_y, 4) ||
         !aligned(q, 16) || !aligned(q_t, 16) || !aligned(y_bf16, 16))

@@ -193,33 +193,46 @@ __device__ inline void narrow_write_transposed(const unsigned (&w)[16][2], uint8
     }
 }
 
-// ---- The 128-row x 256-column workgroup tile of the kernels that write FP8 codes in both layouts ----
+// ---- The 128 x 128 workgroup tile of the kernels that write FP8 codes in both layouts ----
 //
-// 256 lanes; a lane owns a patch of 16 rows x 8 columns, a wave is 4 lanes stacked x 16 side by side (64 rows x 128
-// columns: its loads of BF16 input cover 256 contiguous bytes of a row, its stores of codes a whole 128-byte line),
-// the four waves tile 128 x 256.  The transposed patches (16-byte column pieces after the register transpose)
-// go through a [256 columns][128 rows] byte tile in LDS (rows padded to 144 bytes against bank conflicts) and
+// 256 lanes; a lane owns a patch of 8 rows x 8 columns, a wave is 4 lanes stacked x 16 side by side (32 rows x 128
+// columns: its loads of BF16 input cover 256 contiguous bytes of a row, its stores of codes a whole 128-byte line), the four
+// waves are stacked.  Four lanes that follow each other lie side by side: a wave's 8-byte stores of codes are put together from
+// neighbouring lanes, and with lanes that follow each other stacked instead every piece of 8 bytes went out by itself
+// (quantize kernel, slabs, 8192 x 3584: stacked 25.4 us, two side by side 22.6, four 21.6, eight 22.4, sixteen 21.9; 16-byte loads and stores do not
+// care).  The transposed patches (8-byte column pieces after the register transpose) go through a
+// [128 columns][128 rows] byte tile in LDS (rows padded to 136 bytes against bank conflicts) and
 // leave, after one barrier, as 128-byte lines of the transposed tensor, 8 lanes per transposed row.
-constexpr int kTilePitch = kTileRows + 16;        // kTileRows = 128, kTileCols = 256
-constexpr int kTileThreads = 256, kPatchRows = 16;
+// With 16 rows per lane (256 x 128) and with 4 (64 x 128) with the same lanes the same tensor took 23.2 and 24.6 us, 3584 x 18944
+// 52.8 and 56.0 against 50.1: fewer rows leave shorter lines of the transposed copy, more rows fewer waves per CU.
+constexpr int kTileCols = 128, kPatchRows = 8;
+constexpr int kTilePitch = kTileRows + 8;         // kTileRows = 128
+constexpr int kTileThreads = 256;
 constexpr int kTileLdsBytes = kTileCols * kTilePitch;
+
+// Row and column group of a lane in a wave of 4 x 16 patches
+__device__ inline void wave_patch(int& stacked, int& beside) {
+    const int lane = threadIdx.x & (kWave - 1);
+    stacked = (lane >> 2) & 3;
+    beside = (lane & 3) | (lane >> 4) << 2;
+}
 
 // Origin of this lane's patch inside the tile
 __device__ inline void tile_patch_origin(int& tr, int& tc) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    tr = (wave >> 1) * 64 + (lane & 3) * kPatchRows;
-    tc = (wave & 1) * 128 + (lane >> 2) * 8;
+    int stacked, beside;
+    wave_patch(stacked, beside);
+    tr = (threadIdx.x / kWave) * (4 * kPatchRows) + stacked * kPatchRows;
+    tc = beside * 8;
 }
 
-// The patch as FP8 bytes, w[row][k] = columns 4k .. 4k+3: column j of the patch becomes 16 consecutive bytes of
+// The patch as FP8 bytes, w[row][k] = columns 4k .. 4k+3: column j of the patch becomes 8 consecutive bytes of
 // row (tc + j) of the LDS tile, at byte tr.
 __device__ inline void tile_stage_transposed(const unsigned (&w)[kPatchRows][2], int tr, int tc, uint8_t* s_t) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        unsigned col[4][4];
+        unsigned col[4][2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < 2; ++t) {
             unsigned blk[4] = {w[4 * t][k], w[4 * t + 1][k], w[4 * t + 2][k], w[4 * t + 3][k]};
             unsigned o[4];
             transpose4x4_bytes(blk, o);
@@ -228,7 +241,7 @@ __device__ inline void tile_stage_transposed(const unsigned (&w)[kPatchRows][2],
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            *reinterpret_cast<v4u*>(s_t + (tc + 4 * k + c) * kTilePitch + tr) = v4u{col[c][0], col[c][1], col[c][2], col[c][3]};
+            *reinterpret_cast<v2u*>(s_t + (tc + 4 * k + c) * kTilePitch + tr) = v2u{col[c][0], col[c][1]};
     }
 }
 
@@ -236,14 +249,14 @@ __device__ inline void tile_stage_transposed(const unsigned (&w)[kPatchRows][2],
 // starts; transposed row c starts row_stride bytes after row c - 1.  The transposed tensor [cols, rows] as such:
 // dt = qt + (first column) rows + (first row), row_stride = rows.  In slabs of 128 contraction bytes
 // (OperandLayout): dt = qt + (first row / 128) cols 128 + (first column) 128, row_stride = 128, and the tile's
-// 32 KB are one contiguous piece.
+// 16 KB are one contiguous piece.
 __device__ inline void tile_write_transposed(const uint8_t* s_t, uint8_t* dt, int64_t row_stride) {
 #pragma unroll
     for (int m = 0; m < kTileCols * (kTileRows / 16) / kTileThreads; ++m) {
         const int p = threadIdx.x + m * kTileThreads;       // 16-byte piece: column p / 8, rows 16 (p % 8) ..
         const int c = p >> 3, ch = p & 7;
-        const v4u v = *reinterpret_cast<const v4u*>(s_t + c * kTilePitch + ch * 16);
-        *reinterpret_cast<v4u*>(dt + (int64_t)c * row_stride + ch * 16) = v;
+        const v2u lo = *reinterpret_cast<const v2u*>(s_t + c * kTilePitch + ch * 16), hi = *reinterpret_cast<const v2u*>(s_t + c * kTilePitch + ch * 16 + 8);
+        *reinterpret_cast<v4u*>(dt + (int64_t)c * row_stride + ch * 16) = v4u{lo[0], lo[1], hi[0], hi[1]};
     }
 }
 
@@ -313,10 +326,12 @@ __device__ inline void store_codes_upto(const unsigned (&w)[PR][2], uint8_t* dst
 
 // ---- The 64-row x 128-column tile of the same kernels for tensors of few tiles ----
 //
-// A tensor of a few dozen 128 x 256 tiles leaves most of the chip idle and the rest waiting: a lane's sixteen rows are
-// read, converted and written by a handful of waves per CU.  Here a lane owns 4 rows x 8 columns and four times as many
-// workgroups share the tensor; a wave is 4 lanes stacked x 16 side by side (256-byte runs of the input, whole lines of
-// codes), the four waves are stacked.  Guarded edges, any alignment; the transposed copy leaves in 64-byte pieces.
+// A tensor of a few dozen 128 x 128 tiles leaves most of the chip idle.  Here a lane owns 4 rows x 8 columns and twice as many
+// workgroups share the tensor; the lanes of a wave lie as above (256-byte runs of the input, whole lines of
+// codes; 1024 x 1024 quantized 3.3 us with lanes that follow each other stacked, 3.1 so), the four waves are stacked.  Guarded edges, any
+// alignment; the transposed copy leaves in 64-byte pieces.
+// (Eight rows per lane with the same guards, 128 x 128: ragged tensors gain nothing or a few percent, 8100 x 5120 38.3 / 37.9 us, 8112 x 5128
+// 45.0 / 45.7, 4001 x 2730 16.0 / 18.9, 16000 x 9000 176 / 170.)
 constexpr int kSmallRows = 64, kSmallCols = 128, kSmallPatch = 4;
 constexpr int kSmallPitch = kSmallRows + 16, kSmallLdsBytes = kSmallCols * kSmallPitch;
 
@@ -331,6 +346,7 @@ struct SmallGrid {
     unsigned rows, cols, blocks;            // tiles (at most 2^28: tensors have at most 2^40 elements and 2^31 rows), workgroups in all
     unsigned first;                         // first workgroup of this launch
     bool xcd_ranges;
+    bool stacked;                           // lanes that follow each other one above the other instead of side by side
 };
 inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     SmallGrid g;
@@ -339,6 +355,9 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
     g.first = 0;
     g.xcd_ranges = cols % 64 != 0;
+    // (lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
+    // 22.5, 8263 x 5120 39.2 / 39.3 and 39.1 / 39.2, 16000 x 9000 175 / 169 and 174 / 166)
+    g.stacked = rows * cols > (int64_t)40000000;
     return g;
 }
 // launch(grid, workgroups of this launch), once or as often as the launch limit asks for
@@ -356,10 +375,12 @@ __host__ __device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsi
     return true;
 }
 
-__device__ inline void small_patch_origin(int& tr, int& tc) {
-    const int lane = threadIdx.x & (kWave - 1);
-    tr = (threadIdx.x / kWave) * 16 + (lane & 3) * kSmallPatch;
-    tc = (lane >> 2) * 8;
+__device__ inline void small_patch_origin(const SmallGrid& g, int& tr, int& tc) {
+    int stacked, beside;
+    wave_patch(stacked, beside);
+    if (g.stacked) { const int lane = threadIdx.x & (kWave - 1); stacked = lane & 3; beside = lane >> 2; }
+    tr = (threadIdx.x / kWave) * 16 + stacked * kSmallPatch;
+    tc = beside * 8;
 }
 
 __device__ inline void small_stage_transposed(const unsigned (&w)[kSmallPatch][2], int tr, int tc, uint8_t* s_t) {

@@ -23,20 +23,22 @@ inline unsigned max_workgroups() {
     return kMaxWorkgroups;
 }
 
-// The workgroup tile of the kernels that write FP8 codes in both layouts (quantize, and the SwiGLU and RMSNorm
-// kernels that emit FP8 directly); only tensors made of whole tiles have a transposed copy in slabs.
-constexpr int kTileRows = 128, kTileCols = 256;
-inline bool tile_shape_ok(int64_t rows, int64_t cols) { return rows % kTileRows == 0 && cols % kTileCols == 0; }
+// The kernels that write FP8 codes in both layouts (quantize, and the SwiGLU and RMSNorm kernels that emit FP8 directly) work
+// on tiles of 128 rows x 128 columns; a transposed copy in slabs is kept of tensors of 128-row x 256-column blocks.
+constexpr int kTileRows = 128;
+inline bool slab_shape_ok(int64_t rows, int64_t cols) { return rows % 128 == 0 && cols % 256 == 0; }
 
-// Such a tensor takes the tile kernels from `min_tiles` tiles on, below that the 64 x 128 tile, of which there are four
-// times as many (the SwiGLU and RMSNorm kernels have limits of their own, beside their launches).  Quantize kernel, 64 x 128
-// against 128 x 256: 256 x 512 elements (4 tiles) 4.6 / 6.7 us, 2048 x 3072 (192)
-// 6.8 / 7.6, 4096 x 3072 (384) 12.7 / 12.3, 16384 x 5120 60.6 / 56.8: one tile per CU.
+// Tensors of whole tiles take the tile kernels from one tile per CU on, below that the 64 x 128 tile, of which there are
+// twice as many.  64 x 128 / 128 x 128 tile, microseconds, buffers of their own for every pass:
+//   tiles                      64           256          384          768           1792          3584 (8192 x 7168)   5120 (16384 x 5120)
+//   quantize              3.1 / 3.2    5.5 / 5.2    6.8 / 6.6   11.5 / 10.6   29.6 / 24.4     51.3 / 38.0          74.6 / 52.8
+//   SwiGLU codes          5.4 / 6.4    9.4 / 8.2   12.3 / 12.3  19.2 / 17.1   41.0 / 35.2     75.4 / 68.1         109.8 / 84.7
+//   RMSNorm codes         3.4 / 3.6    6.1 / 5.9    7.3 / 7.6   12.1 / 10.0   29.2 / 25.4     52.1 / 46.1          74.1 / 53.9
 // LLMQ_QUANT_TILE=0 / 1 (tests): always the one or, for shapes made of them, always the other.
-inline bool takes_large_tile(int64_t rows, int64_t cols, int64_t min_tiles = 256) {
-    if (!tile_shape_ok(rows, cols)) return false;
+inline bool takes_large_tile(int64_t rows, int64_t cols) {
+    if (rows % 128 != 0 || cols % 128 != 0) return false;
     if (const char* e = tuning_env("LLMQ_QUANT_TILE")) return atoi(e) != 0;
-    return (rows / kTileRows) * (cols / kTileCols) >= min_tiles;
+    return (rows / 128) * (cols / 128) >= 256;
 }
 
 // What the other tensors take when codes in both layouts are wanted:
@@ -172,7 +174,7 @@ int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, 
 // SwiGLU with its extra outputs.  h, d_amax (with partial, the per-workgroup scratch), q and q_t are
 // optional; q_fmt is only read when q is given.  swiglu_blocks() is the number of scratch words.
 // qt_slabs (here and in the RMSNorm recompute launch): q_t in slabs of 128 contraction bytes, as in
-// launch_quantize; needs q_t and tile_shape_ok(M, columns), else -2.
+// launch_quantize; needs q_t and slab_shape_ok(M, columns), else -2.
 int64_t swiglu_blocks(int64_t M, int64_t I);
 int launch_swiglu_fwd(const void* gu, int64_t M, int64_t I, void* h, unsigned* partial, int amax_fmt,
                       float* d_amax, float* d_scale, const float* d_qscale, int q_fmt, uint8_t* q, uint8_t* q_t,

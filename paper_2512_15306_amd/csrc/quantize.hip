@@ -3,7 +3,7 @@
 // quantized tensor is also needed transposed in the backward pass).
 //
 // HBM-bound: per element 2 bytes read, 1 byte written row-major and 1 byte written transposed.  A lane owns a patch of
-// 16 rows x 8 columns (4 x 8 in tensors of few tiles): 16-byte loads, one binary32 multiply and the hardware RNE cast
+// 8 rows x 8 columns (4 x 8 in tensors of few tiles): 16-byte loads, one binary32 multiply and the hardware RNE cast
 // (clamped first, which makes it saturating), 8-byte stores of each row, a byte transpose in registers with byte
 // permutes; the transposed patches leave through LDS in whole pieces of lines.
 #include <stdlib.h>
@@ -35,11 +35,10 @@ __device__ inline const QuantTensor& tensor_of_block(const QuantPair& p, unsigne
     return p.second;
 }
 
-// Tensors of at least 256 whole 128 x 256 tiles (the benchmark's tensors but for its smallest configuration's): full 128-byte
-// lines on all three streams.  A lane owns a 16 x 8 patch, a wave is
-// 4 lanes stacked x 16 side by side, and the transposed copy cannot be written that way from registers (4 stacked
-// lanes hold 64 contiguous bytes of a transposed row), so the transposed patches go through LDS (the tile_*
-// helpers).
+// Tensors of at least 256 whole 128 x 128 tiles (the benchmark's tensors but for its smallest configuration's): full 128-byte
+// lines on all three streams; the transposed patches go through LDS (the tile_* helpers, with what other tiles and lanes
+// measured).  In slabs, against a tile of 128 x 256 with 16 rows per lane and lanes that follow each other stacked: 4096 x 3072 13.4 -> 10.6
+// us, 8192 x 3584 26.4 -> 23.4 (5.0 TB/s), 8192 x 7168 42.4 -> 37.5 (6.3), 16384 x 5120 57.5 -> 51.8 (6.5); plain transposed copy 59.5 -> 52.8.
 template <int FMT, bool STREAM>
 __global__ __launch_bounds__(kTileThreads) void quantize_tile_kernel(const QuantPair pair) {
     __shared__ unsigned s_part[kTileThreads / kWave];
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(kTileThreads) void quantize_small_kernel(const Quan
     if (!small_tile(t.grid, block, brow, bcol)) return;
     const int64_t rows = t.rows, cols = t.cols;
     int tr, tc;
-    small_patch_origin(tr, tc);
+    small_patch_origin(t.grid, tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     v4u in[kSmallPatch];
     float s = 0.0f;
@@ -187,7 +186,7 @@ __global__ __launch_bounds__(kQThreads) void quantize_flat_kernel(const QuantPai
     }
 }
 
-bool quantize_can_write_slabs(int64_t rows, int64_t cols) { return tile_shape_ok(rows, cols); }
+bool quantize_can_write_slabs(int64_t rows, int64_t cols) { return slab_shape_ok(rows, cols); }
 
 // Which kernel a tensor takes, and what the kernel is told about it
 enum QuantKind { kQuantFlat, kQuantElements, kQuantNarrow, kQuantSmall, kQuantTile };

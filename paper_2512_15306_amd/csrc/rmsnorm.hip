@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_apply_fp8_patch_kernel(
     }
 }
 
-// With the transposed copy, tensors made of whole 128 x 256 tiles: lane geometry and LDS transpose of the quantize kernel's tile
+// With the transposed copy, tensors made of whole 128 x 128 tiles: lane geometry and LDS transpose of the quantize kernel's tile
 // variant (full 128-byte lines on every stream; the transposed copy optionally in slabs).
 template <int QFMT, bool WRITE_Y, bool STREAM>
 __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_tile_kernel(
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     unsigned brow, bcol;
     if (!small_tile(grid, grid.first + blockIdx.x, brow, bcol)) return;
     int tr, tc;
-    small_patch_origin(tr, tc);
+    small_patch_origin(grid, tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     const int64_t rows_left = M - r0, cols_left = C - c0;
     v4u in[kSmallPatch];
@@ -594,10 +594,7 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
                          const float* d_qscale, uint8_t* q, uint8_t* q_t, uint16_t* y, hipStream_t stream,
                          bool qt_slabs) {
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
-    // (64 x 128 / 128 x 256 tiles, buffers of their own for every pass: 320 large tiles 10.9 / 12.8 us, 384 14.3 / 14.4, 512 - all resident at
-    // once - 17.0 / 14.5, 640 20.0 / 22.2, 1024 28.1 / 29.2, 1536 43.4 / 43.8, 2048 68 / 60, 4096 139 / 113)
-    const int64_t tiles = (M / kTileRows) * (C / kTileCols);
-    if (q_t && (takes_large_tile(M, C, 1792) || (takes_large_tile(M, C, 384) && tiles <= 512))) {
+    if (q_t && takes_large_tile(M, C)) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
         if (streams_out(2 * M * C, C, 128)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }
@@ -627,7 +624,7 @@ int launch_rmsnorm_apply_fp8(const void* res, const void* w, const float* rstd, 
                              bool qt_slabs) {
     const uint16_t* r = reinterpret_cast<const uint16_t*>(res);
     const uint16_t* wp = reinterpret_cast<const uint16_t*>(w);
-    if (qt_slabs && !(q_t && tile_shape_ok(M, C))) return -2;
+    if (qt_slabs && !(q_t && slab_shape_ok(M, C))) return -2;
     if (fmt == 0) launch_apply<0>(r, wp, rstd, M, C, d_qscale, q, q_t, reinterpret_cast<uint16_t*>(y), stream, qt_slabs);
     else launch_apply<1>(r, wp, rstd, M, C, d_qscale, q, q_t, reinterpret_cast<uint16_t*>(y), stream, qt_slabs);
     return hipGetLastError() == hipSuccess ? 0 : -6;

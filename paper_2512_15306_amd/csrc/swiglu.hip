@@ -200,10 +200,10 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_patch_kernel(
     }
 }
 
-// FP8 codes in both layouts for tensors made of whole 128 x 256 tiles (every benchmark shape): the lane geometry
+// FP8 codes in both layouts for tensors made of whole 128 x 128 tiles (every benchmark shape): the lane geometry
 // and the LDS transpose of the quantize kernel's tile variant, so that all four streams (g, u, q, q_t) move in
-// full 128-byte lines, and the transposed copy can be written in slabs.  The 16 rows of a patch are loaded and
-// converted in two groups of eight (sixteen 16-byte loads in flight per lane).
+// full 128-byte lines, and the transposed copy can be written in slabs.  Sixteen 16-byte loads in flight per lane.
+// (8192 x 18944 in slabs on 128 x 256 tiles, 16 rows per lane in two groups: 187 us, now 174.)
 template <bool WRITE_H, int QFMT, bool STREAM>
 __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_tile_kernel(
     const uint16_t* __restrict__ gu, int64_t I, uint16_t* __restrict__ h,
@@ -216,30 +216,25 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_tile_kernel(
     const int64_t r0 = (int64_t)brow * kTileRows + tr, c0 = (int64_t)bcol * kTileCols + tc;
     const uint16_t* src = gu + r0 * (2 * I) + c0;
     const float s = *d_qscale;
-    constexpr int kGroup = 8;
     unsigned w[kPatchRows][2];
+    v4u g[kPatchRows], u[kPatchRows], o[kPatchRows];
 #pragma unroll
-    for (int i0 = 0; i0 < kPatchRows; i0 += kGroup) {
-        v4u g[kGroup], u[kGroup], o[kGroup];
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i) {
-            g[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)(i0 + i) * 2 * I));
-            u[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)(i0 + i) * 2 * I + I));
-        }
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i) o[i] = swiglu8(g[i], u[i]);
-        if constexpr (WRITE_H) {
-            uint16_t* dst = h + (r0 + i0) * I + c0;
-#pragma unroll
-            for (int i = 0; i < kGroup; ++i) *reinterpret_cast<v4u*>(dst + (int64_t)i * I) = o[i];
-        }
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i) quantize8<QFMT>(o[i], s, w[i0 + i][0], w[i0 + i][1]);
-        uint8_t* dq = q + (r0 + i0) * I + c0;
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i) store_hinted<STREAM>(v2u{w[i0 + i][0], w[i0 + i][1]}, reinterpret_cast<v2u*>(dq + (int64_t)i * I));
-        __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < kPatchRows; ++i) {
+        g[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * 2 * I));
+        u[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * 2 * I + I));
     }
+#pragma unroll
+    for (int i = 0; i < kPatchRows; ++i) o[i] = swiglu8(g[i], u[i]);
+    if constexpr (WRITE_H) {
+        uint16_t* dst = h + r0 * I + c0;
+#pragma unroll
+        for (int i = 0; i < kPatchRows; ++i) *reinterpret_cast<v4u*>(dst + (int64_t)i * I) = o[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kPatchRows; ++i) quantize8<QFMT>(o[i], s, w[i][0], w[i][1]);
+    uint8_t* dq = q + r0 * I + c0;
+#pragma unroll
+    for (int i = 0; i < kPatchRows; ++i) store_hinted<STREAM>(v2u{w[i][0], w[i][1]}, reinterpret_cast<v2u*>(dq + (int64_t)i * I));
     tile_stage_transposed(w, tr, tc, s_t);
     __syncthreads();
     tile_write_transposed(s_t, qt + (int64_t)bcol * kTileCols * qt_row_stride + (int64_t)brow * qt_band_stride, qt_row_stride);
@@ -338,7 +333,7 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_fp8_small_kernel(
     unsigned brow, bcol;
     if (!small_tile(grid, grid.first + blockIdx.x, brow, bcol)) return;
     int tr, tc;
-    small_patch_origin(tr, tc);
+    small_patch_origin(grid, tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     const uint16_t* src = gu + r0 * (2 * I) + c0;
     v4u g[kSmallPatch], u[kSmallPatch];
@@ -543,11 +538,9 @@ static void launch_fwd_patch(const uint16_t* gu, int64_t M, int64_t I, uint16_t*
 template <int QFMT>
 static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h, const float* d_qscale,
                           uint8_t* q, uint8_t* q_t, hipStream_t stream, bool qt_slabs) {
-    if (qt_slabs && !(q_t && tile_shape_ok(M, I))) return -2;
+    if (qt_slabs && !(q_t && slab_shape_ok(M, I))) return -2;
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? I * kTileRows : kTileRows;
-    // (64 x 128 / 128 x 256 tiles, buffers of their own for every pass: 640 large tiles 29.2 / 30.7 us, 768 33.1 / 32.5, 1024 41.9 / 39.2,
-    // 1536 67 / 64, 2560 115 / 94)
-    if (q_t && takes_large_tile(M, I, 768)) {
+    if (q_t && takes_large_tile(M, I)) {
         const unsigned gr = (unsigned)(M / kTileRows), gc = (unsigned)(I / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kTileThreads), 0, stream, gu, I, h, d_qscale, q, q_t, gc, row_stride, band_stride); };
         if (streams_out(2 * M * I, I, 128)) { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, true>); else launch(swiglu_fwd_tile_kernel<false, QFMT, true>); }

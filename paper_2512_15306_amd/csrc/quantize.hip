@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kTileThreads) void quantize_small_kernel(const Quan
     v4u in[kSmallPatch];
     float s = 0.0f;
     if (t.scale.partial == nullptr) s = *t.scale.d_scale;
-    load_patch_upto(in, t.x + r0 * cols + c0, cols, rows - r0, cols - c0);
+    load_patch_upto(in, t.x + r0 * cols + c0, cols, c0, rows - r0, cols - c0);
     if (t.scale.partial != nullptr) s = resolve_scale(t.scale, block == 0, s_part);
     unsigned w[kSmallPatch][2];
 #pragma unroll

@@ -98,7 +98,7 @@ template <bool EDGE>
 __device__ inline v4u rn_load(const uint16_t* row, int idx, int C) {
     if constexpr (!EDGE) return __builtin_nontemporal_load(reinterpret_cast<const v4u*>(row) + idx);
     if (8 * idx + 8 <= C) return __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(row + 8 * idx));
-    return load8_upto(row + 8 * idx, C - 8 * idx);
+    return load8_upto(row + 8 * idx, 8 * idx, C - 8 * idx);
 }
 template <bool EDGE, bool STREAM = false>
 __device__ inline void rn_store(uint16_t* row, int idx, int C, const v4u& v) {
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_row_kernel(
             const int idx = k * kWave + lane;
             if (k * kWave < nvec && idx < nvec) {
                 v4u wv;
-                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
+                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, 8 * idx, C - 8 * idx);
                 else wv = reinterpret_cast<const v4u*>(w)[idx];
                 v4u o = normalize8(r[k], rstd, wv);
                 if (EDGE && idx == nvec - 1) o = keep_upto(o, C % 8);
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
             const int idx = k * kRnThreads + threadIdx.x;
             if (idx < nvec) {
                 v4u wv;
-                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, C - 8 * idx);
+                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, 8 * idx, C - 8 * idx);
                 else wv = reinterpret_cast<const v4u*>(w)[idx];
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i)
@@ -479,8 +479,8 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     const int64_t rows_left = M - r0, cols_left = C - c0;
     v4u in[kSmallPatch];
-    load_patch_upto(in, res + r0 * C + c0, C, rows_left, cols_left);
-    const v4u wv = load8_upto(w + c0, cols_left);
+    load_patch_upto(in, res + r0 * C + c0, C, c0, rows_left, cols_left);
+    const v4u wv = load8_upto(w + c0, c0, cols_left);
     float rs[kSmallPatch];
 #pragma unroll
     for (int i = 0; i < kSmallPatch; ++i) rs[i] = i < rows_left ? rstd[r0 + i] : 0.0f;

@@ -306,8 +306,8 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_edge_kernel(
         if (c0 >= I) continue;
         const uint16_t* src = gu + r0 * (2 * I) + c0;
         v4u g[PR], u[PR], o[PR];
-        load_patch_upto(g, src, 2 * I, M - r0, I - c0);
-        load_patch_upto(u, src + I, 2 * I, M - r0, I - c0);
+        load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
+        load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
 #pragma unroll
         for (int i = 0; i < PR; ++i) {
             o[i] = swiglu8(g[i], u[i]);                     // zeros where nothing is: they do not raise the absmax
@@ -337,8 +337,8 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_fp8_small_kernel(
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     const uint16_t* src = gu + r0 * (2 * I) + c0;
     v4u g[kSmallPatch], u[kSmallPatch];
-    load_patch_upto(g, src, 2 * I, M - r0, I - c0);
-    load_patch_upto(u, src + I, 2 * I, M - r0, I - c0);
+    load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
+    load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
     const float s = *d_qscale;
     unsigned w[kSmallPatch][2];
 #pragma unroll
@@ -368,9 +368,9 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_bwd_edge_kernel(
         if (c0 >= I) continue;
         const uint16_t* src = gu + r0 * (2 * I) + c0;
         v4u g[PR], u[PR], d[PR];
-        load_patch_upto(g, src, 2 * I, M - r0, I - c0);
-        load_patch_upto(u, src + I, 2 * I, M - r0, I - c0);
-        load_patch_upto(d, dh + r0 * I + c0, I, M - r0, I - c0);
+        load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
+        load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
+        load_patch_upto(d, dh + r0 * I + c0, I, c0, M - r0, I - c0);
 #pragma unroll
         for (int i = 0; i < PR; ++i) {
             swiglu_bwd8(d[i], g[i], u[i], g[i], u[i]);

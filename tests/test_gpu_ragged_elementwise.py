@@ -1,4 +1,4 @@
-"""GPU parity of the element-wise kernels at the edges of their tiles (64 x 128 and 128 x 256), vectors and row widths,
+"""GPU parity of the element-wise kernels at the edges of their tiles (64 x 128 and 128 x 128), vectors and row widths,
 byte for byte against the oracle; nothing behind an output may be written."""
 import numpy as np
 import pytest
@@ -177,3 +177,25 @@ def test_rmsnorm_absmax_of_rows_whose_squares_underflow(C, with_x):
     assert bool(torch.isinf(stored[3]).all()) and bool(torch.isfinite(stored[torch.arange(M) != 3]).all())
     llmq.llmq_amax(stored.reshape(-1).clone(), 0, f[2:3], f[3:4], torch.empty(llmq.llmq_amax_workspace_bytes(), dtype=torch.uint8, device=DEV))
     assert f32_bits(f[0:1]) == f32_bits(f[2:3]) == 0x7F800000 and f32_bits(f[1:2]) == f32_bits(f[3:4]) == 0
+
+
+@pytest.mark.parametrize("k", range(9))
+def test_every_remainder_of_rows_and_columns(k, monkeypatch):
+    """The last vector of a row holds 1 to 8 elements (of a tensor narrower than a vector, one element too few for the load that
+    ends with the row), the last piece of a transposed row 1 to 16 codes."""
+    monkeypatch.setenv("LLMQ_CODES_KERNEL", "2")
+    for rows, cols in ((48 + k, 128 + k), (64 + 8 + k, 120 + k), (5, max(1, k)), (130 + 2 * k, 8 + k)):
+        test_codes_of_every_producer(rows, cols, None, "2", k % 2, monkeypatch)
+    for M, I in ((5, 512 + k), (6, 8 + k), (3, max(1, k))):
+        test_swiglu_forward_and_backward_of_ragged_shapes(M, I, "2", monkeypatch)
+    for C in (max(1, k), 8 + k, 2048 + k):
+        for with_x in (True, False):
+            test_rmsnorm_forward_at_the_edges_of_its_widths(5, C, with_x)
+
+
+@pytest.mark.parametrize("rows,cols", [(128, 128), (256, 384)])
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_whole_tiles_that_are_no_slabs(rows, cols, fmt, monkeypatch):
+    """128 x 128 tiles of tensors whose width is no multiple of the 256 columns that slabs come in."""
+    monkeypatch.setenv("LLMQ_QUANT_TILE", "1")
+    test_codes_of_every_producer(rows, cols, None, None, fmt, monkeypatch)

@@ -329,20 +329,18 @@ __device__ inline void store16_codes_upto(uint8_t* p, const v4u& v, int n) {
 // of which rows_left rows and cols_left columns exist
 template <int PR>
 __device__ inline void load_patch_upto(v4u (&in)[PR], const uint16_t* src, int64_t ld, int64_t c0, int64_t rows_left, int64_t cols_left) {
-    if (rows_left <= 0 || cols_left <= 0) {
+    if (rows_left >= PR && cols_left >= 8) {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(src + (int64_t)i * ld));
+    } else if (rows_left <= 0 || cols_left <= 0) {
 #pragma unroll
         for (int i = 0; i < PR; ++i) in[i] = v4u{0, 0, 0, 0};
-        return;
-    }
-    const int drop = cols_left >= 8 ? 0 : 8 - (int)cols_left;
-    if (drop == 0 || c0 >= 8) {
-        const uint16_t* p = src - drop;
+    } else if (cols_left >= 8 || c0 >= 8) {
+        const int drop = cols_left >= 8 ? 0 : 8 - (int)cols_left;
 #pragma unroll
-        for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(p + (int64_t)(i < rows_left ? i : 0) * ld));
-        if (drop != 0 || rows_left < PR) {
+        for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(src - drop + (int64_t)(i < rows_left ? i : 0) * ld));
 #pragma unroll
-            for (int i = 0; i < PR; ++i) in[i] = i < rows_left ? shift_elements(in[i], drop) : v4u{0, 0, 0, 0};
-        }
+        for (int i = 0; i < PR; ++i) in[i] = i < rows_left ? shift_elements(in[i], drop) : v4u{0, 0, 0, 0};
     } else {
 #pragma unroll
         for (int i = 0; i < PR; ++i) in[i] = load8_by_elements(src + (int64_t)i * ld, i < rows_left ? cols_left : 0);

@@ -49,10 +49,10 @@ inline bool takes_large_tile(int64_t rows, int64_t cols) {
 //   narrow   16384 x 8 2.2 / 3.5 / 3.8, 60000 x 16 4.9 / 5.0 / 5.3, 1000000 x 16 42 / 27 / 41;  2048 x 64 2.9 / 3.2 / 3.8, 8000 x 64 5.0 / 3.3 / 4.0,
 //            60000 x 32 9.5 / 4.6 / 6.1, 60000 x 64 23 / 5.4 / 6.7
 //   whole patches, elements / tile   256 x 72 2.3 / 3.8, 2048 x 72 2.9 / 3.9, 2048 x 128 3.6 / 2.9, 8000 x 72 5.5 / 4.0
-//   ragged rows of whole vectors   129 x 2056 3.3 / 3.6, 4001 x 72 3.8 / 3.9, 500 x 1000 4.9 / 4.2, 4001 x 128 5.1 / 3.5
-//   other widths   500 x 500 3.5 / 5.2, 500 x 1001 4.9 / 4.9, 16384 x 33 4.2 / 4.3, 129 x 5001 5.8 / 4.2, 1000 x 1001 8.6 / 5.5
-//   few rows or columns leave most of the tile's lanes idle   7 x 300000 6.8 / 10.3, 17 x 50000 5.2 / 4.9, 200001 x 5 5.0 / 12.7,
-//            60000 x 17 5.6 / 6.6, 60001 x 33 9.5 / 7.1, 200001 x 24 15.2 / 11.8
+//   ragged rows   129 x 2056 3.3 / 3.6, 500 x 500 3.7 / 3.9, 300 x 701 3.5 / 3.8, 1000 x 333 4.2 / 4.0, 2001 x 200 4.6 / 3.5, 500 x 1001 5.1 / 3.9,
+//            500 x 1000 4.9 / 4.2, 1000 x 1001 8.3 / 4.0, 4001 x 128 5.1 / 3.5, 4001 x 2730 62 / 12.8
+//   few rows or columns leave most of the tile's lanes idle   7 x 300000 6.8 / 10.3, 33 x 20000 4.8 / 3.8, 20 x 50001 5.5 / 4.1, 200001 x 5 5.0 / 12.7,
+//            16384 x 33 4.4 / 3.7, 60000 x 33 10.0 / 5.6, 60000 x 17 5.6 / 6.6, 200001 x 24 15.2 / 11.8
 // LLMQ_CODES_KERNEL=0 / 1 / 2 (tests): the one, where it takes the shape.
 enum CodesKind { kCodesElements, kCodesNarrow, kCodesSmall };
 inline bool codes_narrow_ok(int64_t rows, int64_t cols) { return rows % 16 == 0 && cols % 8 == 0 && cols <= 64; }
@@ -64,7 +64,7 @@ inline CodesKind codes_kind(int64_t rows, int64_t cols) {
     }
     if (codes_narrow_ok(rows, cols)) return n < (cols <= 16 ? (int64_t)1 << 20 : (int64_t)5 << 16) ? kCodesElements : kCodesNarrow;
     if (rows % 16 == 0 && cols % 8 == 0) return n < ((int64_t)1 << 17) ? kCodesElements : kCodesSmall;
-    const int64_t worth = cols % 8 == 0 ? (int64_t)3 << 17 : (int64_t)9 << 16;
+    const int64_t worth = (int64_t)3 << 17;
     if (rows < 8 || cols < (cols % 8 == 0 ? 24 : 32)) return kCodesElements;
     return n >= (rows < 16 ? 8 : rows < 32 || cols < 64 ? 2 : 1) * worth ? kCodesSmall : kCodesElements;
 }

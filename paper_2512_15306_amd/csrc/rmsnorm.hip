@@ -582,11 +582,12 @@ int launch_rmsnorm_fwd(const void* res_, const void* x_, const void* w_, int64_t
 
 // The recompute call's kernel where it is not the large tile's or, without the transposed copy, that of whole 4 x 8 patches.
 // Without the transposed copy the 64 x 128 tile is worth its code and its waits only for millions of elements (elements / tile,
-// microseconds: 1001 x 2730 6.3 / 6.6, 2001 x 2001 8.1 / 7.1, 4001 x 512 5.1 / 4.1, 4001 x 200 3.8 / 4.7, 200001 x 33 11.3 / 14.4).
+// microseconds: 250 x 5001 3.7 / 3.9, 4001 x 500 4.9 / 4.2, 1001 x 2001 4.9 / 4.3, 2001 x 1366 7.0 / 5.1, 4001 x 512 5.1 / 4.1, 4001 x 2730 21 / 10, 4001 x 200 3.8 / 4.7,
+// 200001 x 33 11.3 / 14.4).
 static CodesKind apply_kind(int64_t M, int64_t C, bool transpose) {
     if (transpose) return codes_kind(M, C);
     if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) return atoi(e) == 0 ? kCodesElements : kCodesSmall;
-    return M >= 32 && C >= 64 && M * C >= (C % 8 == 0 ? (int64_t)15 << 17 : (int64_t)15 << 18) ? kCodesSmall : kCodesElements;
+    return M >= 32 && C >= 64 && M * C >= (int64_t)15 << 17 ? kCodesSmall : kCodesElements;
 }
 
 template <int QFMT>

@@ -489,21 +489,22 @@ static int64_t edge_blocks(int64_t M, int64_t I) {
 }
 
 // Which kernel ragged (and small or narrow) shapes take: one element per lane, or guarded vectors once there is enough to move
-// for their code and their waits.  Microseconds, elements / vectors, buffers in the caches (on other buffers each pass elements
-// lose a little more: backward of 4001 x 2730 31 / 34, then 43 / 34, of 4001 x 5001 51 / 61, then 73 / 61):
+// for their code and their waits.  Microseconds, elements / vectors, two to six sets of buffers in turn:
 //   forward with h   1001 x 600 6.3 / 7.0, 2001 x 600 7.3 / 7.1, 4001 x 200 6.6 / 7.0, 8001 x 200 8.3 / 7.9, 8001 x 264 8.9 / 8.1,
-//                    200001 x 264 156 / 93;  rows that are no whole vectors 2001 x 1366 10.6 / 14.3, 4001 x 1001 14.2 / 12.2, 8001 x 500 14.2 / 13.9, 8001 x 300 10.0 / 13.0, 60001 x 700 98 / 112
-//   backward         1001 x 2736 11.9 / 11.0, 2001 x 600 7.7 / 8.5, 8001 x 264 11 / 11, 4001 x 200 6.9 / 8.4;  other rows 8001 x 701 19 / 28,
-//                    4001 x 1001 15 / 18, 4001 x 5001 51 / 61, 8001 x 5001 136 / 80
-//   codes in both layouts   500 x 1000 5.1 / 6.3, 1000 x 1000 8.8 / 7.1;  other rows 8000 x 100 6.8 / 8.6, 1000 x 1001 8.7 / 8.6, 4001 x 500
-//                    14.3 / 9.9;  33 x 20000 4.6 / 5.8, 60000 x 33 9.8 / 12.9, 16384 x 8 2.2 / 6.0 (narrow patches 13)
-//   codes alone      4001 x 512 6.6 / 5.6, 1001 x 2001 6.8 / 8.5, 2001 x 2001 12.2 / 10.3
+//                    200001 x 264 156 / 93;  rows that are no whole vectors 1000 x 1001 7.0 / 7.4, 4001 x 500 9.2 / 8.2, 1001 x 2001 9.5 / 8.3, 8000 x 300
+//                    10.2 / 9.6, 2001 x 1366 11.3 / 10.1, 4001 x 1001 13.9 / 10.5, 4001 x 2730 37 / 20, 60001 x 100 19 / 35
+//   backward         1001 x 2736 11.9 / 11.0, 2001 x 600 7.7 / 8.5, 8001 x 264 11 / 11, 4001 x 200 6.9 / 8.4;  other rows 8000 x 300 10.5 / 12.8, 2001 x 1366
+//                    11.7 / 13.3, 4001 x 1001 14.5 / 14.1, 8001 x 515 14.6 / 18.5, 8001 x 701 24.5 / 19.3, 4001 x 2730 42 / 28
+//   codes in both layouts   500 x 1000 5.1 / 6.3, 129 x 5001 6.1 / 5.9, 8000 x 100 7.4 / 6.1, 1000 x 1000 8.8 / 7.1, 1000 x 1001 8.7 / 6.3, 250 x 5001 10.3 / 6.9,
+//                    4001 x 500 14.7 / 7.3;  33 x 20000 4.8 / 5.9, 60000 x 33 10.3 / 11.7, 16384 x 8 2.2 / 6.0 (narrow patches 13)
+//   codes alone      1000 x 1001 4.7 / 6.1, 4001 x 512 6.6 / 5.6, 4001 x 500 6.9 / 6.3, 1001 x 2001 6.9 / 6.4, 8000 x 300 8.1 / 7.6, 4001 x 1001 11.7 / 8.6
 // LLMQ_CODES_KERNEL=0 / 1 / 2 (tests): elements, narrow patches or vectors, where they take the shape.
 static bool edge_worth(int64_t M, int64_t I, bool backward) {
     if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) return atoi(e) != kCodesElements;
     const int64_t n = M * I;
     if (I % 8 == 0) return I >= (backward ? 256 : 200) && n >= (backward ? (int64_t)3 << 19 : (int64_t)1 << 20);
-    return I >= 500 && n >= (int64_t)15 << (backward ? 19 : 18) && 10 * I >= 7 * edge_col_pieces(I) * kSwEdgeCols;       // (a wave takes 512 columns)
+    if (backward) return I >= 256 && n >= (10 * I >= 7 * edge_col_pieces(I) * kSwEdgeCols ? (int64_t)15 << 18 : (int64_t)5 << 20);     // (a wave takes 512 columns)
+    return I >= 256 && n >= (int64_t)15 << 17;
 }
 static CodesKind codes_kind_of(int64_t M, int64_t I, bool transpose) {
     if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) {
@@ -511,9 +512,9 @@ static CodesKind codes_kind_of(int64_t M, int64_t I, bool transpose) {
         return k != kCodesNarrow ? (CodesKind)k : transpose && codes_narrow_ok(M, I) ? kCodesNarrow : kCodesSmall;
     }
     const int64_t n = M * I;
-    if (!transpose) return M >= 32 && I >= 64 && n >= (I % 8 == 0 ? (int64_t)9 << 18 : (int64_t)5 << 20) ? kCodesSmall : kCodesElements;
+    if (!transpose) return M >= 32 && I >= 64 && n >= (int64_t)15 << 17 ? kCodesSmall : kCodesElements;
     if (I >= 32 && n >= ((int64_t)1 << 22) && codes_narrow_ok(M, I)) return kCodesNarrow;       // 1000000 x 32: 105 / 81 / 107 us
-    return M >= 32 && I >= 64 && n >= (I % 8 == 0 ? (int64_t)3 << 18 : (int64_t)5 << 18) ? kCodesSmall : kCodesElements;
+    return M >= 32 && I >= 64 && n >= (int64_t)3 << 18 ? kCodesSmall : kCodesElements;
 }
 
 // Workgroups of the absmax-producing launches (forward with h, backward): an upper bound of the partial

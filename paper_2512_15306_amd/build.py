@@ -1,4 +1,4 @@
-"""Build libllmq.so (the gfx950 kernels and their C ABI) in-tree with hipcc."""
+"""Build libllmq.so (the gfx950 kernels and their C ABI) in-tree with hipcc, and the Python module over it with g++."""
 from __future__ import annotations
 
 import os
@@ -6,11 +6,13 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libllmq.so")
+BINDING = os.path.join(HERE, "_binding.so")       # the Python module of csrc/binding.cpp
 # gemm_tiles_*.hip: the tile kernels of one operand-kind pair and layout each (all tile shapes), so that they compile
 # side by side; the largest come first.
 TILE_SOURCES = ["gemm_tiles_e4m3_e4m3.hip", "gemm_tiles_e5m2_e4m3.hip", "gemm_tiles_e4m3_e5m2.hip", "gemm_tiles_e5m2_e5m2.hip",
@@ -73,9 +75,23 @@ def build(verbose: bool = False) -> str:
         shutil.rmtree(work, ignore_errors=True)
 
 
+def binding_commands(obj: str, lib_dir: str, out: str):
+    """Compile and link commands of the Python module (CPU code; the library is found beside it at run time)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
+    cxx = os.environ.get("CXX", "g++")
+    abi = "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    return ([cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", abi] + [a for i in includes for a in ("-isystem", i)] + ["-c", os.path.join(CSRC, "binding.cpp"), "-o", obj],
+            [cxx, "-shared", obj, "-o", out, "-L", lib_dir, "-lllmq", "-Wl,-rpath,$ORIGIN", "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
+
+
 def _build_in(work: str, hipcc: str, verbose: bool) -> str:
     objs = []
     procs = []
+    binding_obj = os.path.join(work, "binding.o")
+    compile_binding, link_binding = binding_commands(binding_obj, HERE, os.path.join(work, "_binding.so"))
+    procs.append(("binding.cpp", subprocess.Popen(compile_binding, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in SOURCES:
         obj = os.path.join(work, src.replace(".hip", ".o"))
         cmd = [hipcc] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
@@ -102,6 +118,9 @@ def _build_in(work: str, hipcc: str, verbose: bool) -> str:
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp])
     os.replace(tmp, LIB)
+    subprocess.check_call(link_binding)
+    shutil.copy(os.path.join(work, "_binding.so"), BINDING + ".tmp.%d" % os.getpid())
+    os.replace(BINDING + ".tmp.%d" % os.getpid(), BINDING)
     return LIB
 
 

@@ -35,7 +35,8 @@ struct WsLayout {
 
 // Row-major copies and the scratch first, the transposed copies behind them: a workspace that ends after the
 // scratch serves every call that carries LLMQ_NO_TRANSPOSE.
-WsLayout ws_layout(int64_t M, int64_t N, int64_t K) {
+// pieces: with the section for LLMQ_SHARE_TILES, whose size takes a tile choice for each of the three contractions.
+WsLayout ws_layout(int64_t M, int64_t N, int64_t K, bool pieces) {
     WsLayout l;
     size_t off = 0;
     l.xq = off;   off += round256((size_t)M * K);
@@ -48,10 +49,13 @@ WsLayout ws_layout(int64_t M, int64_t N, int64_t K) {
     l.dyqt = off; off += round256((size_t)M * N);
     l.total = off;
     // what the largest of the three contractions may write when its ragged last round of tiles is shared out
-    size_t need = llmq::gemm_scratch_bytes(M, N, K, num_cus());
-    const size_t dgrad = llmq::gemm_scratch_bytes(M, K, N, num_cus()), wgrad = llmq::gemm_scratch_bytes(N, K, M, num_cus());
-    if (dgrad > need) need = dgrad;
-    if (wgrad > need) need = wgrad;
+    size_t need = 0;
+    if (pieces) {
+        need = llmq::gemm_scratch_bytes(M, N, K, num_cus());
+        const size_t dgrad = llmq::gemm_scratch_bytes(M, K, N, num_cus()), wgrad = llmq::gemm_scratch_bytes(N, K, M, num_cus());
+        if (dgrad > need) need = dgrad;
+        if (wgrad > need) need = wgrad;
+    }
     l.pieces = off; l.pieces_bytes = round256(need); off += l.pieces_bytes;
     l.shared_total = off;
     return l;
@@ -64,7 +68,8 @@ llmq::GemmScratch pieces_of(const WsLayout& l, void* ws, int flags) {
     return llmq::GemmScratch{reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + l.pieces), l.pieces_bytes};
 }
 
-int check_linear(int64_t M, int64_t N, int64_t K, const void* ws, size_t ws_bytes, int flags) {
+// l: the layout of the workspace, if the call is in order
+int check_linear(int64_t M, int64_t N, int64_t K, const void* ws, size_t ws_bytes, int flags, WsLayout& l) {
     if (!dim_ok(M) || !dim_ok(N) || !dim_ok(K)) return LLMQ_ERR_SHAPE;
     if (M * K >= kMaxElems || N * K >= kMaxElems || M * N >= kMaxElems) return LLMQ_ERR_SHAPE;
     if (flags & ~(LLMQ_REUSE_X | LLMQ_REUSE_W | LLMQ_REUSE_DY | LLMQ_JIT_X | LLMQ_JIT_W | LLMQ_JIT_DY | LLMQ_NO_TRANSPOSE | LLMQ_SHARE_TILES | LLMQ_SLAB_COPIES)) return LLMQ_ERR_FLAGS;
@@ -77,7 +82,7 @@ int check_linear(int64_t M, int64_t N, int64_t K, const void* ws, size_t ws_byte
         return LLMQ_ERR_FLAGS;
     if (!ws) return LLMQ_ERR_NULL;
     if (!aligned(ws, 256)) return LLMQ_ERR_ALIGN;
-    const WsLayout l = ws_layout(M, N, K);
+    l = ws_layout(M, N, K, (flags & LLMQ_SHARE_TILES) != 0);
     if (ws_bytes < ((flags & LLMQ_NO_TRANSPOSE) ? l.compact : (flags & LLMQ_SHARE_TILES) ? l.shared_total : l.total)) return LLMQ_ERR_WORKSPACE;
     return LLMQ_OK;
 }
@@ -282,23 +287,23 @@ int llmq_bf16_gemm_tn(const void* A_bf16, const void* B_bf16, int64_t R, int64_t
 
 size_t llmq_fp8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (!dim_ok(M) || !dim_ok(N) || !dim_ok(K)) return 0;
-    return ws_layout(M, N, K).total;
+    return ws_layout(M, N, K, false).total;
 }
 
 size_t llmq_fp8_linear_workspace_bytes_no_transpose(int64_t M, int64_t N, int64_t K) {
     if (!dim_ok(M) || !dim_ok(N) || !dim_ok(K)) return 0;
-    return ws_layout(M, N, K).compact;
+    return ws_layout(M, N, K, false).compact;
 }
 
 size_t llmq_fp8_linear_workspace_bytes_shared(int64_t M, int64_t N, int64_t K) {
     if (!dim_ok(M) || !dim_ok(N) || !dim_ok(K)) return 0;
-    return ws_layout(M, N, K).shared_total;
+    return ws_layout(M, N, K, true).shared_total;
 }
 
 int llmq_fp8_linear_workspace_offsets(int64_t M, int64_t N, int64_t K, size_t offsets[6]) {
     if (!offsets) return LLMQ_ERR_NULL;
     if (!dim_ok(M) || !dim_ok(N) || !dim_ok(K)) return LLMQ_ERR_SHAPE;
-    const WsLayout l = ws_layout(M, N, K);
+    const WsLayout l = ws_layout(M, N, K, false);
     offsets[0] = l.xq; offsets[1] = l.xqt; offsets[2] = l.wq; offsets[3] = l.wqt; offsets[4] = l.dyq; offsets[5] = l.dyqt;
     return LLMQ_OK;
 }
@@ -306,7 +311,8 @@ int llmq_fp8_linear_workspace_offsets(int64_t M, int64_t N, int64_t K, size_t of
 int llmq_fp8_linear_fwd(const void* X, const void* W, int64_t M, int64_t N, int64_t K,
                         float* d_scale_x, float* d_scale_w, void* Y, float* d_amax_y,
                         void* ws, size_t ws_bytes, int flags, void* stream) {
-    int st = check_linear(M, N, K, ws, ws_bytes, flags);
+    WsLayout l;
+    int st = check_linear(M, N, K, ws, ws_bytes, flags, l);
     if (st != LLMQ_OK) return st;
     if (flags & (LLMQ_REUSE_DY | LLMQ_JIT_DY)) return LLMQ_ERR_FLAGS;
     const bool qx = !(flags & LLMQ_REUSE_X), qw = !(flags & LLMQ_REUSE_W);
@@ -314,7 +320,6 @@ int llmq_fp8_linear_fwd(const void* X, const void* W, int64_t M, int64_t N, int6
     if ((qx && !aligned(X, 16)) || (qw && !aligned(W, 16)) || !aligned(Y, 16) || !aligned(d_scale_x, 4) ||
         !aligned(d_scale_w, 4) || !aligned(d_amax_y, 4))
         return LLMQ_ERR_ALIGN;
-    const WsLayout l = ws_layout(M, N, K);
     uint8_t* base = static_cast<uint8_t*>(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the first quantize kernel of the call also clears the absmax accumulator of the GEMM
@@ -333,7 +338,8 @@ int llmq_fp8_linear_fwd(const void* X, const void* W, int64_t M, int64_t N, int6
 int llmq_fp8_linear_dgrad(const void* dY, const void* W, int64_t M, int64_t N, int64_t K,
                           float* d_scale_dy, float* d_scale_w, int fmt_dy, void* dX,
                           float* d_amax_dx, void* ws, size_t ws_bytes, int flags, void* stream) {
-    int st = check_linear(M, N, K, ws, ws_bytes, flags);
+    WsLayout l;
+    int st = check_linear(M, N, K, ws, ws_bytes, flags, l);
     if (st != LLMQ_OK) return st;
     if (flags & (LLMQ_REUSE_X | LLMQ_JIT_X)) return LLMQ_ERR_FLAGS;
     if (!fmt_ok(fmt_dy)) return LLMQ_ERR_FORMAT;
@@ -342,7 +348,6 @@ int llmq_fp8_linear_dgrad(const void* dY, const void* W, int64_t M, int64_t N, i
     if ((qd && !aligned(dY, 16)) || (qw && !aligned(W, 16)) || !aligned(dX, 16) || !aligned(d_scale_dy, 4) ||
         !aligned(d_scale_w, 4) || !aligned(d_amax_dx, 4))
         return LLMQ_ERR_ALIGN;
-    const WsLayout l = ws_layout(M, N, K);
     uint8_t* base = static_cast<uint8_t*>(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned* zero = reinterpret_cast<unsigned*>(d_amax_dx);
@@ -362,7 +367,8 @@ int llmq_fp8_linear_dgrad(const void* dY, const void* W, int64_t M, int64_t N, i
 int llmq_fp8_linear_wgrad(const void* dY, const void* X, int64_t M, int64_t N, int64_t K,
                           float* d_scale_dy, float* d_scale_x, int fmt_dy, void* dW,
                           int accumulate, void* ws, size_t ws_bytes, int flags, void* stream) {
-    int st = check_linear(M, N, K, ws, ws_bytes, flags);
+    WsLayout l;
+    int st = check_linear(M, N, K, ws, ws_bytes, flags, l);
     if (st != LLMQ_OK) return st;
     if (flags & (LLMQ_REUSE_W | LLMQ_JIT_W)) return LLMQ_ERR_FLAGS;
     if (!fmt_ok(fmt_dy)) return LLMQ_ERR_FORMAT;
@@ -371,7 +377,6 @@ int llmq_fp8_linear_wgrad(const void* dY, const void* X, int64_t M, int64_t N, i
     if ((qd && !aligned(dY, 16)) || (qx && !aligned(X, 16)) || !aligned(dW, 16) || !aligned(d_scale_dy, 4) ||
         !aligned(d_scale_x, 4))
         return LLMQ_ERR_ALIGN;
-    const WsLayout l = ws_layout(M, N, K);
     uint8_t* base = static_cast<uint8_t*>(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned* part = reinterpret_cast<unsigned*>(base + l.part);

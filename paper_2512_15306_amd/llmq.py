@@ -150,6 +150,19 @@ def _stream() -> int:
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
+# The calls of a training step, marshalled by the compiled module (csrc/binding.cpp): each returns the library's status, or
+# None for arguments it leaves to the ctypes path below (which is also all there is if the module is not built).
+class _NoBinding:
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+try:
+    from . import _binding as _fast
+except ImportError:
+    _fast = _NoBinding()
+
+
 def _check(status: int, where: str) -> None:
     if status != 0:
         raise LlmqError(status, where)
@@ -161,6 +174,9 @@ def llmq_amax_workspace_bytes() -> int:
 
 def llmq_amax(x: torch.Tensor, fmt: int, d_amax: torch.Tensor, d_scale: Optional[torch.Tensor],
               ws: torch.Tensor) -> None:
+    status = _fast.amax(x, fmt, d_amax, d_scale, ws)
+    if status is not None:
+        return _check(status, "llmq_amax") if status else None
     _check(lib().llmq_amax(_dev(x, torch.bfloat16, "x"), x.numel(), fmt, _dev(d_amax, torch.float32, "d_amax"),
                            _dev(d_scale, torch.float32, "d_scale"), _dev(ws, torch.uint8, "ws"), ws.numel(),
                            _stream()), "llmq_amax")
@@ -173,6 +189,9 @@ def llmq_amax_static(x: torch.Tensor, fmt: int, d_amax: torch.Tensor, d_scale: O
 
 def llmq_quantize_fp8(x: torch.Tensor, d_scale: torch.Tensor, fmt: int, q: torch.Tensor,
                       q_t: Optional[torch.Tensor]) -> None:
+    status = _fast.quantize_fp8(x, d_scale, fmt, q, q_t)
+    if status is not None:
+        return _check(status, "llmq_quantize_fp8") if status else None
     rows, cols = x.shape
     if q.numel() != rows * cols or (q_t is not None and q_t.numel() != rows * cols):
         raise ValueError("output size does not match the input")
@@ -183,6 +202,9 @@ def llmq_quantize_fp8(x: torch.Tensor, d_scale: torch.Tensor, fmt: int, q: torch
 
 def llmq_quantize_fp8_slabs(x: torch.Tensor, d_scale: torch.Tensor, fmt: int, q: torch.Tensor, q_t: torch.Tensor) -> None:
     """q_t: rows * cols bytes, the transposed copy as [rows / 128, cols, 128]."""
+    status = _fast.quantize_fp8_slabs(x, d_scale, fmt, q, q_t)
+    if status is not None:
+        return _check(status, "llmq_quantize_fp8_slabs") if status else None
     rows, cols = x.shape
     if q.numel() != rows * cols or q_t.numel() != rows * cols:
         raise ValueError("output size does not match the input")
@@ -254,6 +276,9 @@ def llmq_fp8_gemm_with_scratch(A: torch.Tensor, fmtA: int, a_t_major: bool, B: t
 
 
 def llmq_bf16_gemm_tn(A: torch.Tensor, B: torch.Tensor, c: torch.Tensor, accumulate: bool = False) -> None:
+    status = _fast.bf16_gemm_tn(A, B, c, accumulate)
+    if status is not None:
+        return _check(status, "llmq_bf16_gemm_tn") if status else None
     R, T = A.shape
     C, T2 = B.shape
     if T != T2 or tuple(c.shape) != (R, C):
@@ -282,6 +307,9 @@ def llmq_fp8_linear_workspace_offsets(M: int, N: int, K: int) -> Tuple[int, ...]
 
 def llmq_fp8_linear_fwd(X, W, M: int, N: int, K: int, d_scale_x, d_scale_w, Y, d_amax_y, ws: torch.Tensor,
                         flags: int = 0) -> None:
+    status = _fast.linear_fwd(X, W, M, N, K, d_scale_x, d_scale_w, Y, d_amax_y, ws, flags)
+    if status is not None:
+        return _check(status, "llmq_fp8_linear_fwd") if status else None
     _check(lib().llmq_fp8_linear_fwd(_dev(X, torch.bfloat16, "X"), _dev(W, torch.bfloat16, "W"), M, N, K,
                                      _dev(d_scale_x, torch.float32), _dev(d_scale_w, torch.float32),
                                      _dev(Y, torch.bfloat16, "Y"), _dev(d_amax_y, torch.float32),
@@ -291,6 +319,9 @@ def llmq_fp8_linear_fwd(X, W, M: int, N: int, K: int, d_scale_x, d_scale_w, Y, d
 
 def llmq_fp8_linear_dgrad(dY, W, M: int, N: int, K: int, d_scale_dy, d_scale_w, fmt_dy: int, dX, d_amax_dx,
                           ws: torch.Tensor, flags: int = 0) -> None:
+    status = _fast.linear_dgrad(dY, W, M, N, K, d_scale_dy, d_scale_w, fmt_dy, dX, d_amax_dx, ws, flags)
+    if status is not None:
+        return _check(status, "llmq_fp8_linear_dgrad") if status else None
     _check(lib().llmq_fp8_linear_dgrad(_dev(dY, torch.bfloat16, "dY"), _dev(W, torch.bfloat16, "W"), M, N, K,
                                        _dev(d_scale_dy, torch.float32), _dev(d_scale_w, torch.float32), fmt_dy,
                                        _dev(dX, torch.bfloat16, "dX"), _dev(d_amax_dx, torch.float32),
@@ -300,6 +331,9 @@ def llmq_fp8_linear_dgrad(dY, W, M: int, N: int, K: int, d_scale_dy, d_scale_w, 
 
 def llmq_fp8_linear_wgrad(dY, X, M: int, N: int, K: int, d_scale_dy, d_scale_x, fmt_dy: int, dW,
                           accumulate: bool, ws: torch.Tensor, flags: int = 0) -> None:
+    status = _fast.linear_wgrad(dY, X, M, N, K, d_scale_dy, d_scale_x, fmt_dy, dW, accumulate, ws, flags)
+    if status is not None:
+        return _check(status, "llmq_fp8_linear_wgrad") if status else None
     _check(lib().llmq_fp8_linear_wgrad(_dev(dY, torch.bfloat16, "dY"), _dev(X, torch.bfloat16, "X"), M, N, K,
                                        _dev(d_scale_dy, torch.float32), _dev(d_scale_x, torch.float32), fmt_dy,
                                        _dev(dW, torch.bfloat16, "dW"), int(bool(accumulate)),
@@ -324,6 +358,9 @@ def _swiglu_dims(gu: torch.Tensor) -> Tuple[int, int]:
 
 def llmq_swiglu_fwd(gu: torch.Tensor, h: torch.Tensor, fmt: int, d_amax_h: torch.Tensor,
                     d_scale_h: Optional[torch.Tensor], ws: torch.Tensor) -> None:
+    status = _fast.swiglu_fwd(gu, h, fmt, d_amax_h, d_scale_h, ws)
+    if status is not None:
+        return _check(status, "llmq_swiglu_fwd") if status else None
     M, I = _swiglu_dims(gu)
     if h.numel() != M * I:
         raise ValueError("h must be [M, I]")
@@ -334,6 +371,9 @@ def llmq_swiglu_fwd(gu: torch.Tensor, h: torch.Tensor, fmt: int, d_amax_h: torch
 
 def llmq_swiglu_fwd_fp8(gu: torch.Tensor, d_scale_h: torch.Tensor, fmt: int, q: torch.Tensor,
                         q_t: Optional[torch.Tensor], h: Optional[torch.Tensor] = None) -> None:
+    status = _fast.swiglu_fwd_fp8(gu, d_scale_h, fmt, q, q_t, h)
+    if status is not None:
+        return _check(status, "llmq_swiglu_fwd_fp8") if status else None
     M, I = _swiglu_dims(gu)
     if q.numel() != M * I or (q_t is not None and q_t.numel() != M * I) or (h is not None and h.numel() != M * I):
         raise ValueError("output size does not match [M, I]")
@@ -344,6 +384,9 @@ def llmq_swiglu_fwd_fp8(gu: torch.Tensor, d_scale_h: torch.Tensor, fmt: int, q: 
 
 def llmq_swiglu_fwd_fp8_slabs(gu: torch.Tensor, d_scale_h: torch.Tensor, fmt: int, q: torch.Tensor,
                               q_t: torch.Tensor, h: Optional[torch.Tensor] = None) -> None:
+    status = _fast.swiglu_fwd_fp8_slabs(gu, d_scale_h, fmt, q, q_t, h)
+    if status is not None:
+        return _check(status, "llmq_swiglu_fwd_fp8_slabs") if status else None
     M, I = _swiglu_dims(gu)
     if q.numel() != M * I or q_t.numel() != M * I or (h is not None and h.numel() != M * I):
         raise ValueError("output size does not match [M, I]")
@@ -354,6 +397,9 @@ def llmq_swiglu_fwd_fp8_slabs(gu: torch.Tensor, d_scale_h: torch.Tensor, fmt: in
 
 def llmq_swiglu_bwd(dh: torch.Tensor, gu: torch.Tensor, dgu: torch.Tensor, fmt: int, d_amax_dgu: torch.Tensor,
                     d_scale_dgu: Optional[torch.Tensor], ws: torch.Tensor) -> None:
+    status = _fast.swiglu_bwd(dh, gu, dgu, fmt, d_amax_dgu, d_scale_dgu, ws)
+    if status is not None:
+        return _check(status, "llmq_swiglu_bwd") if status else None
     M, I = _swiglu_dims(gu)
     if dh.numel() != M * I or dgu.numel() != 2 * M * I:
         raise ValueError("dh must be [M, I] and dGU [M, 2I]")
@@ -370,6 +416,9 @@ def llmq_rmsnorm_workspace_bytes(M: int) -> int:
 def llmq_rmsnorm_fwd(res: torch.Tensor, x: Optional[torch.Tensor], w: torch.Tensor, eps: float,
                      res_out: Optional[torch.Tensor], y: torch.Tensor, rstd: torch.Tensor, fmt: int,
                      d_amax_y: torch.Tensor, d_scale_y: Optional[torch.Tensor], ws: torch.Tensor) -> None:
+    status = _fast.rmsnorm_fwd(res, x, w, eps, res_out, y, rstd, fmt, d_amax_y, d_scale_y, ws)
+    if status is not None:
+        return _check(status, "llmq_rmsnorm_fwd") if status else None
     M, C = res.shape
     if w.numel() != C or y.numel() != M * C or rstd.numel() != M or (x is not None and x.numel() != M * C) or \
             (res_out is not None and res_out.numel() != M * C):
@@ -383,6 +432,9 @@ def llmq_rmsnorm_fwd(res: torch.Tensor, x: Optional[torch.Tensor], w: torch.Tens
 
 def llmq_rmsnorm_apply_fp8(res: torch.Tensor, w: torch.Tensor, rstd: torch.Tensor, d_scale_y: torch.Tensor, fmt: int,
                            q: torch.Tensor, q_t: Optional[torch.Tensor], y: Optional[torch.Tensor] = None) -> None:
+    status = _fast.rmsnorm_apply_fp8(res, w, rstd, d_scale_y, fmt, q, q_t, y)
+    if status is not None:
+        return _check(status, "llmq_rmsnorm_apply_fp8") if status else None
     M, C = res.shape
     if w.numel() != C or rstd.numel() != M or q.numel() != M * C or (q_t is not None and q_t.numel() != M * C) or \
             (y is not None and y.numel() != M * C):
@@ -395,6 +447,9 @@ def llmq_rmsnorm_apply_fp8(res: torch.Tensor, w: torch.Tensor, rstd: torch.Tenso
 
 def llmq_rmsnorm_apply_fp8_slabs(res: torch.Tensor, w: torch.Tensor, rstd: torch.Tensor, d_scale_y: torch.Tensor,
                                  fmt: int, q: torch.Tensor, q_t: torch.Tensor, y: Optional[torch.Tensor] = None) -> None:
+    status = _fast.rmsnorm_apply_fp8_slabs(res, w, rstd, d_scale_y, fmt, q, q_t, y)
+    if status is not None:
+        return _check(status, "llmq_rmsnorm_apply_fp8_slabs") if status else None
     M, C = res.shape
     if w.numel() != C or rstd.numel() != M or q.numel() != M * C or q_t.numel() != M * C or \
             (y is not None and y.numel() != M * C):

@@ -90,6 +90,180 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(
     }
 }
 
+// ---- Few outputs: tiles of 64 x 64 or 32 x 32.
+//
+// What a CU reads per K step sets the pace of a problem that has fewer tiles than the chip has CUs: a 128 x 128 tile takes 32 KB and
+// 0.29 us, and the rest of the chip looks on.  Here a workgroup of four waves (2 x 2) has a tile of SIDE x SIDE, 16 or 8 KB a
+// step.  Four K steps make a stage: one wait and two barriers for all four, and 64 (SIDE 64: two stages) or 96 KB (SIDE 32: four) on
+// their way while one is multiplied.  Slabs, swizzle and fragments are those of the tile kernel; the sums have its order, so the bytes are
+// the same.  Operands in rows of whole 16-byte chunks, or in slabs; what lies behind an operand or the end of a row arrives
+// as zeros (offsets beyond the buffer's range).
+constexpr int kMiniSteps = 4;                                            // K steps of a stage
+template <int FA, int FB, int SIDE>
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_mini_kernel(
+    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ C, int R, int Cn, int T,
+    const float* __restrict__ d_sA, const float* __restrict__ d_sB, int accumulate, unsigned* __restrict__ amax_bits, int ldA, int ldB, int ksA, int ksB,
+    int tiles_r, int n_tiles) {
+    constexpr int kOutOfRange = 0x7FFFFF00;
+    constexpr int kSlab = SIDE * BK, kOperand = kMiniSteps * kSlab;      // bytes of one operand in a K step, in a stage
+    constexpr int ST = SIDE == 64 ? 2 : 4, NB = SIDE / 32;               // stages; blocks of 16 x 16 per wave and side
+    // one LDS object per stage and operand or per stage, which the compiler tells apart (see the tile kernel)
+    __shared__ __attribute__((aligned(1024))) uint8_t s_0[32768];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_1[32768];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_2[32768];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_3[32768];
+    static_assert(ST * 2 * kOperand == 4 * 32768, "");
+    const int pos = walk_position(blockIdx.x, n_tiles);
+    if (pos < 0) return;
+    const int tc = pos / tiles_r, tr = pos - tc * tiles_r;               // down the rows: neighbours share the columns' operand
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int r0 = tr * SIDE, c0 = tc * SIDE;
+    const float scale_a = FA == kFmtBf16 ? 1.0f : *d_sA, scale_b = FB == kFmtBf16 ? 1.0f : *d_sB;
+    const int nk = (T + BK - 1) / BK, ns = (nk + kMiniSteps - 1) / kMiniSteps;
+    auto range = [&](int rows_left, int ld, int ks) -> unsigned {
+        const int n = rows_left < SIDE ? rows_left : SIDE;
+        return ks == BK ? (unsigned)((size_t)(n - 1) * ld + T) : (unsigned)((size_t)(T / BK - 1) * ks + (size_t)(n - 1) * ld + BK);
+    };
+    const __amdgpu_buffer_rsrc_t rsA = make_rsrc(A + (size_t)r0 * ldA, range(R - r0, ldA, ksA));
+    const __amdgpu_buffer_rsrc_t rsB = make_rsrc(B + (size_t)c0 * ldB, range(Cn - c0, ldB, ksB));
+    // Loads: an instruction moves 8 rows x 128 bytes; the wave's rows are [SIDE / 4 wave, SIDE / 4 (wave + 1))
+    constexpr int kPerSlab = SIDE / 32, kLoads = 2 * kMiniSteps * kPerSlab;
+    const int ld_row = lane >> 3;
+    auto issue_stage = [&](uint8_t* bufA, uint8_t* bufB, int stage) {
+#pragma unroll
+        for (int j = 0; j < kMiniSteps; ++j) {
+            const int step = stage * kMiniSteps + j;
+#pragma unroll
+            for (int m = 0; m < kPerSlab; ++m) {
+                const int row = wave * (SIDE / 4) + 8 * m + ld_row;      // its index modulo 16 sets the swizzle
+                const int chunk = ((lane & 7) ^ row_swizzle(row & 15)) << 4;
+                const bool there = step < nk && step * BK + chunk < T;   // (T % 16 == 0: a chunk exists or not)
+                const int offA = there ? row * ldA + chunk + (int)((unsigned)step * (unsigned)ksA) : kOutOfRange;
+                const int offB = there ? row * ldB + chunk + (int)((unsigned)step * (unsigned)ksB) : kOutOfRange;
+                const int dst = j * kSlab + (wave * (SIDE / 4) + 8 * m) * BK;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void*)(bufA + dst), 16, offA, 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void*)(bufB + dst), 16, offB, 0, 0, 0);
+            }
+        }
+    };
+    const int wr = wave >> 1, wc = wave & 1;
+    const int fr_row = lane & 15, fr_q = lane >> 4, swz = row_swizzle(fr_row);
+    const int ch0 = ((fr_q * 2) ^ swz) << 4, ch1 = ((fr_q * 2 + 1) ^ swz) << 4;
+    auto fragment = [&](const uint8_t* slab, int first_row) -> v8i {
+        const uint8_t* p = slab + (first_row + fr_row) * BK;
+        const v4i lo = *reinterpret_cast<const v4i*>(p + ch0), hi = *reinterpret_cast<const v4i*>(p + ch1);
+        return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    };
+    v4f acc[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    auto stage_step = [&](uint8_t* bufA, uint8_t* bufB, int stage) __attribute__((always_inline)) {
+        wait_vmcnt<(ST - 1) * kLoads>();                                 // this stage has landed, the later ones are on their way
+        lds_barrier_in_flight();
+        v8i a[kMiniSteps][NB], b[kMiniSteps][NB];
+#pragma unroll
+        for (int j = 0; j < kMiniSteps; ++j)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                a[j][i] = fragment(bufA + j * kSlab, wr * 16 * NB + 16 * i);
+                b[j][i] = fragment(bufB + j * kSlab, wc * 16 * NB + 16 * i);
+            }
+#pragma unroll
+        for (int j = 0; j < kMiniSteps; ++j)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    if constexpr (FA == kFmtBf16) {
+                        const v8i &x = b[j][k], &y = a[j][i];
+                        const v4i x0 = {x[0], x[1], x[2], x[3]}, x1 = {x[4], x[5], x[6], x[7]}, y0 = {y[0], y[1], y[2], y[3]}, y1 = {y[4], y[5], y[6], y[7]};
+                        acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, y0), acc[i][k], 0, 0, 0);
+                        acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x1), __builtin_bit_cast(bf16x8, y1), acc[i][k], 0, 0, 0);
+                    } else {
+                        acc[i][k] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b[j][k], a[j][i], acc[i][k], FB, FA, 0, 0, 0, 0);
+                    }
+                }
+        lds_barrier_in_flight();                                         // everybody has read the stage: it may be overwritten
+        issue_stage(bufA, bufB, stage + ST);                             // (beyond the last stage: nothing is fetched, zeros are written)
+    };
+    auto half = [&](uint8_t* buf) { return SIDE == 64 ? buf : buf + kOperand; };
+    if constexpr (SIDE == 64) {
+        issue_stage(s_0, s_1, 0);
+        issue_stage(s_2, s_3, 1);
+        int st = 0;
+        for (; st + 1 < ns; st += 2) {                                   // (the same order of loads on every way round: the compiler counts them)
+            stage_step(s_0, s_1, st);
+            stage_step(s_2, s_3, st + 1);
+        }
+        if (st < ns) stage_step(s_0, s_1, st);
+    } else {
+        issue_stage(s_0, half(s_0), 0);
+        issue_stage(s_1, half(s_1), 1);
+        issue_stage(s_2, half(s_2), 2);
+        issue_stage(s_3, half(s_3), 3);
+        int st = 0;
+        for (; st + 3 < ns; st += 4) {
+            stage_step(s_0, half(s_0), st);
+            stage_step(s_1, half(s_1), st + 1);
+            stage_step(s_2, half(s_2), st + 2);
+            stage_step(s_3, half(s_3), st + 3);
+        }
+        if (st < ns) stage_step(s_0, half(s_0), st);
+        if (st + 1 < ns) stage_step(s_1, half(s_1), st + 1);
+        if (st + 2 < ns) stage_step(s_2, half(s_2), st + 2);
+    }
+    wait_vmcnt<0>();                                                     // nothing lands in LDS behind the workgroup's end
+    const float inv_a = 1.0f / scale_a, inv_b = 1.0f / scale_b, inv_ab = inv_a * inv_b;
+    const bool one_mul = inv_ab >= 1.17549435e-38f && inv_ab <= 3.402823466e+38f;
+    const float m1 = one_mul ? inv_ab : inv_a, m2 = one_mul ? 1.0f : inv_b;
+    const bool vector = Cn % 4 == 0;
+    unsigned mag = 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int r = r0 + wr * 16 * NB + 16 * i + (lane & 15);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const int c = c0 + wc * 16 * NB + 16 * k + (lane >> 4) * 4;
+            if (r >= R || c >= Cn) continue;
+            uint16_t* dst = C + (size_t)r * Cn + c;
+            const int valid = Cn - c;
+            uint16_t old[4] = {0, 0, 0, 0}, out[4];
+            if (accumulate) {
+                if (vector) {
+                    const v2u o = *reinterpret_cast<const v2u*>(dst);
+                    old[0] = (uint16_t)o[0]; old[1] = (uint16_t)(o[0] >> 16); old[2] = (uint16_t)o[1]; old[3] = (uint16_t)(o[1] >> 16);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (e < valid) old[e] = dst[e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float y = acc[i][k][e] * m1 * m2;
+                if (accumulate) y += __uint_as_float((unsigned)old[e] << 16);
+                out[e] = __builtin_bit_cast(uint16_t, (__bf16)y);
+                const unsigned m = out[e] & 0x7FFFu;
+                if (e < valid) mag = mag > m ? mag : m;
+            }
+            if (vector) *reinterpret_cast<v2u*>(dst) = v2u{out[0] | (unsigned)out[1] << 16, out[2] | (unsigned)out[3] << 16};
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (e < valid) dst[e] = out[e];
+            }
+        }
+    }
+    if (amax_bits) {
+        __syncthreads();
+        mag = block_max_u32<kGemmThreads>(mag, reinterpret_cast<unsigned*>(s_0));
+        if (threadIdx.x == 0) {
+            const unsigned bits = amax_bits_from_bf16_mag(mag);
+            if (bits > __hip_atomic_load(amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax_bits, bits);
+        }
+    }
+}
+
 // BF16 operands, any shape: one output element per lane and trip, binary32 accumulation along t.
 __global__ __launch_bounds__(256) void gemm_bf16_generic_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
@@ -165,7 +339,7 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
 //   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
 //   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
 //   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
-static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus) {
+static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus, double* generic_us = nullptr) {
     if (bf16) {                                                             // (T in bytes)
         const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
         return R * C <= most;
@@ -197,6 +371,7 @@ static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
     // every wave of the generic kernel raises the same word, and atomics on one address follow each other at 9.5 ns (forward call
     // of 300 x 256 -> 1024, 1216 waves: 25 us with it, 13.5 with the tile kernel)
     if (with_amax) generic += 0.0095 * (double)(((R + 15) / 16) * ((C + 15) / 16));
+    if (generic_us) *generic_us = generic;
     return generic < tile + 0.4e-6 * (double)R * (double)C;
 }
 
@@ -232,6 +407,48 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
     return best;
 }
 
+// The small tiles: their side, or 0 for another kernel.  A model in microseconds: rounds of tiles, each with its K steps; against the 128 x 128
+// tile with four LDS stages (3.9 + 0.29 a step) or, for ragged shapes, the guarded one and the generic kernel.  Every workgroup
+// raises the output absmax, and atomics on one address follow each other.  R x C x T, 128 x 128 / 64 x 64 / 32 x 32:
+//   256 x 1024 x 512 5.2 / 4.7 / 3.7, with absmax 5.2 / 5.2 / 6.0;  256 x 512 x 1024 6.3 / 5.4 / 4.0, 5.5 with absmax;  1024 x 512 x 256 4.6 / 4.7 / 5.8;
+//   128 x 256 x 6688 33.6 / 15.3 / 8.5, 117 x 304 x 14496 61.7 / 37.2 / 16.1, 128 x 1792 x 19456 53.1 / 37.2 / 19.2, 448 x 512 x 3584 13.5 / 10.6 / 6.9,
+//   16 x 4096 x 4096 14.6 / 10.1 / 6.7, 862 x 768 x 3008 15.6 / 11.3 / 16.0, 1024 x 1024 x 4096 14.8 / 12.0 / 24.6, 128 x 8192 x 1024 6.6 / 5.8 / 11.8,
+//   1024 x 2048 x 2048 9.9 / 14.6 / 30.5;  generic / 32 x 32: 100 x 136 x 512 4.3 / 3.5, 300 x 300 x 64 2.8 / 3.5
+// LLMQ_GEMM_MINI=32 / 64 / 0 (tests): that side wherever the operands allow it, or never.
+static int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, int num_cus) {
+    if (T >= (1ll << 23) || R >= (1ll << 23) || C >= (1ll << 23) || T < 16 || (!(slabs_a && slabs_b) && T % 16 != 0)) return 0;
+    const int64_t tiles128 = ((R + 127) / 128) * ((C + 127) / 128);
+    if (tiles128 > ((int64_t)1 << 20)) return 0;                          // (32 x 32 tiles then fit a launch)
+    if (const char* e = tuning_env("LLMQ_GEMM_MINI")) return atoi(e);
+    if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
+    if (tiles128 > num_cus) return 0;
+    const double steps = (double)((T + BK - 1) / BK), atomic = with_amax ? 0.0095 : 0.0;
+    const bool ragged = R % 128 != 0 || C % 128 != 0 || T % BK != 0;
+    double best = (ragged ? 4.9 : 3.9) + 0.29 * steps + atomic * (double)tiles128;
+    int side = 0;
+    double generic = 0;
+    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus, &generic) && (bf16 || generic < best)) best = bf16 ? 6.0 : generic;
+    for (int s = 64; s >= 32; s -= 32) {
+        const int64_t tiles = ((R + s - 1) / s) * ((C + s - 1) / s);
+        const double rounds = (double)((tiles + num_cus - 1) / num_cus);
+        const double cost = (s == 64 ? 1.4 + rounds * (2.7 + 0.24 * steps) : 1.2 + rounds * (2.0 + 0.107 * steps)) + atomic * (double)tiles;
+        if (cost < best) { best = cost; side = s; }
+    }
+    return side;
+}
+
+template <int FA, int FB>
+static void launch_mini(int side, const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
+                        void* c, int accumulate, unsigned* amax, hipStream_t stream, bool slabs_a, bool slabs_b) {
+    const int tiles_r = (int)((R + side - 1) / side), tiles = tiles_r * (int)((C + side - 1) / side), grid = (tiles + kXcds - 1) / kXcds * kXcds;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGemmThreads), 0, stream, A, B, reinterpret_cast<uint16_t*>(c), (int)R, (int)C, (int)T, sA, sB, accumulate, amax,
+                           slabs_a ? BK : (int)T, slabs_b ? BK : (int)T, slabs_a ? (int)(R * BK) : BK, slabs_b ? (int)(C * BK) : BK, tiles_r, tiles);
+    };
+    if (side == 32) launch(gemm_mini_kernel<FA, FB, 32>);
+    else launch(gemm_mini_kernel<FA, FB, 64>);
+}
+
 template <int FA, int FB>
 static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T,
                        const float* sA, const float* sB, void* c, int accumulate, unsigned* amax,
@@ -239,6 +456,10 @@ static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C,
     // (an operand in slabs is addressed with 32-bit offsets from its first tile row, 0x7FFFFF00 being out of range)
     const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);
     const bool fits = (!slabs_a || (T + 256) * R < lim) && (!slabs_b || (T + 256) * C < lim);
+    if (fits) {
+        const int side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, num_cus);
+        if (side) { launch_mini<FA, FB>(side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
+    }
     if (fits && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b)) return;
     if (fits && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b)) return;
     if constexpr (FA == kFmtBf16) {

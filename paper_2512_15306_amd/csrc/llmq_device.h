@@ -380,12 +380,14 @@ __device__ inline void store_codes_upto(const unsigned (&w)[PR][2], uint8_t* dst
 constexpr int kSmallRows = 64, kSmallCols = 128, kSmallPatch = 4;
 constexpr int kSmallPitch = kSmallRows + 16, kSmallLdsBytes = kSmallCols * kSmallPitch;
 
-// Rows that do not start at a cache line share lines with the tiles beside them, so neighbours belong on one XCD (own L2;
-// the hardware deals workgroup ids round-robin to them): each XCD then walks a contiguous range of tiles, eight tile columns
-// wide and down the rows.  Where rows do start at lines, plain launch order along the columns is better.  Quantize
-// kernel, launch order / XCD ranges in bands of 2 / 8 / all columns: 8112 x 5128 elements 45.7 / 39.9 / 37.7 / 37.5 us,
-// 1777 x 20000 40.3 / 33.5 / 33.6 / 38.9, 9001 x 3001 32.4 / 31.3 / 30.8 / 31.3, 16000 x 9000 202 / 202 / 174 / 173;  rows of
-// whole lines: 3584 x 21440 69 / 78 / 73 / 85, 8100 x 7168 53.6 / 55.1 / 58.0 / 59.8.
+// Tiles that share cache lines belong on one XCD (own L2; the hardware deals workgroup ids round-robin to them).  Rows that do not
+// start at a line share lines with the tiles beside them, and the lines of the transposed copy, written in 64-byte pieces, are shared with
+// the tiles above and below.  In launch order along the columns those above and below lie on the same XCD if a row has a multiple of
+// eight tiles, which then is the better order; otherwise each XCD walks a contiguous range of tiles, eight tile columns wide and down the
+// rows.  Quantize kernel, launch order / XCD ranges in bands of 2 / 8 / all columns: 8112 x 5128 elements 45.7 / 39.9 / 37.7 / 37.5 us,
+// 1777 x 20000 40.3 / 33.5 / 33.6 / 38.9, 9001 x 3001 32.4 / 31.3 / 30.8 / 31.3, 16000 x 9000 202 / 202 / 174 / 173;  launch order / bands of 8, rows of
+// whole lines: 56 tiles (8100 x 7168) 53 / 57, 40 (8100 x 5120) 39 / 40, 112 (3333 x 14336) 42 / 42;  220 (6096 x 28160) 232 / 166, 158 (1104 x 20224)
+// 25.8 / 22.3, 297 (300 x 38016) 14.1 / 11.9, 22 (4001 x 2816) 14.5 / 12.1, 110 (6096 x 14080) 83 / 82; of less than eight tiles a row either may win.
 constexpr unsigned kSmallXcds = 8, kSmallBand = 8;
 struct SmallGrid {
     unsigned rows, cols, blocks;            // tiles (at most 2^28: tensors have at most 2^40 elements and 2^31 rows), workgroups in all
@@ -399,7 +401,7 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     g.cols = (unsigned)((cols + kSmallCols - 1) / kSmallCols);
     g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
     g.first = 0;
-    g.xcd_ranges = cols % 64 != 0;
+    g.xcd_ranges = cols % 64 != 0 || (g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
     // (lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
     // 22.5, 8263 x 5120 39.2 / 39.3 and 39.1 / 39.2, 16000 x 9000 175 / 169 and 174 / 166)
     g.stacked = rows * cols > (int64_t)40000000;

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "llmq_kernels.h"
 
@@ -325,8 +326,55 @@ __device__ inline void store16_codes_upto(uint8_t* p, const v4u& v, int n) {
     if (n & 7) store8_codes_upto(p + (n & 8), lo, hi, n & 7);
 }
 
+// Runs body with a compile-time answer to whether edges have to be guarded.  `guard` is the same for every lane of a wave (of a workgroup, if
+// body holds a barrier), so tiles inside the tensor run straight-line code that requests everything before it waits; with the guards'
+// branches in the way the patches, the weights and the row factors were waited for one after the other.  Codes, guards per lane / so: SwiGLU
+// 8100 x 7168 64.1 / 60.8 us, 12001 x 5000 80.8 / 78.0; RMSNorm 16101 x 4096 52.0 / 46.6, 12001 x 5000 56.6 / 52.1.  One patch and nothing else
+// (quantize) has nothing to gain: 8112 x 5128 44.3 / 45.3, 1777 x 2730 6.9 / 7.4; it asks lane by lane.
+template <class F>
+__device__ inline void with_guard(bool guard, F body) {
+    if (guard) body(std::true_type{});
+    else body(std::false_type{});
+}
+
 // A patch of PR rows x 8 columns of BF16 values at src = column c0 (a multiple of 8) of its first row, rows `ld` elements apart,
-// of which rows_left rows and cols_left columns exist
+// of which rows_left rows and cols_left columns exist.  Patches of several tensors that are guarded alike are requested together: the guards'
+// branches, one patch after the other, would wait for each patch before the next one is requested (SwiGLU backward, 9001 x 6001: 155 us
+// patch by patch, 131 so; forward 85 / 73).
+template <int PR>
+struct Patch {
+    v4u (&in)[PR];
+    const uint16_t* src;
+    int64_t ld;
+};
+template <int PR>
+__device__ inline Patch<PR> patch(v4u (&in)[PR], const uint16_t* src, int64_t ld) { return Patch<PR>{in, src, ld}; }
+template <int PR>
+__device__ inline void request_patch(const Patch<PR>& p, int drop, int64_t rows_left) {
+#pragma unroll
+    for (int i = 0; i < PR; ++i) p.in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(p.src - drop + (int64_t)(i < rows_left ? i : 0) * p.ld));
+}
+template <int PR>
+__device__ inline void shift_patch(const Patch<PR>& p, int drop, int64_t rows_left) {
+#pragma unroll
+    for (int i = 0; i < PR; ++i) p.in[i] = i < rows_left ? shift_elements(p.in[i], drop) : v4u{0, 0, 0, 0};
+}
+template <int PR>
+__device__ inline void load_patch_by_elements(const Patch<PR>& p, int64_t rows_left, int64_t cols_left) {
+#pragma unroll
+    for (int i = 0; i < PR; ++i) p.in[i] = load8_by_elements(p.src + (int64_t)i * p.ld, i < rows_left ? cols_left : 0);
+}
+template <int... PR>
+__device__ inline void load_patches_upto(int64_t c0, int64_t rows_left, int64_t cols_left, const Patch<PR>&... p) {
+    if (rows_left > 0 && cols_left > 0 && (cols_left >= 8 || c0 >= 8)) {
+        const int drop = cols_left >= 8 ? 0 : 8 - (int)cols_left;
+        (request_patch(p, drop, rows_left), ...);
+        if (((rows_left < PR) || ...) || drop != 0) (shift_patch(p, drop, rows_left), ...);
+    } else {
+        (load_patch_by_elements(p, rows_left, cols_left), ...);
+    }
+}
+// One patch, where the tile's guard is not known to the whole wave
 template <int PR>
 __device__ inline void load_patch_upto(v4u (&in)[PR], const uint16_t* src, int64_t ld, int64_t c0, int64_t rows_left, int64_t cols_left) {
     if (rows_left >= PR && cols_left >= 8) {
@@ -335,15 +383,8 @@ __device__ inline void load_patch_upto(v4u (&in)[PR], const uint16_t* src, int64
     } else if (rows_left <= 0 || cols_left <= 0) {
 #pragma unroll
         for (int i = 0; i < PR; ++i) in[i] = v4u{0, 0, 0, 0};
-    } else if (cols_left >= 8 || c0 >= 8) {
-        const int drop = cols_left >= 8 ? 0 : 8 - (int)cols_left;
-#pragma unroll
-        for (int i = 0; i < PR; ++i) in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(src - drop + (int64_t)(i < rows_left ? i : 0) * ld));
-#pragma unroll
-        for (int i = 0; i < PR; ++i) in[i] = i < rows_left ? shift_elements(in[i], drop) : v4u{0, 0, 0, 0};
     } else {
-#pragma unroll
-        for (int i = 0; i < PR; ++i) in[i] = load8_by_elements(src + (int64_t)i * ld, i < rows_left ? cols_left : 0);
+        load_patches_upto(c0, rows_left, cols_left, patch(in, src, ld));
     }
 }
 template <int PR>
@@ -402,9 +443,10 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
     g.first = 0;
     g.xcd_ranges = cols % 64 != 0 || (g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
-    // (lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
-    // 22.5, 8263 x 5120 39.2 / 39.3 and 39.1 / 39.2, 16000 x 9000 175 / 169 and 174 / 166)
-    g.stacked = rows * cols > (int64_t)40000000;
+    // Lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
+    // 22.7, 8100 x 7168 40.8 / 47.8 and 42.0 / 49.1, 16101 x 4096 44.8 / 53.4 and 46.5 / 55.0, 12001 x 5000 50.6 / 52.8 and 51.4 / 54.5; only large
+    // tensors whose rows do not start at lines prefer them stacked, 16000 x 9000 172 / 167 and 168 / 168.
+    g.stacked = cols % 64 != 0 && rows * cols > (int64_t)100000000;
     return g;
 }
 // launch(grid, workgroups of this launch), once or as often as the launch limit asks for
@@ -420,6 +462,11 @@ __host__ __device__ inline bool small_tile(const SmallGrid& g, unsigned id, unsi
     const unsigned band = g.xcd_ranges && kSmallBand < g.cols ? kSmallBand : g.cols;
     band_walk(pos, g.rows, g.cols, band, brow, bcol);
     return true;
+}
+
+// Whether the tile reaches over the tensor's edge
+__device__ inline bool small_tile_guard(int64_t R0, int64_t C0, int64_t rows, int64_t cols) {
+    return rows - R0 < kSmallRows || cols - C0 < kSmallCols;
 }
 
 __device__ inline void small_patch_origin(const SmallGrid& g, int& tr, int& tc) {

@@ -477,27 +477,30 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
     int tr, tc;
     small_patch_origin(grid, tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
-    const int64_t rows_left = M - r0, cols_left = C - c0;
-    v4u in[kSmallPatch];
-    load_patch_upto(in, res + r0 * C + c0, C, c0, rows_left, cols_left);
-    const v4u wv = load8_upto(w + c0, c0, cols_left);
-    float rs[kSmallPatch];
+    with_guard(small_tile_guard(R0, C0, M, C), [&](auto guard) {
+        const int64_t rows_left = guard ? M - r0 : kSmallPatch, cols_left = guard ? C - c0 : 8;
+        v4u in[kSmallPatch];
+        v4u wv[1];
+        load_patches_upto(c0, rows_left, cols_left, patch(in, res + r0 * C + c0, C), patch(wv, w + c0, 0));
+        float rs[kSmallPatch];
 #pragma unroll
-    for (int i = 0; i < kSmallPatch; ++i) rs[i] = i < rows_left ? rstd[r0 + i] : 0.0f;
-    const float s = *d_qscale;
-    unsigned wq[kSmallPatch][2];
+        for (int i = 0; i < kSmallPatch; ++i) rs[i] = i < rows_left ? rstd[r0 + i] : 0.0f;
+        const float s = *d_qscale;
+        unsigned wq[kSmallPatch][2];
 #pragma unroll
-    for (int i = 0; i < kSmallPatch; ++i) {
-        in[i] = normalize8(in[i], rs[i], wv);
-        quantize8<QFMT>(in[i], s, wq[i][0], wq[i][1]);
-    }
-    if (y) store_patch_upto(in, y + r0 * C + c0, C, rows_left, cols_left);
-    store_codes_upto(wq, q + r0 * C + c0, C, rows_left, cols_left);
-    if constexpr (TRANSPOSE) {
-        small_stage_transposed(wq, tr, tc, s_t);
-        __syncthreads();
-        small_write_transposed_upto(s_t, qt + C0 * qt_row_stride + (R0 / kTileRows) * qt_band_stride + R0 % kTileRows, qt_row_stride, M - R0, C - C0);
-    }
+        for (int i = 0; i < kSmallPatch; ++i) {
+            in[i] = normalize8(in[i], rs[i], wv[0]);
+            quantize8<QFMT>(in[i], s, wq[i][0], wq[i][1]);
+        }
+        if (y) store_patch_upto(in, y + r0 * C + c0, C, rows_left, cols_left);
+        store_codes_upto(wq, q + r0 * C + c0, C, rows_left, cols_left);
+        if constexpr (TRANSPOSE) {
+            small_stage_transposed(wq, tr, tc, s_t);
+            __syncthreads();
+            small_write_transposed_upto(s_t, qt + C0 * qt_row_stride + (R0 / kTileRows) * qt_band_stride + R0 % kTileRows, qt_row_stride,
+                                        guard ? M - R0 : kSmallRows, guard ? C - C0 : kSmallCols);
+        }
+    });
 }
 
 int64_t rmsnorm_blocks(int64_t M) { return (M + kRnRowsPerBlock - 1) / kRnRowsPerBlock; }

@@ -96,7 +96,7 @@ __device__ inline float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0
 
 // Eight elements: one 16-byte vector of g and of u -> one 16-byte vector of h.
 template <bool NORMAL>
-__device__ inline v4u swiglu8_as(const v4u& g, const v4u& u) {
+__device__ __forceinline__ v4u swiglu8_as(const v4u& g, const v4u& u) {
     v4u o;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -122,7 +122,7 @@ __device__ inline void swiglu_bwd_f32(float d, float g, float u, float& dg, floa
 
 // Eight elements of dh, g and u -> eight of the gate's and of the up branch's gradient (which may replace g and u)
 template <bool NORMAL>
-__device__ inline void swiglu_bwd8_as(const v4u& d, const v4u& g, const v4u& u, v4u& og, v4u& ou) {
+__device__ __forceinline__ void swiglu_bwd8_as(const v4u& d, const v4u& g, const v4u& u, v4u& og, v4u& ou) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         float dg0, du0, dg1, du1;
@@ -292,6 +292,10 @@ __device__ inline void swiglu_edge_origin(int64_t piece, unsigned col_pieces, in
     r0 = g * kSwEdgeRows;
     c0 = (piece - g * col_pieces) * kSwEdgeCols + (threadIdx.x & (kWave - 1)) * 8;
 }
+// Whether any lane's patch reaches over the tensor's edge (lanes beside the tensor have left): the same for all of a wave's lanes
+__device__ inline bool swiglu_edge_guard(int64_t r0, int64_t c0, int64_t M, int64_t I) {
+    return __ballot(M - r0 < kSwEdgeRows || I - c0 < 8) != 0;
+}
 
 __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_edge_kernel(
     const uint16_t* __restrict__ gu, int64_t M, int64_t I, uint16_t* __restrict__ h, unsigned* __restrict__ partial,
@@ -306,17 +310,19 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_edge_kernel(
         if (c0 >= I) continue;
         const uint16_t* src = gu + r0 * (2 * I) + c0;
         v4u g[PR], u[PR], o[PR];
-        load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
-        load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
+        with_guard(swiglu_edge_guard(r0, c0, M, I), [&](auto guard) {
+            const int64_t rows_left = guard ? M - r0 : PR, cols_left = guard ? I - c0 : 8;
+            load_patches_upto(c0, rows_left, cols_left, patch(g, src, 2 * I), patch(u, src + I, 2 * I));
 #pragma unroll
-        for (int i = 0; i < PR; ++i) {
-            o[i] = swiglu8(g[i], u[i]);                     // zeros where nothing is: they do not raise the absmax
-            m0 = pk_max_mag(m0, o[i][0]);
-            m1 = pk_max_mag(m1, o[i][1]);
-            m2 = pk_max_mag(m2, o[i][2]);
-            m3 = pk_max_mag(m3, o[i][3]);
-        }
-        store_patch_upto(o, h + r0 * I + c0, I, M - r0, I - c0);
+            for (int i = 0; i < PR; ++i) {
+                o[i] = swiglu8(g[i], u[i]);                 // zeros where nothing is: they do not raise the absmax
+                m0 = pk_max_mag(m0, o[i][0]);
+                m1 = pk_max_mag(m1, o[i][1]);
+                m2 = pk_max_mag(m2, o[i][2]);
+                m3 = pk_max_mag(m3, o[i][3]);
+            }
+            store_patch_upto(o, h + r0 * I + c0, I, rows_left, cols_left);
+        });
     }
     const unsigned mag = block_max_u32<kSwThreads>(fold_max(m0, m1, m2, m3), s_part);
     if (threadIdx.x == 0) partial[blockIdx.x] = mag;
@@ -336,23 +342,26 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_fp8_small_kernel(
     small_patch_origin(grid, tr, tc);
     const int64_t R0 = (int64_t)brow * kSmallRows, C0 = (int64_t)bcol * kSmallCols, r0 = R0 + tr, c0 = C0 + tc;
     const uint16_t* src = gu + r0 * (2 * I) + c0;
-    v4u g[kSmallPatch], u[kSmallPatch];
-    load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
-    load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
-    const float s = *d_qscale;
-    unsigned w[kSmallPatch][2];
+    with_guard(small_tile_guard(R0, C0, M, I), [&](auto guard) {
+        const int64_t rows_left = guard ? M - r0 : kSmallPatch, cols_left = guard ? I - c0 : 8;
+        v4u g[kSmallPatch], u[kSmallPatch];
+        load_patches_upto(c0, rows_left, cols_left, patch(g, src, 2 * I), patch(u, src + I, 2 * I));
+        const float s = *d_qscale;
+        unsigned w[kSmallPatch][2];
 #pragma unroll
-    for (int i = 0; i < kSmallPatch; ++i) {
-        g[i] = swiglu8(g[i], u[i]);
-        quantize8<QFMT>(g[i], s, w[i][0], w[i][1]);
-    }
-    if (h) store_patch_upto(g, h + r0 * I + c0, I, M - r0, I - c0);
-    store_codes_upto(w, q + r0 * I + c0, I, M - r0, I - c0);
-    if constexpr (TRANSPOSE) {
-        small_stage_transposed(w, tr, tc, s_t);
-        __syncthreads();
-        small_write_transposed_upto(s_t, qt + C0 * qt_row_stride + (R0 / kTileRows) * qt_band_stride + R0 % kTileRows, qt_row_stride, M - R0, I - C0);
-    }
+        for (int i = 0; i < kSmallPatch; ++i) {
+            g[i] = swiglu8(g[i], u[i]);
+            quantize8<QFMT>(g[i], s, w[i][0], w[i][1]);
+        }
+        if (h) store_patch_upto(g, h + r0 * I + c0, I, rows_left, cols_left);
+        store_codes_upto(w, q + r0 * I + c0, I, rows_left, cols_left);
+        if constexpr (TRANSPOSE) {
+            small_stage_transposed(w, tr, tc, s_t);
+            __syncthreads();
+            small_write_transposed_upto(s_t, qt + C0 * qt_row_stride + (R0 / kTileRows) * qt_band_stride + R0 % kTileRows, qt_row_stride,
+                                        guard ? M - R0 : kSmallRows, guard ? I - C0 : kSmallCols);
+        }
+    });
 }
 
 __global__ __launch_bounds__(kSwThreads) void swiglu_bwd_edge_kernel(
@@ -368,20 +377,21 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_bwd_edge_kernel(
         if (c0 >= I) continue;
         const uint16_t* src = gu + r0 * (2 * I) + c0;
         v4u g[PR], u[PR], d[PR];
-        load_patch_upto(g, src, 2 * I, c0, M - r0, I - c0);
-        load_patch_upto(u, src + I, 2 * I, c0, M - r0, I - c0);
-        load_patch_upto(d, dh + r0 * I + c0, I, c0, M - r0, I - c0);
+        with_guard(swiglu_edge_guard(r0, c0, M, I), [&](auto guard) {
+            const int64_t rows_left = guard ? M - r0 : PR, cols_left = guard ? I - c0 : 8;
+            load_patches_upto(c0, rows_left, cols_left, patch(g, src, 2 * I), patch(u, src + I, 2 * I), patch(d, dh + r0 * I + c0, I));
 #pragma unroll
-        for (int i = 0; i < PR; ++i) {
-            swiglu_bwd8(d[i], g[i], u[i], g[i], u[i]);
-            m0 = pk_max_mag(pk_max_mag(m0, g[i][0]), u[i][0]);
-            m1 = pk_max_mag(pk_max_mag(m1, g[i][1]), u[i][1]);
-            m2 = pk_max_mag(pk_max_mag(m2, g[i][2]), u[i][2]);
-            m3 = pk_max_mag(pk_max_mag(m3, g[i][3]), u[i][3]);
-        }
-        uint16_t* dst = dgu + r0 * (2 * I) + c0;
-        store_patch_upto(g, dst, 2 * I, M - r0, I - c0);
-        store_patch_upto(u, dst + I, 2 * I, M - r0, I - c0);
+            for (int i = 0; i < PR; ++i) {
+                swiglu_bwd8(d[i], g[i], u[i], g[i], u[i]);
+                m0 = pk_max_mag(pk_max_mag(m0, g[i][0]), u[i][0]);
+                m1 = pk_max_mag(pk_max_mag(m1, g[i][1]), u[i][1]);
+                m2 = pk_max_mag(pk_max_mag(m2, g[i][2]), u[i][2]);
+                m3 = pk_max_mag(pk_max_mag(m3, g[i][3]), u[i][3]);
+            }
+            uint16_t* dst = dgu + r0 * (2 * I) + c0;
+            store_patch_upto(g, dst, 2 * I, rows_left, cols_left);
+            store_patch_upto(u, dst + I, 2 * I, rows_left, cols_left);
+        });
     }
     const unsigned mag = block_max_u32<kSwThreads>(fold_max(m0, m1, m2, m3), s_part);
     if (threadIdx.x == 0) partial[blockIdx.x] = mag;

@@ -199,3 +199,26 @@ def test_whole_tiles_that_are_no_slabs(rows, cols, fmt, monkeypatch):
     """128 x 128 tiles of tensors whose width is no multiple of the 256 columns that slabs come in."""
     monkeypatch.setenv("LLMQ_QUANT_TILE", "1")
     test_codes_of_every_producer(rows, cols, None, None, fmt, monkeypatch)
+
+
+@pytest.mark.parametrize("rows,cols", [(12545, 8001), (12551, 8008)])
+def test_large_ragged_codes_are_those_of_their_bands(rows, cols):
+    """Above 100M elements the lanes of the guarded tile lie differently: the codes are those of bands of rows by themselves."""
+    x = torch.randn(rows, cols, device=DEV).to(torch.bfloat16)
+    w = torch.randn(cols, device=DEV).to(torch.bfloat16)
+    rstd = torch.rand(rows, device=DEV) + 0.5
+    scale = torch.full((1,), 90.0, device=DEV)
+
+    def codes(a, b):
+        n = (b - a) * cols
+        out = [torch.zeros(n, dtype=torch.uint8, device=DEV) for _ in range(4)]
+        llmq.llmq_quantize_fp8(x[a:b], scale, 0, out[0].view(b - a, cols), out[1])
+        llmq.llmq_rmsnorm_apply_fp8(x[a:b], w, rstd[a:b], scale, 0, out[2].view(b - a, cols), out[3], None)
+        return out[0].view(b - a, cols), out[1].view(cols, b - a), out[2].view(b - a, cols), out[3].view(cols, b - a)
+
+    q, qt, n, nt = codes(0, rows)
+    assert torch.equal(qt, q.t()) and torch.equal(nt, n.t())
+    for a in range(0, rows, 4000):
+        b = min(rows, a + 4000)
+        bq, _, bn, _ = codes(a, b)
+        assert torch.equal(q[a:b], bq) and torch.equal(n[a:b], bn)

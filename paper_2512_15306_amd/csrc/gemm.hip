@@ -375,9 +375,14 @@ static bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
     return generic < tile + 0.4e-6 * (double)R * (double)C;
 }
 
-// Tile and kind of a ragged problem, by the same model with the tiles rounded up.  Against the best of the four tiles, forced, over
-// 28 shapes from 1000^3 to 9000^2 x 1000: 0.7 % behind on average with aligned rows, 2.6 % with unaligned ones and 1.4 % with both
+// Tile and kind of a ragged problem, by the same model with the tiles rounded up.  Against the best of the four tiles of even sides, forced,
+// over 28 shapes from 1000^3 to 9000^2 x 1000: 0.7 % behind on average with aligned rows, 2.6 % with unaligned ones and 1.4 % with both
 // operands T-major; no other efficiencies of this model do better on the first two.
+// Tiles of 192 rows (aligned rows only) stand between the others where those would need another round: without / with them, operands in rows,
+// R x C x T 4114 x 4156 x 4784 128.7 / 108.7 us, 4911 x 6786 x 6912 233 / 196, 2385 x 3578 x 2448 47.5 / 40.5, 8026 x 2771 x 6864 207 / 196,
+// 5971 x 1623 x 1104 29.0 / 27.0;  B T-major 2385 x 3584 x 2448 36.5 / 29.7;  both T-major 4128 x 4160 x 4784 110 / 93, 4912 x 6800 x 6912
+// 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128, which one workgroup per CU
+// takes (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.  Tiles of 192 columns would need another staging of the output.
 EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
@@ -387,20 +392,21 @@ EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool t
     best.edge = aligned_a && aligned_b ? kEdge : kEdgeUnaligned;
     if (const char* force = tuning_env("LLMQ_GEMM_EDGE_TILE")) {
         const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
-        if ((ni == 2 || ni == 4) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
+        if ((ni == 2 || ni == 4 || (ni == 3 && best.edge == kEdge)) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
         if (ni == 0) return best;                             // 0x0: the generic kernel
     }
     if (generic_is_faster(R, C, T, ta, tb, accumulate, with_amax, bf16, num_cus)) return best;
     if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
     double best_cost = 0;
-    for (int ni = 4; ni >= 2; ni -= 2)
+    for (int ni = 4; ni >= 2; --ni)
         for (int nj = 4; nj >= 2; nj -= 2) {
+            if (ni == 3 && best.edge != kEdge) continue;
             const int64_t tiles = ((R + 64 * ni - 1) / (64 * ni)) * ((C + 64 * nj - 1) / (64 * nj));
             if (tiles > kMaxWorkgroups) continue;
             const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;
             const int64_t slots = resident_slots(num_cus, ni, nj);
             const int64_t rounds = (tiles + slots - 1) / slots;
-            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : (ni == nj ? 1.0 : 0.77);
+            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : ni == 3 ? (nj == 4 ? 0.83 : T <= 1024 && !tb ? 0.68 : 0.74) : (ni == nj ? 1.0 : 0.77);
             const double cost = (double)rounds * per_cu * ni * nj / e;
             if (best.ni == 0 || cost < best_cost * 0.97) { best.ni = ni; best.nj = nj; best_cost = cost; }
         }

@@ -1349,6 +1349,8 @@ bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
         return true;
     switch (ec.ni * 8 + ec.nj) {
         LLMQ_EDGE_CASE(4, 4) LLMQ_EDGE_CASE(4, 2) LLMQ_EDGE_CASE(2, 4) LLMQ_EDGE_CASE(2, 2)
+        case 3 * 8 + 4: launch_edge<FA, FB, 3, 4, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); return true;
+        case 3 * 8 + 2: launch_edge<FA, FB, 3, 2, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); return true;
         default: break;
     }
 #undef LLMQ_EDGE_CASE

@@ -182,3 +182,11 @@ def test_more_tiles_than_compute_units(T, monkeypatch):
                 first = c.clone().view(torch.int16)
                 assert_gemm_close(c[torch.from_numpy(rows).to(DEV)][:, torch.from_numpy(cols).to(DEV)], y, S, "large")
             assert torch.equal(first, c.view(torch.int16))
+
+
+@pytest.mark.parametrize("tile", ["3x4", "3x2"])
+@pytest.mark.parametrize("R,C,T", [(1, 8, 16), (191, 130, 112), (192, 17, 144), (193, 264, 400), (400, 256, 272), (577, 513, 128)])
+def test_tiles_of_192_rows(R, C, T, tile, monkeypatch):
+    """Below, at and above their edges (aligned rows only: the transposed layouts of the others keep the tiles of even sides)."""
+    test_ragged_fp8(R, C, T, tile, monkeypatch)
+    test_ragged_bf16(R, C, T, tile, monkeypatch)

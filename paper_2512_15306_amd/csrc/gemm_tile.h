@@ -26,6 +26,7 @@
 //     each XCD (own L2) a contiguous range of tiles, walked in bands 4 tile-rows high;
 //   - the host picks NI x NJ per problem so that the tiles fill the 256 CUs in whole rounds.
 // Ragged shapes take the same kernel with guarded edges (EDGE below).
+// Contractions of few outputs take tiles of 64 x 64 or 32 x 32 (gemm_mini_kernel in gemm.hip).
 // Generic kernel: any shape, one wavefront per 16x16 outputs, guarded loads; for ragged problems so small that it finishes before
 // a tile kernel has filled its LDS (generic_is_faster in gemm.hip), contractions shorter than 16 bytes and the operand mixes no
 // tile kernel is built for.

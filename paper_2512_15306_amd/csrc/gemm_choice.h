@@ -1,0 +1,140 @@
+// Host side of the contractions: which kernel a problem takes.  Plain functions of the sizes, without a kernel in sight.
+#pragma once
+#include <stdint.h>
+#include <stdlib.h>
+
+#include "llmq_kernels.h"
+
+namespace llmq {
+
+constexpr int BK = 128;                                     // contraction bytes of a K step
+constexpr int kXcds = 8;
+constexpr int kNoEdge = 0, kEdge = 1, kEdgeUnaligned = 2;    // kinds of the tile kernel (gemm_tile.h)
+
+// Workgroups of the tile kernel resident on the chip at once (a multiple of the XCD count);
+// LLMQ_GEMM_SLOTS overrides it for tests, so that small problems meet the many-rounds code paths.
+inline int resident_slots(int num_cus, int ni, int nj) {
+    if (const char* e = tuning_env("LLMQ_GEMM_SLOTS")) { const int v = atoi(e); if (v >= kXcds && v % kXcds == 0) return v; }
+    return (num_cus / kXcds) * kXcds * ((ni == 2 && nj == 2) ? 2 : 1);
+}
+
+struct EdgeChoice {
+    int ni, nj;       // 0, 0: the generic kernel
+    int edge;         // kEdge or kEdgeUnaligned
+};
+
+// Whether the generic kernel finishes first.  Its waves of 16 x 16 outputs (BF16: lanes of one output) have no LDS to fill
+// and no tile to write out, which makes it the faster one for small problems, as long as its operands can be loaded in
+// vectors or the contraction is one K step long.  FP8: the same sums, so the same bytes.  A model in microseconds: waits of
+// one wave, and for every further round of workgroups per CU; fitted to 1712 shapes in four layouts up to 4001 x 1001 outputs
+// and T = 2048.  Generic / tile kernel:
+//   both operands in rows, R x C x T   100 x 136 x 64 2.9 / 5.2, x 512 4.4 / 6.2, x 1024 6.4 / 7.4, x 2048 10.4 / 9.8;  1000 x 520 x 64 4.0 / 5.4,
+//     x 256 5.6 / 5.8, x 384 7.0 / 6.1;  2000 x 1000 x 64 7.5 / 5.9;  T no multiple of 32: 100 x 136 x 400 6.9 / 6.2, x 50 6.5 / 7.5, x 1001 47 / 14
+//   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
+//   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
+//   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
+inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus, double* generic_us = nullptr) {
+    if (bf16) {                                                             // (T in bytes)
+        const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
+        return R * C <= most;
+    }
+    if (R * C > ((int64_t)1 << 23)) return false;
+    const double steps = (double)((T + BK - 1) / BK);
+    const int64_t workgroups = ((R + 31) / 32) * ((C + 31) / 32);
+    const double more = (double)((workgroups + num_cus - 1) / num_cus - 1);
+    const bool one = T <= BK, odd_width = C % 8 != 0;
+    double generic, tile;
+    if (!ta && !tb && T % 16 == 0) {
+        generic = (T % 32 == 0 ? 2.5 : 5.4) + 0.5 * steps + more * (0.25 + 0.44 * steps);
+        tile = 4.9 + 0.29 * steps;
+    } else if (!ta && !tb && one) {
+        generic = 6.6 + more * 0.03 * (double)T;
+        tile = 7.2;
+    } else if (!ta && one) {
+        generic = T <= 16 ? 6.3 + more * 0.6 : T % 32 == 0 ? 6.0 + more * 0.8 : 7.9 + more * 0.02 * (double)T;
+        tile = T % 16 == 0 && C % 16 == 0 ? 5.0 : 6.5;
+    } else if (ta && one) {
+        generic = T <= 16 ? 6.7 + more * 0.6 : (C <= 32 ? 7.9 : 9.2) + more * 0.9;
+        tile = R % 16 == 0 && C % 16 == 0 ? 5.0 : 6.5;
+    } else {
+        return false;
+    }
+    const double rows = R < 16 ? 16.0 : R > 64 ? 64.0 : (double)R;          // that a wave of the tile kernel writes out
+    if (odd_width) tile += (rows - 16.0) / 48.0 * 2.1;
+    if (accumulate) { generic += 0.9 + 0.68 * more; tile += odd_width ? 1.2 : 0.6; }
+    // every wave of the generic kernel raises the same word, and atomics on one address follow each other at 9.5 ns (forward call
+    // of 300 x 256 -> 1024, 1216 waves: 25 us with it, 13.5 with the tile kernel)
+    if (with_amax) generic += 0.0095 * (double)(((R + 15) / 16) * ((C + 15) / 16));
+    if (generic_us) *generic_us = generic;
+    return generic < tile + 0.4e-6 * (double)R * (double)C;
+}
+
+// Tile and kind of a ragged problem, by the same model with the tiles rounded up.  Against the best of the four tiles of even sides, forced,
+// over 28 shapes from 1000^3 to 9000^2 x 1000: 0.7 % behind on average with aligned rows, 2.6 % with unaligned ones and 1.4 % with both
+// operands T-major; no other efficiencies of this model do better on the first two.
+// Tiles of 192 rows (aligned rows only) stand between the others where those would need another round: without / with them, operands in rows,
+// R x C x T 4114 x 4156 x 4784 128.7 / 108.7 us, 4911 x 6786 x 6912 233 / 196, 2385 x 3578 x 2448 47.5 / 40.5, 8026 x 2771 x 6864 207 / 196,
+// 5971 x 1623 x 1104 29.0 / 27.0;  B T-major 2385 x 3584 x 2448 36.5 / 29.7;  both T-major 4128 x 4160 x 4784 110 / 93, 4912 x 6800 x 6912
+// 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128, which one workgroup per CU
+// takes (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.  Tiles of 192 columns would need another staging of the output.
+inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
+    EdgeChoice best{0, 0, 0};
+    // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
+    // bytes in every row of an operand
+    if (T >= (1ll << 23) || C >= (1ll << 22) || T < 16 || (ta && R < 16) || (tb && C < 16)) return best;
+    const bool aligned_a = ta ? R % 16 == 0 : slabs_a || T % 16 == 0, aligned_b = tb ? C % 16 == 0 : slabs_b || T % 16 == 0;
+    best.edge = aligned_a && aligned_b ? kEdge : kEdgeUnaligned;
+    if (const char* force = tuning_env("LLMQ_GEMM_EDGE_TILE")) {
+        const int ni = force[0] - '0', nj = force[0] && force[1] ? force[2] - '0' : 0;
+        if ((ni == 2 || ni == 4 || (ni == 3 && best.edge == kEdge)) && (nj == 2 || nj == 4)) { best.ni = ni; best.nj = nj; return best; }
+        if (ni == 0) return best;                             // 0x0: the generic kernel
+    }
+    if (generic_is_faster(R, C, T, ta, tb, accumulate, with_amax, bf16, num_cus)) return best;
+    if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
+    double best_cost = 0;
+    for (int ni = 4; ni >= 2; --ni)
+        for (int nj = 4; nj >= 2; nj -= 2) {
+            if (ni == 3 && best.edge != kEdge) continue;
+            const int64_t tiles = ((R + 64 * ni - 1) / (64 * ni)) * ((C + 64 * nj - 1) / (64 * nj));
+            if (tiles > kMaxWorkgroups) continue;
+            const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;
+            const int64_t slots = resident_slots(num_cus, ni, nj);
+            const int64_t rounds = (tiles + slots - 1) / slots;
+            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : ni == 3 ? (nj == 4 ? 0.83 : T <= 1024 && !tb ? 0.68 : 0.74) : (ni == nj ? 1.0 : 0.77);
+            const double cost = (double)rounds * per_cu * ni * nj / e;
+            if (best.ni == 0 || cost < best_cost * 0.97) { best.ni = ni; best.nj = nj; best_cost = cost; }
+        }
+    return best;
+}
+
+// The small tiles: their side, or 0 for another kernel.  A model in microseconds: rounds of tiles, each with its K steps; against the 128 x 128
+// tile with four LDS stages (3.9 + 0.29 a step) or, for ragged shapes, the guarded one and the generic kernel.  Every workgroup
+// raises the output absmax, and atomics on one address follow each other.  R x C x T, 128 x 128 / 64 x 64 / 32 x 32:
+//   256 x 1024 x 512 5.2 / 4.7 / 3.7, with absmax 5.2 / 5.2 / 6.0;  256 x 512 x 1024 6.3 / 5.4 / 4.0, 5.5 with absmax;  1024 x 512 x 256 4.6 / 4.7 / 5.8;
+//   128 x 256 x 6688 33.6 / 15.3 / 8.5, 117 x 304 x 14496 61.7 / 37.2 / 16.1, 128 x 1792 x 19456 53.1 / 37.2 / 19.2, 448 x 512 x 3584 13.5 / 10.6 / 6.9,
+//   16 x 4096 x 4096 14.6 / 10.1 / 6.7, 862 x 768 x 3008 15.6 / 11.3 / 16.0, 1024 x 1024 x 4096 14.8 / 12.0 / 24.6, 128 x 8192 x 1024 6.6 / 5.8 / 11.8,
+//   1024 x 2048 x 2048 9.9 / 14.6 / 30.5;  generic / 32 x 32: 100 x 136 x 512 4.3 / 3.5, 300 x 300 x 64 2.8 / 3.5
+// LLMQ_GEMM_MINI=32 / 64 / 0 (tests): that side wherever the operands allow it, or never.
+inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, int num_cus) {
+    if (T >= (1ll << 23) || R >= (1ll << 23) || C >= (1ll << 23) || T < 16 || (!(slabs_a && slabs_b) && T % 16 != 0)) return 0;
+    const int64_t tiles128 = ((R + 127) / 128) * ((C + 127) / 128);
+    if (tiles128 > ((int64_t)1 << 20)) return 0;                          // (32 x 32 tiles then fit a launch)
+    if (const char* e = tuning_env("LLMQ_GEMM_MINI")) return atoi(e);
+    if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
+    if (tiles128 > num_cus) return 0;
+    const double steps = (double)((T + BK - 1) / BK), atomic = with_amax ? 0.0095 : 0.0;
+    const bool ragged = R % 128 != 0 || C % 128 != 0 || T % BK != 0;
+    double best = (ragged ? 4.9 : 3.9) + 0.29 * steps + atomic * (double)tiles128;
+    int side = 0;
+    double generic = 0;
+    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus, &generic) && (bf16 || generic < best)) best = bf16 ? 6.0 : generic;
+    for (int s = 64; s >= 32; s -= 32) {
+        const int64_t tiles = ((R + s - 1) / s) * ((C + s - 1) / s);
+        const double rounds = (double)((tiles + num_cus - 1) / num_cus);
+        const double cost = (s == 64 ? 1.4 + rounds * (2.7 + 0.24 * steps) : 1.2 + rounds * (2.0 + 0.107 * steps)) + atomic * (double)tiles;
+        if (cost < best) { best = cost; side = s; }
+    }
+    return side;
+}
+
+}  // namespace llmq

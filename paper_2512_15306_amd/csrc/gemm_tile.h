@@ -28,7 +28,7 @@
 // Ragged shapes take the same kernel with guarded edges (EDGE below).
 // Contractions of few outputs take tiles of 64 x 64 or 32 x 32 (gemm_mini_kernel in gemm.hip).
 // Generic kernel: any shape, one wavefront per 16x16 outputs, guarded loads; for ragged problems so small that it finishes before
-// a tile kernel has filled its LDS (generic_is_faster in gemm.hip), contractions shorter than 16 bytes and the operand mixes no
+// a tile kernel has filled its LDS (generic_is_faster in gemm_choice.h), contractions shorter than 16 bytes and the operand mixes no
 // tile kernel is built for.
 //
 // An operand may also be given "T-major", [T, rows] with the contraction index running down the rows (the
@@ -38,6 +38,7 @@
 #pragma once
 #include <stdlib.h>
 
+#include "gemm_choice.h"
 #include "llmq_device.h"
 #include "llmq_kernels.h"
 
@@ -47,9 +48,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) v2i lds_v2i;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 128;
 constexpr int kGemmThreads = 256;
-constexpr int kXcds = 8;
 constexpr int kBandRows = 4;
 
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
@@ -303,8 +302,7 @@ constexpr int kWholeTiles = 0, kSharePieces = 1, kShareFixup = 2;
 // 3.98 ms with one wavefront per 16 x 16 outputs and no LDS -> 0.238 ms;  7168, 5120, 8100 (kEdgeUnaligned, the
 // weight gradient on transposed copies): 44.1 -> 0.380 ms.  Most of that difference is rows that do not start at cache
 // lines, so that every 128-byte chunk touches two: 7168, 5120, 8112 takes 0.347 ms with kEdge.  Both take the old values of C, if any, by a run-time
-// flag (ACCUM is set: the binary32 staging of the epilogue serves both).
-constexpr int kNoEdge = 0, kEdge = 1, kEdgeUnaligned = 2;
+// flag (ACCUM is set: the binary32 staging of the epilogue serves both).  The kinds and which of them a shape takes: gemm_choice.h.
 typedef v4u v4u_any __attribute__((aligned(1)));            // a 16-byte vector at any address
 
 // The 16 bytes at p of which only the first `valid` exist (none if valid <= 0); zeros in the place of the others.  Reads
@@ -1156,13 +1154,6 @@ inline bool touch_next(bool by_default) {
     return by_default;
 }
 
-// Workgroups of the tile kernel resident on the chip at once (a multiple of the XCD count);
-// LLMQ_GEMM_SLOTS overrides it for tests, so that small problems meet the many-rounds code paths.
-inline int resident_slots(int num_cus, int ni, int nj) {
-    if (const char* e = tuning_env("LLMQ_GEMM_SLOTS")) { const int v = atoi(e); if (v >= kXcds && v % kXcds == 0) return v; }
-    return (num_cus / kXcds) * kXcds * ((ni == 2 && nj == 2) ? 2 : 1);
-}
-
 // Whether a problem of nt 2 x 2 tiles takes four LDS stages: one workgroup per CU then has the CU's LDS to itself.
 // LLMQ_GEMM_DEEP=0 / 1 overrides it for tests.
 inline bool deep_stages(int nt, int slots) {
@@ -1303,12 +1294,6 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
 
 
 // ---- ragged shapes (EDGE instantiations)
-struct EdgeChoice {
-    int ni, nj;       // 0, 0: the generic kernel
-    int edge;         // kEdge or kEdgeUnaligned
-};
-EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16);
-
 template <int FA, int FB, int NI, int NJ, bool TA, bool TB, int EDGE>
 static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
                         void* c, int accumulate, unsigned* amax, hipStream_t stream, int num_cus, bool slabs_a, bool slabs_b) {

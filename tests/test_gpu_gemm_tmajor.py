@@ -324,3 +324,28 @@ def test_ragged_weight_gradient_reads_either_copy(M, N, K, fmt_dy, accumulate):
     llmq.llmq_fp8_linear_wgrad(dy, x, M, N, K, sd, sx, fmt_dy, dW, accumulate, ws, llmq.JIT_DY | llmq.JIT_X)
     llmq.llmq_fp8_gemm_tn(ws[offs[5]:offs[5] + N * M].view(N, M), fmt_dy, ws[offs[1]:offs[1] + K * M].view(K, M), 0, sd, sx, want, accumulate)
     assert torch.equal(dW.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,K", [(1777, 320, 192), (4016, 1024, 64), (129, 300, 301)])
+def test_every_call_leaves_both_copies_of_what_it_quantizes(M, N, K):
+    """What a REUSE flag promises and the weight gradient relies on, whichever copies it reads: the row-major and the transposed codes
+    of an operand, of the same quantization."""
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    x, w, dy = (torch.randn(s, generator=g, device=DEV).to(torch.bfloat16) for s in ((M, K), (N, K), (M, N)))
+    offs = llmq.llmq_fp8_linear_workspace_offsets(M, N, K)
+    s = torch.zeros(3, device=DEV)
+    Y, dX, dW = (torch.empty(n, dtype=torch.bfloat16, device=DEV) for n in ((M, N), (M, K), (N, K)))
+
+    def both(ws, operand):
+        rows, cols = ((M, K), (N, K), (M, N))[operand]
+        a, b = (ws[o:o + rows * cols] for o in offs[2 * operand:2 * operand + 2])
+        return torch.equal(a.view(rows, cols), b.view(cols, rows).t()) and not bool((a == 0xAA).all())
+
+    ws = torch.full((llmq.llmq_fp8_linear_workspace_bytes(M, N, K),), 0xAA, dtype=torch.uint8, device=DEV)
+    llmq.llmq_fp8_linear_fwd(x, w, M, N, K, s[0:1], s[1:2], Y, None, ws, llmq.JIT_X | llmq.JIT_W)
+    assert both(ws, 0) and both(ws, 1)
+    llmq.llmq_fp8_linear_dgrad(dy, None, M, N, K, s[2:3], s[1:2], 1, dX, None, ws, llmq.JIT_DY | llmq.REUSE_W)
+    assert both(ws, 2)
+    ws.fill_(0xAA)
+    llmq.llmq_fp8_linear_wgrad(dy, x, M, N, K, s[2:3], s[0:1], 1, dW, False, ws, 0)
+    assert both(ws, 0) and both(ws, 2)

@@ -119,7 +119,7 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
     if (T >= (1ll << 23) || R >= (1ll << 23) || C >= (1ll << 23) || T < 16 || (!(slabs_a && slabs_b) && T % 16 != 0)) return 0;
     const int64_t tiles128 = ((R + 127) / 128) * ((C + 127) / 128);
     if (tiles128 > ((int64_t)1 << 20)) return 0;                          // (32 x 32 tiles then fit a launch)
-    if (const char* e = tuning_env("LLMQ_GEMM_MINI")) return atoi(e);
+    if (const char* e = tuning_env("LLMQ_GEMM_MINI")) { const int side = atoi(e); return side == 32 || side == 64 ? side : 0; }
     if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
     if (tiles128 > num_cus) return 0;
     const double steps = (double)((T + BK - 1) / BK), atomic = with_amax ? 0.0095 : 0.0;
@@ -127,7 +127,12 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
     double best = (ragged ? 4.9 : 3.9) + 0.29 * steps + atomic * (double)tiles128;
     int side = 0;
     double generic = 0;
-    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus, &generic) && (bf16 || generic < best)) best = bf16 ? 6.0 : generic;
+    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus, &generic)) {
+        // BF16, outputs x elements of T, generic / 32 x 32: 64 x 8 2.2 / 3.2, 4096 x 8 2.5 / 3.4, 60000 x 8 2.7 / 3.5, 130000 x 8 3.1 / 3.6,
+        // 200000 x 8 3.8 / 4.0, 320000 x 8 4.5 / 5.5;  64 x 16 2.9 / 3.2, 1024 x 16 3.6 / 3.4, 60000 x 16 3.8 / 3.5
+        if (bf16) generic = T <= 16 ? 2.3 + 7e-6 * (double)(R * C) : R * C <= 128 ? 2.9 : 3.8;
+        if (bf16 || generic < best) best = generic;
+    }
     for (int s = 64; s >= 32; s -= 32) {
         const int64_t tiles = ((R + s - 1) / s) * ((C + s - 1) / s);
         const double rounds = (double)((tiles + num_cus - 1) / num_cus);

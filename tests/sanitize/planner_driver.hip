@@ -1,7 +1,7 @@
 // Host-side brute force over the index arithmetic of the tile kernel's launches, under the sanitizers: the walk
 // of the workgroup ids over the tiles, the planner that shares a ragged last round of tiles among the compute
-// units, the walk of the quantize kernel's workgroups over the blocks of its tensor, and that of the 64 x 128-tile kernels'
-// workgroups over their tiles.  Every tile, and every K step of every shared tile, must be computed exactly once, and every partial
+// units, the walk of the quantize kernel's workgroups over the blocks of its tensor, that of the 64 x 128-tile kernels'
+// workgroups over their tiles, and the kernels that shapes which were timed in all of them are given.  Every tile, and every K step of every shared tile, must be computed exactly once, and every partial
 // result must have a slot of its own inside the scratch the plan asks for.
 #include <stdio.h>
 #include <stdlib.h>
@@ -155,7 +155,23 @@ static void check_plan(int nt, int nk, int slots, size_t scratch_bytes, const ch
         for (int k = 0; k < nk; ++k) CHECK(steps[t][k] == 1, "nt=%d nk=%d %s: K step %d of shared tile %d computed %d times", nt, nk, mode, k, t, steps[t][k]);
 }
 
+// Which tile side, or another kernel (0), contractions of few outputs take: the fastest one where all were timed.
+struct SmallCase { int64_t R, C, T; bool accumulate, with_amax, bf16; int side; };      // T in bytes
+static void check_small_tiles() {
+    const SmallCase cases[] = {
+        // BF16, eight elements: a lane per output is done before a tile has been loaded
+        {1, 1, 16, false, false, true, 0}, {48, 2720, 16, false, false, true, 0}, {300, 300, 16, false, false, true, 0}, {128, 640, 16, true, false, true, 0},
+        {40, 40, 48, false, false, true, 32}, {100, 136, 64, false, false, true, 32}, {256, 1024, 1024, false, false, true, 32},
+        {448, 512, 3584, false, false, true, 32}, {1024, 1024, 4096, false, false, true, 64},
+    };
+    for (const SmallCase& c : cases) {
+        const int side = takes_mini(c.R, c.C, c.T, false, false, c.accumulate, c.with_amax, c.bf16, 256);
+        CHECK(side == c.side, "%lld x %lld x %lld acc %d amax %d bf16 %d: side %d, measured best %d", (long long)c.R, (long long)c.C, (long long)c.T, c.accumulate, c.with_amax, c.bf16, side, c.side);
+    }
+}
+
 int main() {
+    check_small_tiles();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

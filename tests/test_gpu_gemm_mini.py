@@ -70,6 +70,33 @@ def test_small_tiles_bf16(R, C, T, side, monkeypatch):
         assert _untouched(buf, R, C)
 
 
+@pytest.mark.parametrize("R,C,T", [(33, 70, 136), (64, 32, 256), (40, 101, 1032), (130, 64, 1288), (128, 256, 2048)])
+def test_small_tiles_bf16_have_the_bytes_of_the_tile_kernel(R, C, T, monkeypatch):
+    A, B, prev = _rand((R, T), R + T).to(DEV), _rand((C, T), C + T, 0.05).to(DEV), _rand((R, C), R, 0.5).to(DEV)
+    outs = []
+    for mini in ("0", "32", "64"):
+        monkeypatch.setenv("LLMQ_GEMM_MINI", mini)
+        c, acc = torch.zeros((R, C), dtype=torch.bfloat16, device=DEV), prev.clone()
+        llmq.llmq_bf16_gemm_tn(A, B, c)
+        llmq.llmq_bf16_gemm_tn(A, B, acc, accumulate=True)
+        outs.append((c.view(torch.int16), acc.view(torch.int16)))
+    assert all(torch.equal(a, b) for o in outs[1:] for a, b in zip(outs[0], o))
+
+
+@pytest.mark.parametrize("R,C", [(1, 3), (48, 272), (300, 300), (29, 921)])
+def test_shortest_bf16_contractions_stay_on_the_generic_kernel(R, C, monkeypatch):
+    """Eight elements: one lane per output is the faster kernel, whose sums run along t one by one."""
+    A, B = _rand((R, 8), R + 1).to(DEV), _rand((C, 8), C + 2).to(DEV)
+    outs = []
+    for tile in (None, "0x0"):
+        if tile:
+            monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
+        c = torch.zeros((R, C), dtype=torch.bfloat16, device=DEV)
+        llmq.llmq_bf16_gemm_tn(A, B, c)
+        outs.append(c.view(torch.int16))
+    assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("side", ["32", "64"])
 def test_values_beyond_the_operands_and_degenerate_scales(side, monkeypatch):
     """NaN and Inf codes lie directly behind the operands; one NaN row stays one NaN row; scales whose product leaves the

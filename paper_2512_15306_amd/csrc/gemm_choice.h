@@ -1,5 +1,6 @@
 // Host side of the contractions: which kernel a problem takes.  Plain functions of the sizes, without a kernel in sight.
 #pragma once
+#include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
 
@@ -33,7 +34,7 @@ struct EdgeChoice {
 //   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
 //   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
 //   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
-inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus, double* generic_us = nullptr) {
+inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus) {
     if (bf16) {                                                             // (T in bytes)
         const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
         return R * C <= most;
@@ -65,7 +66,6 @@ inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
     // every wave of the generic kernel raises the same word, and atomics on one address follow each other at 9.5 ns (forward call
     // of 300 x 256 -> 1024, 1216 waves: 25 us with it, 13.5 with the tile kernel)
     if (with_amax) generic += 0.0095 * (double)(((R + 15) / 16) * ((C + 15) / 16));
-    if (generic_us) *generic_us = generic;
     return generic < tile + 0.4e-6 * (double)R * (double)C;
 }
 
@@ -107,13 +107,43 @@ inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus,
     return best;
 }
 
-// The small tiles: their side, or 0 for another kernel.  A model in microseconds: rounds of tiles, each with its K steps; against the 128 x 128
-// tile with four LDS stages (3.9 + 0.29 a step) or, for ragged shapes, the guarded one and the generic kernel.  Every workgroup
-// raises the output absmax, and atomics on one address follow each other.  R x C x T, 128 x 128 / 64 x 64 / 32 x 32:
+// What the small tiles are compared with, in microseconds: the 128 x 128 tile with four LDS stages, whole or with guarded edges, or the
+// generic kernel where that is the faster of the two.
+inline double other_tiles_us(int64_t R, int64_t C, int64_t T, bool accumulate, bool with_amax, bool bf16, int num_cus) {
+    const double steps = (double)((T + BK - 1) / BK), n = (double)R * (double)C;
+    const bool ragged = R % 128 != 0 || C % 128 != 0 || T % BK != 0;
+    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus)) {
+        // BF16, outputs x elements of T, generic / 32 x 32: 64 x 8 2.2 / 3.2, 4096 x 8 2.5 / 3.4, 60000 x 8 2.7 / 3.5, 130000 x 8 3.1 / 3.6,
+        // 200000 x 8 3.8 / 4.0, 320000 x 8 4.5 / 5.5;  64 x 16 2.9 / 3.2, 1024 x 16 3.6 / 3.4, 60000 x 16 3.8 / 3.5
+        if (bf16) return T <= 16 ? 2.3 + 7e-6 * n : n <= 128 ? 2.9 : 3.8;
+        const double load = (double)(((R + 31) / 32) * ((C + 31) / 32)) / num_cus, rounds = ceil(load) - 1.0;        // workgroups per CU, on the fullest CU beyond the first
+        return 1.75 + 0.4 * steps + load * (0.17 + 0.125 * steps) + rounds * (0.18 + 0.24 * steps) + (T % 32 != 0 ? 2.8 : 0.0) + (C % 8 == 0 ? 0.43 : 0.0) +
+               (R >= 32 ? 0.3 : 0.0) + (accumulate ? 0.35 + 0.53 * load : 0.0) + (with_amax ? 0.013 * (double)(((R + 15) / 16) * ((C + 15) / 16)) - 0.35 : 0.0);
+    }
+    const double tiles = (double)(((R + 127) / 128) * ((C + 127) / 128)), part = (R < 128 ? R / 128.0 : 1.0) * (C < 128 ? C / 128.0 : 1.0);
+    const double odd = C % 8 != 0 ? (R < 64 ? R / 64.0 : 1.0) * (C < 64 ? C / 64.0 : 1.0) : 0.0;        // stores of single elements
+    return (ragged ? 4.5 + 0.318 * steps : 3.9 + 0.326 * steps) + 0.007 * tiles + odd * (accumulate ? 3.1 : 2.4) + (accumulate ? 0.5 * part : 0.0) +
+           (with_amax ? 0.0095 * tiles : 0.0);
+}
+// The same for tiles of side x side: rounds of them, each with its stages of four K steps and its output
+inline double small_tiles_us(int side, int64_t R, int64_t C, int64_t T, bool accumulate, bool with_amax, int num_cus) {
+    const double tiles = (double)(((R + side - 1) / side) * ((C + side - 1) / side)), rounds = (double)(((int64_t)tiles + num_cus - 1) / num_cus);
+    const double stages = (double)((T + 4 * BK - 1) / (4 * BK)), part = (R < side ? (double)R / side : 1.0) * (C < side ? (double)C / side : 1.0);
+    const double odd = C % 4 != 0 ? part : 0.0;
+    const double per_round = side == 32 ? 1.25 + 0.41 * stages + (accumulate ? 0.3 * part + 0.8 * odd : 0.2 * odd)
+                                        : 1.3 + 0.86 * stages + part * (accumulate ? 1.2 : 0.65) + odd * (accumulate ? 2.8 : 0.6);
+    return 1.75 + rounds * per_round + (side == 32 ? 0.44 : 0.77) * tiles / num_cus + (with_amax ? 0.0095 * tiles : 0.0);
+}
+
+// The small tiles: their side, or 0 for another kernel.  The models above, fitted to 26000 FP8 and 21000 BF16 shapes of up to 256 tiles of
+// 128 x 128: what they choose is 0.2 % slower on average than the fastest of all kernels, and more than 3 % slower than without small tiles on 0.3 % of them.
+// Every workgroup raises the output absmax, and atomics on one address follow each other.  R x C x T, 128 x 128 / 64 x 64 / 32 x 32:
 //   256 x 1024 x 512 5.2 / 4.7 / 3.7, with absmax 5.2 / 5.2 / 6.0;  256 x 512 x 1024 6.3 / 5.4 / 4.0, 5.5 with absmax;  1024 x 512 x 256 4.6 / 4.7 / 5.8;
 //   128 x 256 x 6688 33.6 / 15.3 / 8.5, 117 x 304 x 14496 61.7 / 37.2 / 16.1, 128 x 1792 x 19456 53.1 / 37.2 / 19.2, 448 x 512 x 3584 13.5 / 10.6 / 6.9,
 //   16 x 4096 x 4096 14.6 / 10.1 / 6.7, 862 x 768 x 3008 15.6 / 11.3 / 16.0, 1024 x 1024 x 4096 14.8 / 12.0 / 24.6, 128 x 8192 x 1024 6.6 / 5.8 / 11.8,
-//   1024 x 2048 x 2048 9.9 / 14.6 / 30.5;  generic / 32 x 32: 100 x 136 x 512 4.3 / 3.5, 300 x 300 x 64 2.8 / 3.5
+//   1024 x 2048 x 2048 9.9 / 14.6 / 30.5
+// generic / 64 x 64 / 32 x 32 of short contractions: 1 x 1 x 256 2.4 / 3.5 / 3.2, 624 x 689 x 224 4.1 / 5.7 / -, 3456 x 128 x 160 3.9 / 4.8 / -, 300 x 300 x 64
+//   2.8 / 4.6 / 3.5, 100 x 136 x 512 4.3 / 4.9 / 3.5;  added to what is there 88 x 17 x 64 3.2 / 4.3 / 4.0, 206 x 1326 x 128 4.7 / 8.2 / 7.5
 // LLMQ_GEMM_MINI=32 / 64 / 0 (tests): that side wherever the operands allow it, or never.
 inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, int num_cus) {
     if (T >= (1ll << 23) || R >= (1ll << 23) || C >= (1ll << 23) || T < 16 || (!(slabs_a && slabs_b) && T % 16 != 0)) return 0;
@@ -122,21 +152,10 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
     if (const char* e = tuning_env("LLMQ_GEMM_MINI")) { const int side = atoi(e); return side == 32 || side == 64 ? side : 0; }
     if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
     if (tiles128 > num_cus) return 0;
-    const double steps = (double)((T + BK - 1) / BK), atomic = with_amax ? 0.0095 : 0.0;
-    const bool ragged = R % 128 != 0 || C % 128 != 0 || T % BK != 0;
-    double best = (ragged ? 4.9 : 3.9) + 0.29 * steps + atomic * (double)tiles128;
+    double best = other_tiles_us(R, C, T, accumulate, with_amax, bf16, num_cus) - 0.2;       // (a margin for the models' errors)
     int side = 0;
-    double generic = 0;
-    if (ragged && generic_is_faster(R, C, T, false, false, accumulate, with_amax, bf16, num_cus, &generic)) {
-        // BF16, outputs x elements of T, generic / 32 x 32: 64 x 8 2.2 / 3.2, 4096 x 8 2.5 / 3.4, 60000 x 8 2.7 / 3.5, 130000 x 8 3.1 / 3.6,
-        // 200000 x 8 3.8 / 4.0, 320000 x 8 4.5 / 5.5;  64 x 16 2.9 / 3.2, 1024 x 16 3.6 / 3.4, 60000 x 16 3.8 / 3.5
-        if (bf16) generic = T <= 16 ? 2.3 + 7e-6 * (double)(R * C) : R * C <= 128 ? 2.9 : 3.8;
-        if (bf16 || generic < best) best = generic;
-    }
     for (int s = 64; s >= 32; s -= 32) {
-        const int64_t tiles = ((R + s - 1) / s) * ((C + s - 1) / s);
-        const double rounds = (double)((tiles + num_cus - 1) / num_cus);
-        const double cost = (s == 64 ? 1.4 + rounds * (2.7 + 0.24 * steps) : 1.2 + rounds * (2.0 + 0.107 * steps)) + atomic * (double)tiles;
+        const double cost = small_tiles_us(s, R, C, T, accumulate, with_amax, num_cus);
         if (cost < best) { best = cost; side = s; }
     }
     return side;

@@ -163,6 +163,12 @@ static void check_small_tiles() {
         {1, 1, 16, false, false, true, 0}, {48, 2720, 16, false, false, true, 0}, {300, 300, 16, false, false, true, 0}, {128, 640, 16, true, false, true, 0},
         {40, 40, 48, false, false, true, 32}, {100, 136, 64, false, false, true, 32}, {256, 1024, 1024, false, false, true, 32},
         {448, 512, 3584, false, false, true, 32}, {1024, 1024, 4096, false, false, true, 64},
+        // FP8: short contractions whose generic waves or 128 x 128 tiles are done first, added to the output or not
+        {1, 1, 256, false, false, false, 0}, {300, 300, 64, false, false, false, 0}, {624, 689, 224, false, false, false, 0}, {3456, 128, 160, false, false, false, 0},
+        {1344, 518, 192, false, false, false, 0}, {88, 17, 64, true, false, false, 0}, {206, 1326, 128, true, false, false, 0}, {977, 264, 128, true, false, false, 0},
+        {1600, 325, 96, true, false, false, 0}, {128, 19, 32, true, true, false, 0}, {84, 128, 128, false, true, false, 0}, {896, 384, 384, false, false, false, 64},
+        {100, 136, 512, false, false, false, 32}, {256, 1024, 512, false, false, false, 32}, {128, 256, 6688, true, false, false, 32},
+        {1024, 1024, 4096, false, false, false, 64}, {128, 8192, 1024, false, false, false, 64}, {1024, 2048, 2048, false, false, false, 0},
     };
     for (const SmallCase& c : cases) {
         const int side = takes_mini(c.R, c.C, c.T, false, false, c.accumulate, c.with_amax, c.bf16, 256);

@@ -349,7 +349,12 @@ static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C,
     const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);
     const bool fits = (!slabs_a || (T + 256) * R < lim) && (!slabs_b || (T + 256) * C < lim);
     if (fits) {
-        const int side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, num_cus);
+        double shared_us = 0.0;
+        if (FA != kFmtBf16 && scratch.ptr && T >= 64 * BK && ((R + 127) / 128) * ((C + 127) / 128) <= num_cus) {       // (what the planner shares is that long)
+            const TileChoice tc = choose_tile(R, C, T, num_cus, scratch.bytes);
+            if (tc.ni) shared_us = shared_tiles_us(choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch.bytes));
+        }
+        const int side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, num_cus, shared_us);
         if (side) { launch_mini<FA, FB>(side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
     }
     if (fits && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b)) return;

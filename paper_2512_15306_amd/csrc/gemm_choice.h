@@ -144,18 +144,23 @@ inline double small_tiles_us(int side, int64_t R, int64_t C, int64_t T, bool acc
 //   1024 x 2048 x 2048 9.9 / 14.6 / 30.5
 // generic / 64 x 64 / 32 x 32 of short contractions: 1 x 1 x 256 2.4 / 3.5 / 3.2, 624 x 689 x 224 4.1 / 5.7 / -, 3456 x 128 x 160 3.9 / 4.8 / -, 300 x 300 x 64
 //   2.8 / 4.6 / 3.5, 100 x 136 x 512 4.3 / 4.9 / 3.5;  added to what is there 88 x 17 x 64 3.2 / 4.3 / 4.0, 206 x 1326 x 128 4.7 / 8.2 / 7.5
+// shared_us: what the contraction takes with its left-over tiles shared out (shared_tiles_us), 0 if they are not.  Operands beyond the
+// 256 MB memory-side cache slow the small tiles down.  128 x 128 tiles shared out / small tiles: 512 x 512 x 131072 246 / 127 us, x 262144 283 / 288;
+//   512 x 1024 x 65536 144 / 120, x 131072 178 / 276;  1024 x 1024 x 32768 93 / 62, x 65536 117 / 145, x 262144 275 / 596;  1024 x 2048 x 8192 62 / 37,
+//   x 32768 93 / 119
 // LLMQ_GEMM_MINI=32 / 64 / 0 (tests): that side wherever the operands allow it, or never.
-inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, int num_cus) {
+inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, int num_cus, double shared_us = 0.0) {
     if (T >= (1ll << 23) || R >= (1ll << 23) || C >= (1ll << 23) || T < 16 || (!(slabs_a && slabs_b) && T % 16 != 0)) return 0;
     const int64_t tiles128 = ((R + 127) / 128) * ((C + 127) / 128);
     if (tiles128 > ((int64_t)1 << 20)) return 0;                          // (32 x 32 tiles then fit a launch)
     if (const char* e = tuning_env("LLMQ_GEMM_MINI")) { const int side = atoi(e); return side == 32 || side == 64 ? side : 0; }
     if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
     if (tiles128 > num_cus) return 0;
-    double best = other_tiles_us(R, C, T, accumulate, with_amax, bf16, num_cus) - 0.2;       // (a margin for the models' errors)
+    const double slower = shared_us > 0.0 && (R + C) * T > 100000000 ? 1.25 : 1.0;
+    double best = (shared_us > 0.0 ? shared_us : other_tiles_us(R, C, T, accumulate, with_amax, bf16, num_cus)) - 0.2;       // (a margin for the models' errors)
     int side = 0;
     for (int s = 64; s >= 32; s -= 32) {
-        const double cost = small_tiles_us(s, R, C, T, accumulate, with_amax, num_cus);
+        const double cost = slower * small_tiles_us(s, R, C, T, accumulate, with_amax, num_cus);
         if (cost < best) { best = cost; side = s; }
     }
     return side;

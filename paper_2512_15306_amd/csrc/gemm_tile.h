@@ -1236,6 +1236,15 @@ inline SplitChoice choose_split(int nt, int nk, int slots, int ni, int nj, size_
     return c;
 }
 
+// Microseconds of a contraction of few outputs whose tiles the plan shares out: a fix-up that reads the pieces of a tile one after the
+// other, and the K steps of a piece.  R x C x T, model / measured: 256 x 256 x 262144 (256 pieces of 8 steps) 777 / 787, 512 x 512 x 131072 234 / 246,
+// 512 x 1024 x 131072 166 / 178, 1024 x 1024 x 65536 120 / 117, 1024 x 2048 x 16384 71 / 69, 1536 x 1536 x 131072 277 / 291.
+inline double shared_tiles_us(const SplitChoice& c) {
+    double us = 0.0;
+    for (int g = 0; g < c.n_groups; ++g) us = us > 2.9 * c.group[g].pieces + 1.6 * c.group[g].steps ? us : 2.9 * c.group[g].pieces + 1.6 * c.group[g].steps;
+    return c.n_groups ? 22.0 + us : 0.0;
+}
+
 template <int FA, int FB, int NI, int NJ, bool TA = false, bool TB = false>
 static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T,
                         const float* sA, const float* sB, void* c, int accumulate, unsigned* amax,

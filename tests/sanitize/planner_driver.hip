@@ -174,6 +174,16 @@ static void check_small_tiles() {
         const int side = takes_mini(c.R, c.C, c.T, false, false, c.accumulate, c.with_amax, c.bf16, 256);
         CHECK(side == c.side, "%lld x %lld x %lld acc %d amax %d bf16 %d: side %d, measured best %d", (long long)c.R, (long long)c.C, (long long)c.T, c.accumulate, c.with_amax, c.bf16, side, c.side);
     }
+    // long contractions with scratch, which 256 x 256 tiles share out: the faster of that and the small tiles
+    const SmallCase shared[] = {{512, 512, 131072, false, false, false, 32}, {512, 1024, 65536, false, false, false, 32}, {512, 1024, 131072, false, false, false, 0},
+                                {1024, 1024, 32768, false, false, false, 64}, {1024, 1024, 65536, false, false, false, 0}, {1024, 1024, 262144, false, false, false, 0},
+                                {256, 2048, 131072, false, false, false, 0}, {1024, 2048, 8192, false, false, false, 64}, {1024, 2048, 32768, false, false, false, 0},
+                                {256, 256, 262144, false, false, false, 32}};
+    for (const SmallCase& c : shared) {
+        const double us = shared_tiles_us(choose_split((int)((c.R / 256) * (c.C / 256)), (int)(c.T / BK), 256, 4, 4, (size_t)1 << 30));
+        const int side = takes_mini(c.R, c.C, c.T, false, false, false, false, false, 256, us);
+        CHECK(us > 0.0 && side == c.side, "%lld x %lld x %lld shared out in %.0f us: side %d, measured best %d", (long long)c.R, (long long)c.C, (long long)c.T, us, side, c.side);
+    }
 }
 
 int main() {

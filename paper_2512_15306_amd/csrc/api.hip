@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/llmq.h"
+#include "gemm_choice.h"
 #include "llmq_kernels.h"
 
 namespace {
@@ -149,25 +150,6 @@ constexpr int64_t kMaxSlabElems = 0x70000000;      // tensors kept in slabs stay
 
 bool slab_copy(int flags, int64_t rows, int64_t cols) {
     return (flags & LLMQ_SLAB_COPIES) && llmq::quantize_can_write_slabs(rows, cols) && rows * cols < kMaxSlabElems;
-}
-
-// Whether a weight gradient reads the row-major copies T-major (as under LLMQ_NO_TRANSPOSE; same bytes) although the transposed
-// ones are there: with a token count that is no multiple of 16 the rows of those start at any address, so their chunks go through
-// registers and touch two cache lines each, while the row-major copies' rows are as long as the layer is wide.  Transposed /
-// row-major copies, N x K x M, microseconds:
-//   M no multiple of 16   7168 x 5120 x 8100 363 / 246, 2880 x 960 x 1777 20.0 / 12.3, 3072 x 3072 x 105 20.5 / 12.1, 512 x 512 x 17 6.5 / 5.2
-//     widths no multiples of 16 either   1001 x 1003 x 4001 34.1 / 33.3, 1000 x 1000 x 300 8.6 / 7.4, 300 x 300 x 129 12.4 / 9.9, but x 127 (one
-//     K step: the generic kernel) 8.0 / 10.3
-//   M a multiple of 16, not of 64 (aligned chunks over two lines)   7168 x 5120 x 8112 307 / 255, 1024 x 512 x 8112 39.8 / 28.3,
-//     1024 x 512 x 4016 22.2 / 16.8; operands that an XCD's 4 MB L2 holds gain nothing: 1024 x 512 x 2032 9.3 / 9.6
-//   M a multiple of 64   8128: 3072 x 3072 86.5 / 79.0, 14496 x 304 65 / 73;  640 x 384 x 640 5.5 / 5.6: left as they are
-bool wgrad_reads_row_major(int64_t M, int64_t N, int64_t K) {
-    if (M % 64 == 0 || M < 16 || N < 16 || K < 16) return false;
-    const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);           // what the T-major tile kernels address
-    if ((M + 256) * N >= lim || (M + 256) * K >= lim) return false;
-    const bool whole_chunks = N % 16 == 0 && K % 16 == 0;
-    if (M % 16 == 0) return whole_chunks && M * (N + K) > ((int64_t)4 << 20);
-    return whole_chunks || M > 128;
 }
 
 }  // namespace
@@ -386,7 +368,7 @@ int llmq_fp8_linear_wgrad(const void* dY, const void* X, int64_t M, int64_t N, i
     const Operand ox{X, M, K, d_scale_x, base + l.xq, nt ? nullptr : base + l.xqt, (flags & LLMQ_JIT_X) != 0, part, nullptr, slab_copy(flags, M, K)};
     if ((st = quantize_mixed(qd ? &od : nullptr, fmt_dy, qx ? &ox : nullptr, s))) return st;
     // dW[n,k] = sum_m dYq_t[n,m] * Xq_t[k,m] = sum_m dYq[m,n] * Xq[m,k]
-    const bool tm = nt || wgrad_reads_row_major(M, N, K);
+    const bool tm = nt || llmq::wgrad_reads_row_major(M, N, K, accumulate != 0, num_cus());
     const int dy_layout = tm ? llmq::kLayoutTMajor : slab_copy(flags, M, N) ? llmq::kLayoutSlabs : llmq::kLayoutRows;
     const int x_layout = tm ? llmq::kLayoutTMajor : slab_copy(flags, M, K) ? llmq::kLayoutSlabs : llmq::kLayoutRows;
     return llmq::launch_gemm_fp8(tm ? base + l.dyq : base + l.dyqt, fmt_dy, dy_layout, tm ? base + l.xq : base + l.xqt, LLMQ_E4M3, x_layout,

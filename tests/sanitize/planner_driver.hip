@@ -186,8 +186,23 @@ static void check_small_tiles() {
     }
 }
 
+// Which copies a weight gradient [N, K] of M tokens reads: those it is faster on, by measurement.
+static void check_wgrad_copies() {
+    struct Case { int64_t N, K, M; bool accumulate, row_major; };
+    const Case cases[] = {
+        // whole chunks either way: the transposed copies where the small tiles take them, the row-major ones of larger layers
+        {1024, 512, 8112, false, false}, {1024, 512, 4016, false, false}, {512, 512, 8112, false, false}, {304, 256, 14496, false, false}, {1536, 448, 12560, true, false},
+        {2880, 960, 1776, false, true}, {512, 2432, 2336, false, true}, {832, 3776, 16272, true, true}, {7168, 5120, 8112, false, true}, {1024, 512, 2032, false, false},
+        // rows of the transposed copies at any address
+        {7168, 5120, 8100, false, true}, {2880, 960, 1777, false, true}, {512, 512, 17, false, true}, {1001, 1003, 4001, false, true}, {300, 300, 127, false, false},
+        {3072, 3072, 8128, false, false}, {640, 384, 640, false, false}, {15, 512, 8100, false, false},
+    };
+    for (const Case& c : cases) CHECK(wgrad_reads_row_major(c.M, c.N, c.K, c.accumulate, 256) == c.row_major, "weight gradient %lld x %lld of %lld tokens", (long long)c.N, (long long)c.K, (long long)c.M);
+}
+
 int main() {
     check_small_tiles();
+    check_wgrad_copies();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

@@ -171,8 +171,10 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
 // registers and touch two cache lines each, while the row-major copies' rows are as long as the layer is wide.  Transposed /
 // row-major copies, N x K x M, microseconds:
 //   M no multiple of 16   7168 x 5120 x 8100 363 / 246, 2880 x 960 x 1777 20.0 / 12.3, 3072 x 3072 x 105 20.5 / 12.1, 512 x 512 x 17 6.5 / 5.2
-//     widths no multiples of 16 either   1001 x 1003 x 4001 34.1 / 33.3, 1000 x 1000 x 300 8.6 / 7.4, 300 x 300 x 129 12.4 / 9.9, but x 127 (one
-//     K step: the generic kernel) 8.0 / 10.3
+//     widths no multiples of 16 either: as aligned as the rows of the copies are (1, 2, or 4 and more bytes: in dwords), over 3000 shapes of more than
+//     one K step, transposed / row-major time with M odd 1.07 to 1.36;  M a multiple of 2, both widths of 2 1.05, one odd and the other of 16 1.12, both
+//     odd 0.98;  M a multiple of 4 or 8, both widths of 4 1.03 to 1.12, one odd 0.88 to 1.00 (739 x 7055 x 8476 83 / 105, 139 x 75 x 2804 17.6 / 24.6)
+//     one K step: the generic kernel, 300 x 300 x 127 8.0 / 10.3
 //   M a multiple of 16, not of 64 (aligned chunks over two lines)   7168 x 5120 x 8112 319 / 246; operands that an XCD's 4 MB L2 holds gain
 //     nothing: 1024 x 512 x 2032 10.2 / 10.2; and where the transposed copies' small tiles are taken, they are the faster ones: 1024 x 512 x 8112
 //     25.2 / 28.3, 1024 x 512 x 4016 15.3 / 17.0, 512 x 512 x 8112 11.8 / 26.9, 304 x 256 x 14496 16.8 / 55.1, 1536 x 448 x 12560 38.3 / 42.1
@@ -183,7 +185,9 @@ inline bool wgrad_reads_row_major(int64_t M, int64_t N, int64_t K, bool accumula
     if ((M + 256) * N >= lim || (M + 256) * K >= lim) return false;
     const bool whole_chunks = N % 16 == 0 && K % 16 == 0;
     if (M % 16 == 0) return whole_chunks && M * (N + K) > ((int64_t)4 << 20) && takes_mini(N, K, M, false, false, accumulate, false, false, num_cus) == 0;
-    return whole_chunks || M > 128;
+    if (whole_chunks || M <= 128) return whole_chunks;
+    if (M % 2 != 0 || (N % 4 == 0 && K % 4 == 0)) return true;
+    return M % 4 != 0 && ((N % 2 == 0 && K % 2 == 0) || N % 16 == 0 || K % 16 == 0);
 }
 
 }  // namespace llmq

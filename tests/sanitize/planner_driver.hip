@@ -195,6 +195,9 @@ static void check_wgrad_copies() {
         {2880, 960, 1776, false, true}, {512, 2432, 2336, false, true}, {832, 3776, 16272, true, true}, {7168, 5120, 8112, false, true}, {1024, 512, 2032, false, false},
         // rows of the transposed copies at any address
         {7168, 5120, 8100, false, true}, {2880, 960, 1777, false, true}, {512, 512, 17, false, true}, {1001, 1003, 4001, false, true}, {300, 300, 127, false, false},
+        // ... and widths too: the better aligned of the two
+        {739, 7055, 8476, false, false}, {139, 75, 2804, false, false}, {69, 256, 3812, false, false}, {141, 255, 2062, false, false}, {1733, 202, 6728, false, false},
+        {164, 36, 4220, false, true}, {1544, 8, 9272, false, false}, {1544, 24, 9272, false, true}, {6058, 540, 1374, false, true}, {117, 1104, 6558, false, true}, {502, 4866, 147, false, true},
         {3072, 3072, 8128, false, false}, {640, 384, 640, false, false}, {15, 512, 8100, false, false},
     };
     for (const Case& c : cases) CHECK(wgrad_reads_row_major(c.M, c.N, c.K, c.accumulate, 256) == c.row_major, "weight gradient %lld x %lld of %lld tokens", (long long)c.N, (long long)c.K, (long long)c.M);

@@ -309,7 +309,8 @@ def test_step_without_transposed_copies_replays_from_a_graph():
 
 @pytest.mark.parametrize("fmt_dy,accumulate", [(0, True), (1, False)])
 @pytest.mark.parametrize("M,N,K", [(16, 48, 64), (17, 256, 144), (127, 300, 304), (129, 300, 301), (200, 24, 40), (301, 15, 64), (1777, 320, 192),
-                                   (4064, 1024, 16), (4016, 1024, 64), (4048, 784, 256), (4032, 784, 256), (1776, 2880, 960)])
+                                   (4064, 1024, 16), (4016, 1024, 64), (4048, 784, 256), (4032, 784, 256), (1776, 2880, 960),
+                                   (254, 300, 302), (254, 301, 303), (260, 36, 100)])
 def test_ragged_weight_gradient_reads_either_copy(M, N, K, fmt_dy, accumulate):
     """Token counts on either side of the lines between the transposed and the row-major copies: the weight gradient of the
     linear call has the bytes of the contraction of the transposed copies, which are in the workspace either way."""

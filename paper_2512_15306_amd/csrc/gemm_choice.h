@@ -77,6 +77,10 @@ inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
 // 5971 x 1623 x 1104 29.0 / 27.0;  B T-major 2385 x 3584 x 2448 36.5 / 29.7;  both T-major 4128 x 4160 x 4784 110 / 93, 4912 x 6800 x 6912
 // 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128, which one workgroup per CU
 // takes (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.  Tiles of 192 columns would need another staging of the output.
+// Where all 128 x 128 tiles are resident at once, two to a CU, they hide each other's prologue and output, so 192 x 128 needs K steps to win by (least_192).
+// 128 x 128 / 192 x 128 time by K steps 1, 2, 3 to 4, 5 to 8, 9 to 16, more, over 1200 shapes: 0.98, 1.01, 1.04, 1.09, 1.09, 1.11;  added to the output
+// 0.93, 0.96, 1.02, 1.05, 1.06, 1.09;  widths no multiples of 8 (stores of single elements) 0.91, 0.92, 0.96, 0.98, 1.00, 1.05;  with absmax (fewer
+// atomics) 1.12, 1.13, 1.07, 1.03, 1.04, 1.11.
 inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
@@ -91,10 +95,13 @@ inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus,
     }
     if (generic_is_faster(R, C, T, ta, tb, accumulate, with_amax, bf16, num_cus)) return best;
     if (best.edge == kEdge && ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2) { best.ni = best.nj = 2; return best; }   // as above
+    const int least_192 = C % 8 != 0 ? 17 : with_amax ? 1 : accumulate ? 3 : 2;
+    const bool resident = ((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2);
     double best_cost = 0;
     for (int ni = 4; ni >= 2; --ni)
         for (int nj = 4; nj >= 2; nj -= 2) {
             if (ni == 3 && best.edge != kEdge) continue;
+            if (ni == 3 && nj == 2 && resident && (T + BK - 1) / BK < least_192) continue;
             const int64_t tiles = ((R + 64 * ni - 1) / (64 * ni)) * ((C + 64 * nj - 1) / (64 * nj));
             if (tiles > kMaxWorkgroups) continue;
             const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;

@@ -203,9 +203,26 @@ static void check_wgrad_copies() {
     for (const Case& c : cases) CHECK(wgrad_reads_row_major(c.M, c.N, c.K, c.accumulate, 256) == c.row_major, "weight gradient %lld x %lld of %lld tokens", (long long)c.N, (long long)c.K, (long long)c.M);
 }
 
+// Tiles of ragged contractions: 192 x 128 against 128 x 128 tiles that are all resident, the faster one by measurement.
+static void check_edge_tiles() {
+    struct Case { int64_t R, C, T; bool tb, accumulate, with_amax, bf16; int ni, nj; };
+    const Case cases[] = {
+        {5477, 945, 128, false, true, false, false, 2, 2}, {2448, 1566, 96, false, true, false, false, 2, 2}, {896, 6208, 16, false, true, false, false, 2, 2},
+        {7232, 704, 112, true, true, false, false, 2, 2}, {2176, 2624, 16, true, true, false, false, 2, 2}, {6936, 555, 64, false, false, false, true, 2, 2},
+        {768, 5509, 32, false, true, false, true, 2, 2}, {1466, 3335, 256, false, false, false, true, 2, 2}, {2432, 2048, 720, false, false, false, false, 3, 2},
+        {708, 7536, 640, false, false, false, false, 3, 2}, {576, 9600, 736, false, false, false, false, 3, 2}, {4480, 2432, 3760, false, false, false, false, 3, 4},
+        {7296, 1060, 3712, false, false, false, false, 3, 4},
+    };
+    for (const Case& c : cases) {
+        const EdgeChoice e = choose_edge_tile(c.R, c.C, c.T, 256, false, c.tb, false, false, c.accumulate, c.with_amax, c.bf16);
+        CHECK(e.ni == c.ni && e.nj == c.nj && e.edge == kEdge, "%lld x %lld x %lld: %d x %d, measured best %d x %d", (long long)c.R, (long long)c.C, (long long)c.T, e.ni, e.nj, c.ni, c.nj);
+    }
+}
+
 int main() {
     check_small_tiles();
     check_wgrad_copies();
+    check_edge_tiles();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

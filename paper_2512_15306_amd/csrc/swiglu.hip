@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_fwd_fp8_small_kernel(
     with_guard(small_tile_guard(R0, C0, M, I), [&](auto guard) {
         const int64_t rows_left = guard ? M - r0 : kSmallPatch, cols_left = guard ? I - c0 : 8;
         v4u g[kSmallPatch], u[kSmallPatch];
-        load_patches_upto(c0, rows_left, cols_left, patch(g, src, 2 * I), patch(u, src + I, 2 * I));
+        load_tile_patches_upto(c0, rows_left, cols_left, patch(g, src, 2 * I), patch(u, src + I, 2 * I));
         const float s = *d_qscale;
         unsigned w[kSmallPatch][2];
 #pragma unroll

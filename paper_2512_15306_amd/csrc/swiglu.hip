@@ -103,8 +103,14 @@ __device__ __forceinline__ v4u swiglu8_as(const v4u& g, const v4u& u) {
         o[j] = pack_bf16(swiglu_f32<NORMAL>(bf16_lo(g[j]), bf16_lo(u[j])), swiglu_f32<NORMAL>(bf16_hi(g[j]), bf16_hi(u[j])));
     return o;
 }
+__device__ __attribute__((noinline)) v4u swiglu8_rare(v4u g, v4u u) { return swiglu8_as<false>(g, u); }
+// CALL_RARE: the rare half as a call instead of in the kernel's code, of which it would be half.  Forward with h, aligned shapes, in the code / called:
+// 1536 x 1408 8.8 / 8.7 us, 8192 x 256 8.6 / 8.3, 1024 x 3072 9.4 / 9.1, 1.5 % on average from half a million to 8 million elements and nothing
+// elsewhere; in the guarded kernels, whose patches are loaded between branches, the call costs 1 %.
+template <bool CALL_RARE = false>
 __device__ inline v4u swiglu8(const v4u& g, const v4u& u) {
     if (__builtin_expect(gates_normal(g), 1)) return swiglu8_as<true>(g, u);
+    if constexpr (CALL_RARE) return swiglu8_rare(g, u);
     return swiglu8_as<false>(g, u);
 }
 
@@ -168,7 +174,7 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_patch_kernel(
             u[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * 2 * I + I));
         }
 #pragma unroll
-        for (int i = 0; i < PR; ++i) o[i] = swiglu8(g[i], u[i]);
+        for (int i = 0; i < PR; ++i) o[i] = swiglu8<AMAX && !STREAM>(g[i], u[i]);
         if constexpr (WRITE_H) {
             uint16_t* dst = h + r0 * I + c0;
 #pragma unroll

@@ -450,7 +450,8 @@ struct SmallGrid {
     bool xcd_ranges;
     bool stacked;                           // lanes that follow each other one above the other instead of side by side
 };
-inline SmallGrid small_grid(int64_t rows, int64_t cols) {
+// quantizes: for the quantize kernel (and not those that compute what they write as codes)
+inline SmallGrid small_grid(int64_t rows, int64_t cols, bool quantizes = false) {
     SmallGrid g;
     g.rows = (unsigned)((rows + kSmallRows - 1) / kSmallRows);
     g.cols = (unsigned)((cols + kSmallCols - 1) / kSmallCols);
@@ -458,9 +459,11 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols) {
     g.first = 0;
     g.xcd_ranges = cols % 64 != 0 || (g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
     // Lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
-    // 22.7, 8100 x 7168 40.8 / 47.8 and 42.0 / 49.1, 16101 x 4096 44.8 / 53.4 and 46.5 / 55.0, 12001 x 5000 50.6 / 52.8 and 51.4 / 54.5; only large
-    // tensors whose rows do not start at lines prefer them stacked, 16000 x 9000 172 / 167 and 168 / 168.
-    g.stacked = cols % 64 != 0 && rows * cols > (int64_t)100000000;
+    // 22.7, 8100 x 7168 40.8 / 47.8 and 42.0 / 49.1, 12001 x 5000 50.6 / 52.8 and 51.4 / 54.5.  Once the tensor and its codes (4 bytes an element) no longer
+    // fit the 256 MB memory-side cache, stacked lanes take less: quantize, millions of elements 40 to 50 0.93, 55 to 60 1.02, 60 to 70 1.05, more 1.06
+    // (16221 x 4296 86.5 / 78.0, 9579 x 11200 108 / 99);  RMSNorm codes 40 to 50 0.92, 60 to 65 0.98, more 1.00 to 1.03, but of odd widths 0.98 to 0.99
+    // throughout;  SwiGLU codes, 6 bytes an element, 50 to 60 0.98, more 0.99 to 1.01.
+    g.stacked = quantizes ? rows * cols > (int64_t)60000000 : cols % 8 == 0 && rows * cols > (int64_t)66000000;
     return g;
 }
 // launch(grid, workgroups of this launch), once or as often as the launch limit asks for

@@ -219,8 +219,18 @@ static void check_edge_tiles() {
     }
 }
 
+// How the lanes of the 64 x 128 tile lie, and where codes leave it for the 128 x 128 tile: the faster one by measurement.
+static void check_code_tiles() {
+    struct Case { int64_t rows, cols; bool quantizes, stacked; };
+    const Case cases[] = {{16221, 4296, true, true}, {9579, 11200, true, true}, {12446, 5904, true, true}, {12545, 8001, true, true}, {8100, 7168, true, false},
+                          {12001, 4000, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false}, {12545, 8008, false, true}, {12545, 8001, false, false},
+                          {8100, 7168, false, false}, {1777, 960, false, false}};
+    for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
+}
+
 int main() {
     check_small_tiles();
+    check_code_tiles();
     check_wgrad_copies();
     check_edge_tiles();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);

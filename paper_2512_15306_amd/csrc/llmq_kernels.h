@@ -34,11 +34,14 @@ inline bool slab_shape_ok(int64_t rows, int64_t cols) { return rows % 128 == 0 &
 //   quantize              3.1 / 3.2    5.5 / 5.2    6.8 / 6.6   11.5 / 10.6   29.6 / 24.4     51.3 / 38.0          74.6 / 52.8
 //   SwiGLU codes          5.4 / 6.4    9.4 / 8.2   12.3 / 12.3  19.2 / 17.1   41.0 / 35.2     75.4 / 68.1         109.8 / 84.7
 //   RMSNorm codes         3.4 / 3.6    6.1 / 5.9    7.3 / 7.6   12.1 / 10.0   29.2 / 25.4     52.1 / 46.1          74.1 / 53.9
+// resident: workgroups of the tile kernel that the chip holds at once, if a little more than that is worse than two rounds of the small tile (RMSNorm
+// codes, 768: three per CU): 760 tiles 11.7 / 10.0, 770 11.9 / 12.9, 864 12.7 / 13.1, 960 14.2 / 14.8, 1008 14.7 / 15.2, 1053 15.4 / 15.6, 1092 16.0 / 15.8.
 // LLMQ_QUANT_TILE=0 / 1 (tests): always the one or, for shapes made of them, always the other.
-inline bool takes_large_tile(int64_t rows, int64_t cols) {
+inline bool takes_large_tile(int64_t rows, int64_t cols, int64_t resident = 0) {
     if (rows % 128 != 0 || cols % 128 != 0) return false;
     if (const char* e = tuning_env("LLMQ_QUANT_TILE")) return atoi(e) != 0;
-    return (rows / 128) * (cols / 128) >= 256;
+    const int64_t tiles = (rows / 128) * (cols / 128);
+    return tiles >= 256 && (resident == 0 || tiles <= resident || tiles >= resident * 4 / 3);
 }
 
 // What the other tensors take when codes in both layouts are wanted:

@@ -226,6 +226,11 @@ static void check_code_tiles() {
                           {12001, 4000, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false}, {12545, 8008, false, true}, {12545, 8001, false, false},
                           {8100, 7168, false, false}, {1777, 960, false, false}};
     for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
+    struct Tiles { int64_t rows, cols; int resident; bool large; };
+    const Tiles tiles[] = {{2432, 5120, 768, true}, {2816, 4480, 768, false}, {1920, 8192, 768, false}, {1152, 14336, 768, false}, {1664, 10752, 768, true}, {3456, 5376, 768, true},
+                           {16384, 5120, 768, true}, {1920, 8192, 0, true}, {1024, 2048, 0, false}, {1024, 4096, 0, true}, {1024, 4100, 0, false}};
+    for (const Tiles& c : tiles)
+        CHECK(takes_large_tile(c.rows, c.cols, c.resident) == c.large, "128 x 128 tiles for %lld x %lld, %d resident", (long long)c.rows, (long long)c.cols, c.resident);
 }
 
 int main() {

@@ -459,11 +459,14 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols, bool quantizes = false) 
     g.first = 0;
     g.xcd_ranges = cols % 64 != 0 || (g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
     // Lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
-    // 22.7, 8100 x 7168 40.8 / 47.8 and 42.0 / 49.1, 12001 x 5000 50.6 / 52.8 and 51.4 / 54.5.  Once the tensor and its codes (4 bytes an element) no longer
-    // fit the 256 MB memory-side cache, stacked lanes take less: quantize, millions of elements 40 to 50 0.93, 55 to 60 1.02, 60 to 70 1.05, more 1.06
-    // (16221 x 4296 86.5 / 78.0, 9579 x 11200 108 / 99);  RMSNorm codes 40 to 50 0.92, 60 to 65 0.98, more 1.00 to 1.03, but of odd widths 0.98 to 0.99
-    // throughout;  SwiGLU codes, 6 bytes an element, 50 to 60 0.98, more 0.99 to 1.01.
-    g.stacked = quantizes ? rows * cols > (int64_t)60000000 : cols % 8 == 0 && rows * cols > (int64_t)66000000;
+    // 22.7, two sets of buffers in turn 8100 x 7168 41.3 / 48.6 and 42.7 / 50.0.  Once tensor and codes (4 bytes an element) crowd the 256 MB memory-side
+    // cache, stacked lanes take less.  Absmax and quantize of four tensors in turn:
+    //   whole vectors, rows that do not start at lines   9001 x 4008 48.6 / 49.8, 11001 x 3912 65.4 / 63.5, 12001 x 5000 102.4 / 95.3, 16221 x 4296 116.8 /
+    //     107.9, 16000 x 9000 225.8 / 217.0;  rows of whole lines   8101 x 4416 44.1 / 48.9, 16101 x 4096 85.3 / 84.9, 16101 x 6144 126.9 / 124.1,
+    //     9579 x 11200 149.4 / 140.6;  odd widths   6001 x 6001 51.4 / 58.0, 16001 x 8001 189.5 / 194.8, 12001 x 16001 313.9 / 311.2
+    // RMSNorm codes, millions of elements 40 to 50 0.92, 60 to 65 0.98, more 1.00 to 1.03, but of odd widths 0.98 to 0.99 throughout;  SwiGLU codes, 6
+    // bytes an element, 50 to 60 0.98, more 0.99 to 1.01.
+    g.stacked = cols % 8 == 0 && rows * cols > (int64_t)(quantizes && cols % 64 != 0 ? 40000000 : 66000000);
     return g;
 }
 // launch(grid, workgroups of this launch), once or as often as the launch limit asks for

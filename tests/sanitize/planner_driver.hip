@@ -222,9 +222,9 @@ static void check_edge_tiles() {
 // How the lanes of the 64 x 128 tile lie, and where codes leave it for the 128 x 128 tile: the faster one by measurement.
 static void check_code_tiles() {
     struct Case { int64_t rows, cols; bool quantizes, stacked; };
-    const Case cases[] = {{16221, 4296, true, true}, {9579, 11200, true, true}, {12446, 5904, true, true}, {12545, 8001, true, true}, {8100, 7168, true, false},
-                          {12001, 4000, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false}, {12545, 8008, false, true}, {12545, 8001, false, false},
-                          {8100, 7168, false, false}, {1777, 960, false, false}};
+    const Case cases[] = {{16221, 4296, true, true}, {9579, 11200, true, true}, {12446, 5904, true, true}, {11001, 3912, true, true}, {12001, 5000, true, true},
+                          {9001, 4008, true, false}, {8101, 4416, true, false}, {8100, 7168, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false},
+                          {16001, 8001, true, false}, {12545, 8008, false, true}, {12001, 5000, false, false}, {12545, 8001, false, false}, {1777, 960, false, false}};
     for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
     struct Tiles { int64_t rows, cols; int resident; bool large; };
     const Tiles tiles[] = {{2432, 5120, 768, true}, {2816, 4480, 768, false}, {1920, 8192, 768, false}, {1152, 14336, 768, false}, {1664, 10752, 768, true}, {3456, 5376, 768, true},

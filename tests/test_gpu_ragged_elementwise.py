@@ -201,10 +201,10 @@ def test_whole_tiles_that_are_no_slabs(rows, cols, fmt, monkeypatch):
     test_codes_of_every_producer(rows, cols, None, None, fmt, monkeypatch)
 
 
-@pytest.mark.parametrize("rows,cols", [(12545, 8001), (12551, 8008)])
+@pytest.mark.parametrize("rows,cols", [(12545, 8001), (12551, 8008), (9579, 7104)])
 def test_large_ragged_codes_are_those_of_their_bands(rows, cols):
-    """Above 60M elements (RMSNorm codes of whole vectors: 66M) the lanes of the guarded tile lie differently: the codes are those of bands of
-    rows by themselves."""
+    """Above 66M elements in whole vectors (quantize, rows that do not start at lines: 40M) the lanes of the guarded tile lie differently: the
+    codes are those of bands of rows by themselves."""
     x = torch.randn(rows, cols, device=DEV).to(torch.bfloat16)
     w = torch.randn(cols, device=DEV).to(torch.bfloat16)
     rstd = torch.rand(rows, device=DEV) + 0.5

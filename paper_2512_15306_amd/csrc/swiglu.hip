@@ -519,7 +519,12 @@ static bool edge_worth(int64_t M, int64_t I, bool backward) {
     if (const char* e = tuning_env("LLMQ_CODES_KERNEL")) return atoi(e) != kCodesElements;
     const int64_t n = M * I;
     if (I % 8 == 0) return I >= (backward ? 256 : 200) && n >= (backward ? (int64_t)3 << 19 : (int64_t)1 << 20);
-    if (backward) return I >= 256 && n >= (10 * I >= 7 * edge_col_pieces(I) * kSwEdgeCols ? (int64_t)15 << 18 : (int64_t)5 << 20);     // (a wave takes 512 columns)
+    // (a wave takes 512 columns.  Elements / vectors, two sets of buffers and twelve: all but full waves, 4 to 5 million elements 1.01 and 1.35, 7 to 8 1.11 and
+    // 1.41;  used to 0.6 to 0.7, 5 to 8 million 0.88 and 1.16;  less 0.80 and 1.06, 8 to 11 million 0.92 and 1.23)
+    if (backward) {
+        const int64_t wave_cols = edge_col_pieces(I) * kSwEdgeCols;
+        return I >= 256 && n >= (10 * I >= 7 * wave_cols ? (int64_t)15 << 18 : 100 * I >= 63 * wave_cols ? (int64_t)5 << 20 : (int64_t)1 << 23);
+    }
     return I >= 256 && n >= (int64_t)15 << 17;
 }
 static CodesKind codes_kind_of(int64_t M, int64_t I, bool transpose) {
@@ -528,7 +533,9 @@ static CodesKind codes_kind_of(int64_t M, int64_t I, bool transpose) {
         return k != kCodesNarrow ? (CodesKind)k : transpose && codes_narrow_ok(M, I) ? kCodesNarrow : kCodesSmall;
     }
     const int64_t n = M * I;
-    if (!transpose) return M >= 32 && I >= 64 && n >= (int64_t)15 << 17 ? kCodesSmall : kCodesElements;
+    // (two sets of buffers and twelve, elements / tiles: up to 512 columns, 1.75 to 2 million elements 0.82 and 0.87, 2 to 2.36 0.93 and 0.94, 2.36 to 3 1.10 and
+    // 1.03;  more columns 1.75 to 2 0.95 and 0.98, 2 to 2.36 1.03 and 1.01)
+    if (!transpose) return M >= 32 && I >= 64 && n >= (I < 512 ? (int64_t)9 << 18 : (int64_t)15 << 17) ? kCodesSmall : kCodesElements;
     if (I >= 32 && n >= ((int64_t)1 << 22) && codes_narrow_ok(M, I)) return kCodesNarrow;       // 1000000 x 32: 105 / 81 / 107 us
     return M >= 32 && I >= 64 && n >= (int64_t)3 << 18 ? kCodesSmall : kCodesElements;
 }

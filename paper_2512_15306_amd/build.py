@@ -1,4 +1,5 @@
-"""Build libllmq.so (the gfx950 kernels and their C ABI) in-tree with hipcc, and the Python module over it with g++."""
+"""Build libllmq.so (the gfx950 kernels and their C ABI) in-tree with hipcc, and the Python module over it with g++.  The library needs
+nothing but hipcc: where the module does not build, the library is there without it (and llmq.py takes the ctypes path)."""
 from __future__ import annotations
 
 import os
@@ -86,12 +87,35 @@ def binding_commands(obj: str, lib_dir: str, out: str):
             [cxx, "-shared", obj, "-o", out, "-L", lib_dir, "-lllmq", "-Wl,-rpath,$ORIGIN", "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
 
 
+def _run_binding(command):
+    """A command of the module's build as a process, or None with a message where it cannot even start."""
+    try:
+        return subprocess.Popen(command, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    except OSError as e:
+        print("%s: %s" % (command[0], e), file=sys.stderr)
+        return None
+
+
+def _finish_binding(process) -> bool:
+    if process is None:
+        return False
+    out, _ = process.communicate()
+    if process.returncode != 0:
+        print(out, file=sys.stderr)
+    return process.returncode == 0
+
+
 def _build_in(work: str, hipcc: str, verbose: bool) -> str:
     objs = []
     procs = []
-    binding_obj = os.path.join(work, "binding.o")
-    compile_binding, link_binding = binding_commands(binding_obj, HERE, os.path.join(work, "_binding.so"))
-    procs.append(("binding.cpp", subprocess.Popen(compile_binding, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    new_lib, new_binding = os.path.join(work, "libllmq.so"), os.path.join(work, "_binding.so")
+    compile_binding = link_binding = binding = None
+    try:
+        compile_binding, link_binding = binding_commands(os.path.join(work, "binding.o"), work, new_binding)
+    except ImportError as e:                          # no PyTorch here
+        print("binding.cpp: %s" % e, file=sys.stderr)
+    if compile_binding:
+        binding = _run_binding(compile_binding)
     for src in SOURCES:
         obj = os.path.join(work, src.replace(".hip", ".o"))
         cmd = [hipcc] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
@@ -110,18 +134,30 @@ def _build_in(work: str, hipcc: str, verbose: bool) -> str:
             print("FAILED: %s\n%s" % (src, out), file=sys.stderr)
         elif verbose and out.strip():
             print(out)
+    binding_built = _finish_binding(binding)
     if failed:
         raise RuntimeError("hipcc failed")
     for src in sorted(CHECKED_SOURCES):
         with open(os.path.join(work, src.replace(".hip", "-hip-amdgcn-amd-amdhsa-gfx950.s"))) as f:
             check_accumulator_reads(src, f.read())
-    tmp = LIB + ".tmp.%d" % os.getpid()
-    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp])
-    os.replace(tmp, LIB)
-    subprocess.check_call(link_binding)
-    shutil.copy(os.path.join(work, "_binding.so"), BINDING + ".tmp.%d" % os.getpid())
-    os.replace(BINDING + ".tmp.%d" % os.getpid(), BINDING)
+    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", new_lib])
+    binding_built = binding_built and _finish_binding(_run_binding(link_binding))
+    # Both are there (or the module is not going to be): now they replace the old ones.  A module of another build must not stay
+    # beside the new library.
+    if os.path.exists(BINDING):
+        os.remove(BINDING)
+    _replace(new_lib, LIB)
+    if binding_built:
+        _replace(new_binding, BINDING)
+    else:
+        print("FAILED: binding.cpp: the calls of llmq.py take the ctypes path", file=sys.stderr)
     return LIB
+
+
+def _replace(new: str, path: str) -> None:
+    tmp = path + ".tmp.%d" % os.getpid()
+    shutil.copy(new, tmp)
+    os.replace(tmp, path)
 
 
 if __name__ == "__main__":

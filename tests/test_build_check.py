@@ -1,6 +1,10 @@
 """The build's check of the generated assembly of the tile kernels (paper_2512_15306_amd/build.py): the MFMAs are
 written out as inline assembly, so nothing but MFMAs may touch accumulator registers between the first MFMA and the
 wait states behind the K loop.  Here the check itself is tested, on hand-written assembly text."""
+import os
+import shutil
+import stat
+
 import pytest
 
 from paper_2512_15306_amd import build
@@ -70,3 +74,35 @@ def test_kernels_without_mfma_are_skipped_but_others_still_count():
     build.check_accumulator_reads("mixed.hip", adder + kernel(GOOD))
     with pytest.raises(RuntimeError, match="no tile kernel found"):
         build.check_accumulator_reads("only_adder.hip", adder)
+
+
+def failing_compiler(tmp_path, when):
+    """A C++ compiler that fails if its command line holds `when`, and writes what it is asked for otherwise."""
+    exe = tmp_path / "cxx"
+    exe.write_text("#!/bin/sh\ncase \"$*\" in *%s*) echo no such luck; exit 1;; esac\nwhile [ \"$1\" != -o ]; do shift; done; echo module > \"$2\"\n" % when)
+    exe.chmod(exe.stat().st_mode | stat.S_IXUSR)
+    return str(exe)
+
+
+@pytest.mark.parametrize("fails", ["binding.cpp", "-shared", "missing", None])
+def test_the_library_does_not_need_the_module(fails, tmp_path, monkeypatch, capsys):
+    """A module that does not compile or link, or has no compiler: the library is built and replaces the old one, and no module of
+    another build stays beside it."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not found")
+    lib, module = tmp_path / "libllmq.so", tmp_path / "_binding.so"
+    lib.write_text("old")
+    module.write_text("old")
+    monkeypatch.setattr(build, "SOURCES", ["calibrate.hip"])
+    monkeypatch.setattr(build, "CHECKED_SOURCES", set())
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "BINDING", str(module))
+    monkeypatch.setenv("CXX", str(tmp_path / "nothing") if fails == "missing" else failing_compiler(tmp_path, fails or "never"))
+    assert build.build() == str(lib)
+    assert lib.read_bytes()[:4] == b"\x7fELF"
+    if fails:
+        assert not module.exists() and "FAILED: binding.cpp" in capsys.readouterr().err
+    else:
+        assert module.read_text() == "module\n"
+    assert sorted(os.listdir(tmp_path)) == sorted(["libllmq.so"] + ([] if fails else ["_binding.so"]) + ([] if fails == "missing" else ["cxx"]))

@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch  # imported first on purpose: the library then binds to the HIP runtime PyTorch loaded
@@ -26,6 +27,7 @@ LAYOUT_ROWS, LAYOUT_T_MAJOR, LAYOUT_SLABS = 0, 1, 2
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libllmq.so")
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 _lib = None
 
 EXPORTS = ["llmq_status_string", "llmq_version", "llmq_amax_workspace_bytes", "llmq_amax", "llmq_amax_static", "llmq_quantize_fp8", "llmq_quantize_fp8_slabs", "llmq_fp8_gemm_tn", "llmq_fp8_gemm", "llmq_fp8_gemm_scratch_bytes", "llmq_fp8_gemm_with_scratch", "llmq_bf16_gemm_tn",
@@ -157,10 +159,29 @@ class _NoBinding:
         return lambda *args: None
 
 
-try:
-    from . import _binding as _fast
-except ImportError:
-    _fast = _NoBinding()
+class _UnloadedBinding:
+    """In the module's place until the first call, which loads the library and then the module, if it calls that same library."""
+
+    def __getattr__(self, name):
+        global _fast
+        loaded = lib()._name
+        if _fast is self:
+            _fast = _load_binding(loaded)
+        return getattr(_fast, name)
+
+
+def _load_binding(loaded: str):
+    if not os.path.exists(BINDING_PATH) or os.path.realpath(loaded) != os.path.realpath(os.path.join(_HERE, "libllmq.so")):
+        return _NoBinding()
+    try:
+        from . import _binding
+        return _binding
+    except ImportError as e:                     # built against another PyTorch or Python, say
+        warnings.warn("%s does not load (%s): calls go through ctypes, which takes the host several microseconds more each; build it again" % (BINDING_PATH, e), RuntimeWarning)
+        return _NoBinding()
+
+
+_fast = _UnloadedBinding()
 
 
 def _check(status: int, where: str) -> None:

@@ -1,5 +1,10 @@
 """The compiled module behind the calls of a training step: it takes the plain case, gives what the ctypes path gives, and leaves
 everything else, errors included, to that path."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -18,6 +23,58 @@ def test_module_is_built_and_declines_what_is_not_plain():
     assert f.amax() is None and f.linear_fwd(None, None) is None
     with pytest.raises(ValueError, match="must live on the GPU"):
         llmq.llmq_amax(cpu, 0, one, one, torch.zeros(4096, dtype=torch.uint8))
+
+
+def _package(tmp_path, *files):
+    """The binding's Python part in a package of its own, with these files beside it"""
+    pkg = tmp_path / "pkg"
+    pkg.mkdir()
+    (pkg / "__init__.py").write_text("")
+    for f in ("llmq.py",) + files:
+        shutil.copy(os.path.join(os.path.dirname(llmq.__file__), f), pkg / f)
+    return pkg
+
+
+def _python(tmp_path, code):
+    return subprocess.run([sys.executable, "-W", "always", "-c", code], cwd=tmp_path, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+
+
+def test_another_library_gets_every_call(tmp_path):
+    """A program that points LIB_PATH at another build of the library has that one called throughout: the module, which calls the one
+    beside it, is left out."""
+    other = tmp_path / "other"
+    other.mkdir()
+    shutil.copy(llmq.LIB_PATH, other / "libllmq.so")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(llmq.__file__)))
+    code = """if 1:
+        import sys; sys.path.insert(0, %r)
+        from paper_2512_15306_amd import llmq
+        assert "_binding" not in "".join(m for m in sys.modules if m.startswith("paper")), "loaded before any call"
+        path = llmq.LIB_PATH
+        llmq.LIB_PATH = %r
+        f = llmq._fast.amax
+        print(type(llmq._fast).__name__, llmq.lib()._name, f(1, 2))
+        llmq._lib, llmq._fast, llmq.LIB_PATH = None, llmq._UnloadedBinding(), path
+        print(llmq._fast.__file__)
+        llmq.llmq_amax_workspace_bytes()
+        """
+    p = _python(tmp_path, code % (root, str(other / "libllmq.so")))
+    lines = [l for l in p.stdout.splitlines() if "amdgpu.ids" not in l]
+    assert p.returncode == 0 and lines[0] == "_NoBinding %s None" % (other / "libllmq.so") and lines[1].endswith("_binding.so"), p.stdout
+
+
+def test_a_module_that_does_not_load_is_reported(tmp_path):
+    """Not a word where the module is not built; a warning, and the ctypes path, where it is and cannot be loaded."""
+    pkg = _package(tmp_path, "libllmq.so")
+    code = "from pkg import llmq; print(llmq._fast.amax(1), type(llmq._fast).__name__)"
+    p = _python(tmp_path, code)
+    assert p.returncode == 0 and "None _NoBinding" in p.stdout and "RuntimeWarning" not in p.stdout, p.stdout
+    (pkg / "_binding.so").write_text("of another build")
+    p = _python(tmp_path, code)
+    assert p.returncode == 0 and "None _NoBinding" in p.stdout and "RuntimeWarning" in p.stdout and "does not load" in p.stdout, p.stdout
+    os.remove(pkg / "libllmq.so")
+    p = _python(tmp_path, code)
+    assert p.returncode != 0 and "libllmq.so is not built" in p.stdout, p.stdout
 
 
 class Calls:

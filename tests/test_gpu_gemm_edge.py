@@ -105,9 +105,13 @@ def test_ragged_bf16(R, C, T, tile, monkeypatch):
         assert _untouched(buf, R, C)
 
 
+@pytest.mark.parametrize("tile", [None, "2x2", "4x4", "3x4", "3x2"])
 @pytest.mark.parametrize("fa,T", [(0, 272), (1, 272), (0, 275), (1, 275)])
-def test_values_beyond_the_operands_do_not_reach_the_results(fa, T):
-    """NaN and Inf codes lie directly behind the operands in memory; one NaN row inside stays one NaN row."""
+def test_values_beyond_the_operands_do_not_reach_the_results(fa, T, tile, monkeypatch):
+    """NaN and Inf codes lie directly behind the operands in memory; one NaN row inside stays one NaN row.  The kernel the sizes choose, and
+    the guarded tiles of every height (192 rows: aligned rows only)."""
+    if tile:
+        monkeypatch.setenv("LLMQ_GEMM_EDGE_TILE", tile)
     R, C = 130, 72
     nan, inf = (0x7F, 0x7F) if fa == 0 else (0x7E, 0x7C)
     A, B = _rand_codes((R, T), fa, 3), _rand_codes((C, T), 0, 4)
@@ -145,7 +149,7 @@ def test_values_beyond_t_major_operands_do_not_reach_the_results(fa, T):
             a, b = (bufA[:R * T].view(T, R) if ta else bufA[:R * T].view(R, T)), bufB[:C * T].view(T, C)
             a.copy_(_operand(A, ta))
             b.copy_(_operand(B, True))
-            for tile in ("2x2", "4x4", "0x0"):
+            for tile in ("2x2", "4x4", "3x4", "3x2", "0x0"):
                 with pytest.MonkeyPatch.context() as mp:
                     mp.setenv("LLMQ_GEMM_EDGE_TILE", tile)
                     print("beyond T-major: fa=%d R=%d C=%d T=%d ta=%d tile=%s" % (fa, R, C, T, ta, tile), flush=True)
@@ -185,8 +189,10 @@ def test_more_tiles_than_compute_units(T, monkeypatch):
 
 
 @pytest.mark.parametrize("tile", ["3x4", "3x2"])
-@pytest.mark.parametrize("R,C,T", [(1, 8, 16), (191, 130, 112), (192, 17, 144), (193, 264, 400), (400, 256, 272), (577, 513, 128)])
+@pytest.mark.parametrize("R,C,T", [(1, 8, 16), (191, 130, 112), (192, 17, 144), (193, 264, 400), (400, 256, 272), (577, 513, 128),
+                                   (208, 272, 400), (208, 272, 401), (384, 144, 133), (192, 16, 17)])
 def test_tiles_of_192_rows(R, C, T, tile, monkeypatch):
-    """Below, at and above their edges (aligned rows only: the transposed layouts of the others keep the tiles of even sides)."""
+    """Below, at and above their edges.  Aligned rows only, which the layouts have by different sizes: operands in rows by T, T-major ones by R
+    and C (the last four shapes: whole 16-byte chunks T-major, A in E4M3 and E5M2, T inside a K step); the others keep the tiles of even sides."""
     test_ragged_fp8(R, C, T, tile, monkeypatch)
     test_ragged_bf16(R, C, T, tile, monkeypatch)

@@ -100,6 +100,32 @@ __device__ inline v4u rn_load(const uint16_t* row, int idx, int C) {
     if (8 * idx + 8 <= C) return __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(row + 8 * idx));
     return load8_upto(row + 8 * idx, 8 * idx, C - 8 * idx);
 }
+// Rows of more than 2048 columns: every vector is loaded at once, the last one as the row's last eight elements, and shifted where it is used
+// (rn_last), by one branch that the other vectors' lanes skip together.  With the shift beside each load (rn_load) a lane of eight vectors and their
+// addition took 279 registers, now 128, and 7616 x 9885 325 us (161 with the last vector loaded element by element, 137 so); 4001 x 10001 169 (83,
+// 76), without the addition 70 (42, 41).
+__device__ inline const v4u_at2* rn_vector(const uint16_t* row, unsigned at, int C) {       // (32-bit offsets from a uniform address)
+    const unsigned end = 2u * (unsigned)(C - 8);
+    return reinterpret_cast<const v4u_at2*>(reinterpret_cast<const uint8_t*>(row) + (at < end ? at : end));
+}
+template <bool EDGE>
+__device__ inline v4u rn_load_wide(const uint16_t* row, int idx, unsigned at, int C) {
+    if constexpr (!EDGE) return __builtin_nontemporal_load(reinterpret_cast<const v4u*>(row) + idx);
+    return __builtin_nontemporal_load(rn_vector(row, at, C));
+}
+template <bool EDGE, bool STREAM>
+__device__ inline void rn_store_wide(uint16_t* row, int idx, unsigned at, int last, int C, const v4u& v) {
+    if constexpr (!EDGE) store_hinted<STREAM>(v, reinterpret_cast<v4u*>(row) + idx);
+    else if (idx < last) *reinterpret_cast<v4u_at2*>(reinterpret_cast<uint8_t*>(row) + at) = v;
+    else store8_upto(row + 8 * last, v, C - 8 * last);
+}
+// k: vector idx of the row is the lane's k-th
+template <bool EDGE>
+__device__ inline void rn_last(v4u& v, int k, int last, int C) {
+    if constexpr (EDGE) {
+        if (k == last / kRnThreads && (int)threadIdx.x == last % kRnThreads) v = shift_elements(v, 8 * last + 8 - C);
+    }
+}
 template <bool EDGE, bool STREAM = false>
 __device__ inline void rn_store(uint16_t* row, int idx, int C, const v4u& v) {
     if constexpr (!EDGE) store_hinted<STREAM>(v, reinterpret_cast<v4u*>(row) + idx);
@@ -210,6 +236,10 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
     for (int p = 0; p < kRnRowsPerBlock; p += ROWS) {
         const int64_t row = (int64_t)blockIdx.x * kRnRowsPerBlock + p;
         if (row >= M) break;                                 // the same for the whole workgroup
+        // Byte offset of the lane's k-th vector.  Opaque in every trip, or the compiler keeps an address for each vector of each tensor across them.
+        unsigned lane_at = 16u * threadIdx.x;
+        if constexpr (EDGE) asm volatile("" : "+v"(lane_at));
+        auto at = [&](int k) { return lane_at + (unsigned)(k * kRnThreads * 16); };
         v4u r[ROWS][VPL], xv[ROWS][HAS_X ? VPL : 1];
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
@@ -218,8 +248,8 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
                 const int idx = k * kRnThreads + threadIdx.x;
                 r[i][k] = v4u{0, 0, 0, 0};
                 if (row + i < M && idx < nvec) {
-                    r[i][k] = rn_load<EDGE>(res + (row + i) * C, idx, C);
-                    if constexpr (HAS_X) xv[i][k] = rn_load<EDGE>(x + (row + i) * C, idx, C);
+                    r[i][k] = rn_load_wide<EDGE>(res + (row + i) * C, idx, at(k), C);
+                    if constexpr (HAS_X) xv[i][k] = rn_load_wide<EDGE>(x + (row + i) * C, idx, at(k), C);
                 }
             }
 #pragma unroll
@@ -229,11 +259,13 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
             for (int k = 0; k < VPL; ++k) {
                 const int idx = k * kRnThreads + threadIdx.x;
                 if (row + i < M && idx < nvec) {
+                    rn_last<EDGE>(r[i][k], k, nvec - 1, C);
                     if constexpr (HAS_X) {
+                        rn_last<EDGE>(xv[i][k], k, nvec - 1, C);
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             r[i][k][j] = rn_pack(rn_lo(r[i][k][j]) + rn_lo(xv[i][k][j]), rn_hi(r[i][k][j]) + rn_hi(xv[i][k][j]));
-                        rn_store<EDGE, STREAM>(res_out + (row + i) * C, idx, C, r[i][k]);
+                        rn_store_wide<EDGE, STREAM>(res_out + (row + i) * C, idx, at(k), nvec - 1, C, r[i][k]);
                     }
                     if constexpr (ONE_WAVE) s_rows[i][idx] = r[i][k];
                     else add_squares(r[i][k], ss);
@@ -278,14 +310,15 @@ __global__ __launch_bounds__(kRnThreads) void rmsnorm_rows_kernel(
             const int idx = k * kRnThreads + threadIdx.x;
             if (idx < nvec) {
                 v4u wv;
-                if constexpr (EDGE) wv = load8_upto(w + 8 * idx, 8 * idx, C - 8 * idx);
+                if constexpr (EDGE) wv = *rn_vector(w, at(k), C);
                 else wv = reinterpret_cast<const v4u*>(w)[idx];
+                rn_last<EDGE>(wv, k, nvec - 1, C);
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i)
                     if (row + i < M) {
                         v4u o = normalize8(r[i][k], rstd[i], wv);
                         if (EDGE && idx == nvec - 1) o = keep_upto(o, C % 8);
-                        rn_store<EDGE, STREAM>(y + (row + i) * C, idx, C, o);
+                        rn_store_wide<EDGE, STREAM>(y + (row + i) * C, idx, at(k), nvec - 1, C, o);
                         m0 = pk_max_mag(m0, o[0]);
                         m1 = pk_max_mag(m1, o[1]);
                         m2 = pk_max_mag(m2, o[2]);

@@ -2,8 +2,10 @@
 written out as inline assembly, so nothing but MFMAs may touch accumulator registers between the first MFMA and the
 wait states behind the K loop.  Here the check itself is tested, on hand-written assembly text."""
 import os
+import re
 import shutil
 import stat
+import subprocess
 
 import pytest
 
@@ -106,3 +108,14 @@ def test_the_library_does_not_need_the_module(fails, tmp_path, monkeypatch, caps
     else:
         assert module.read_text() == "module\n"
     assert sorted(os.listdir(tmp_path)) == sorted(["libllmq.so"] + ([] if fails else ["_binding.so"]) + ([] if fails == "missing" else ["cxx"]))
+
+
+def test_the_guarded_norm_of_wide_rows_fits_four_waves_to_a_simd(tmp_path):
+    """Registers of rmsnorm_rows_kernel with guarded rows: 128 leave four waves to a SIMD.  (279, as it once had, were twice the time.)"""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not found")
+    asm = tmp_path / "rmsnorm.s"
+    subprocess.run([hipcc] + build.FLAGS + ["--cuda-device-only", "-S", os.path.join(build.CSRC, "rmsnorm.hip"), "-o", str(asm)], check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    counts = {m.group(1): int(m.group(2)) for m in re.finditer(r"\.amdhsa_kernel _ZN4llmq\d+rmsnorm_rows_kernelI(Lb[01]ELb1ELi\d+E)Lb.*?next_free_vgpr (\d+)", asm.read_text(), re.S)}
+    assert len(counts) == 8 and max(counts.values()) <= 128, counts

@@ -80,7 +80,8 @@ inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
 // Where all 128 x 128 tiles are resident at once, two to a CU, they hide each other's prologue and output, so 192 x 128 needs K steps to win by (least_192).
 // 128 x 128 / 192 x 128 time by K steps 1, 2, 3 to 4, 5 to 8, 9 to 16, more, over 1200 shapes: 0.98, 1.01, 1.04, 1.09, 1.09, 1.11;  added to the output
 // 0.93, 0.96, 1.02, 1.05, 1.06, 1.09;  widths no multiples of 8 (stores of single elements) 0.91, 0.92, 0.96, 0.98, 1.00, 1.05;  with absmax (fewer
-// atomics) 1.12, 1.13, 1.07, 1.03, 1.04, 1.11.
+// atomics) 1.12, 1.13, 1.07, 1.03, 1.04, 1.11.  192 x 256 tiles of odd widths lose the same way where there are several rounds of them: 3328 x 10548 x 128 added
+// to the output 50.7 / 60.7, 7105 x 4754 x 64 43.2 / 56.7.
 inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
@@ -107,7 +108,8 @@ inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus,
             const int per_cu = (ni == 2 && nj == 2) ? 2 : 1;
             const int64_t slots = resident_slots(num_cus, ni, nj);
             const int64_t rounds = (tiles + slots - 1) / slots;
-            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : ni == 3 ? (nj == 4 ? 0.83 : T <= 1024 && !tb ? 0.68 : 0.74) : (ni == nj ? 1.0 : 0.77);
+            const bool odd_rounds = C % 8 != 0 && T <= 8 * BK && rounds > 1;      // (outputs of single elements, round after round)
+            const double e = per_cu == 2 ? (T <= 3072 ? 0.90 : 0.80) : ni == 3 ? (nj == 4 ? (odd_rounds ? 0.74 : 0.83) : T <= 1024 && !tb ? 0.68 : 0.74) : (ni == nj ? 1.0 : 0.77);
             const double cost = (double)rounds * per_cu * ni * nj / e;
             if (best.ni == 0 || cost < best_cost * 0.97) { best.ni = ni; best.nj = nj; best_cost = cost; }
         }

@@ -211,7 +211,7 @@ static void check_edge_tiles() {
         {7232, 704, 112, true, true, false, false, 2, 2}, {2176, 2624, 16, true, true, false, false, 2, 2}, {6936, 555, 64, false, false, false, true, 2, 2},
         {768, 5509, 32, false, true, false, true, 2, 2}, {1466, 3335, 256, false, false, false, true, 2, 2}, {2432, 2048, 720, false, false, false, false, 3, 2},
         {708, 7536, 640, false, false, false, false, 3, 2}, {576, 9600, 736, false, false, false, false, 3, 2}, {4480, 2432, 3760, false, false, false, false, 3, 4},
-        {7296, 1060, 3712, false, false, false, false, 3, 4},
+        {7296, 1060, 3712, false, false, false, false, 3, 4}, {7105, 4754, 64, false, true, false, false, 2, 2},
     };
     for (const Case& c : cases) {
         const EdgeChoice e = choose_edge_tile(c.R, c.C, c.T, 256, false, c.tb, false, false, c.accumulate, c.with_amax, c.bf16);

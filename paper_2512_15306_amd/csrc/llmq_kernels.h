@@ -28,20 +28,28 @@ inline unsigned max_workgroups() {
 constexpr int kTileRows = 128;
 inline bool slab_shape_ok(int64_t rows, int64_t cols) { return rows % 128 == 0 && cols % 256 == 0; }
 
-// Tensors of whole tiles take the tile kernels from one tile per CU on, below that the 64 x 128 tile, of which there are
-// twice as many.  64 x 128 / 128 x 128 tile, microseconds, buffers of their own for every pass:
-//   tiles                      64           256          384          768           1792          3584 (8192 x 7168)   5120 (16384 x 5120)
-//   quantize              3.1 / 3.2    5.5 / 5.2    6.8 / 6.6   11.5 / 10.6   29.6 / 24.4     51.3 / 38.0          74.6 / 52.8
-//   SwiGLU codes          5.4 / 6.4    9.4 / 8.2   12.3 / 12.3  19.2 / 17.1   41.0 / 35.2     75.4 / 68.1         109.8 / 84.7
-//   RMSNorm codes         3.4 / 3.6    6.1 / 5.9    7.3 / 7.6   12.1 / 10.0   29.2 / 25.4     52.1 / 46.1          74.1 / 53.9
-// resident: workgroups of the tile kernel that the chip holds at once, if a little more than that is worse than two rounds of the small tile (RMSNorm
-// codes, 768: three per CU): 760 tiles 11.7 / 10.0, 770 11.9 / 12.9, 864 12.7 / 13.1, 960 14.2 / 14.8, 1008 14.7 / 15.2, 1053 15.4 / 15.6, 1092 16.0 / 15.8.
+// Tensors of whole tiles take the tile kernels from about one tile per CU on, below that the 64 x 128 tile, of which there are
+// twice as many; where the chip's next round of the large ones would be nearly empty, the small tile again.  Those with more to compute or to hold
+// in registers have fewer workgroups resident and feel their rounds further up.  64 x 128 / 128 x 128 tile, microseconds, buffers of their own for every pass:
+//   tiles                      256          320          384          512          540          640          720          960         1792         3584 (8192 x 7168)
+//   quantize               5.6 /  5.3   6.3 /  6.3   6.8 /  6.7   8.0 /  7.8   9.5 /  9.2  10.4 / 10.2  11.5 / 10.9  15.3 / 14.4  29.6 / 24.4  51.3 / 38.0
+//   RMSNorm codes          5.7 /  5.9   6.5 /  7.2   6.9 /  7.7   8.1 /  8.7   9.5 /  9.3  10.5 /  9.7  11.7 / 10.0  15.6 / 15.4  29.2 / 25.4  52.1 / 46.1
+//     and the output       6.8 /  7.2   8.7 /  8.2   8.9 /  8.8  12.6 / 10.1  14.6 / 13.6  15.5 / 13.8  18.0 / 14.2  23.3 / 19.9
+//   SwiGLU codes           8.7 /  8.4  10.3 / 11.8  10.7 / 12.2  12.9 / 13.3  14.2 / 15.9  14.7 / 16.4  16.8 / 16.7  21.9 / 20.3  41.0 / 35.2  75.4 / 68.1
+//     and the output       9.8 /  9.6  11.2 / 12.7  11.8 / 13.1  14.1 / 14.0  18.2 / 17.8  19.3 / 18.2  22.1 / 19.5  29.0 / 26.9
+//   RMSNorm codes beyond three resident workgroups per CU: 760 tiles 11.7 / 10.0, 770 11.9 / 12.9, 864 12.7 / 13.1, two sets of buffers in turn 960 14.2 / 14.8, 1008 14.7 /
+//   15.2, 1053 15.4 / 15.6, 1092 16.0 / 15.8;  SwiGLU codes 680 16.3 / 16.5, 760 18.0 / 16.9;  with the output 392 13.4 / 13.2
 // LLMQ_QUANT_TILE=0 / 1 (tests): always the one or, for shapes made of them, always the other.
-inline bool takes_large_tile(int64_t rows, int64_t cols, int64_t resident = 0) {
+struct LargeTiles {
+    int64_t least;                              // the fewest tiles
+    int64_t after, before;                      // ... but not for more than the one and less than the other
+};
+constexpr LargeTiles kQuantizeTiles{256, 0, 0}, kNormTiles{513, 768, 1024}, kNormOutputTiles{320, 0, 0}, kSwigluTiles{256, 256, 704}, kSwigluOutputTiles{256, 256, 392};
+inline bool takes_large_tile(int64_t rows, int64_t cols, LargeTiles range) {
     if (rows % 128 != 0 || cols % 128 != 0) return false;
     if (const char* e = tuning_env("LLMQ_QUANT_TILE")) return atoi(e) != 0;
     const int64_t tiles = (rows / 128) * (cols / 128);
-    return tiles >= 256 && (resident == 0 || tiles <= resident || tiles >= resident * 4 / 3);
+    return tiles >= range.least && (tiles <= range.after || tiles >= range.before);
 }
 
 // What the other tensors take when codes in both layouts are wanted:

@@ -192,7 +192,7 @@ bool quantize_can_write_slabs(int64_t rows, int64_t cols) { return slab_shape_ok
 enum QuantKind { kQuantFlat, kQuantElements, kQuantNarrow, kQuantSmall, kQuantTile };
 static QuantKind quant_kind(const QuantJob& j) {
     if (!j.q_t) return kQuantFlat;
-    if (takes_large_tile(j.rows, j.cols)) return kQuantTile;
+    if (takes_large_tile(j.rows, j.cols, kQuantizeTiles)) return kQuantTile;
     if (j.qt_slabs) return kQuantSmall;
     const CodesKind k = codes_kind(j.rows, j.cols);
     return k == kCodesElements ? kQuantElements : k == kCodesNarrow ? kQuantNarrow : kQuantSmall;

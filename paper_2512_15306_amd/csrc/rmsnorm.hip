@@ -626,13 +626,12 @@ static CodesKind apply_kind(int64_t M, int64_t C, bool transpose) {
     return M >= 32 && C >= 64 && M * C >= (int64_t)15 << 17 ? kCodesSmall : kCodesElements;
 }
 
-constexpr int64_t kApplyResidentTiles = 3 * 256;
 template <int QFMT>
 static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rstd, int64_t M, int64_t C,
                          const float* d_qscale, uint8_t* q, uint8_t* q_t, uint16_t* y, hipStream_t stream,
                          bool qt_slabs) {
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? C * kTileRows : kTileRows;
-    if (q_t && takes_large_tile(M, C, kApplyResidentTiles)) {
+    if (q_t && takes_large_tile(M, C, y ? kNormOutputTiles : kNormTiles)) {
         const unsigned tr = (unsigned)(M / kTileRows), tcn = (unsigned)(C / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tr * tcn), dim3(kTileThreads), 0, stream, res, w, rstd, C, d_qscale, q, q_t, y, tcn, row_stride, band_stride); };
         if (streams_out(2 * M * C, C, 128)) { if (y) launch(rmsnorm_apply_fp8_tile_kernel<QFMT, true, true>); else launch(rmsnorm_apply_fp8_tile_kernel<QFMT, false, true>); }

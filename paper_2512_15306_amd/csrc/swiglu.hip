@@ -564,7 +564,7 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
                           uint8_t* q, uint8_t* q_t, hipStream_t stream, bool qt_slabs) {
     if (qt_slabs && !(q_t && slab_shape_ok(M, I))) return -2;
     const int64_t row_stride = qt_slabs ? kTileRows : M, band_stride = qt_slabs ? I * kTileRows : kTileRows;
-    if (q_t && takes_large_tile(M, I)) {
+    if (q_t && takes_large_tile(M, I, h ? kSwigluOutputTiles : kSwigluTiles)) {
         const unsigned gr = (unsigned)(M / kTileRows), gc = (unsigned)(I / kTileCols);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(gr * gc), dim3(kTileThreads), 0, stream, gu, I, h, d_qscale, q, q_t, gc, row_stride, band_stride); };
         if (streams_out(2 * M * I, I, 128)) { if (h) launch(swiglu_fwd_tile_kernel<true, QFMT, true>); else launch(swiglu_fwd_tile_kernel<false, QFMT, true>); }

@@ -226,11 +226,16 @@ static void check_code_tiles() {
                           {9001, 4008, true, false}, {8101, 4416, true, false}, {8100, 7168, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false},
                           {16001, 8001, true, false}, {12545, 8008, false, true}, {12001, 5000, false, false}, {12545, 8001, false, false}, {1777, 960, false, false}};
     for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
-    struct Tiles { int64_t rows, cols; int resident; bool large; };
-    const Tiles tiles[] = {{2432, 5120, 768, true}, {2816, 4480, 768, false}, {1920, 8192, 768, false}, {1152, 14336, 768, false}, {1664, 10752, 768, true}, {3456, 5376, 768, true},
-                           {16384, 5120, 768, true}, {1920, 8192, 0, true}, {1024, 2048, 0, false}, {1024, 4096, 0, true}, {1024, 4100, 0, false}};
+    struct Tiles { int64_t rows, cols; LargeTiles range; bool large; };
+    const Tiles tiles[] = {{1024, 4096, kQuantizeTiles, true}, {1024, 4100, kQuantizeTiles, false}, {1024, 2048, kQuantizeTiles, false}, {1920, 8192, kQuantizeTiles, true},
+                           {1024, 4096, kNormTiles, false}, {2048, 2560, kNormTiles, false}, {2048, 4096, kNormTiles, false}, {2432, 5120, kNormTiles, true}, {2816, 4480, kNormTiles, false},
+                           {1920, 8192, kNormTiles, false}, {1152, 14336, kNormTiles, false}, {1664, 10752, kNormTiles, true}, {3456, 5376, kNormTiles, true}, {16384, 5120, kNormTiles, true},
+                           {1024, 4096, kNormOutputTiles, false}, {2048, 2560, kNormOutputTiles, true}, {2048, 4096, kNormOutputTiles, true}, {1920, 8192, kNormOutputTiles, true},
+                           {1024, 4096, kSwigluTiles, true}, {2048, 2560, kSwigluTiles, false}, {2048, 4096, kSwigluTiles, false}, {2048, 5120, kSwigluTiles, false}, {2304, 5120, kSwigluTiles, true},
+                           {1024, 2048, kSwigluTiles, false}, {1024, 4096, kSwigluOutputTiles, true}, {2048, 2560, kSwigluOutputTiles, false}, {2048, 3072, kSwigluOutputTiles, false},
+                           {2816, 2560, kSwigluOutputTiles, true}, {2048, 5120, kSwigluOutputTiles, true}};
     for (const Tiles& c : tiles)
-        CHECK(takes_large_tile(c.rows, c.cols, c.resident) == c.large, "128 x 128 tiles for %lld x %lld, %d resident", (long long)c.rows, (long long)c.cols, c.resident);
+        CHECK(takes_large_tile(c.rows, c.cols, c.range) == c.large, "128 x 128 tiles for %lld x %lld, from %lld", (long long)c.rows, (long long)c.cols, (long long)c.range.least);
 }
 
 int main() {

@@ -450,14 +450,18 @@ struct SmallGrid {
     bool xcd_ranges;
     bool stacked;                           // lanes that follow each other one above the other instead of side by side
 };
-// quantizes: for the quantize kernel (and not those that compute what they write as codes)
-inline SmallGrid small_grid(int64_t rows, int64_t cols, bool quantizes = false) {
+// quantizes: for the quantize kernel (and not those that compute what they write as codes); transposed: with the transposed copy.
+// Codes alone share lines only where the rows do not start at them, and stacked lanes only make their stores narrower.  RMSNorm codes, three sets of
+// buffers in turn, side by side in launch order / in XCD ranges / stacked so: 357 x 16064 5.6 / 5.5 / 6.3 us, 2571 x 8448 14.2 / 13.6 / 15.8,
+// 6762 x 2752 12.6 / 12.4 / 14.7, 10134 x 3840 21.0 / 21.6 / 24.2, 12005 x 7488 44.7 / 46.6 / 50.6, 13543 x 9984 71.3 / 83.2 / 86.6;  rows beside the lines 9254 x 7448 49.9 / 42.5 / 44.0,
+// 10043 x 14456 156 / 114 / 114.
+inline SmallGrid small_grid(int64_t rows, int64_t cols, bool quantizes, bool transposed) {
     SmallGrid g;
     g.rows = (unsigned)((rows + kSmallRows - 1) / kSmallRows);
     g.cols = (unsigned)((cols + kSmallCols - 1) / kSmallCols);
     g.blocks = (g.rows * g.cols + kSmallXcds - 1) / kSmallXcds * kSmallXcds;
     g.first = 0;
-    g.xcd_ranges = cols % 64 != 0 || (g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
+    g.xcd_ranges = cols % 64 != 0 || ((transposed || rows * cols <= 20000000) && g.cols > kSmallXcds && g.cols % kSmallXcds != 0);
     // Lanes side by side / stacked, quantize and RMSNorm codes: 1024 x 1024 3.1 / 3.3 and 3.4 / 3.8 us, 4133 x 5120 20.1 / 22.3 and 20.5 /
     // 22.7, two sets of buffers in turn 8100 x 7168 41.3 / 48.6 and 42.7 / 50.0.  Once tensor and codes (4 bytes an element) crowd the 256 MB memory-side
     // cache, stacked lanes take less.  Absmax and quantize of four tensors in turn:
@@ -466,7 +470,7 @@ inline SmallGrid small_grid(int64_t rows, int64_t cols, bool quantizes = false) 
     //     9579 x 11200 149.4 / 140.6;  odd widths   6001 x 6001 51.4 / 58.0, 16001 x 8001 189.5 / 194.8, 12001 x 16001 313.9 / 311.2
     // RMSNorm codes, millions of elements 40 to 50 0.92, 60 to 65 0.98, more 1.00 to 1.03, but of odd widths 0.98 to 0.99 throughout;  SwiGLU codes, 6
     // bytes an element, 50 to 60 0.98, more 0.99 to 1.01.
-    g.stacked = cols % 8 == 0 && rows * cols > (int64_t)(quantizes && cols % 64 != 0 ? 40000000 : 66000000);
+    g.stacked = transposed && cols % 8 == 0 && rows * cols > (int64_t)(quantizes && cols % 64 != 0 ? 40000000 : 66000000);
     return g;
 }
 // launch(grid, workgroups of this launch), once or as often as the launch limit asks for

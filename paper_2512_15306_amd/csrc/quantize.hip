@@ -215,7 +215,7 @@ static QuantTensor quant_tensor(const QuantJob& j, QuantKind kind) {
     } else if (kind == kQuantTile) {
         t.blocks = (unsigned)((j.rows / kTileRows) * (j.cols / kTileCols));
     } else {
-        t.grid = small_grid(j.rows, j.cols, true);
+        t.grid = small_grid(j.rows, j.cols, true, true);
         t.blocks = t.grid.blocks;
     }
     return t;

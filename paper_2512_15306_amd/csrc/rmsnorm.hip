@@ -649,7 +649,7 @@ static void launch_apply(const uint16_t* res, const uint16_t* w, const float* rs
         hipLaunchKernelGGL(rmsnorm_apply_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kRnThreads), 0, stream,
                            res, w, rstd, M, C, d_qscale, q, q_t, y);
     } else {
-        small_launches(small_grid(M, C), [&](const SmallGrid& g, unsigned blocks) {
+        small_launches(small_grid(M, C, false, q_t != nullptr), [&](const SmallGrid& g, unsigned blocks) {
             if (q_t) hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, true>), dim3(blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
             else hipLaunchKernelGGL((rmsnorm_apply_fp8_small_kernel<QFMT, false>), dim3(blocks), dim3(kTileThreads), 0, stream, res, w, rstd, M, C, d_qscale, q, q_t, y, g, row_stride, band_stride);
         });

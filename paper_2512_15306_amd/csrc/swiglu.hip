@@ -579,7 +579,7 @@ static int launch_fwd_fp8(const uint16_t* gu, int64_t M, int64_t I, uint16_t* h,
         hipLaunchKernelGGL(swiglu_fwd_fp8_narrow_kernel<QFMT>, dim3((unsigned)((M + kNarrowRows - 1) / kNarrowRows)), dim3(kSwThreads), 0, stream,
                            gu, M, I, h, d_qscale, q, q_t);
     } else {
-        small_launches(small_grid(M, I), [&](const SmallGrid& g, unsigned blocks) {
+        small_launches(small_grid(M, I, false, q_t != nullptr), [&](const SmallGrid& g, unsigned blocks) {
             if (q_t) hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, true>), dim3(blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
             else hipLaunchKernelGGL((swiglu_fwd_fp8_small_kernel<QFMT, false>), dim3(blocks), dim3(kTileThreads), 0, stream, gu, M, I, h, d_qscale, q, q_t, g, row_stride, band_stride);
         });

@@ -69,8 +69,8 @@ static void check_bands(unsigned gr, unsigned gc, unsigned band) {
 
 // The 64 x 128-tile kernels: every tile once, whatever the launches are cut into; no id but the padding ones without a tile, id 0
 // with one (it stores the scale); on ragged pitches each XCD's ids (congruent modulo 8) on one contiguous range of the walk.
-static void check_small(int64_t rows, int64_t cols) {
-    const SmallGrid g = small_grid(rows, cols);
+static void check_small(int64_t rows, int64_t cols, bool transposed) {
+    const SmallGrid g = small_grid(rows, cols, false, transposed);
     CHECK(g.rows == (unsigned)((rows + 63) / 64) && g.cols == (unsigned)((cols + 127) / 128) && g.first == 0, "%lld x %lld", (long long)rows, (long long)cols);
     CHECK(g.blocks % 8 == 0 && g.blocks >= g.rows * g.cols && g.blocks < g.rows * g.cols + 8, "%lld x %lld: %u workgroups", (long long)rows, (long long)cols, g.blocks);
     std::vector<int> seen((size_t)g.rows * g.cols, 0), in_launches(g.blocks, 0);
@@ -225,7 +225,13 @@ static void check_code_tiles() {
     const Case cases[] = {{16221, 4296, true, true}, {9579, 11200, true, true}, {12446, 5904, true, true}, {11001, 3912, true, true}, {12001, 5000, true, true},
                           {9001, 4008, true, false}, {8101, 4416, true, false}, {8100, 7168, true, false}, {4133, 5120, true, false}, {1777, 2730, true, false},
                           {16001, 8001, true, false}, {12545, 8008, false, true}, {12001, 5000, false, false}, {12545, 8001, false, false}, {1777, 960, false, false}};
-    for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
+    for (const Case& c : cases) CHECK(small_grid(c.rows, c.cols, c.quantizes, true).stacked == c.stacked, "lanes for %lld x %lld (quantize %d)", (long long)c.rows, (long long)c.cols, c.quantizes);
+    struct Alone { int64_t rows, cols; bool ranges; };          // without the transposed copy
+    const Alone alone[] = {{13543, 9984, false}, {12005, 7488, false}, {10134, 3840, false}, {357, 16064, true}, {6762, 2752, true}, {9254, 7448, true}, {10043, 14456, true}, {12001, 5001, true}};
+    for (const Alone& c : alone) {
+        const SmallGrid g = small_grid(c.rows, c.cols, false, false);
+        CHECK(g.xcd_ranges == c.ranges && !g.stacked, "codes alone of %lld x %lld", (long long)c.rows, (long long)c.cols);
+    }
     struct Tiles { int64_t rows, cols; LargeTiles range; bool large; };
     const Tiles tiles[] = {{1024, 4096, kQuantizeTiles, true}, {1024, 4100, kQuantizeTiles, false}, {1024, 2048, kQuantizeTiles, false}, {1920, 8192, kQuantizeTiles, true},
                            {1024, 4096, kNormTiles, false}, {2048, 2560, kNormTiles, false}, {2048, 4096, kNormTiles, false}, {2432, 5120, kNormTiles, true}, {2816, 4480, kNormTiles, false},
@@ -263,7 +269,7 @@ int main() {
         if (most) setenv("LLMQ_MAX_WORKGROUPS", most, 1);
         else unsetenv("LLMQ_MAX_WORKGROUPS");
         for (int64_t r : {1, 64, 65, 130, 640, 1025, 5000})
-            for (int64_t c : {1, 24, 128, 129, 192, 1000, 1024, 1152, 1300, 4097, 9000}) check_small(r, c);
+            for (int64_t c : {1, 24, 128, 129, 192, 1000, 1024, 1152, 1300, 4097, 9000}) { check_small(r, c, true); check_small(r, c, false); }
     }
     unsetenv("LLMQ_MAX_WORKGROUPS");
     const char* modes[] = {nullptr, "1", "a2", "a3", "a5", "a16", "0"};

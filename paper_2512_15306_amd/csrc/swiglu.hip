@@ -106,7 +106,7 @@ __device__ __forceinline__ v4u swiglu8_as(const v4u& g, const v4u& u) {
 __device__ __attribute__((noinline)) v4u swiglu8_rare(v4u g, v4u u) { return swiglu8_as<false>(g, u); }
 // CALL_RARE: the rare half as a call instead of in the kernel's code, of which it would be half.  Forward with h, aligned shapes, in the code / called:
 // 1536 x 1408 8.8 / 8.7 us, 8192 x 256 8.6 / 8.3, 1024 x 3072 9.4 / 9.1, 1.5 % on average from half a million to 8 million elements and nothing
-// elsewhere; in the guarded kernels, whose patches are loaded between branches, the call costs 1 %.
+// elsewhere; codes without the transposed copy 4096 x 9216 39.3 / 36.8, 8960 x 4992 45.0 / 42.0, 8704 x 4224 39.2 / 37.5, on average 0.5 % above 16 million elements; in the guarded kernels, whose patches are loaded between branches, the call costs 1 %.
 template <bool CALL_RARE = false>
 __device__ inline v4u swiglu8(const v4u& g, const v4u& u) {
     if (__builtin_expect(gates_normal(g), 1)) return swiglu8_as<true>(g, u);
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kSwThreads) void swiglu_fwd_patch_kernel(
             u[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(src + (int64_t)i * 2 * I + I));
         }
 #pragma unroll
-        for (int i = 0; i < PR; ++i) o[i] = swiglu8<AMAX && !STREAM>(g[i], u[i]);
+        for (int i = 0; i < PR; ++i) o[i] = swiglu8<!STREAM>(g[i], u[i]);
         if constexpr (WRITE_H) {
             uint16_t* dst = h + r0 * I + c0;
 #pragma unroll

@@ -341,41 +341,49 @@ __device__ inline void with_guard(bool guard, F body) {
 // of which rows_left rows and cols_left columns exist.  Patches of several tensors that are guarded alike are requested together: the guards'
 // branches, one patch after the other, would wait for each patch before the next one is requested (SwiGLU backward, 9001 x 6001: 155 us
 // patch by patch, 131 so; forward 85 / 73).
-template <int PR>
+// SHARED: one row, which the tiles above and below read too, so its loads leave it in the caches (RMSNorm codes behind the forward pass that writes
+// their input, the weight read past the caches / so: 4133 x 5120 61.4 / 58.2 us for both calls, 3001 x 5128 47.2 / 44.7, 8263 x 7168 155.8 / 151.7).
+template <int PR, bool SHARED>
 struct Patch {
+    static constexpr int rows = PR;
     v4u (&in)[PR];
     const uint16_t* src;
     int64_t ld;
 };
 template <int PR>
-__device__ inline Patch<PR> patch(v4u (&in)[PR], const uint16_t* src, int64_t ld) { return Patch<PR>{in, src, ld}; }
-template <int PR>
-__device__ inline void request_patch(const Patch<PR>& p, int drop, int64_t rows_left) {
+__device__ inline Patch<PR, false> patch(v4u (&in)[PR], const uint16_t* src, int64_t ld) { return Patch<PR, false>{in, src, ld}; }
+__device__ inline Patch<1, true> shared_row(v4u (&in)[1], const uint16_t* src) { return Patch<1, true>{in, src, 0}; }
+template <int PR, bool SHARED>
+__device__ inline void request_patch(const Patch<PR, SHARED>& p, int drop, int64_t rows_left) {
 #pragma unroll
-    for (int i = 0; i < PR; ++i) p.in[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u_at2*>(p.src - drop + (int64_t)(i < rows_left ? i : 0) * p.ld));
+    for (int i = 0; i < PR; ++i) {
+        const v4u_at2* src = reinterpret_cast<const v4u_at2*>(p.src - drop + (int64_t)(i < rows_left ? i : 0) * p.ld);
+        if constexpr (SHARED) p.in[i] = *src;
+        else p.in[i] = __builtin_nontemporal_load(src);
+    }
 }
-template <int PR>
-__device__ inline void shift_patch(const Patch<PR>& p, int drop, int64_t rows_left) {
+template <int PR, bool SHARED>
+__device__ inline void shift_patch(const Patch<PR, SHARED>& p, int drop, int64_t rows_left) {
 #pragma unroll
     for (int i = 0; i < PR; ++i) p.in[i] = i < rows_left ? shift_elements(p.in[i], drop) : v4u{0, 0, 0, 0};
 }
-template <int PR>
-__device__ inline void load_patch_by_elements(const Patch<PR>& p, int64_t rows_left, int64_t cols_left) {
+template <int PR, bool SHARED>
+__device__ inline void load_patch_by_elements(const Patch<PR, SHARED>& p, int64_t rows_left, int64_t cols_left) {
 #pragma unroll
     for (int i = 0; i < PR; ++i) p.in[i] = load8_by_elements(p.src + (int64_t)i * p.ld, i < rows_left ? cols_left : 0);
 }
-template <int PR>
-__device__ inline void zero_patch(const Patch<PR>& p) {
+template <int PR, bool SHARED>
+__device__ inline void zero_patch(const Patch<PR, SHARED>& p) {
 #pragma unroll
     for (int i = 0; i < PR; ++i) p.in[i] = v4u{0, 0, 0, 0};
 }
 // (of patches of which a row and a column exist)
-template <int... PR>
-__device__ inline void load_patches_upto(int64_t c0, int64_t rows_left, int64_t cols_left, const Patch<PR>&... p) {
+template <class... P>
+__device__ inline void load_patches_upto(int64_t c0, int64_t rows_left, int64_t cols_left, const P&... p) {
     if (cols_left >= 8 || c0 >= 8) {
         const int drop = cols_left >= 8 ? 0 : 8 - (int)cols_left;
         (request_patch(p, drop, rows_left), ...);
-        if (((rows_left < PR) || ...) || drop != 0) (shift_patch(p, drop, rows_left), ...);
+        if (((rows_left < P::rows) || ...) || drop != 0) (shift_patch(p, drop, rows_left), ...);
     } else {
         (load_patch_by_elements(p, rows_left, cols_left), ...);
     }
@@ -383,8 +391,8 @@ __device__ inline void load_patches_upto(int64_t c0, int64_t rows_left, int64_t 
 // The same of a tile's lanes, whose patches may lie beside the tensor.  Those are zeros at once: as loads of no element of any row, one guard
 // after the other, they were what a small launch waited for (patch by patch / requested together / so: RMSNorm codes 1652 x 1024 4.29 / 4.57 / 3.82 us,
 // 2275 x 256 4.14 / 4.48 / 3.72; SwiGLU codes 161 x 8192 6.04 / 6.26 / 5.14, 1447 x 856 6.69 / 6.34 / 5.31).
-template <int... PR>
-__device__ inline void load_tile_patches_upto(int64_t c0, int64_t rows_left, int64_t cols_left, const Patch<PR>&... p) {
+template <class... P>
+__device__ inline void load_tile_patches_upto(int64_t c0, int64_t rows_left, int64_t cols_left, const P&... p) {
     if (rows_left > 0 && cols_left > 0) load_patches_upto(c0, rows_left, cols_left, p...);
     else (zero_patch(p), ...);
 }

@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kTileThreads) void rmsnorm_apply_fp8_small_kernel(
         const int64_t rows_left = guard ? M - r0 : kSmallPatch, cols_left = guard ? C - c0 : 8;
         v4u in[kSmallPatch];
         v4u wv[1];
-        load_tile_patches_upto(c0, rows_left, cols_left, patch(in, res + r0 * C + c0, C), patch(wv, w + c0, 0));
+        load_tile_patches_upto(c0, rows_left, cols_left, patch(in, res + r0 * C + c0, C), shared_row(wv, w + c0));
         float rs[kSmallPatch];
 #pragma unroll
         for (int i = 0; i < kSmallPatch; ++i) rs[i] = i < rows_left ? rstd[r0 + i] : 0.0f;

@@ -109,7 +109,7 @@ int llmq_quantize_fp8(const void* x_bf16, int64_t rows, int64_t cols, const floa
  * The same with the transposed copy stored in slabs of 128 contraction bytes, the form the backward contractions
  * read fastest (LLMQ_LAYOUT_SLABS of llmq_fp8_gemm, there with rows = cols of x and T = rows of x):
  *   q_t byte of element (j, i) of the transposed tensor at (i / 128) * cols * 128 + j * 128 + i % 128.
- * A 128 x 256 tile of x is then one contiguous 32 KB piece of q_t instead of 256 pieces of 128 bytes.  rows must
+ * A 128 x 128 tile of x is then one contiguous 16 KB piece of q_t instead of 128 pieces of 128 bytes.  rows must
  * be a multiple of 128 and cols a multiple of 256 (LLMQ_ERR_SHAPE otherwise); q_t must not be NULL.
  */
 int llmq_quantize_fp8_slabs(const void* x_bf16, int64_t rows, int64_t cols, const float* d_scale, int fmt,
@@ -257,8 +257,8 @@ int llmq_fp8_linear_workspace_offsets(int64_t M, int64_t N, int64_t K, size_t of
 /* The transposed copies Xq_t, Wq_t, dYq_t are stored in slabs of 128 contraction bytes (LLMQ_LAYOUT_SLABS of the
  * contraction that reads them) instead of as plain transposed tensors, wherever the quantizer can write them so
  * (the untransposed tensor has a multiple of 128 rows and of 256 columns, less than 0x70000000 elements; other
- * tensors keep the plain form): a 128 x 256 tile of a tensor then lands as one contiguous 32 KB piece of its
- * transposed copy instead of 256 pieces of 128 bytes, and every K step of a backward contraction reads one
+ * tensors keep the plain form): a 128 x 128 tile of a tensor then lands as one contiguous 16 KB piece of its
+ * transposed copy instead of 128 pieces of 128 bytes, and every K step of a backward contraction reads one
  * contiguous piece per operand.  Results are the same bytes as without the flag.  Copies made under this flag can
  * only be reused (LLMQ_REUSE_*) by calls that carry it too (the producers that write FP8 directly make such
  * copies with llmq_swiglu_fwd_fp8_slabs and llmq_rmsnorm_apply_fp8_slabs), and copies made without it (or by

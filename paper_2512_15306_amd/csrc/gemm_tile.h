@@ -252,7 +252,7 @@ __device__ constexpr int row_swizzle(int row) { return (((row >> 1) & 3) << 1) |
 //   slabs   : K step by K step, byte (r, t) at (t / 128) rows 128 + r 128 + t % 128: each K step of all rows is one
 //             contiguous piece (T a multiple of 128).  The kernel reads it like `rows` with a row pitch of 128 bytes
 //             and rows x 128 bytes from one K step to the next; the tile kernel of the quantizer writes its transposed
-//             copy that way, a whole tile's transposed bytes as one contiguous 32 KB piece.
+//             copy that way, a whole tile's transposed bytes as one contiguous 16 KB piece.
 // How one operand slab sits in memory and in LDS, and how its MFMA fragments are read.
 //   TMAJOR = false: the operand is [rows, T], a slab is 64 NX rows of 128 B; LDS keeps the rows, 128 B
 //     each, the 16-byte chunk index XOR-ed with row_swizzle(row); a lane reads the 32 contiguous

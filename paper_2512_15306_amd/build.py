@@ -33,18 +33,29 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextr
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+def _registers(line: str):
+    """The vector and accumulator registers an instruction names, as (file, number)."""
+    found = {(f, int(n)) for f, n in re.findall(r"\b([av])(\d+)\b", line)}
+    for f, lo, hi in re.findall(r"\b([av])\[(\d+):(\d+)\]", line):
+        found.update((f, n) for n in range(int(lo), int(hi) + 1))
+    return found
+
+
 def check_accumulator_reads(src: str, asm: str) -> None:
     """The tile kernels write their MFMAs out as inline assembly, so the compiler does not know that an
     accumulator read must keep its distance from the MFMA that wrote it.  The kernels' own code keeps it: nothing
-    but MFMAs touches the accumulator registers (other than to zero them from an ordinary register) from the first MFMA to the wait states
-    behind the K loop (`s_nop 15`).  Code the register allocator adds on its own (copies between the register files, spills of
-    accumulators) would not, so any such instruction in that stretch of the generated assembly is a build error."""
+    but MFMAs touches the registers MFMAs write (accumulator registers, and in the largest tiles ordinary ones too) from the
+    first MFMA to the wait states behind the K loop (`s_nop 15`).  Code the register allocator adds on its own (copies between
+    the register files, spills of accumulators) would not, so any such instruction in that stretch of the generated assembly is
+    a build error.  Allowed is the zeroing of the accumulators, which may be repeated on the path of a single K step, behind the K
+    loop in the text: writes of an ordinary register to the accumulator file, and, in a block without MFMAs that only code in
+    front of the first MFMA jumps to, to the ordinary registers among the accumulators."""
     bad = []
     checked = 0
     for m in re.finditer(r"^(_ZN4llmq16gemm_tile_kernel\w*):[^\n]*\n(.*?)^\.Lfunc_end", asm, re.S | re.M):
         name, body = m.group(1), m.group(2)
         code = [l.split(";")[0].strip() for l in body.splitlines()]
-        code = [l for l in code if l and not l.endswith(":")]
+        code = [l for l in code if l and (not l.startswith(".") or l.startswith(".LBB")) and (not l.endswith(":") or l.startswith(".LBB"))]
         mfma = [i for i, l in enumerate(code) if l.startswith("v_mfma_")]
         if not mfma:
             continue                                  # the kernel that only adds up pieces
@@ -53,14 +64,28 @@ def check_accumulator_reads(src: str, asm: str) -> None:
         if drain is None:
             bad.append("%s: no wait states behind the last MFMA" % name)
             continue
-        for l in code[mfma[0]:drain]:
-            # (the zeroing of the accumulators, a write from an ordinary register, may be repeated on the path of a
-            # single K step, which follows the K loop in the text)
-            if re.fullmatch(r"v_accvgpr_write_b32 a\d+, v\d+", l):
+        accumulators = {("a", n) for n in range(256)}
+        for i in mfma:
+            accumulators |= _registers(code[i].split()[1])
+        label_at = {l[:-1]: i for i, l in enumerate(code) if l.endswith(":")}
+        jumps = [(i, label_at[l.split()[-1]]) for i, l in enumerate(code) if re.match(r"s_c?branch", l) and l.split()[-1] in label_at]
+        zeroing, end = set(), mfma[0]                 # lines of blocks that may zero accumulators
+        for i in range(mfma[0], drain):
+            if not code[i].endswith(":") or not re.match(r"s_branch|s_endpgm", code[i - 1]):
                 continue
-            if not l.startswith("v_mfma_") and re.search(r"\ba(\d+|\[\d+:\d+\])", l):
-                bad.append("%s: %s" % (name, l))
-                break
+            end = next((k for k in range(i + 1, drain) if code[k].endswith(":") or re.match(r"s_c?branch", code[k])), drain)
+            if all(k < mfma[0] for k, to in jumps if to == i) and not any(i < k < end for k in mfma):
+                zeroing.update(range(i, end))
+        for i in range(mfma[0], drain):
+            l = code[i]
+            if l.startswith("v_mfma_") or l.endswith(":") or not (_registers(l) & accumulators):
+                continue
+            if re.fullmatch(r"v_accvgpr_write_b32 a\d+, v\d+", l) and (i in zeroing or ("v", int(l.split("v")[-1])) not in accumulators):
+                continue
+            if i in zeroing and re.match(r"v_mov_b(32|64)_e32 ", l):
+                continue
+            bad.append("%s: %s" % (name, l))
+            break
     if not checked:
         raise RuntimeError("%s: no tile kernel found in the generated assembly" % src)
     if bad:

@@ -329,6 +329,23 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
     return best;
 }
 
+TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
+                   GemmScratch scratch) {
+    const size_t scratch_bytes = (scratch.ptr && !ta && !tb && !bf16) ? scratch.bytes : 0;
+    TilePlan base{0, 0, kNoEdge};
+    double scale = 1.0;
+    const TileChoice tc = choose_tile(R, C, T, num_cus, scratch_bytes, bf16);
+    if (tc.ni) {
+        base = {tc.ni, tc.nj, kNoEdge};
+        const SplitChoice sc = choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch_bytes);
+        scale = sc.cost_us / sc.whole_cost_us;
+    } else if (!ta || tb) {
+        const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, with_amax, bf16);
+        base = {ec.ni, ec.nj, ec.edge};
+    }
+    return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, base, scale);
+}
+
 template <int FA, int FB>
 static void launch_mini(int side, const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
                         void* c, int accumulate, unsigned* amax, hipStream_t stream, bool slabs_a, bool slabs_b) {
@@ -357,8 +374,11 @@ static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C,
         const int side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, num_cus, shared_us);
         if (side) { launch_mini<FA, FB>(side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
     }
-    if (fits && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b)) return;
-    if (fits && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b)) return;
+    if (fits) {
+        const TilePlan tile = plan_tile(R, C, T, num_cus, false, false, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, scratch);
+        if (tile.ni && tile.edge == kNoEdge && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile)) return;
+        if (tile.ni && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b, tile)) return;
+    }
     if constexpr (FA == kFmtBf16) {
         const int64_t n = R * C;
         int64_t blocks = (n + 255) / 256;

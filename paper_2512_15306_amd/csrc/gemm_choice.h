@@ -19,6 +19,10 @@ inline int resident_slots(int num_cus, int ni, int nj) {
     return (num_cus / kXcds) * kXcds * ((ni == 2 && nj == 2) ? 2 : 1);
 }
 
+struct TileChoice {
+    int ni, nj;       // 0, 0: no tuned tile divides the problem
+};
+
 struct EdgeChoice {
     int ni, nj;       // 0, 0: the generic kernel
     int edge;         // kEdge or kEdgeUnaligned
@@ -116,6 +120,69 @@ inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus,
     return best;
 }
 
+// ---- A second look at problems of many tiles.
+//
+// A tile and its form: kNoEdge where the tile divides the problem, kEdge where it is guarded (or a large tile adds to the output).
+struct TilePlan { int ni, nj, edge; };       // ni = 0: the generic kernel
+
+// Microseconds of a contraction of `tiles` tiles: a launch, then for every round of tiles the prologue and output of a tile and its K steps.  A last
+// round that is not full takes less than a full one: under the power cap the CUs that have a tile run faster.  One table for FP8 and BF16 (a step is
+// 128 bytes of the contraction in both).  Fitted to 515 shapes of 700 to 16384 rows and columns and T of 256 to 16384 in all layouts, every tile forced on
+// every shape: 9 % root mean square, most of it at T = 256 to 512.
+inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accumulate, int64_t slots) {
+    struct Fit { int ni, nj; double whole_tile, whole_step, guarded_tile, guarded_step; };
+    static const Fit fits[] = {{4, 5, 9.5, 1.507, 11.8, 1.532}, {5, 4, 8.6, 1.500, 11.2, 1.508}, {4, 4, 7.4, 1.243, 9.2, 1.268}, {3, 4, 5.9, 0.984, 7.3, 1.009},
+                               {4, 3, 5.7, 1.009, 0, 0},        {3, 3, 4.2, 0.870, 0, 0},        {4, 2, 4.2, 0.788, 5.5, 0.822}, {2, 4, 4.5, 0.794, 5.5, 0.813},
+                               {3, 2, 2.2, 0.616, 2.7, 0.618},  {2, 3, 4.2, 0.695, 0, 0},        {2, 2, 3.2, 0.829, 4.1, 0.873}};
+    const double rest = (double)(tiles % slots) / (double)slots;
+    const double rounds = (double)(tiles / slots) + (rest > 0 ? 0.69 + 0.31 * rest : 0.0);
+    for (const Fit& f : fits)
+        if (f.ni == p.ni && f.nj == p.nj) {
+            const bool guarded = p.edge != kNoEdge;
+            return 3.1 + rounds * ((guarded ? f.guarded_tile : f.whole_tile) + (double)steps * (guarded ? f.guarded_step : f.whole_step) +
+                                   (accumulate ? 2.6 * p.ni * p.nj / 16.0 : 0.0));
+        }
+    return 0.0;
+}
+
+// What the models of choose_tile and choose_edge_tile do not weigh: the large tiles 256 x 320 (4 x 5) and 320 x 256 (5 x 4), and guarded tiles of 256 x 256
+// and 192 x 256 also where a smaller tile divides the problem.  Returns `base`, their choice, or a tile that tile_us has 2 % or more ahead of it.
+//   Large tiles: an eighth fewer operand bytes per product from L2 to LDS and from LDS to registers, which is what the power cap leaves the matrix cores
+//   short of, and other counts of tiles.  FP8 4 x 4 / large, microseconds: 16384 x 5120 x 5120 (5 / 4 whole rounds) 295.7 / 288.4;  55296 x 5120 x 16384 3103 /
+//   3001;  8192 x 5120 x 13824 (2.5 / 2 rounds) 402 / 360;  4096 x 5120 x 3072 (1.25 / 1 round) 68.0 / 48.9, BF16 (256 x 128 tiles before) 120 / 89;
+//   4096 x 2560 x 4096 (one round of either) 40.3 / 47.9.
+//   Guarded tiles, 128 x 128 that divide the problem / guarded: 4480 x 2176 x 8320 94.6 / 68.2 (192 x 256), 1792 x 7552 x 4096 60.2 / 49.8 (256 x 256),
+//   3584 x 5632 x 7680 142.7 / 109.5 (256 x 320), 4480 x 13184 x 3072 182 / 142 (320 x 256).
+// Over the 515 shapes: 3.7 % faster than without on average, none more than 1 % slower.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
+// scale: what sharing out the last round of `base` saves of its time.  LLMQ_GEMM_ANY_TILE=IxJ (tests): that tile, guarded if need be; 0: `base`.
+inline TilePlan better_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, const TilePlan& base, double scale) {
+    // 32-bit offsets from the first row of a tile of up to 320; whole 16-byte chunks; A T-major alone has no guarded form
+    if ((ta && !tb) || T < 16 || T >= (1ll << 22) || C >= (1ll << 22)) return base;
+    if (!(ta ? R % 16 == 0 : slabs_a || T % 16 == 0) || !(tb ? C % 16 == 0 : slabs_b || T % 16 == 0)) return base;
+    auto form = [&](int ni, int nj) {
+        const bool guarded = R % (64 * ni) != 0 || C % (64 * nj) != 0 || T % BK != 0 || (accumulate && ni * nj > 16);
+        return TilePlan{ni, nj, guarded ? kEdge : kNoEdge};
+    };
+    const char* force = tuning_env("LLMQ_GEMM_ANY_TILE");
+    if (force && force[0] >= '2' && force[0] <= '5' && force[1] == 'x') return form(force[0] - '0', force[2] - '0');
+    if (base.ni == 0 || T < 2 * BK) return base;                          // (the table starts there)
+    if (force || tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_SPLIT")) return base;       // (tests of the other tiles)
+    auto us = [&](const TilePlan& p) -> double {
+        const int64_t tiles = ((R + 64 * p.ni - 1) / (64 * p.ni)) * ((C + 64 * p.nj - 1) / (64 * p.nj));
+        return tiles > kMaxWorkgroups ? 0.0 : tile_us(p, tiles, (T + BK - 1) / BK, accumulate, resident_slots(num_cus, p.ni, p.nj));
+    };
+    if (((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2 && base.ni == 2 && base.nj == 2) return base;       // four LDS stages
+    TilePlan best = base;
+    double best_us = us(base) * scale * 0.98;
+    const int others[4][2] = {{4, 5}, {5, 4}, {4, 4}, {3, 4}};
+    for (const auto& o : others) {
+        const TilePlan p = form(o[0], o[1]);
+        const double t = us(p);
+        if (t > 0.0 && t < best_us) { best = p; best_us = t; }
+    }
+    return best;
+}
+
 // What the small tiles are compared with, in microseconds: the 128 x 128 tile with four LDS stages, whole or with guarded edges, or the
 // generic kernel where that is the faster of the two.
 inline double other_tiles_us(int64_t R, int64_t C, int64_t T, bool accumulate, bool with_amax, bool bf16, int num_cus) {
@@ -163,7 +230,7 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
     const int64_t tiles128 = ((R + 127) / 128) * ((C + 127) / 128);
     if (tiles128 > ((int64_t)1 << 20)) return 0;                          // (32 x 32 tiles then fit a launch)
     if (const char* e = tuning_env("LLMQ_GEMM_MINI")) { const int side = atoi(e); return side == 32 || side == 64 ? side : 0; }
-    if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
+    if (tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_ANY_TILE") || tuning_env("LLMQ_GEMM_DEEP") || tuning_env("LLMQ_GEMM_SPLIT")) return 0;     // (tests of the other kernels)
     if (tiles128 > num_cus) return 0;
     const double slower = shared_us > 0.0 && (R + C) * T > 100000000 ? 1.25 : 1.0;
     double best = (shared_us > 0.0 ? shared_us : other_tiles_us(R, C, T, accumulate, with_amax, bf16, num_cus)) - 0.2;       // (a margin for the models' errors)

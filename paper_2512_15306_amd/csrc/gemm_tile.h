@@ -5,10 +5,10 @@
 //   C[r,c] = bf16( (sum_t A[r,t] * B[c,t]) / (sA * sB) ),   A [R,T] fp8, B [Cn,T] fp8.
 //
 // Tuned kernel (template on the wave tile NI x NJ in units of 32: workgroup tile BM x BN with
-// BM = 64 NI, BN = 64 NJ, both in {128, 192, 256}; R % BM == 0, Cn % BN == 0, T % 128 == 0)
+// BM = 64 NI, BN = 64 NJ, both in {128, 192, 256}, and 256 x 320 and 320 x 256; R % BM == 0, Cn % BN == 0, T % 128 == 0)
 //   - one workgroup of 4 wavefronts (2 x 2) per output tile, one workgroup per CU; a wavefront owns
 //     2 NI x 2 NJ blocks of v_mfma_f32_16x16x128_f8f6f4 with fp32 accumulators (256 registers per lane at
-//     4 x 4: the whole accumulator file);
+//     4 x 4: the whole accumulator file; 4 x 5 and 5 x 4 keep a fifth of theirs in ordinary registers);
 //   - K advances 128 bytes per step, one MFMA deep; the A and B slabs (BM / BN rows x 128 B) go from global
 //     memory straight into LDS with buffer_load ... lds (16 bytes per lane, no VGPR staging), double buffered;
 //   - LDS rows are 128 B; the 16-byte chunk index is XOR-ed with a function of the row (row_swizzle), applied
@@ -178,6 +178,13 @@ __device__ inline void lds_barrier_in_flight() {
 constexpr int kFmtBf16 = 2;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// The accumulator file holds 64 blocks of 16 x 16 (256 registers per lane), a wave tile of 8 x 8.  The blocks beyond the
+// eighth row or column of a 4 x 5 or 5 x 4 tile (16 of its 80) are kept in ordinary vector registers, where a tile that size is bound by what
+// the kernel has of them: 64 registers of accumulators, 144 of fragments and about 40 of addresses are 255 of 256, without a spill in the K loop (the
+// epilogues that add to the output need more than that in the unguarded form, so these tiles add in the guarded one).  What they are for:
+// better_tile in gemm_choice.h.
+constexpr int kBlocksInFile = 8;
+
 // The accumulators of a wave tile of MI x MJ blocks of 16 x 16, four registers per block and lane.
 template <int MI, int MJ>
 struct BlockAcc {
@@ -199,7 +206,8 @@ __device__ inline void static_for(F&& f) {
 // v_mfma_f32_16x16x128_f8f6f4 rather than 32x32x64: on random FP8 bits, where the board's power cap and not the
 // issue rate sets the speed, a register-only loop of the 16x16x128 form sustains 4.22 PFLOP/s against 3.83-3.85
 // for 32x32x64 (both 4.98 on constant bits): it adds 128 products per accumulator update instead of 64.
-template <int FA, int FB>
+// IN_V: the accumulator block sits in ordinary vector registers (see kBlocksInFile).
+template <int FA, int FB, bool IN_V>
 __device__ inline void mma_block(v4f& c, const v8i& a, const v8i& b) {
     static_assert((FA == kFmtBf16) == (FB == kFmtBf16), "BF16 operands come in pairs");
     // The instructions are written out so that the accumulator can be constrained to the accumulator register file
@@ -213,10 +221,17 @@ __device__ inline void mma_block(v4f& c, const v8i& a, const v8i& b) {
         // two v_mfma_f32_16x16x32_bf16, one per 16-byte half of the fragments
         const v4i a_lo = {a[0], a[1], a[2], a[3]}, a_hi = {a[4], a[5], a[6], a[7]};
         const v4i b_lo = {b[0], b[1], b[2], b[3]}, b_hi = {b[4], b[5], b[6], b[7]};
-        asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_lo), "v"(a_lo));
-        asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_hi), "v"(a_hi));
-    } else {
+        if constexpr (IN_V) {
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(b_lo), "v"(a_lo));
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(b_hi), "v"(a_hi));
+        } else {
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_lo), "v"(a_lo));
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_hi), "v"(a_hi));
+        }
+    } else if constexpr (IN_V) {
         // cbsz / blgp: formats of the first / second operand
+        asm("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:%3 blgp:%4" : "+v"(c) : "v"(b), "v"(a), "n"(FB), "n"(FA));
+    } else {
         asm("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:%3 blgp:%4" : "+a"(c) : "v"(b), "v"(a), "n"(FB), "n"(FA));
     }
 }
@@ -232,7 +247,7 @@ __device__ inline void mma_quadrant(BlockAcc<MI, MJ>& acc, const v8i (&a)[HI], c
     static_for<HI * HJ>([&](auto tag) {
         constexpr int m = decltype(tag)::value;
         constexpr int i = J_OUTER ? m % HI : m / HJ, j = J_OUTER ? m / HI : m % HJ;
-        mma_block<FA, FB>(acc.t[I0 + i][J0 + j], a[i], b[j]);
+        mma_block<FA, FB, (I0 + i >= kBlocksInFile || J0 + j >= kBlocksInFile)>(acc.t[I0 + i][J0 + j], a[i], b[j]);
         side(tag);
         __builtin_amdgcn_sched_barrier(0);
     });
@@ -270,16 +285,18 @@ template <int NX, bool TMAJOR>
 struct SlabShape {
     static constexpr int kRows = 64 * NX;                     // operand rows (output rows or columns) of the tile
     static constexpr int kUnits = kRows / 16;                 // T-major: 16-byte units per LDS row
-    static constexpr int kPeriod = NX == 4 ? 2 : NX == 2 ? 1 : 3;       // T-major: load instructions per pattern
+    static constexpr int kPeriod = NX == 4 ? 2 : NX == 2 ? 1 : NX;      // T-major: load instructions per pattern
     static constexpr int kPeriodRows = 64 * kPeriod / kUnits;           // T-major: slab rows per pattern
     static constexpr int kReadsPerFrag = TMAJOR ? 4 : 2;
     static constexpr int kLines = TMAJOR ? (kRows + 127) / 128 : 1;     // 128-byte lines per memory row of a slab
     // XOR mask of the 16-byte unit index of LDS row k.  One transposing read of 32 lanes touches 8 consecutive
     // rows x 2 neighbouring units (x 2 halves); the mask moves in steps of two units so that these 16 units fall
-    // into 16 different groups of four banks: rows are 64 / 48 / 32 banks long for NX = 4 / 3 / 2.
+    // into 16 different groups of four banks: rows are 80 / 64 / 48 / 32 banks long for NX = 5 / 4 / 3 / 2.
     // The two halves of 16 lanes of such a read sit 32 LDS rows apart (K quarters of the 16x16x128 fragment), i.e. a
     // multiple of 64 banks: bit 5 of the row goes into the lowest bit of the mask to separate them.
     __device__ static int swizzle_of_row(int k) { return ((NX == 4 ? k & 7 : NX == 2 ? (k >> 1) & 3 : (k >> 2) & 1) << 1) | ((k >> 5) & 1); }
+    // Masks of NX = 5 and 3 are below four units, so the units of a row keep their distance of four or more.
+    static constexpr int kMasked = NX == 4 || NX == 2 ? 8 : 4;
 };
 
 // MODE: kWholeTiles ignores the plan and computes one whole tile per workgroup, with nothing of the sharing logic
@@ -429,9 +446,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         const int unit = 64 * m + lane, row = unit / S::kUnits, col = unit % S::kUnits;
         return row * ld + ((col ^ S::swizzle_of_row(row + 32 * wave)) << 4);      // the wave moves slab rows [32 wave, 32 wave + 32)
     };
-    int ld_voffA[3], ld_voffB[3];
+    int ld_voffA[5], ld_voffB[5];
 #pragma unroll
-    for (int m = 0; m < 3; ++m) {
+    for (int m = 0; m < 5; ++m) {
         ld_voffA[m] = TA ? (m < SA::kPeriod ? tmajor_voff(SA{}, m, ldA) : 0) : rows_voff(m & 1, ldA);
         ld_voffB[m] = TB ? (m < SB::kPeriod ? tmajor_voff(SB{}, m, ldB) : 0) : rows_voff(m & 1, ldB);
     }
@@ -567,19 +584,19 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
     for (int i = 0; i < MJ; ++i)
         tm_offB[i] = tm_row * BN + (((MJ * wc + i) ^ SB::swizzle_of_row(tm_row)) << 4) + ((lane & 1) << 3);
     // read number p of a fragment set: 8-byte quarter p % 4 of fragment p / 4
-    auto read_piece_tmajor = [&](const uint8_t* slab, const int* offs, int pitch, auto& f, auto piece) {
-        constexpr int p = decltype(piece)::value, i = p >> 2, q = p & 3;
-        const v2i r = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(slab + offs[i] + 8 * q * pitch));
+    auto read_piece_tmajor = [&](auto shape, const uint8_t* slab, const int* offs, auto first_block, int pitch, auto& f, auto piece) {
+        constexpr int p = decltype(piece)::value, i = p >> 2, q = p & 3, kMasked = decltype(shape)::kMasked, block = decltype(first_block)::value + i;
+        const v2i r = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(slab + offs[block % kMasked] + (block / kMasked) * (16 * kMasked) + 8 * q * pitch));
         f[i][2 * q] = r[0], f[i][2 * q + 1] = r[1];
     };
     // first_block: 0 or HI / HJ, the half of the wave tile's block rows / columns the set f is for
     auto read_pieceA = [&](uint8_t* slab, auto first_block, auto& f, auto piece) {
         constexpr int kFirst = decltype(first_block)::value;
-        if constexpr (TA) read_piece_tmajor(slab, tm_offA + kFirst, BM, f, piece); else read_piece_rows(slab, offA, kFirst, f, piece);
+        if constexpr (TA) read_piece_tmajor(SA{}, slab, tm_offA, IntTag<kFirst>{}, BM, f, piece); else read_piece_rows(slab, offA, kFirst, f, piece);
     };
     auto read_pieceB = [&](uint8_t* slab, auto first_block, auto& f, auto piece) {
         constexpr int kFirst = decltype(first_block)::value;
-        if constexpr (TB) read_piece_tmajor(slab, tm_offB + kFirst, BN, f, piece); else read_piece_rows(slab, offB, kFirst, f, piece);
+        if constexpr (TB) read_piece_tmajor(SB{}, slab, tm_offB, IntTag<kFirst>{}, BN, f, piece); else read_piece_rows(slab, offB, kFirst, f, piece);
     };
 
     // The accumulators start from a zero the compiler cannot see through: a known constant it would re-create
@@ -884,7 +901,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         // The staging of the accumulating epilogue below, with or without old values.  Widths that are multiples of 8
         // move 16 bytes per lane through a buffer that ends with the output's last row (pieces beside the output get an
         // offset outside it); other widths go element by element, neighbouring lanes on neighbouring columns.
-        constexpr int kSlots = 4 * NJ, kPitch = 32 * kSlots;
+        // (kSlots no divisor of 64, i.e. NJ = 5: rows of the stage are 16 bytes longer instead of rotated, which keeps them in
+        // different banks as well and needs one address register for all pieces of a row; the rotation modulo 20 takes one for each)
+        constexpr int kSlots = 4 * NJ;
+        constexpr bool kRest = kWave % kSlots != 0;
+        constexpr int kPitch = 32 * kSlots + (kRest ? 16 : 0);
         uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
         static_assert(32 * kPitch <= kSlabA && 32 * kPitch <= kSlabB - 16, "32 staged rows fit the start of any slab");
         const int row0 = tr * BM + wr * 32 * NI, col0 = tc * BN + wc * 32 * NJ;
@@ -895,9 +916,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
         const int piece0 = fr_q >> 1, unit_off = (fr_q & 1) * (16 * kSlots);
         const bool vector = Cn % 8 == 0;
         // the piece a lane moves first; the others of 32 rows lie kRowStep rows further down each
-        constexpr int kRowStep = kWave / kSlots, kPiecesPerLane = 32 * kSlots / kWave;
+        // (kSlots no divisor of 64: the last lanes have no piece, and of the last row step only the rows below 32 are there)
+        constexpr int kRowStep = kWave / kSlots, kPiecesPerLane = (32 + kRowStep - 1) / kRowStep;
         const int pr = lane / kSlots, sl = lane % kSlots;
-        const unsigned voff = 8 * sl < cols_left ? (unsigned)(pr * Cn + 8 * sl) * 2 : kOutOfRange;
+        const unsigned voff = 8 * sl < cols_left && (!kRest || pr < kRowStep) ? (unsigned)(pr * Cn + 8 * sl) * 2 : kOutOfRange;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             __builtin_amdgcn_sched_barrier(0);
@@ -907,22 +929,32 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                 uint8_t* srow = stage + row * kPitch + unit_off;
 #pragma unroll
                 for (int j = 0; j < MJ; ++j)
-                    *reinterpret_cast<v4f*>(srow + (((2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
+                    *reinterpret_cast<v4f*>(srow + ((kRest ? 2 * j + piece0 : (2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
             }
             __builtin_amdgcn_sched_barrier(0);
+            auto there = [&](int k) { return !kRest || (pr < kRowStep && pr + k * kRowStep < 32); };
+            auto offset = [&](int k) -> unsigned {
+                const unsigned off = voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2;
+                return kRest && k == kPiecesPerLane - 1 && !there(k) ? kOutOfRange : off;
+            };
             auto pieces = [&](auto with_old) __attribute__((always_inline)) {
                 constexpr bool OLD = decltype(with_old)::value;
-                v4u old[OLD ? kPiecesPerLane : 1];                           // all of them on their way before the first is needed
+                // all old values are on their way before the first is needed (kRest: four at a time, which is what there are registers for)
+                constexpr int kAtOnce = kRest ? 4 : kPiecesPerLane;
+#pragma unroll
+                for (int k0 = 0; k0 < kPiecesPerLane; k0 += kAtOnce) {
+                constexpr int kEnd = kPiecesPerLane;
+                v4u old[OLD ? kPiecesPerLane : 1];
+                if constexpr (kRest) __builtin_amdgcn_sched_barrier(0);
                 if constexpr (OLD) {
 #pragma unroll
-                    for (int k = 0; k < kPiecesPerLane; ++k) old[k] = __builtin_amdgcn_raw_buffer_load_b128(rsC, voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2, 0, 0);
+                    for (int k = k0; k < kEnd && k < k0 + kAtOnce; ++k) old[k] = __builtin_amdgcn_raw_buffer_load_b128(rsC, offset(k), 0, 0);
                 }
 #pragma unroll
-                for (int k = 0; k < kPiecesPerLane; ++k) {
+                for (int k = k0; k < kEnd && k < k0 + kAtOnce; ++k) {
                     const int r = pr + k * kRowStep;
-                    const uint8_t* src = stage + r * kPitch + (((sl + r) % kSlots) << 4);
+                    const uint8_t* src = stage + r * kPitch + ((kRest ? sl : (sl + r) % kSlots) << 4);
                     v4f y0 = *reinterpret_cast<const v4f*>(src), y1 = *reinterpret_cast<const v4f*>(src + 16 * kSlots);
-                    const unsigned off = voff + (unsigned)((i * 32 + k * kRowStep) * Cn) * 2;
                     if constexpr (OLD) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -933,11 +965,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                     }
                     const v2u w0 = __builtin_bit_cast(v2u, __builtin_convertvector(y0, bf16x4)), w1 = __builtin_bit_cast(v2u, __builtin_convertvector(y1, bf16x4));
                     const v4u out = {w0[0], w0[1], w1[0], w1[1]};
-                    if (i * 32 + r < rows_left && 8 * sl < cols_left) {
+                    if (i * 32 + r < rows_left && 8 * sl < cols_left && there(k)) {
 #pragma unroll
                         for (int w = 0; w < 4; ++w) edge_mag = pk_max_mag(edge_mag, out[w]);
                     }
-                    __builtin_amdgcn_raw_buffer_store_b128(out, rsC, off, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(out, rsC, offset(k), 0, 0);
+                }
                 }
             };
             if (vector) {
@@ -949,7 +982,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
 #pragma unroll
                 for (int cc = 0; cc < 32 * NJ; cc += kWave) {
                     if (cc >= cols_left) break;
-                    const int c = cc + lane;
+                    const int c = (32 * NJ) % kWave == 0 || cc + lane < 32 * NJ ? cc + lane : cols_left;        // (past the wave's columns: none)
                     const uint8_t* src = stage + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4;
                     const unsigned coff = c < cols_left ? (unsigned)(i * 32 * Cn + c) * 2 : kOutOfRange;
                     auto rows_from = [&](auto at_once, int r0) __attribute__((always_inline)) {
@@ -961,7 +994,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                             for (int k = 0; k < kRowsAtOnce; ++k) old[k] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(rsC, coff + (unsigned)((r0 + k) * Cn) * 2, 0, 0) << 16;
                         }
 #pragma unroll
-                        for (int k = 0; k < kRowsAtOnce; ++k) y[k] = *reinterpret_cast<const float*>(src + (r0 + k) * kPitch + ((((c >> 3) + r0 + k) % kSlots) << 4));
+                        for (int k = 0; k < kRowsAtOnce; ++k) y[k] = *reinterpret_cast<const float*>(src + (r0 + k) * kPitch + ((kRest ? c >> 3 : ((c >> 3) + r0 + k) % kSlots) << 4));
 #pragma unroll
                         for (int k = 0; k < kRowsAtOnce; ++k) {
                             if (accumulate) y[k] += __uint_as_float(old[k]);
@@ -1058,10 +1091,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                 for (int j = 0; j < MJ; ++j)
                     *reinterpret_cast<v4f*>(srow + (((2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
             }
-            v4f lo[kPiecesPerLane], hi[kPiecesPerLane];
+            // (a tile with accumulators in ordinary registers has room for half of the pieces at a time)
+            constexpr int kAtOnce = NI * NJ > 16 ? kPiecesPerLane / 2 : kPiecesPerLane;
 #pragma unroll
-            for (int k = 0; k < kPiecesPerLane; ++k) {
-                const int p = lane + k * kWave;
+            for (int k0 = 0; k0 < kPiecesPerLane; k0 += kAtOnce) {
+            v4f lo[kAtOnce], hi[kAtOnce];
+#pragma unroll
+            for (int k = 0; k < kAtOnce; ++k) {
+                const int p = lane + (k0 + k) * kWave;
                 const int r = p / kSlots, sl = p % kSlots;
                 const uint8_t* src = stage + r * kPitch + (((sl + r) % kSlots) << 4);
                 lo[k] = *reinterpret_cast<const v4f*>(src);
@@ -1069,10 +1106,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
             }
             if constexpr (V::kEpilogueFence) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = 0; k < kPiecesPerLane; ++k) {
+            for (int k = k0; k < k0 + kAtOnce; ++k) {
                 const int p = lane + k * kWave;
                 const int r = i * 32 + p / kSlots, sl = p % kSlots;
-                v4f y0 = lo[k], y1 = hi[k];
+                v4f y0 = lo[k - k0], y1 = hi[k - k0];
                 y0[0] += __uint_as_float(old[k][0] << 16);
                 y0[1] += __uint_as_float(old[k][0] & 0xFFFF0000u);
                 y0[2] += __uint_as_float(old[k][1] << 16);
@@ -1086,6 +1123,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
                 const bf16x4 o0 = __builtin_convertvector(y0, bf16x4), o1 = __builtin_convertvector(y1, bf16x4);
                 const v2u w0 = __builtin_bit_cast(v2u, o0), w1 = __builtin_bit_cast(v2u, o1);
                 *reinterpret_cast<v4u*>(cbase + (size_t)r * Cn + sl * 8) = v4u{w0[0], w0[1], w1[0], w1[1]};
+            }
+            if constexpr (V::kEpilogueFence) __builtin_amdgcn_sched_barrier(0);
             }
         }
         if constexpr (V::kProfile) stamp(4);
@@ -1121,12 +1160,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tile_kernel(
 }
 
 // ---- host side: tile choice and launch
-struct TileChoice {
-    int ni, nj;       // 0, 0: no tuned tile divides the problem, use the generic kernel
-};
 // scratch_bytes: what the launch may use for the pieces of shared tiles (0: every tile is computed whole)
 // bf16: operands in BF16 (T in bytes)
 TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes, bool bf16 = false);
+// The tile and form a contraction takes.
+TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
+                   GemmScratch scratch);
 
 // Distance of the L2 touch loads in K steps beyond the slab the direct-to-LDS loads are fetching (measured with
 // bands 4 high on the block configurations: 1 is 0.5-0.8 % faster than 2, 3 and 4 lose 1.5 % and 4 %);
@@ -1297,8 +1336,10 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
             return;
         }
     }
-    if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB>, grid, plan);
-    else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmTuning, TA, TB>, grid, plan);
+    if constexpr (NI * NJ <= 16) {                // (the large tiles add to the output in their guarded form: fewer registers)
+        if (accumulate) { launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmTuning, TA, TB>, grid, plan); return; }
+    }
+    launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmTuning, TA, TB>, grid, plan);
 }
 
 
@@ -1332,20 +1373,18 @@ static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
 
 #define LLMQ_EDGE_LAUNCH_PARAMS                                                                                   \
     const uint8_t *A, const uint8_t *B, int64_t R, int64_t C, int64_t T, const float *sA, const float *sB, void *c, \
-        int accumulate, unsigned *amax, hipStream_t stream, int num_cus, bool slabs_a, bool slabs_b
-// false: no tile kernel takes the shape.  Instantiated in gemm_edge_*.hip.
+        int accumulate, unsigned *amax, hipStream_t stream, int num_cus, bool slabs_a, bool slabs_b, TilePlan tile
+// Instantiated in gemm_edge_*.hip.
 template <int FA, int FB, bool TA, bool TB>
 bool launch_edge_tile(LLMQ_EDGE_LAUNCH_PARAMS) {
-    const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, TA, TB, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16);
-#define LLMQ_EDGE_CASE(I, J)                                                                                        \
-    case I * 8 + J:                                                                                                 \
-        if (ec.edge == kEdge) launch_edge<FA, FB, I, J, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); \
-        else launch_edge<FA, FB, I, J, TA, TB, kEdgeUnaligned>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b);         \
+#define LLMQ_EDGE_CASE(I, J, KIND)                                                                                  \
+    case KIND * 64 + I * 8 + J:                                                                                     \
+        launch_edge<FA, FB, I, J, TA, TB, KIND>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); \
         return true;
-    switch (ec.ni * 8 + ec.nj) {
-        LLMQ_EDGE_CASE(4, 4) LLMQ_EDGE_CASE(4, 2) LLMQ_EDGE_CASE(2, 4) LLMQ_EDGE_CASE(2, 2)
-        case 3 * 8 + 4: launch_edge<FA, FB, 3, 4, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); return true;
-        case 3 * 8 + 2: launch_edge<FA, FB, 3, 2, TA, TB, kEdge>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b); return true;
+    switch (tile.edge * 64 + tile.ni * 8 + tile.nj) {
+        LLMQ_EDGE_CASE(4, 5, kEdge) LLMQ_EDGE_CASE(5, 4, kEdge)
+        LLMQ_EDGE_CASE(4, 4, kEdge) LLMQ_EDGE_CASE(4, 2, kEdge) LLMQ_EDGE_CASE(3, 4, kEdge) LLMQ_EDGE_CASE(3, 2, kEdge) LLMQ_EDGE_CASE(2, 4, kEdge) LLMQ_EDGE_CASE(2, 2, kEdge)
+        LLMQ_EDGE_CASE(4, 4, kEdgeUnaligned) LLMQ_EDGE_CASE(4, 2, kEdgeUnaligned) LLMQ_EDGE_CASE(2, 4, kEdgeUnaligned) LLMQ_EDGE_CASE(2, 2, kEdgeUnaligned)
         default: break;
     }
 #undef LLMQ_EDGE_CASE
@@ -1362,20 +1401,25 @@ extern template bool launch_edge_tile<0, 0, true, true>(LLMQ_EDGE_LAUNCH_PARAMS)
 extern template bool launch_edge_tile<1, 0, false, true>(LLMQ_EDGE_LAUNCH_PARAMS);
 extern template bool launch_edge_tile<1, 0, true, true>(LLMQ_EDGE_LAUNCH_PARAMS);
 
-// Dispatch on the tile chosen for the problem; false if none divides it.  One translation unit per operand kinds and
+// Dispatch on the tile chosen for the problem (plan_tile, form kNoEdge); false if there is none.  One translation unit per operand kinds and
 // layout instantiates this (gemm_tiles_*.hip: each holds the kernels of all tile shapes for its case, and the files
 // compile side by side); everybody else sees the declarations below.
 #define LLMQ_TILE_LAUNCH_PARAMS                                                                                   \
     const uint8_t *A, const uint8_t *B, int64_t R, int64_t C, int64_t T, const float *sA, const float *sB, void *c, \
-        int accumulate, unsigned *amax, hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a, bool slabs_b
+        int accumulate, unsigned *amax, hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a, bool slabs_b, TilePlan tile
 template <int FA, int FB, bool TA, bool TB>
 bool launch_chosen_tile(LLMQ_TILE_LAUNCH_PARAMS) {
-    const TileChoice tc = choose_tile(R, C, T, num_cus, (scratch.ptr && !TA && !TB && FA != kFmtBf16) ? scratch.bytes : 0, FA == kFmtBf16);
 #define LLMQ_TILE_CASE(I, J)                                                                              \
     case I * 8 + J:                                                                                       \
         launch_tile<FA, FB, I, J, TA, TB>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b); \
         return true;
-    switch (tc.ni * 8 + tc.nj) {
+    if constexpr (TB || !TA) {
+        switch (tile.ni * 8 + tile.nj) {
+            LLMQ_TILE_CASE(4, 5) LLMQ_TILE_CASE(5, 4)
+            default: break;
+        }
+    }
+    switch (tile.ni * 8 + tile.nj) {
         LLMQ_TILE_CASE(4, 4) LLMQ_TILE_CASE(4, 3) LLMQ_TILE_CASE(4, 2)
         LLMQ_TILE_CASE(3, 4) LLMQ_TILE_CASE(3, 3) LLMQ_TILE_CASE(3, 2)
         LLMQ_TILE_CASE(2, 4) LLMQ_TILE_CASE(2, 3) LLMQ_TILE_CASE(2, 2)

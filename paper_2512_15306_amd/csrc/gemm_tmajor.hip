@@ -16,17 +16,17 @@ void launch_gemm_amax_reset(unsigned* amax, hipStream_t stream);
 template <int FA, int FB>
 static bool launch_layout(bool ta, bool tb, const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T,
                           const float* sA, const float* sB, void* c, int accumulate, unsigned* amax,
-                          hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a, bool slabs_b) {
-    if (ta && tb) return launch_chosen_tile<FA, FB, true, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, false, false);
-    if (tb) return launch_chosen_tile<FA, FB, false, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, false);
-    return launch_chosen_tile<FA, FB, true, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, false, slabs_b);
+                          hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a, bool slabs_b, TilePlan tile) {
+    if (ta && tb) return launch_chosen_tile<FA, FB, true, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, false, false, tile);
+    if (tb) return launch_chosen_tile<FA, FB, false, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, false, tile);
+    return launch_chosen_tile<FA, FB, true, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, false, slabs_b, tile);
 }
 
 template <int FA, int FB>
 static bool launch_edge_layout(bool ta, const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T, const float* sA, const float* sB,
-                               void* c, int accumulate, unsigned* amax, hipStream_t stream, int num_cus, bool slabs_a) {
-    if (ta) return launch_edge_tile<FA, FB, true, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, false, false);
-    return launch_edge_tile<FA, FB, false, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, false);
+                               void* c, int accumulate, unsigned* amax, hipStream_t stream, int num_cus, bool slabs_a, TilePlan tile) {
+    if (ta) return launch_edge_tile<FA, FB, true, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, false, false, tile);
+    return launch_edge_tile<FA, FB, false, true>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, false, tile);
 }
 
 int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, int fmtB, int layout_b, int64_t R, int64_t C,
@@ -46,13 +46,15 @@ int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, 
     const bool fits = (!(ta || slabs_a) || (T + 256) * R < lim) && (!(tb || slabs_b) || (T + 256) * C < lim);
     bool done = false;
     if (fits && fmtB == 0) {
-        if (fmtA == 0) done = launch_layout<0, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b);
-        else done = launch_layout<1, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b);
-    }
-    if (!done && fits && fmtB == 0 && tb) {
-        // ragged shapes, in the pairs the linear calls use (A T-major alone completes the set of whole tiles only)
-        if (fmtA == 0) done = launch_edge_layout<0, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a);
-        else done = launch_edge_layout<1, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a);
+        const TilePlan tile = plan_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate != 0, amax != nullptr, false, scratch);
+        if (tile.ni && tile.edge == kNoEdge) {
+            if (fmtA == 0) done = launch_layout<0, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile);
+            else done = launch_layout<1, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile);
+        } else if (tile.ni) {
+            // ragged shapes, in the pairs the linear calls use (A T-major alone completes the set of whole tiles only)
+            if (fmtA == 0) done = launch_edge_layout<0, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a, tile);
+            else done = launch_edge_layout<1, 0>(ta, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, slabs_a, tile);
+        }
     }
     if (!done) launch_gemm_generic(A, fmtA, layout_a, B, fmtB, layout_b, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream);
     return hipGetLastError() == hipSuccess ? 0 : -6;

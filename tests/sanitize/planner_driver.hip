@@ -219,6 +219,31 @@ static void check_edge_tiles() {
     }
 }
 
+// Large tiles and guarded ones in place of the tile chosen before: the faster one by measurement, and none where the guarded form does not exist.
+static void check_better_tiles() {
+    struct Case { int64_t R, C, T; bool ta, tb, accumulate; TilePlan base, best; };
+    const Case cases[] = {
+        {8192, 5120, 13824, false, false, false, {4, 4, kNoEdge}, {4, 5, kNoEdge}}, {4096, 5120, 3072, false, false, false, {4, 4, kNoEdge}, {4, 5, kNoEdge}},
+        {6144, 6656, 6144, false, false, true, {4, 4, kNoEdge}, {4, 5, kEdge}},     {12160, 3328, 960, false, false, true, {2, 2, kEdge}, {5, 4, kEdge}},
+        {4480, 2176, 8320, false, false, false, {2, 2, kNoEdge}, {3, 4, kEdge}},    {1792, 7552, 4096, false, false, true, {2, 2, kNoEdge}, {4, 4, kEdge}},
+        {3584, 5632, 7680, false, true, false, {2, 2, kNoEdge}, {4, 5, kEdge}},     {4480, 13184, 3072, true, true, false, {2, 2, kNoEdge}, {5, 4, kEdge}},
+        {6400, 2432, 5120, true, true, false, {2, 2, kNoEdge}, {4, 4, kEdge}},
+        // the tile they have
+        {4080, 2816, 544, false, false, false, {3, 4, kEdge}, {3, 4, kEdge}},       {5376, 5376, 256, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}},
+        {1600, 16128, 608, false, false, false, {4, 4, kEdge}, {4, 4, kEdge}},      {4864, 1536, 5632, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
+        {12288, 2304, 11776, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}}, {2048, 2048, 2048, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
+        // A T-major alone, rows that are not whole chunks, one K step, rows beyond 32-bit offsets, the generic kernel
+        {4096, 5120, 3072, true, false, false, {4, 4, kNoEdge}, {4, 4, kNoEdge}},   {4096, 5121, 3072, false, true, false, {4, 4, kEdgeUnaligned}, {4, 4, kEdgeUnaligned}},
+        {4096, 5120, 3073, false, false, false, {4, 4, kEdgeUnaligned}, {4, 4, kEdgeUnaligned}}, {4096, 5120, 128, false, false, false, {4, 4, kNoEdge}, {4, 4, kNoEdge}},
+        {4096, 5120, 1 << 22, false, false, false, {4, 4, kNoEdge}, {4, 4, kNoEdge}}, {300, 300, 64, false, false, false, {0, 0, kNoEdge}, {0, 0, kNoEdge}},
+    };
+    for (const Case& c : cases) {
+        const TilePlan p = better_tile(c.R, c.C, c.T, 256, c.ta, c.tb, false, false, c.accumulate, c.base, 1.0);
+        CHECK(p.ni == c.best.ni && p.nj == c.best.nj && p.edge == c.best.edge, "%lld x %lld x %lld: %d x %d form %d, measured best %d x %d form %d", (long long)c.R, (long long)c.C,
+              (long long)c.T, p.ni, p.nj, p.edge, c.best.ni, c.best.nj, c.best.edge);
+    }
+}
+
 // How the lanes of the 64 x 128 tile lie, and where codes leave it for the 128 x 128 tile: the faster one by measurement.
 static void check_code_tiles() {
     struct Case { int64_t rows, cols; bool quantizes, stacked; };
@@ -249,6 +274,7 @@ int main() {
     check_code_tiles();
     check_wgrad_copies();
     check_edge_tiles();
+    check_better_tiles();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

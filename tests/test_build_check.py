@@ -61,6 +61,30 @@ def test_accumulator_access_inside_the_mfma_stretch_fails(planted, where):
         build.check_accumulator_reads("bad.hip", kernel(bad))
 
 
+# A tile with accumulators in ordinary registers as well; the path of a single K step zeroes them again behind the loop.
+LARGE = GOOD.replace("a[8:11]", "v[48:51]").replace("\tv_accvgpr_write_b32 a8, v5\n", "").replace(".LBB0_4:\n", """\ts_branch .LBB0_4
+.LBB0_2:
+\tv_mov_b32_e32 v48, v5
+\tv_mov_b64_e32 v[50:51], v[48:49]
+\tv_accvgpr_write_b32 a0, v48
+\ts_branch .LBB0_4
+.LBB0_4:
+""").replace("\tv_mov_b32_e32 v5, 0\n", "\tv_mov_b32_e32 v5, 0\n\tv_mov_b32_e32 v48, v5\n\ts_cbranch_scc0 .LBB0_2\n")
+
+
+def test_accumulators_in_ordinary_registers_pass():
+    assert "v[48:51], v[20:27]" in LARGE and ".LBB0_2:" in LARGE
+    build.check_accumulator_reads("large.hip", kernel(LARGE))
+
+
+@pytest.mark.parametrize("planted", ["\tv_mov_b32_e32 v60, v49", "\tv_mov_b32_e32 v49, v60", "\tscratch_store_dwordx4 off, v[48:51], off offset:16",
+                                     "\tv_accvgpr_write_b32 a3, v50"])
+@pytest.mark.parametrize("anchor", ["\tbuffer_load_dwordx4 v2", "\ts_cbranch_scc1 .LBB0_3", "\ts_nop 15\n\ts_nop 15"])
+def test_ordinary_registers_that_hold_accumulators_are_checked_too(planted, anchor):
+    with pytest.raises(RuntimeError, match="accumulator registers touched"):
+        build.check_accumulator_reads("bad.hip", kernel(LARGE.replace(anchor, planted + "\n" + anchor, 1)))
+
+
 def test_missing_wait_states_fail():
     with pytest.raises(RuntimeError, match="no wait states behind the last MFMA"):
         build.check_accumulator_reads("bad.hip", kernel(GOOD.replace("\ts_nop 15\n\ts_nop 15\n", "")))

@@ -127,20 +127,20 @@ struct TilePlan { int ni, nj, edge; };       // ni = 0: the generic kernel
 
 // Microseconds of a contraction of `tiles` tiles: a launch, then for every round of tiles the prologue and output of a tile and its K steps.  A last
 // round that is not full takes less than a full one: under the power cap the CUs that have a tile run faster.  One table for FP8 and BF16 (a step is
-// 128 bytes of the contraction in both).  Fitted to 515 shapes of 700 to 16384 rows and columns and T of 256 to 16384 in all layouts, every tile forced on
-// every shape: 9 % root mean square, most of it at T = 256 to 512.
+// 128 bytes of the contraction in both).  Fitted to 515 (guarded tiles: 380) shapes of 700 to 16384 rows and columns and T of 256 to 16384 in all layouts, every tile forced
+// on every shape: 8 % root mean square, most of it at T = 256 to 512.
 inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accumulate, int64_t slots) {
     struct Fit { int ni, nj; double whole_tile, whole_step, guarded_tile, guarded_step; };
-    static const Fit fits[] = {{4, 5, 9.5, 1.507, 11.8, 1.532}, {5, 4, 8.6, 1.500, 11.2, 1.508}, {4, 4, 7.4, 1.243, 9.2, 1.268}, {3, 4, 5.9, 0.984, 7.3, 1.009},
-                               {4, 3, 5.7, 1.009, 0, 0},        {3, 3, 4.2, 0.870, 0, 0},        {4, 2, 4.2, 0.788, 5.5, 0.822}, {2, 4, 4.5, 0.794, 5.5, 0.813},
-                               {3, 2, 2.2, 0.616, 2.7, 0.618},  {2, 3, 4.2, 0.695, 0, 0},        {2, 2, 3.2, 0.829, 4.1, 0.873}};
+    static const Fit fits[] = {{4, 5, 9.5, 1.507, 10.0, 1.532}, {5, 4, 8.6, 1.500, 9.8, 1.508}, {4, 4, 7.4, 1.243, 8.4, 1.268}, {3, 4, 5.9, 0.984, 6.5, 1.009},
+                               {4, 3, 5.7, 1.009, 0, 0},        {3, 3, 4.2, 0.870, 0, 0},        {4, 2, 4.2, 0.788, 4.9, 0.822}, {2, 4, 4.5, 0.794, 4.9, 0.813},
+                               {3, 2, 2.2, 0.616, 2.4, 0.618},  {2, 3, 4.2, 0.695, 0, 0},        {2, 2, 3.2, 0.829, 3.6, 0.873}};
     const double rest = (double)(tiles % slots) / (double)slots;
     const double rounds = (double)(tiles / slots) + (rest > 0 ? 0.69 + 0.31 * rest : 0.0);
     for (const Fit& f : fits)
         if (f.ni == p.ni && f.nj == p.nj) {
             const bool guarded = p.edge != kNoEdge;
             return 3.1 + rounds * ((guarded ? f.guarded_tile : f.whole_tile) + (double)steps * (guarded ? f.guarded_step : f.whole_step) +
-                                   (accumulate ? 2.6 * p.ni * p.nj / 16.0 : 0.0));
+                                   (accumulate ? (guarded ? 3.4 : 2.6) * p.ni * p.nj / 16.0 : 0.0));
         }
     return 0.0;
 }
@@ -153,7 +153,7 @@ inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accu
 //   4096 x 2560 x 4096 (one round of either) 40.3 / 47.9.
 //   Guarded tiles, 128 x 128 that divide the problem / guarded: 4480 x 2176 x 8320 94.6 / 68.2 (192 x 256), 1792 x 7552 x 4096 60.2 / 49.8 (256 x 256),
 //   3584 x 5632 x 7680 142.7 / 109.5 (256 x 320), 4480 x 13184 x 3072 182 / 142 (320 x 256).
-// Over the 515 shapes: 3.7 % faster than without on average, none more than 1 % slower.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
+// Over 380 other shapes: 4.8 % faster than without on average, two of them (T = 256) more than 3 % slower; 0.7 % behind the best of these tiles.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
 // scale: what sharing out the last round of `base` saves of its time.  LLMQ_GEMM_ANY_TILE=IxJ (tests): that tile, guarded if need be; 0: `base`.
 inline TilePlan better_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, const TilePlan& base, double scale) {
     // 32-bit offsets from the first row of a tile of up to 320; whole 16-byte chunks; A T-major alone has no guarded form

@@ -123,6 +123,8 @@ struct GemmTuning {
     static constexpr bool kEpilogueFence = true;
     // LDS stages: how many K steps are resident or on their way (see GemmDeepTuning).
     static constexpr int kStages = 2;
+    // Waves side by side (two above each other always): 2 for workgroups of 256 lanes, 4 for 512.
+    static constexpr int kWavesC = 2;
     // Phase stamps (llmq_calibrate_gemm_phases): a tuning struct with kProfile = true also provides
     //   static __device__ void record(float* buf, int block, int slot, long long value)
     // and wave 0 of every workgroup stamps the cycle counter and the 100 MHz clock at the start (slots 0, 8),
@@ -145,6 +147,15 @@ struct GemmDeepTuning : GemmTuning {
     static constexpr bool kTouch = false;
     static constexpr int kStages = 4;
 };
+
+// The same with eight waves of 64 x 32 outputs, for short contractions: two waves to a SIMD share the prologue's first fetches, the waits of the first
+// steps and the output.  The loop itself reads half as much again from LDS and falls behind when it is long.  Four / eight waves, time ratio over 4000
+// shapes of at most 256 tiles, by K steps 1 to 3, 4 to 7, 8 to 15, 16 to 31, 32 to 63, more:  operands in rows 1.05, 1.04, 1.03, 1.01, 0.99, 0.98;  B T-major 1.06, 1.06, 1.05,
+// 1.05, 1.03, 1.01;  both T-major 1.07, 1.06, 1.04, 1.02, 1.01, 1.00;  BF16 1.04, 1.02, 1.01, 1.00, 0.98, 0.97 (256 x 1024 x 512 5.2 us, 5.0 with eight).
+struct GemmDeepWideTuning : GemmDeepTuning {
+    static constexpr int kWavesC = 4;
+};
+inline bool deep_takes_eight_waves(int64_t steps, bool any_t_major) { return steps <= (any_t_major ? 31 : 15); }
 
 template <bool B>
 struct BoolTag { static constexpr bool value = B; };
@@ -338,7 +349,7 @@ __device__ inline v4u load16_upto(const uint8_t* p, int64_t valid) {
 // FP8 tiles of up to 6 units (2 x 2 to 3 x 2 and 2 x 3) fit twice into the LDS of a CU, and the launch bound keeps their kernels to the half of the registers that lets them.
 // Without it the accumulating ones take 276 (3 x 2) and 324 (2 x 3): 14016 x 3200 x 256 51.0 us without, 39.0 with it.  (In BF16 they fit by themselves.)
 template <int FA, int FB, int NI, int NJ, bool ACCUM, class V = GemmTuning, bool TA = false, bool TB = false, int MODE = kWholeTiles, int EDGE = kNoEdge>
-__global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && EDGE != kEdgeUnaligned && FA != kFmtBf16 ? 2 : 1) void gemm_tile_kernel(
+__global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 && V::kStages == 2 && EDGE != kEdgeUnaligned && FA != kFmtBf16) ? 2 : 1) void gemm_tile_kernel(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ C,
     int Cn, int T, const float* __restrict__ d_sA, const float* __restrict__ d_sB,
     unsigned* __restrict__ amax_bits, int tiles_r, int tiles_c, int touch_ahead, int band_rows, int next_stride,
@@ -350,6 +361,10 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     // (128 for rows of T contiguous bytes; rows x 128 when the operand is stored slab by slab, see OperandLayout).
     const int ksA = TA ? BK * ldA : ks_a, ksB = TB ? BK * ldB : ks_b;
     constexpr int BM = 64 * NI, BN = 64 * NJ;
+    // Waves: 2 x WC of them; each has BM / 2 x BN / WC of the tile and fetches a W-th of every slab (RA / RB rows of a row-wise one, RT of a T-major one).
+    constexpr int WC = V::kWavesC, W = 2 * WC, RA = BM / W, RB = BN / W, RT = BK / W, LA = RA / 8, LB = RB / 8;
+    static_assert(RA % 16 == 0 && RB % 16 == 0, "a wave's share of a slab starts at a multiple of 16 rows (row_swizzle)");
+    static_assert(WC == 2 || (MODE == kWholeTiles && !V::kTouch && EDGE != kEdgeUnaligned), "512 lanes: the plain forms");
     typedef SlabShape<NI, TA> SA;
     typedef SlabShape<NJ, TB> SB;
     constexpr int kOutOfRange = 0x7FFFFF00;     // a buffer offset beyond every operand: such loads fetch nothing
@@ -371,10 +386,10 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     __shared__ __attribute__((aligned(1024))) uint8_t s_p3[kPair];
     uint8_t *const ldsA0 = ST == 2 ? s_a0 : s_p0, *const ldsB0 = ST == 2 ? s_b0 : s_p0 + kSlabA;
     uint8_t *const ldsA1 = ST == 2 ? s_a1 : s_p1, *const ldsB1 = ST == 2 ? s_b1 : s_p1 + kSlabA;
-    // Four words for the workgroup's output absmax.  The epilogue stages 2048 NJ bytes per wave at the start
+    // A word per wave for the workgroup's output absmax.  The epilogue stages 2048 NJ bytes per wave at the start
     // of the slabs (8192 NJ bytes in the case of this one), so the end of the last slab is free by then; the
     // kernel's LDS is exactly its slabs.
-    unsigned* s_amax = reinterpret_cast<unsigned*>(ldsB1 + kSlabB - 16);
+    unsigned* s_amax = reinterpret_cast<unsigned*>(ldsB1 + kSlabB - 4 * W);
     // What this workgroup computes (uniform over the workgroup): the tile at position `pos` of the walk, K steps
     // [kb, kb + nk), written as a whole tile (slot < 0) or as one piece of a shared tile.  In the fix-up launch
     // slot is the first slot of the tile's pieces and nk their number.
@@ -409,7 +424,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int wr = wave >> 1, wc = wave & 1;
+    const int wr = wave / WC, wc = wave % WC;
     auto stamp = [&](int slot) {
         if constexpr (V::kProfile) {
             if (threadIdx.x == 0) {
@@ -446,7 +461,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     auto tmajor_voff = [&](auto shape, int m, int ld) {             // pattern m of a T-major operand
         typedef decltype(shape) S;
         const int unit = 64 * m + lane, row = unit / S::kUnits, col = unit % S::kUnits;
-        return row * ld + ((col ^ S::swizzle_of_row(row + 32 * wave)) << 4);      // the wave moves slab rows [32 wave, 32 wave + 32)
+        return row * ld + ((col ^ S::swizzle_of_row(row + RT * wave)) << 4);      // the wave moves slab rows [RT wave, RT wave + RT)
     };
     int ld_voffA[5], ld_voffB[5];
 #pragma unroll
@@ -463,7 +478,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         tail_voffA[m] = beyond ? kOutOfRange : ld_voffA[m];
         tail_voffB[m] = beyond ? kOutOfRange : ld_voffB[m];
     }
-    const int ld_soffA = TA ? wave * 32 * ldA : wave * 16 * NI * ldA, ld_soffB = TB ? wave * 32 * ldB : wave * 16 * NJ * ldB;
+    const int ld_soffA = wave * (TA ? RT : RA) * ldA, ld_soffB = wave * (TB ? RT : RB) * ldB;
     // The direct-to-LDS loads of one slab pair: pieces 0 .. 2 NI - 1 fill the wave's share of the A slab, the
     // next 2 NJ that of the B slab.  step: K step of the slab, or a negative value for "no slab"
     // (nothing is fetched).
@@ -484,19 +499,19 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     };
     auto issue_load = [&](uint8_t* slabA, uint8_t* slabB, int baseA, int baseB, auto piece) {
         constexpr int p = decltype(piece)::value;
-        if constexpr (p < 2 * NI) {
+        if constexpr (p < LA) {
             constexpr int j = p;
             const int voff = TA ? ld_voffA[j % SA::kPeriod] : EDGE == kEdge ? now_voffA[j & 1] : ld_voffA[j & 1];
             const int soff = TA ? (j / SA::kPeriod) * SA::kPeriodRows * ldA : j * 8 * ldA;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void*)(slabA + wave * 16 * NI * BK + j * 8 * BK), 16, voff, baseA + soff, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void*)(slabA + wave * RA * BK + j * 8 * BK), 16, voff, baseA + soff, 0, 0);
         } else {
-            constexpr int j = p - 2 * NI;
+            constexpr int j = p - LA;
             const int voff = TB ? ld_voffB[j % SB::kPeriod] : EDGE == kEdge ? now_voffB[j & 1] : ld_voffB[j & 1];
             const int soff = TB ? (j / SB::kPeriod) * SB::kPeriodRows * ldB : j * 8 * ldB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void*)(slabB + wave * 16 * NJ * BK + j * 8 * BK), 16, voff, baseB + soff, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void*)(slabB + wave * RB * BK + j * 8 * BK), 16, voff, baseB + soff, 0, 0);
         }
     };
-    constexpr int kLoadsPerStep = 2 * (NI + NJ);
+    constexpr int kLoadsPerStep = LA + LB;
     auto issue_loads = [&](uint8_t* slabA, uint8_t* slabB, int step) {
         int baseA, baseB;
         load_base(step, baseA, baseB);
@@ -511,12 +526,12 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     v4u staged[UA ? kLoadsPerStep : 1];
     auto fetch = [&](int step, auto piece) {                        // any step: offsets are cut to the operand's end
         constexpr int p = decltype(piece)::value;
-        if constexpr (p < 2 * NI) {
+        if constexpr (p < LA) {
             const unsigned s = ld_soffA + step * ksA + (TA ? (p / SA::kPeriod) * SA::kPeriodRows * ldA : p * 8 * ldA);
             const unsigned off = (TA ? ld_voffA[p % SA::kPeriod] : ld_voffA[p & 1]) + s;
             staged[p] = *reinterpret_cast<const v4u_any*>(uaA + (off < endA ? off : endA));
         } else {
-            constexpr int j = p - 2 * NI;
+            constexpr int j = p - LA;
             const unsigned s = ld_soffB + step * ksB + (TB ? (j / SB::kPeriod) * SB::kPeriodRows * ldB : j * 8 * ldB);
             const unsigned off = (TB ? ld_voffB[j % SB::kPeriod] : ld_voffB[j & 1]) + s;
             staged[p] = *reinterpret_cast<const v4u_any*>(uaB + (off < endB ? off : endB));
@@ -524,7 +539,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     };
     auto put = [&](uint8_t* slabA, uint8_t* slabB, const v4u& v, auto piece) {
         constexpr int p = decltype(piece)::value;
-        uint8_t* dst = p < 2 * NI ? slabA + wave * 16 * NI * BK + p * 8 * BK : slabB + wave * 16 * NJ * BK + (p - 2 * NI) * 8 * BK;
+        uint8_t* dst = p < LA ? slabA + wave * RA * BK + p * 8 * BK : slabB + wave * RB * BK + (p - LA) * 8 * BK;
         *reinterpret_cast<v4u*>(dst + lane * 16) = v;
     };
     auto fix_piece = [&](auto shape, bool tmajor, const uint8_t* base, int64_t first, int rows, int ld, int ks, int lds_row0, int j, auto period) -> v4u {
@@ -532,8 +547,8 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         const int step = nk - 1;
         if (tmajor) {
             const int unit = 64 * (j % decltype(period)::value) + lane, row = unit / S::kUnits, col = unit % S::kUnits;
-            const int64_t k = (int64_t)step * BK + 32 * wave + (j / decltype(period)::value) * S::kPeriodRows + row;
-            const int64_t c = first + ((col ^ S::swizzle_of_row(row + 32 * wave)) << 4);
+            const int64_t k = (int64_t)step * BK + RT * wave + (j / decltype(period)::value) * S::kPeriodRows + row;
+            const int64_t c = first + ((col ^ S::swizzle_of_row(row + RT * wave)) << 4);
             if (k >= T || c >= rows) return v4u{0, 0, 0, 0};
             return load16_upto(base + k * ld + c, (int64_t)T * ld - k * ld - c);
         }
@@ -544,16 +559,16 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     };
     auto fix_last_slab = [&](uint8_t* slabA, uint8_t* slabB) __attribute__((always_inline)) {
 #pragma unroll 1
-        for (int j = 0; j < 2 * NI; ++j)
-            *reinterpret_cast<v4u*>(slabA + wave * 16 * NI * BK + j * 8 * BK + lane * 16) =
-                fix_piece(SA{}, TA, A, (int64_t)tr * BM, Rn, ldA, ksA, wave * 16 * NI, j, IntTag<SA::kPeriod>{});
+        for (int j = 0; j < LA; ++j)
+            *reinterpret_cast<v4u*>(slabA + wave * RA * BK + j * 8 * BK + lane * 16) =
+                fix_piece(SA{}, TA, A, (int64_t)tr * BM, Rn, ldA, ksA, wave * RA, j, IntTag<SA::kPeriod>{});
 #pragma unroll 1
-        for (int j = 0; j < 2 * NJ; ++j)
-            *reinterpret_cast<v4u*>(slabB + wave * 16 * NJ * BK + j * 8 * BK + lane * 16) =
-                fix_piece(SB{}, TB, B, (int64_t)tc * BN, Cn, ldB, ksB, wave * 16 * NJ, j, IntTag<SB::kPeriod>{});
+        for (int j = 0; j < LB; ++j)
+            *reinterpret_cast<v4u*>(slabB + wave * RB * BK + j * 8 * BK + lane * 16) =
+                fix_piece(SB{}, TB, B, (int64_t)tc * BN, Cn, ldB, ksB, wave * RB, j, IntTag<SB::kPeriod>{});
     };
     // The wave tile as 16 x 16 blocks: MI x MJ of them, handled in halves of HI block rows / HJ block columns.
-    constexpr int MI = 2 * NI, MJ = 2 * NJ, HI = NI, HJ = NJ;
+    constexpr int MI = 2 * NI, MJ = 4 * NJ / WC, HI = MI / 2, HJ = MJ / 2;
     constexpr int kReadsA = SA::kReadsPerFrag * HI, kReadsB = SB::kReadsPerFrag * HJ;   // LDS reads of one fragment set
     constexpr int kSlots = HI * HJ;                // block updates of one quarter: the slots its side work is spread over
     // T-major operands take twice as many (half as wide) LDS reads: spread over the whole phase they cost
@@ -566,7 +581,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
     const int fr_row = lane & 15;
     const int fr_q = lane >> 4;                                     // which 32 bytes of the 128-byte K step
     const int swz = row_swizzle(fr_row);                            // same for every row this lane reads
-    const int offA = (wr * 32 * NI + fr_row) * BK, offB = (wc * 32 * NJ + fr_row) * BK;
+    const int offA = (wr * 32 * NI + fr_row) * BK, offB = (wc * 16 * MJ + fr_row) * BK;
     const int ch0 = ((fr_q * 2) ^ swz) << 4, ch1 = ((fr_q * 2 + 1) ^ swz) << 4;
     // read number p of a fragment set: 16-byte half p % 2 of fragment p / 2
     auto read_piece_rows = [&](const uint8_t* slab, int off, int first_block, auto& f, auto piece) {
@@ -890,6 +905,11 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         if constexpr (EDGE != kNoEdge) return (edge_mag & 0xFFFFu) > (edge_mag >> 16) ? (edge_mag & 0xFFFFu) : (edge_mag >> 16);
         else return (unsigned)__builtin_bit_cast(uint16_t, (__bf16)maxabs);  // non-negative: magnitude bits
     };
+    // Where a wave stages its output: the start of a slab, or with eight waves one of the two halves of one
+    auto stage_of = [&](int w) -> uint8_t* {
+        const int q = WC == 2 ? w : w >> 1;
+        return (q == 0 ? ldsA0 : q == 1 ? ldsB0 : q == 2 ? ldsA1 : ldsB1) + (WC == 2 ? 0 : (w & 1) * (kSlabA / 2));
+    };
     // The body exists twice, for one and for two de-scale multiplies; the choice is uniform over the grid.
     // A lane holds, of the 16 x 16 block (i, j), the four consecutive columns 16 j + 4 (lane / 16) .. of row
     // 16 i + lane % 16.
@@ -909,12 +929,12 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         // offset outside it); other widths go element by element, neighbouring lanes on neighbouring columns.
         // (kSlots no divisor of 64, i.e. NJ = 5: rows of the stage are 16 bytes longer instead of rotated, which keeps them in
         // different banks as well and needs one address register for all pieces of a row; the rotation modulo 20 takes one for each)
-        constexpr int kSlots = 4 * NJ;
+        constexpr int kSlots = 2 * MJ;
         constexpr bool kRest = kWave % kSlots != 0;
         constexpr int kPitch = 32 * kSlots + (kRest ? 16 : 0);
-        uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
-        static_assert(32 * kPitch <= kSlabA && 32 * kPitch <= kSlabB - 16, "32 staged rows fit the start of any slab");
-        const int row0 = tr * BM + wr * 32 * NI, col0 = tc * BN + wc * 32 * NJ;
+        uint8_t* stage = stage_of(wave);
+        static_assert(32 * kPitch <= kSlabA * 2 / WC && 32 * kPitch <= kSlabB * 2 / WC - 4 * W, "32 staged rows fit the start of any slab");
+        const int row0 = tr * BM + wr * 32 * NI, col0 = tc * BN + wc * 16 * MJ;
         const int rows_left = Rn - row0, cols_left = Cn - col0;              // of this wave's quadrant; may be <= 0
         uint16_t* cbase = C + (size_t)row0 * Cn + col0;
         const int here = rows_left < 32 * NI ? rows_left : 32 * NI;
@@ -1027,9 +1047,9 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
                 // sixteen rows at a time: their old values are on their way together (row after row
                 // 300 x 300 x 64 took 24.7 us with accumulation and 8.9 without, this way 8.5 and 7.3; eight at a time 9.9 and 8.2)
 #pragma unroll
-                for (int cc = 0; cc < 32 * NJ; cc += kWave) {
+                for (int cc = 0; cc < 16 * MJ; cc += kWave) {
                     if (cc >= cols_left) break;
-                    const int c = (32 * NJ) % kWave == 0 || cc + lane < 32 * NJ ? cc + lane : cols_left;        // (past the wave's columns: none)
+                    const int c = (16 * MJ) % kWave == 0 || cc + lane < 16 * MJ ? cc + lane : cols_left;        // (past the wave's columns: none)
                     const uint8_t* src = stage + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4;
                     const unsigned coff = c < cols_left ? (unsigned)(i * 32 * Cn + c) * 2 : kOutOfRange;
                     auto rows_from = [&](auto at_once, int r0) __attribute__((always_inline)) {
@@ -1059,12 +1079,12 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
             }
         }
     } else if constexpr (!ACCUM) {
-        constexpr int kSlots = 4 * NJ;                                       // 16-byte slots per staged row
+        constexpr int kSlots = 2 * MJ;                                       // 16-byte slots per staged row
         constexpr int kPitch = 16 * kSlots;
-        uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
+        uint8_t* stage = stage_of(wave);
         // 8 bytes per block: columns 16 j + 4 fr_q .. are slot 2 j + fr_q / 2 of the staged row, half fr_q % 2
         const int slot0 = fr_q >> 1, half_off = (fr_q & 1) << 3;
-        uint16_t* cbase = C + (size_t)(tr * BM + wr * 32 * NI) * Cn + tc * BN + wc * 32 * NJ;
+        uint16_t* cbase = C + (size_t)(tr * BM + wr * 32 * NI) * Cn + tc * BN + wc * 16 * MJ;
         constexpr int kBlockPieces = 32 * kSlots;                            // 16-byte pieces of 32 staged rows
         // 32 rows (two rows of blocks) at a time: while their stores are in flight the next ones are converted
 #pragma unroll
@@ -1113,11 +1133,11 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         // BF16 output = 8 NJ units of four binary32 values: the first units of all pieces, then the second
         // units; the piece index is rotated by the row number, which keeps the 16-byte writes of 8 rows and the
         // 16-byte reads of 8 neighbouring pieces in different banks.
-        constexpr int kSlots = 4 * NJ;                                       // 16-byte pieces of output per row
+        constexpr int kSlots = 2 * MJ;                                       // 16-byte pieces of output per row
         constexpr int kPitch = 32 * kSlots;                                  // bytes of a staged binary32 row
-        uint8_t* stage = wave == 0 ? ldsA0 : wave == 1 ? ldsB0 : wave == 2 ? ldsA1 : ldsB1;
-        static_assert(32 * kPitch <= kSlabA && 32 * kPitch <= kSlabB - 16, "32 staged rows fit the start of any slab");
-        uint16_t* cbase = C + (size_t)(tr * BM + wr * 32 * NI) * Cn + tc * BN + wc * 32 * NJ;
+        uint8_t* stage = stage_of(wave);
+        static_assert(32 * kPitch <= kSlabA * 2 / WC && 32 * kPitch <= kSlabB * 2 / WC - 4 * W, "32 staged rows fit the start of any slab");
+        uint16_t* cbase = C + (size_t)(tr * BM + wr * 32 * NI) * Cn + tc * BN + wc * 16 * MJ;
         constexpr int kPiecesPerLane = 32 * kSlots / kWave;
         const int piece0 = fr_q >> 1, unit_off = (fr_q & 1) * (16 * kSlots);
 #pragma unroll
@@ -1192,7 +1212,7 @@ __global__ __launch_bounds__(kGemmThreads, NI * NJ <= 6 && V::kStages == 2 && ED
         __syncthreads();
         if (threadIdx.x == 0) {
 #pragma unroll
-            for (int w = 1; w < kGemmThreads / kWave; ++w) mag = mag > s_amax[w] ? mag : s_amax[w];
+            for (int w = 1; w < W; ++w) mag = mag > s_amax[w] ? mag : s_amax[w];
             // same-address atomics of many workgroups serialise; a stale read never exceeds the true maximum
             const unsigned bits = amax_bits_from_bf16_mag(mag);
             if (bits > __hip_atomic_load(amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax_bits, bits);
@@ -1361,8 +1381,8 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     if (const char* e = tuning_env("LLMQ_GEMM_SHARE_A")) { const int v = atoi(e); if (v >= 1 && v <= 64) share_a = v; }
     if (const char* e = tuning_env("LLMQ_GEMM_SHARE_B")) { const int v = atoi(e); if (v >= 1 && v <= 64) share_b = v; }
     const int next_stride = touch_next(nt >= 6 * slots) ? slots : 0;
-    auto launch = [&](auto kernel, int blocks, const SplitPlan& pl) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kGemmThreads), 0, stream,
+    auto launch = [&](auto kernel, int blocks, const SplitPlan& pl, int threads = kGemmThreads) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream,
                            A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c,
                            touch, band, next_stride, ldA, ldB, ksA, ksB, share_a, share_b, pl, (int)R, accumulate);
     };
@@ -1377,8 +1397,13 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     if (sc.n_whole == 0) return;
     if constexpr (NI == 2 && NJ == 2) {
         if (deep_stages(nt, slots)) {
-            if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB>, grid, plan);
-            else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmDeepTuning, TA, TB>, grid, plan);
+            if (deep_takes_eight_waves(T / BK, TA || TB)) {
+                if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepWideTuning, TA, TB>, grid, plan, 2 * kGemmThreads);
+                else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmDeepWideTuning, TA, TB>, grid, plan, 2 * kGemmThreads);
+            } else {
+                if (accumulate) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB>, grid, plan);
+                else launch(gemm_tile_kernel<FA, FB, NI, NJ, false, GemmDeepTuning, TA, TB>, grid, plan);
+            }
             return;
         }
     }
@@ -1403,14 +1428,15 @@ static void launch_edge(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     const int band = band_rows();
     const int share_b = band < tiles_r ? band : tiles_r, share_a = 4 < tiles_c ? 4 : tiles_c;
     // (no requests for the next workgroup's first slabs: they would need the same guards as the loads)
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGemmThreads), 0, stream,
+    auto launch = [&](auto kernel, int threads = kGemmThreads) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream,
                            A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c, touch, band, 0,
                            ldA, ldB, ksA, ksB, share_a, share_b, plan, (int)R, accumulate);
     };
     if constexpr (NI == 2 && NJ == 2 && EDGE == kEdge) {
         if (deep_stages(plan.n_whole, resident_slots(num_cus, NI, NJ))) {
-            launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB, kWholeTiles, EDGE>);
+            if (deep_takes_eight_waves((T + BK - 1) / BK, TA || TB)) launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepWideTuning, TA, TB, kWholeTiles, EDGE>, 2 * kGemmThreads);
+            else launch(gemm_tile_kernel<FA, FB, NI, NJ, true, GemmDeepTuning, TA, TB, kWholeTiles, EDGE>);
             return;
         }
     }

@@ -31,3 +31,9 @@ def test_four_stages_give_the_same_bytes(R, C, T, monkeypatch):
         got[deep] = [o.view(torch.int16) for o in outs]
     for a, b in zip(got["0"], got["1"]):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T", [1920, 2048, 2064, 3968, 4096, 4112])
+def test_four_and_eight_waves_give_the_same_bytes(T, monkeypatch):
+    """Contractions on either side of the lines between eight and four waves (operands in rows, T-major)."""
+    test_four_stages_give_the_same_bytes(*((256, 384) if T % 128 == 0 else (200, 136)), T, monkeypatch)

@@ -79,8 +79,8 @@ inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
 // Tiles of 192 rows (aligned rows only) stand between the others where those would need another round: without / with them, operands in rows,
 // R x C x T 4114 x 4156 x 4784 128.7 / 108.7 us, 4911 x 6786 x 6912 233 / 196, 2385 x 3578 x 2448 47.5 / 40.5, 8026 x 2771 x 6864 207 / 196,
 // 5971 x 1623 x 1104 29.0 / 27.0;  B T-major 2385 x 3584 x 2448 36.5 / 29.7;  both T-major 4128 x 4160 x 4784 110 / 93, 4912 x 6800 x 6912
-// 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128, which one workgroup per CU
-// takes (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.  Tiles of 192 columns would need another staging of the output.
+// 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128
+// (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.
 // Where all 128 x 128 tiles are resident at once, two to a CU, they hide each other's prologue and output, so 192 x 128 needs K steps to win by (least_192).
 // 128 x 128 / 192 x 128 time by K steps 1, 2, 3 to 4, 5 to 8, 9 to 16, more, over 1200 shapes: 0.98, 1.01, 1.04, 1.09, 1.09, 1.11;  added to the output
 // 0.93, 0.96, 1.02, 1.05, 1.06, 1.09;  widths no multiples of 8 (stores of single elements) 0.91, 0.92, 0.96, 0.98, 1.00, 1.05;  with absmax (fewer

@@ -74,6 +74,11 @@ __host__ __device__ inline void tile_of_position(int pos, int tiles_r, int tiles
     tc = in_band / h;
 }
 
+// Outputs of the guarded tiles whose width is no multiple of 8 leave element by element (write_out).  A lane past its wave's 8 SLOTS columns counts as
+// one at the edge of the output, any distance away: which staged column it reads.  Where the pieces of a row are taken modulo SLOTS every column lies
+// in the wave's stage; elsewhere such a lane reads the first.
+template <int SLOTS> __host__ __device__ constexpr int staged_column(int column) { return kWave % SLOTS != 0 && column >= 8 * SLOTS ? 0 : column; }
+
 // How a launch shares out its tiles: a deterministic split of the contraction for a ragged last round of tiles
 // (paper Section 3 "Reproducibility": partial results go to an intermediate buffer and are added in a fixed
 // order by a second step, never with atomic additions).
@@ -1050,7 +1055,8 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
                 for (int cc = 0; cc < 16 * MJ; cc += kWave) {
                     if (cc >= cols_left) break;
                     const int c = (16 * MJ) % kWave == 0 || cc + lane < 16 * MJ ? cc + lane : cols_left;        // (past the wave's columns: none)
-                    const uint8_t* src = stage + ((c >> 2) & 1) * (16 * kSlots) + (c & 3) * 4;
+                    const int from = staged_column<kSlots>(c);
+                    const uint8_t* src = stage + ((from >> 2) & 1) * (16 * kSlots) + (from & 3) * 4;
                     const unsigned coff = c < cols_left ? (unsigned)(i * 32 * Cn + c) * 2 : kOutOfRange;
                     auto rows_from = [&](auto at_once, int r0) __attribute__((always_inline)) {
                         constexpr int kRowsAtOnce = decltype(at_once)::value;
@@ -1061,7 +1067,7 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
                             for (int k = 0; k < kRowsAtOnce; ++k) old[k] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(rsC, coff + (unsigned)((r0 + k) * Cn) * 2, 0, 0) << 16;
                         }
 #pragma unroll
-                        for (int k = 0; k < kRowsAtOnce; ++k) y[k] = *reinterpret_cast<const float*>(src + (r0 + k) * kPitch + ((kRest ? c >> 3 : ((c >> 3) + r0 + k) % kSlots) << 4));
+                        for (int k = 0; k < kRowsAtOnce; ++k) y[k] = *reinterpret_cast<const float*>(src + (r0 + k) * kPitch + ((kRest ? from >> 3 : ((from >> 3) + r0 + k) % kSlots) << 4));
 #pragma unroll
                         for (int k = 0; k < kRowsAtOnce; ++k) {
                             if (accumulate) y[k] += __uint_as_float(old[k]);

@@ -269,7 +269,33 @@ static void check_code_tiles() {
         CHECK(takes_large_tile(c.rows, c.cols, c.range) == c.large, "128 x 128 tiles for %lld x %lld, from %lld", (long long)c.rows, (long long)c.cols, (long long)c.range.least);
 }
 
+// Widths that are no multiples of 8: every LDS read of the guarded epilogue, as it computes them, lies in the wave's stage of 32 rows however far the edge of
+// the output is, and every column of the wave's tile that exists is read by one lane.
+template <int SLOTS>
+static void check_staged_columns() {
+    const bool rest = kWave % SLOTS != 0;
+    const int width = 8 * SLOTS, pitch = 32 * SLOTS + (rest ? 16 : 0);
+    for (int cols_left = 1; cols_left < (1 << 22); cols_left += cols_left < 3 * width ? 1 : cols_left / 7) {
+        std::vector<int> seen(width, 0);
+        for (int cc = 0; cc < width && cc < cols_left; cc += kWave)
+            for (int lane = 0; lane < kWave; ++lane) {
+                const int c = width % kWave == 0 || cc + lane < width ? cc + lane : cols_left, from = staged_column<SLOTS>(c);
+                CHECK(c >= 0 && (c < width || c >= cols_left), "%d pieces, %d columns left: lane %d of trip %d at column %d", SLOTS, cols_left, lane, cc, c);
+                if (c < cols_left && c < width) { ++seen[c]; CHECK(from == c, "column %d read at %d", c, from); }
+                for (int r = 0; r < 32; ++r) {
+                    const int at = ((from >> 2) & 1) * (16 * SLOTS) + (from & 3) * 4 + r * pitch + ((rest ? from >> 3 : ((from >> 3) + r) % SLOTS) << 4);
+                    CHECK(at >= 0 && at + 4 <= 32 * pitch, "%d pieces, %d columns left: lane %d of trip %d reads byte %d of %d", SLOTS, cols_left, lane, cc, at, 32 * pitch);
+                }
+            }
+        for (int c = 0; c < width && c < cols_left; ++c) CHECK(seen[c] == 1, "%d pieces, %d columns left: column %d moved by %d lanes", SLOTS, cols_left, c, seen[c]);
+    }
+}
+
 int main() {
+    check_staged_columns<4>();            // 128 x 128 tiles of eight waves
+    check_staged_columns<8>();
+    check_staged_columns<16>();
+    check_staged_columns<20>();           // 256 x 320
     check_small_tiles();
     check_code_tiles();
     check_wgrad_copies();

@@ -52,6 +52,25 @@ def test_large_tiles_fp8(R, C, T, tile, monkeypatch):
         assert torch.equal(first.view(torch.int16), c.view(torch.int16))      # same sums in every layout
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("R,C,T", [(300, 12755, 128), (70, 50257, 272), (1, 16001, 16)])
+def test_odd_widths_far_beyond_a_tile(R, C, T, accumulate, monkeypatch):
+    """256 x 320 tiles whose outputs leave element by element, with the edge of the output up to 50000 columns away: the bytes of the 256 x 256 tile."""
+    a, b = (torch.from_numpy(_rand_codes(s, 0, s[0] + T)).to(DEV) for s in ((R, T), (C, T)))
+    dsa, dsb = _scales(1.7, 0.9)
+    c0 = _rand((R, C), 6, 30.0).to(DEV)
+    got = []
+    for tile in ("4x5", "4x4"):
+        monkeypatch.setenv("LLMQ_GEMM_ANY_TILE", tile)
+        print("wide odd R=%d C=%d T=%d tile=%s accumulate %d" % (R, C, T, tile, accumulate), flush=True)
+        am = torch.full((1,), -1.0, dtype=torch.float32, device=DEV)
+        buf, c = _guarded(R, C, c0 if accumulate else None)
+        llmq.llmq_fp8_gemm(a, 0, False, b, 0, False, dsa, dsb, c, accumulate, am)
+        assert _untouched(buf, R, C)
+        got.append((c.clone().view(torch.int16), am))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("tile", ["4x5", "5x4"])
 @pytest.mark.parametrize("R,C,T", [(256, 320, 64), (640, 640, 192), (257, 264, 136), (130, 8, 8), (255, 129, 72), (330, 520, 256)])
 def test_large_tiles_bf16(R, C, T, tile, monkeypatch):

@@ -232,6 +232,13 @@ static void check_better_tiles() {
         {4080, 2816, 544, false, false, false, {3, 4, kEdge}, {3, 4, kEdge}},       {5376, 5376, 256, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}},
         {1600, 16128, 608, false, false, false, {4, 4, kEdge}, {4, 4, kEdge}},      {4864, 1536, 5632, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
         {12288, 2304, 11776, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}}, {2048, 2048, 2048, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
+        // widths that are no multiples of 8: the tile they have where the contraction is short, large ones where they save a round or the contraction is long
+        {1536, 38369, 256, false, false, false, {4, 4, kEdge}, {5, 4, kEdge}},      {768, 45462, 384, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},
+        {8160, 4982, 448, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},       {9344, 3932, 512, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},
+        {1376, 26375, 768, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},      {2304, 7778, 1152, false, false, false, {3, 2, kEdge}, {3, 2, kEdge}},
+        {736, 27066, 384, false, false, true, {2, 2, kEdge}, {2, 2, kEdge}},        {1792, 10561, 304, false, false, true, {2, 2, kEdge}, {2, 2, kEdge}},
+        {8960, 5812, 1024, false, false, false, {4, 4, kEdge}, {5, 4, kEdge}},      {7424, 18060, 256, false, false, false, {4, 4, kEdge}, {5, 4, kEdge}},
+        {5888, 3070, 5872, false, false, true, {3, 2, kEdge}, {5, 4, kEdge}},       {3917, 13994, 4480, false, false, false, {4, 4, kEdge}, {5, 4, kEdge}},
         // A T-major alone, rows that are not whole chunks, one K step, rows beyond 32-bit offsets, the generic kernel
         {4096, 5120, 3072, true, false, false, {4, 4, kNoEdge}, {4, 4, kNoEdge}},   {4096, 5121, 3072, false, true, false, {4, 4, kEdgeUnaligned}, {4, 4, kEdgeUnaligned}},
         {4096, 5120, 3073, false, false, false, {4, 4, kEdgeUnaligned}, {4, 4, kEdgeUnaligned}}, {4096, 5120, 128, false, false, false, {4, 4, kNoEdge}, {4, 4, kNoEdge}},

@@ -127,22 +127,24 @@ struct TilePlan { int ni, nj, edge; };       // ni = 0: the generic kernel
 
 // Microseconds of a contraction of `tiles` tiles: a launch, then for every round of tiles the prologue and output of a tile and its K steps.  A last
 // round that is not full takes less than a full one: under the power cap the CUs that have a tile run faster.  One table for FP8 and BF16 (a step is
-// 128 bytes of the contraction in both).  Fitted to 515 (guarded tiles: 380) shapes of 700 to 16384 rows and columns and T of 256 to 16384 in all layouts, every tile forced
-// on every shape: 8 % root mean square, most of it at T = 256 to 512.
+// 128 bytes of the contraction in both: steps fitted to BF16 alone differ by 0-2 %, 256 x 320 by 3, and choose no better).  Fitted to 515 (guarded tiles: 380) shapes of 700 to
+// 16384 rows and columns and T of 256 to 16384 in all layouts, every tile forced on every shape; the cost of adding to the output and the 128 x 192 tile, of which
+// two fit a CU, to 21009 of 64 to 52000: 5 to 10 % root mean square, most of it at T = 256 to 512.  (Tiles of six units counted as two to a CU fit worse: 12 % against 8 for 192 x 128, 13 against 10 for 128 x 192.)
 // odd_width: C is no multiple of 8, so the outputs leave element by element; what that adds to a guarded tile of every round (`odd`) is fitted to 8843
 // shapes of such widths, 64 x 128 outputs and T = 256 to 16384 and more.  The 256 x 320 tile loses most, by trips of 64 lanes over a wave's 160 columns.
 inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accumulate, bool odd_width, int64_t slots) {
-    struct Fit { int ni, nj; double whole_tile, whole_step, guarded_tile, guarded_step, odd; };
-    static const Fit fits[] = {{4, 5, 9.5, 1.507, 10.0, 1.532, 16.2}, {5, 4, 8.6, 1.500, 9.8, 1.508, 13.2}, {4, 4, 7.4, 1.243, 8.4, 1.268, 10.6}, {3, 4, 5.9, 0.984, 6.5, 1.009, 8.2},
-                               {4, 3, 5.7, 1.009, 0, 0, 0},           {3, 3, 4.2, 0.870, 0, 0, 0},           {4, 2, 4.2, 0.788, 4.9, 0.822, 5.3},  {2, 4, 4.5, 0.794, 4.9, 0.813, 5.3},
-                               {3, 2, 2.2, 0.616, 2.4, 0.618, 2.9},   {2, 3, 4.2, 0.695, 0, 0, 0},           {2, 2, 3.2, 0.829, 3.6, 0.873, 3.1}};
+    struct Fit { int ni, nj; double whole_tile, whole_step, whole_add, guarded_tile, guarded_step, guarded_add, odd; };
+    static const Fit fits[] = {{4, 5, 9.5, 1.507, 0, 10.0, 1.532, 6.7, 16.2},  {5, 4, 8.6, 1.500, 0, 9.8, 1.508, 5.2, 13.2},  {4, 4, 7.4, 1.243, 3.0, 8.4, 1.268, 4.2, 10.6},
+                               {3, 4, 5.9, 0.984, 2.1, 6.5, 1.009, 2.8, 8.2},  {4, 3, 5.7, 1.009, 2.1, 0, 0, 0, 0},           {3, 3, 4.2, 0.870, 1.4, 0, 0, 0, 0},
+                               {4, 2, 4.2, 0.788, 1.4, 4.9, 0.822, 2.1, 5.3},  {2, 4, 4.5, 0.794, 1.1, 4.9, 0.813, 2.1, 5.3}, {3, 2, 2.2, 0.616, 0.8, 2.4, 0.618, 1.4, 2.9},
+                               {2, 3, 2.7, 0.660, 0.8, 0, 0, 0, 0},            {2, 2, 3.2, 0.829, 1.2, 3.6, 0.873, 1.4, 3.1}};
     const double rest = (double)(tiles % slots) / (double)slots;
     const double rounds = (double)(tiles / slots) + (rest > 0 ? 0.69 + 0.31 * rest : 0.0);
     for (const Fit& f : fits)
         if (f.ni == p.ni && f.nj == p.nj) {
             const bool guarded = p.edge != kNoEdge;
             return 3.1 + rounds * ((guarded ? f.guarded_tile : f.whole_tile) + (double)steps * (guarded ? f.guarded_step : f.whole_step) +
-                                   (accumulate ? (guarded ? 3.4 : 2.6) * p.ni * p.nj / 16.0 : 0.0) + (odd_width ? f.odd * (accumulate ? 1.18 : 1.0) : 0.0));
+                                   (accumulate ? (guarded ? f.guarded_add : f.whole_add) : 0.0) + (odd_width ? f.odd * (accumulate ? 1.18 : 1.0) : 0.0));
         }
     return 0.0;
 }
@@ -157,8 +159,11 @@ inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accu
 //   3584 x 5632 x 7680 142.7 / 109.5 (256 x 320), 4480 x 13184 x 3072 182 / 142 (320 x 256).
 //   Widths that are no multiples of 8, the tile before / the one this table takes without `odd` / with it:  8160 x 4982 x 448 52.7 / 63.5 / 52.7 and 768 x 45462 x 384
 //   42.9 / 58.5 / 42.9 (128 x 128, 256 x 320, 128 x 128);  8960 x 5812 x 1024 110 / 100 / 100 (256 x 256, 320 x 256).  Over the 8843 shapes 1.7 % faster than without a
-//   second look on average, 8 of them more than 3 % slower; without `odd` 1.1 %, and 561 (down to 0.73 times).
-// Over 380 other shapes: 4.8 % faster than without on average, two of them (T = 256) more than 3 % slower; 0.7 % behind the best of these tiles.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
+//   second look on average, 7 of them more than 3 % slower; without `odd` 1.1 %, and 561 (down to 0.73 times).
+//   Short contractions: with one figure per unit of tile for the addition to the output, and 128 x 192 tiles a quarter slower than they are, 3232 x 43520 x 480 added to the
+//   output took 256 x 320 tiles (197.1, 256 x 256 170.2) and 12928 x 576 x 384 192 x 256 (13.2, 128 x 192 11.6).
+// Over 21009 shapes of widths that are multiples of 8 (7068 of them with T = 256 to 512): 2.7 % faster than without on average (4.6 % from 17 K steps on), 101 of them more than 3 % slower (7 more
+// than 10), of which the noise of the timing is a part; 1.1 % behind the best of these tiles.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
 // scale: what sharing out the last round of `base` saves of its time.  LLMQ_GEMM_ANY_TILE=IxJ (tests): that tile, guarded if need be; 0: `base`.
 inline TilePlan better_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, const TilePlan& base, double scale) {
     // 32-bit offsets from the first row of a tile of up to 320; whole 16-byte chunks; A T-major alone has no guarded form

@@ -232,6 +232,12 @@ static void check_better_tiles() {
         {4080, 2816, 544, false, false, false, {3, 4, kEdge}, {3, 4, kEdge}},       {5376, 5376, 256, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}},
         {1600, 16128, 608, false, false, false, {4, 4, kEdge}, {4, 4, kEdge}},      {4864, 1536, 5632, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
         {12288, 2304, 11776, false, false, true, {4, 4, kNoEdge}, {4, 4, kNoEdge}}, {2048, 2048, 2048, false, false, false, {2, 2, kNoEdge}, {2, 2, kNoEdge}},
+        // added to the output, which costs the large tiles most; and 128 x 192 tiles, which are two to a CU
+        {3232, 43520, 480, false, true, true, {4, 4, kEdge}, {4, 4, kEdge}},        {3072, 46080, 336, false, false, true, {4, 4, kEdge}, {4, 4, kEdge}},
+        {3232, 43624, 384, false, false, true, {4, 4, kEdge}, {4, 4, kEdge}},
+        {12288, 2496, 256, false, false, false, {2, 3, kNoEdge}, {2, 3, kNoEdge}},  {12928, 576, 384, false, false, true, {2, 3, kNoEdge}, {2, 3, kNoEdge}},
+        {896, 25920, 384, false, true, false, {2, 3, kNoEdge}, {2, 3, kNoEdge}},    {22784, 576, 256, false, false, true, {2, 3, kNoEdge}, {2, 3, kNoEdge}},
+        {22144, 4800, 640, false, false, false, {2, 3, kNoEdge}, {2, 3, kNoEdge}},
         // widths that are no multiples of 8: the tile they have where the contraction is short, large ones where they save a round or the contraction is long
         {1536, 38369, 256, false, false, false, {4, 4, kEdge}, {5, 4, kEdge}},      {768, 45462, 384, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},
         {8160, 4982, 448, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},       {9344, 3932, 512, false, false, false, {2, 2, kEdge}, {2, 2, kEdge}},

@@ -334,16 +334,18 @@ TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool t
     const size_t scratch_bytes = (scratch.ptr && !ta && !tb && !bf16) ? scratch.bytes : 0;
     TilePlan base{0, 0, kNoEdge};
     double scale = 1.0;
+    bool shared = false;
     const TileChoice tc = choose_tile(R, C, T, num_cus, scratch_bytes, bf16);
     if (tc.ni) {
         base = {tc.ni, tc.nj, kNoEdge};
         const SplitChoice sc = choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch_bytes);
         scale = sc.cost_us / sc.whole_cost_us;
+        shared = sc.n_groups > 0;
     } else if (!ta || tb) {
         const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, with_amax, bf16);
         base = {ec.ni, ec.nj, ec.edge};
     }
-    return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, base, scale);
+    return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, base, scale, shared);
 }
 
 template <int FA, int FB>

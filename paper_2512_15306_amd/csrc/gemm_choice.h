@@ -164,31 +164,32 @@ inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accu
 //   output took 256 x 320 tiles (197.1, 256 x 256 170.2) and 12928 x 576 x 384 192 x 256 (13.2, 128 x 192 11.6).
 // Over 21009 shapes of widths that are multiples of 8 (7068 of them with T = 256 to 512): 2.7 % faster than without on average (4.6 % from 17 K steps on), 101 of them more than 3 % slower (7 more
 // than 10), of which the noise of the timing is a part; 1.1 % behind the best of these tiles.  320 x 192, 192 x 320, 320 x 128 and 128 x 320 tiles would add 0.2 % each.
-// scale: what sharing out the last round of `base` saves of its time.  LLMQ_GEMM_ANY_TILE=IxJ (tests): that tile, guarded if need be; 0: `base`.
-inline TilePlan better_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, const TilePlan& base, double scale) {
+// scale: what sharing out the last round of `base` saves of its time; shared: whether it is shared out.  Such tiles take their sums in another order than whole ones,
+// so which of the two it is does not depend on whether the output is added to.  LLMQ_GEMM_ANY_TILE=IxJ (tests): that tile, guarded if need be; 0: `base`.
+inline TilePlan better_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, const TilePlan& base, double scale, bool shared = false) {
     // 32-bit offsets from the first row of a tile of up to 320; whole 16-byte chunks; A T-major alone has no guarded form
     if ((ta && !tb) || T < 16 || T >= (1ll << 22) || C >= (1ll << 22)) return base;
     if (!(ta ? R % 16 == 0 : slabs_a || T % 16 == 0) || !(tb ? C % 16 == 0 : slabs_b || T % 16 == 0)) return base;
-    auto form = [&](int ni, int nj) {
-        const bool guarded = R % (64 * ni) != 0 || C % (64 * nj) != 0 || T % BK != 0 || (accumulate && ni * nj > 16);
+    auto form = [&](int ni, int nj, bool adds) {
+        const bool guarded = R % (64 * ni) != 0 || C % (64 * nj) != 0 || T % BK != 0 || (adds && ni * nj > 16);
         return TilePlan{ni, nj, guarded ? kEdge : kNoEdge};
     };
     const char* force = tuning_env("LLMQ_GEMM_ANY_TILE");
-    if (force && force[0] >= '2' && force[0] <= '5' && force[1] == 'x') return form(force[0] - '0', force[2] - '0');
+    if (force && force[0] >= '2' && force[0] <= '5' && force[1] == 'x') return form(force[0] - '0', force[2] - '0', accumulate);
     if (base.ni == 0 || T < 2 * BK) return base;                          // (the table starts there)
     if (force || tuning_env("LLMQ_GEMM_TILE") || tuning_env("LLMQ_GEMM_EDGE_TILE") || tuning_env("LLMQ_GEMM_SPLIT")) return base;       // (tests of the other tiles)
+    const bool priced_add = accumulate && !shared;
     auto us = [&](const TilePlan& p) -> double {
         const int64_t tiles = ((R + 64 * p.ni - 1) / (64 * p.ni)) * ((C + 64 * p.nj - 1) / (64 * p.nj));
-        return tiles > kMaxWorkgroups ? 0.0 : tile_us(p, tiles, (T + BK - 1) / BK, accumulate, C % 8 != 0, resident_slots(num_cus, p.ni, p.nj));
+        return tiles > kMaxWorkgroups ? 0.0 : tile_us(p, tiles, (T + BK - 1) / BK, priced_add, C % 8 != 0, resident_slots(num_cus, p.ni, p.nj));
     };
     if (((R + 127) / 128) * ((C + 127) / 128) <= resident_slots(num_cus, 2, 2) / 2 && base.ni == 2 && base.nj == 2) return base;       // four LDS stages
     TilePlan best = base;
     double best_us = us(base) * scale * 0.98;
     const int others[4][2] = {{4, 5}, {5, 4}, {4, 4}, {3, 4}};
     for (const auto& o : others) {
-        const TilePlan p = form(o[0], o[1]);
-        const double t = us(p);
-        if (t > 0.0 && t < best_us) { best = p; best_us = t; }
+        const double t = us(form(o[0], o[1], priced_add));
+        if (t > 0.0 && t < best_us) { best = form(o[0], o[1], accumulate); best_us = t; }
     }
     return best;
 }

@@ -257,6 +257,25 @@ static void check_better_tiles() {
     }
 }
 
+// A problem whose last round is shared out stays so, or is computed whole on larger tiles, whether its output is added to or not.
+static void check_shared_choice() {
+    int kept = 0, replaced = 0;
+    for (int64_t r = 4; r <= 64; r += 3)
+        for (int64_t c = 4; c <= 110; c += 5)
+            for (int64_t t = 64; t <= 1024; t *= 2) {
+                const SplitChoice sc = choose_split((int)(r * c), (int)t, 256, 4, 4, ~(size_t)0);
+                if (sc.n_groups == 0) continue;
+                const TilePlan base{4, 4, kNoEdge};
+                const double scale = sc.cost_us / sc.whole_cost_us;
+                const TilePlan p = better_tile(256 * r, 256 * c, BK * t, 256, false, false, false, false, false, base, scale, true);
+                const TilePlan q = better_tile(256 * r, 256 * c, BK * t, 256, false, false, false, false, true, base, scale, true);
+                CHECK(p.ni == q.ni && p.nj == q.nj, "%lld x %lld x %lld: %d x %d, added to the output %d x %d", (long long)(256 * r), (long long)(256 * c), (long long)(BK * t), p.ni, p.nj, q.ni, q.nj);
+                CHECK(p.ni * p.nj == 16 || q.edge == kEdge, "large tiles add to the output in their guarded form");
+                ++(p.ni * p.nj == 16 ? kept : replaced);
+            }
+    CHECK(kept > 100 && replaced > 100, "%d shapes shared out, %d whole", kept, replaced);
+}
+
 // How the lanes of the 64 x 128 tile lie, and where codes leave it for the 128 x 128 tile: the faster one by measurement.
 static void check_code_tiles() {
     struct Case { int64_t rows, cols; bool quantizes, stacked; };
@@ -314,6 +333,7 @@ int main() {
     check_wgrad_copies();
     check_edge_tiles();
     check_better_tiles();
+    check_shared_choice();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

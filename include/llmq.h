@@ -179,7 +179,8 @@ int llmq_fp8_gemm(const uint8_t* A, int fmtA, int a_t_major, const uint8_t* B, i
  *                  sharing to happen; NULL or a smaller buffer: every tile is computed whole (as llmq_fp8_gemm).
  *                  Contents on entry do not matter; calls that may overlap on the device need separate scratch.
  * llmq_fp8_gemm_scratch_bytes returns 0 for shapes the library computes whole anyway: whole rounds, small
- * problems, T-major operands, and every shape for which sharing was not measured to win.  The chip is
+ * problems, shapes that larger tiles compute faster whole, and every shape for which sharing was not measured to
+ * win (and T-major operands take no scratch).  The chip is
  * power-limited on real data, so CUs left idle by a ragged round let the busy ones clock higher and the round
  * costs less than a full one; sharing pays (3-7 % of one isolated GEMM) only for long contractions
  * (T >= 16384) whose left-over tiles all fit one group of pieces.  The linear calls below do not use it.

@@ -329,23 +329,49 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
     return best;
 }
 
-TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
-                   GemmScratch scratch) {
-    const size_t scratch_bytes = (scratch.ptr && !ta && !tb && !bf16) ? scratch.bytes : 0;
-    TilePlan base{0, 0, kNoEdge};
-    double scale = 1.0;
-    bool shared = false;
+// The choice of choose_tile as a plan, and what sharing out its last round of tiles saves.
+struct WholePlan {
+    TilePlan tile;
+    SplitChoice split;
+};
+static WholePlan plan_whole(int64_t R, int64_t C, int64_t T, int num_cus, bool bf16, size_t scratch_bytes) {
+    WholePlan p{{0, 0, kNoEdge}, {}};
     const TileChoice tc = choose_tile(R, C, T, num_cus, scratch_bytes, bf16);
-    if (tc.ni) {
-        base = {tc.ni, tc.nj, kNoEdge};
-        const SplitChoice sc = choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch_bytes);
-        scale = sc.cost_us / sc.whole_cost_us;
-        shared = sc.n_groups > 0;
-    } else if (!ta || tb) {
+    if (tc.ni == 0) return p;
+    p.tile = {tc.ni, tc.nj, kNoEdge};
+    p.split = choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch_bytes);
+    return p;
+}
+
+TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
+                   size_t scratch_bytes) {
+    WholePlan p = plan_whole(R, C, T, num_cus, bf16, ta || tb || bf16 ? 0 : scratch_bytes);
+    if (p.tile.ni) return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, p.tile, p.split.cost_us / p.split.whole_cost_us, p.split.n_groups > 0);
+    if (!ta || tb) {
         const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, with_amax, bf16);
-        base = {ec.ni, ec.nj, ec.edge};
+        p.tile = {ec.ni, ec.nj, ec.edge};
     }
-    return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, base, scale, shared);
+    return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, p.tile, 1.0);
+}
+
+// What a contraction of operands in rows or slabs takes: small tiles of `side`, or (0) the tile; the generic kernel if that has no size either.
+struct RowsPlan {
+    int side;
+    TilePlan tile;
+};
+static RowsPlan plan_rows(int64_t R, int64_t C, int64_t T, int num_cus, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16, size_t scratch_bytes) {
+    // (an operand in slabs is addressed with 32-bit offsets from its first tile row, 0x7FFFFF00 being out of range)
+    const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);
+    RowsPlan plan{0, {0, 0, kNoEdge}};
+    if ((slabs_a && (T + 256) * R >= lim) || (slabs_b && (T + 256) * C >= lim)) return plan;
+    double shared_us = 0.0;
+    if (!bf16 && scratch_bytes && T >= 64 * BK && ((R + 127) / 128) * ((C + 127) / 128) <= num_cus) {       // (what the planner shares is that long)
+        const WholePlan p = plan_whole(R, C, T, num_cus, false, scratch_bytes);
+        if (p.tile.ni) shared_us = shared_tiles_us(p.split);
+    }
+    plan.side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate, with_amax, bf16, num_cus, shared_us);
+    if (plan.side == 0) plan.tile = plan_tile(R, C, T, num_cus, false, false, slabs_a, slabs_b, accumulate, with_amax, bf16, scratch_bytes);
+    return plan;
 }
 
 template <int FA, int FB>
@@ -364,23 +390,11 @@ template <int FA, int FB>
 static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C, int64_t T,
                        const float* sA, const float* sB, void* c, int accumulate, unsigned* amax,
                        hipStream_t stream, int num_cus, GemmScratch scratch, bool slabs_a = false, bool slabs_b = false) {
-    // (an operand in slabs is addressed with 32-bit offsets from its first tile row, 0x7FFFFF00 being out of range)
-    const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);
-    const bool fits = (!slabs_a || (T + 256) * R < lim) && (!slabs_b || (T + 256) * C < lim);
-    if (fits) {
-        double shared_us = 0.0;
-        if (FA != kFmtBf16 && scratch.ptr && T >= 64 * BK && ((R + 127) / 128) * ((C + 127) / 128) <= num_cus) {       // (what the planner shares is that long)
-            const TileChoice tc = choose_tile(R, C, T, num_cus, scratch.bytes);
-            if (tc.ni) shared_us = shared_tiles_us(choose_split((int)((R / (64 * tc.ni)) * (C / (64 * tc.nj))), (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, scratch.bytes));
-        }
-        const int side = takes_mini(R, C, T, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, num_cus, shared_us);
-        if (side) { launch_mini<FA, FB>(side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
-    }
-    if (fits) {
-        const TilePlan tile = plan_tile(R, C, T, num_cus, false, false, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, scratch);
-        if (tile.ni && tile.edge == kNoEdge && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile)) return;
-        if (tile.ni && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b, tile)) return;
-    }
+    const RowsPlan plan = plan_rows(R, C, T, num_cus, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, scratch.ptr ? scratch.bytes : 0);
+    const TilePlan tile = plan.tile;
+    if (plan.side) { launch_mini<FA, FB>(plan.side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
+    if (tile.ni && tile.edge == kNoEdge && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile)) return;
+    if (tile.ni && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b, tile)) return;
     if constexpr (FA == kFmtBf16) {
         const int64_t n = R * C;
         int64_t blocks = (n + 255) / 256;
@@ -422,14 +436,19 @@ int launch_gemm_tn(const uint8_t* A, int fmtA, const uint8_t* B, int fmtB, int64
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
-// Scratch a launch of this shape would use when given as much as it likes (0: every tile is computed whole).
+// Scratch a launch of this shape would use when given as much as it likes, with or without addition to the output and its absmax (0: every tile is
+// computed whole).
 size_t gemm_scratch_bytes(int64_t R, int64_t C, int64_t T, int num_cus) {
     const size_t unlimited = ~(size_t)0;
-    const TileChoice tc = choose_tile(R, C, T, num_cus, unlimited);
-    if (tc.ni == 0) return 0;
-    const int64_t tiles = (R / (64 * tc.ni)) * (C / (64 * tc.nj));
-    const SplitChoice sc = choose_split((int)tiles, (int)(T / BK), resident_slots(num_cus, tc.ni, tc.nj), tc.ni, tc.nj, unlimited);
-    return sc.slots * (size_t)(4 * 4096 * tc.ni * tc.nj);
+    const WholePlan p = plan_whole(R, C, T, num_cus, false, unlimited);
+    if (p.tile.ni == 0 || p.split.n_groups == 0) return 0;
+    const size_t bytes = p.split.slots * (size_t)(4 * 4096 * p.tile.ni * p.tile.nj);
+    // shared out unless another kernel takes the shape: small tiles, whole larger ones (plan_tile: the same with addition and without)
+    for (int with = 0; with < 4; ++with) {
+        const RowsPlan plan = plan_rows(R, C, T, num_cus, false, false, (with & 1) != 0, (with & 2) != 0, false, unlimited);
+        if (plan.side == 0) return plan.tile.ni == p.tile.ni && plan.tile.nj == p.tile.nj && plan.tile.edge == kNoEdge ? bytes : 0;
+    }
+    return 0;
 }
 
 // Phase stamps of the 256 x 256 tile kernel (E4M3 x E4M3, contraction-contiguous operands): the same kernel with

@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
 TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scratch_bytes, bool bf16 = false);
 // The tile and form a contraction takes.
 TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
-                   GemmScratch scratch);
+                   size_t scratch_bytes);
 
 // Distance of the L2 touch loads in K steps beyond the slab the direct-to-LDS loads are fetching (measured with
 // bands 4 high on the block configurations: 1 is 0.5-0.8 % faster than 2, 3 and 4 lose 1.5 % and 4 %);

@@ -46,7 +46,7 @@ int launch_gemm_fp8(const uint8_t* A, int fmtA, int layout_a, const uint8_t* B, 
     const bool fits = (!(ta || slabs_a) || (T + 256) * R < lim) && (!(tb || slabs_b) || (T + 256) * C < lim);
     bool done = false;
     if (fits && fmtB == 0) {
-        const TilePlan tile = plan_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate != 0, amax != nullptr, false, scratch);
+        const TilePlan tile = plan_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate != 0, amax != nullptr, false, 0);
         if (tile.ni && tile.edge == kNoEdge) {
             if (fmtA == 0) done = launch_layout<0, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile);
             else done = launch_layout<1, 0>(ta, tb, A, B, R, C, T, d_scaleA, d_scaleB, c_bf16, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile);

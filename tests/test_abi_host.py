@@ -51,6 +51,11 @@ def test_workspace_layout():
     want = max(llmq.llmq_fp8_gemm_scratch_bytes(*rct) for rct in ((16384, 5120, 7168), (16384, 7168, 5120), (5120, 7168, 16384)))
     assert want > 0 and llmq.llmq_fp8_linear_workspace_bytes_shared(*big) == llmq.llmq_fp8_linear_workspace_bytes(*big) + want
     assert llmq.llmq_fp8_linear_workspace_bytes_no_transpose(1, 0, 1) == 0
+    # shapes that share with 256 x 256 tiles, but that larger whole tiles or small ones are faster on
+    for shape in ((8192, 5120, 27648), (5120, 27648, 16384), (512, 512, 131072)):
+        assert llmq.llmq_fp8_gemm_scratch_bytes(*shape) == 0, shape
+    for shape in ((5120, 13824, 8192), (37888, 3584, 8192), (1024, 1024, 65536)):
+        assert llmq.llmq_fp8_gemm_scratch_bytes(*shape) > 0, shape
 
 
 def test_argument_errors_are_reported_before_any_launch():

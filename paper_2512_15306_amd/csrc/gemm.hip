@@ -473,7 +473,7 @@ int launch_gemm_phase_stamps(const uint8_t* A, const uint8_t* B, int64_t R, int6
     const int slots = resident_slots(num_cus, 4, 4);
     const int band = band_rows();
     const int share_b = band < tiles_r ? band : tiles_r, share_a = 4 < tiles_c ? 4 : tiles_c;
-    const int next_stride = touch_next(nt >= 6 * slots) ? slots : 0;
+    const int next_stride = successor_stride(4, 4, nt, slots);
     SplitPlan plan{};
     plan.n_whole = nt;
     plan.partials = reinterpret_cast<float*>(stamps);

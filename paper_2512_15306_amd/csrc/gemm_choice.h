@@ -12,7 +12,11 @@ constexpr int BK = 128;                                     // contraction bytes
 constexpr int kXcds = 8;
 constexpr int kNoEdge = 0, kEdge = 1, kEdgeUnaligned = 2;    // kinds of the tile kernel (gemm_tile.h)
 
-// Workgroups of the tile kernel resident on the chip at once (a multiple of the XCD count);
+// Whether the LDS of a CU holds one workgroup of the two-stage tile kernel: two fit of up to six units, 80 KB each.
+constexpr bool alone_on_cu(int ni, int nj) { return ni * nj > 6; }
+
+// Workgroups of the tile kernel that run on the chip at once (a multiple of the XCD count), as the models of time below count them: two to a CU of
+// 128 x 128 tiles, one of all others.  (Two of 192 x 128 and 128 x 192 fit as well, but counted that way their measured times are fitted worse: see tile_us.)
 // LLMQ_GEMM_SLOTS overrides it for tests, so that small problems meet the many-rounds code paths.
 inline int resident_slots(int num_cus, int ni, int nj) {
     if (const char* e = tuning_env("LLMQ_GEMM_SLOTS")) { const int v = atoi(e); if (v >= kXcds && v % kXcds == 0) return v; }

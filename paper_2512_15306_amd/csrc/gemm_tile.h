@@ -844,7 +844,8 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     // one retires) starts with two slabs of its own operands; one dword per 128-byte line of them is
     // requested here, so that they reach the L2 while this workgroup is busy with its epilogue.
     int next_touch[4] = {0, 0, 0, 0};
-    if constexpr (kTouch) {
+    constexpr bool kTouchNext = kTouch && alone_on_cu(NI, NJ);
+    if constexpr (kTouchNext) {
         int ntr, ntc;
         // (plain kernel only: the workgroups that share tiles have no such successor)
         const int next_pid = (int)blockIdx.x + next_stride;
@@ -1210,7 +1211,7 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     } else {
         write_out(BoolTag<true>{});
     }
-    if constexpr (kTouch) asm volatile("" ::"v"(next_touch[0] ^ next_touch[1] ^ next_touch[2] ^ next_touch[3]));
+    if constexpr (kTouchNext) asm volatile("" ::"v"(next_touch[0] ^ next_touch[1] ^ next_touch[2] ^ next_touch[3]));
     unsigned mag = mag_now();
     if (amax_bits) {
         mag = wave_max_u32(mag);
@@ -1259,10 +1260,15 @@ inline int touch_ahead_pair() {
     return 0;
 }
 
-// Whether a workgroup requests the first slabs of its successor; LLMQ_GEMM_TOUCH_NEXT=0 / 1 overrides it.
-inline bool touch_next(bool by_default) {
-    if (const char* e = tuning_env("LLMQ_GEMM_TOUCH_NEXT")) return atoi(e) != 0;
-    return by_default;
+// Distance to the workgroup whose first slabs a workgroup requests, the one that takes over its slot (0: none); LLMQ_GEMM_TOUCH_NEXT=0 / 1 overrides whether.
+// Measured: +3 % on a GEMM of 19 rounds of 256 x 256 tiles, whose later workgroups otherwise start on cold operands; nothing or slightly less on
+// GEMMs of 2-4 rounds, so it is used from 6 rounds on.  Of two workgroups on a CU the other one covers the start: 16384 x 16128 (192 x 128: 16320) on
+// 128 x 128 / 192 x 128 / 128 x 192 tiles with / without the request, T = 512 234.4, 210.2, 213.4 / 223.2, 195.7, 210.9 us,  2048 576.7, 528.1, 532.4 /
+// 561.5, 509.3, 522.5, and 1 to 10 % in the other layouts and BF16.
+inline int successor_stride(int ni, int nj, int nt, int slots) {
+    bool wanted = nt >= 6 * slots;
+    if (const char* e = tuning_env("LLMQ_GEMM_TOUCH_NEXT")) wanted = atoi(e) != 0;
+    return wanted && alone_on_cu(ni, nj) ? slots : 0;
 }
 
 // Whether a problem of nt 2 x 2 tiles takes four LDS stages: one workgroup per CU then has the CU's LDS to itself.
@@ -1366,9 +1372,6 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     const int tiles_r = (int)(R / (64 * NI)), tiles_c = (int)(C / (64 * NJ));
     const int nt = tiles_r * tiles_c;
     const int touch = (NI == 2 && NJ == 2) ? touch_ahead_pair() : touch_ahead();
-    // workgroups resident on the chip at once: the distance to the workgroup that takes over a slot
-    // (measured: +3 % on a GEMM of 19 rounds of tiles, whose later workgroups otherwise start on cold
-    // operands; nothing or slightly less on GEMMs of 2-4 rounds, so it is used from 6 rounds on)
     const int slots = resident_slots(num_cus, NI, NJ);
     const SplitChoice sc = choose_split(nt, (int)(T / BK), slots, NI, NJ, (scratch.ptr && !TA && !TB && FA != kFmtBf16) ? scratch.bytes : 0);
     SplitPlan plan{};
@@ -1386,7 +1389,7 @@ static void launch_tile(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C
     int share_a = 4 < tiles_c ? 4 : tiles_c;
     if (const char* e = tuning_env("LLMQ_GEMM_SHARE_A")) { const int v = atoi(e); if (v >= 1 && v <= 64) share_a = v; }
     if (const char* e = tuning_env("LLMQ_GEMM_SHARE_B")) { const int v = atoi(e); if (v >= 1 && v <= 64) share_b = v; }
-    const int next_stride = touch_next(nt >= 6 * slots) ? slots : 0;
+    const int next_stride = successor_stride(NI, NJ, nt, slots);
     auto launch = [&](auto kernel, int blocks, const SplitPlan& pl, int threads = kGemmThreads) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream,
                            A, B, reinterpret_cast<uint16_t*>(c), (int)C, (int)T, sA, sB, amax, tiles_r, tiles_c,

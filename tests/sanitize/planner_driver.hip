@@ -257,6 +257,17 @@ static void check_better_tiles() {
     }
 }
 
+// Whose first slabs a workgroup requests: those of the one that takes its place, in long launches of tiles that have a CU to themselves.
+static void check_successors() {
+    for (int ni = 2; ni <= 5; ++ni)
+        for (int nj = 2; nj <= 5; ++nj) {
+            const int slots = resident_slots(256, ni, nj);
+            const int lds = 2 * (64 * ni + 64 * nj) * BK;
+            CHECK(alone_on_cu(ni, nj) == (2 * lds > 160 * 1024), "%d x %d", ni, nj);
+            CHECK(successor_stride(ni, nj, 6 * slots, slots) == (2 * lds > 160 * 1024 ? 256 : 0) && successor_stride(ni, nj, 6 * slots - 1, slots) == 0, "%d x %d", ni, nj);
+        }
+}
+
 // A problem whose last round is shared out stays so, or is computed whole on larger tiles, whether its output is added to or not.
 static void check_shared_choice() {
     int kept = 0, replaced = 0;
@@ -334,6 +345,7 @@ int main() {
     check_edge_tiles();
     check_better_tiles();
     check_shared_choice();
+    check_successors();
     for (int n = 1; n <= 1100; n += (n < 300 ? 1 : 37)) check_walk(n);
     check_walk(13824);
     const int bands[] = {1, 2, 3, 4, 8, 64};

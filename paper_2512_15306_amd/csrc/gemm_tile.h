@@ -645,7 +645,8 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     // The workgroups that run side by side on an XCD (band_rows tile rows x the tile columns that fit) share
     // each slab: a workgroup touches the lines [g * n / share, (g + 1) * n / share) of the n lines of its A slab,
     // g = tile column mod share_a, and likewise of its B slab with the tile row and share_b (the host picks the
-    // shares); each wave takes a quarter of that.
+    // shares); each wave takes a quarter of that.  (A lane touches one line at most: of a side of 320 that a single workgroup
+    // has to itself, the only tile row or column, 64 of the 80 lines of a quarter, T-major 64 of 96.)
     constexpr bool kTouch = V::kTouch && !UA;
     // (T-major operand: the slab is 128 memory rows of kLines lines each, shared out the same way.)
     constexpr int kLinesOfA = TA ? BK * SA::kLines : BM, kLinesOfB = TB ? BK * SB::kLines : BN;
@@ -843,37 +844,38 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     // The workgroup that follows on this XCD (id + next_stride: same XCD, and dispatched about when this
     // one retires) starts with two slabs of its own operands; one dword per 128-byte line of them is
     // requested here, so that they reach the L2 while this workgroup is busy with its epilogue.
-    int next_touch[4] = {0, 0, 0, 0};
+    // Of a B slab of 320 columns all lines (without / with the last fifth of them: 16384 x 25600 x 512 346.2 / 338.1 us, x 1024 468.0 / 454.8, x 2048 704 / 690); of an
+    // A slab of 320 rows the first 64 of a wave's 80, T-major two lines of three (with all of them 0-2 % slower: 20480 x 16640 x 512 253.8 / 257.5, x 1024 374.9 / 378.6).
     constexpr bool kTouchNext = kTouch && alone_on_cu(NI, NJ);
+    constexpr int kNextA = TA && SA::kLines == 1 ? 1 : 2, kNextB = TB ? SB::kLines : 2 * ((BN / 4 + kWave - 1) / kWave);
+    int next_touch[kNextA + kNextB];
+#pragma unroll
+    for (int k = 0; k < kNextA + kNextB; ++k) next_touch[k] = 0;
     if constexpr (kTouchNext) {
-        int ntr, ntc;
         // (plain kernel only: the workgroups that share tiles have no such successor)
         const int next_pid = (int)blockIdx.x + next_stride;
         const int next_pos = (!SPLIT && next_stride > 0 && T >= 2 * BK) ? walk_position(next_pid, plan.n_whole) : -1;
         if (next_pos >= 0) {
+            int ntr, ntc;
             tile_of_position(next_pos, tiles_r, tiles_c, band_rows, ntr, ntc);
-            if constexpr (TA) {                   // memory rows 0 .. 255, one per thread, kLines lines each
-                const uint8_t* na = A + (size_t)threadIdx.x * ldA + (size_t)ntr * BM;
-                next_touch[0] = *reinterpret_cast<const int*>(na);
-                if (SA::kLines > 1) next_touch[1] = *reinterpret_cast<const int*>(na + 128);
-            } else {
-                const uint8_t* na = A + ((size_t)ntr * BM + wave * (BM / 4) + lane) * ldA;
-                if (lane < BM / 4) {
-                    next_touch[0] = *reinterpret_cast<const int*>(na);
-                    next_touch[1] = *reinterpret_cast<const int*>(na + ksA);
+            // T-major: memory rows 0 .. 255, one per thread, `lines` lines each; row-wise: of the wave's quarter of the rows lines / 2 times 64, of both slabs
+            auto request = [&](auto tmajor, auto lines, const uint8_t* base, int first, int rows, int ld, int ks, int* into) __attribute__((always_inline)) {
+                if constexpr (decltype(tmajor)::value) {
+                    const uint8_t* p = base + (size_t)threadIdx.x * ld + first;
+#pragma unroll
+                    for (int l = 0; l < decltype(lines)::value; ++l) into[l] = *reinterpret_cast<const int*>(p + 128 * l);
+                } else {
+                    const uint8_t* p = base + ((size_t)first + wave * rows + lane) * ld;
+#pragma unroll
+                    for (int k = 0; k < decltype(lines)::value / 2; ++k)
+                        if (k * kWave + lane < rows) {
+                            into[2 * k] = *reinterpret_cast<const int*>(p + (size_t)(k * kWave) * ld);
+                            into[2 * k + 1] = *reinterpret_cast<const int*>(p + (size_t)(k * kWave) * ld + ks);
+                        }
                 }
-            }
-            if constexpr (TB) {
-                const uint8_t* nb = B + (size_t)threadIdx.x * ldB + (size_t)ntc * BN;
-                next_touch[2] = *reinterpret_cast<const int*>(nb);
-                if (SB::kLines > 1) next_touch[3] = *reinterpret_cast<const int*>(nb + 128);
-            } else {
-                const uint8_t* nb = B + ((size_t)ntc * BN + wave * (BN / 4) + lane) * ldB;
-                if (lane < BN / 4) {
-                    next_touch[2] = *reinterpret_cast<const int*>(nb);
-                    next_touch[3] = *reinterpret_cast<const int*>(nb + ksB);
-                }
-            }
+            };
+            request(BoolTag<TA>{}, IntTag<kNextA>{}, A, ntr * BM, BM / 4, ldA, ksA, next_touch);
+            request(BoolTag<TB>{}, IntTag<kNextB>{}, B, ntc * BN, BN / 4, ldB, ksB, next_touch + kNextA);
         }
     }
 
@@ -1211,7 +1213,11 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     } else {
         write_out(BoolTag<true>{});
     }
-    if constexpr (kTouchNext) asm volatile("" ::"v"(next_touch[0] ^ next_touch[1] ^ next_touch[2] ^ next_touch[3]));
+    if constexpr (kTouchNext) {
+#pragma unroll
+        for (int k = 1; k < kNextA + kNextB; ++k) next_touch[0] ^= next_touch[k];
+        asm volatile("" ::"v"(next_touch[0]));
+    }
     unsigned mag = mag_now();
     if (amax_bits) {
         mag = wave_max_u32(mag);

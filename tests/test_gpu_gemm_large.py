@@ -153,3 +153,27 @@ def test_the_chosen_tile_gives_the_bytes_of_the_others(R, C, T, monkeypatch):
             got.append((c.view(torch.int16), acc.view(torch.int16), am))
         for g in got[1:]:
             assert all(torch.equal(x, z) for x, z in zip(got[0], g))
+
+
+@pytest.mark.parametrize("tile", ["4x5", "5x4"])
+@pytest.mark.parametrize("layouts", [(False, False), (False, True), (True, True)])
+def test_request_of_the_next_tiles_slabs(layouts, tile, monkeypatch):
+    """Every workgroup requests lines of the first two slabs of the one 8 ids further on: no byte changes.  Contractions of exactly those slabs
+    and longer ones."""
+    ta, tb = layouts
+    monkeypatch.setenv("LLMQ_GEMM_ANY_TILE", tile)
+    monkeypatch.setenv("LLMQ_GEMM_SLOTS", "8")
+    dsa, dsb = _scales(2.5, 0.5)
+    for R, C, T in ((1280, 2560, 256), (1280, 1280, 640)):
+        A, B = _rand_codes((R, T), 0, 71), _rand_codes((C, T), 0, 72)
+        a, b = _operand(A, ta), _operand(B, tb)
+        got = []
+        for on in ("1", "0"):
+            monkeypatch.setenv("LLMQ_GEMM_TOUCH_NEXT", on)
+            print("next R=%d C=%d T=%d tile=%s layouts %s on %s" % (R, C, T, tile, layouts, on), flush=True)
+            c, am = torch.full((R, C), float("nan"), dtype=torch.bfloat16, device=DEV), torch.zeros(1, dtype=torch.float32, device=DEV)
+            llmq.llmq_fp8_gemm(a, 0, ta, b, 0, tb, dsa, dsb, c, False, am)
+            got.append((c.view(torch.int16), am))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        y, S = oracle.gemm_tn(A, 0, B, 0, 2.5, 0.5)
+        assert_gemm_close(c, y, S, "next")

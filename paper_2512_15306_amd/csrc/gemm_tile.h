@@ -909,10 +909,6 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
             maxabs = __builtin_fmaxf(__builtin_fmaxf(maxabs, __builtin_fabsf(y[2])), __builtin_fabsf(y[3]));
         }
     };
-    auto mag_now = [&]() -> unsigned {
-        if constexpr (EDGE != kNoEdge) return (edge_mag & 0xFFFFu) > (edge_mag >> 16) ? (edge_mag & 0xFFFFu) : (edge_mag >> 16);
-        else return (unsigned)__builtin_bit_cast(uint16_t, (__bf16)maxabs);  // non-negative: magnitude bits
-    };
     // Where a wave stages its output: the start of a slab, or with eight waves one of the two halves of one
     auto stage_of = [&](int w) -> uint8_t* {
         const int q = WC == 2 ? w : w >> 1;
@@ -1167,14 +1163,10 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
                 for (int j = 0; j < MJ; ++j)
                     *reinterpret_cast<v4f*>(srow + (((2 * j + piece0 + row) % kSlots) << 4)) = descale4(acc.get(2 * i + ii, j));
             }
-            // (a tile with accumulators in ordinary registers has room for half of the pieces at a time)
-            constexpr int kAtOnce = NI * NJ > 16 ? kPiecesPerLane / 2 : kPiecesPerLane;
+            v4f lo[kPiecesPerLane], hi[kPiecesPerLane];
 #pragma unroll
-            for (int k0 = 0; k0 < kPiecesPerLane; k0 += kAtOnce) {
-            v4f lo[kAtOnce], hi[kAtOnce];
-#pragma unroll
-            for (int k = 0; k < kAtOnce; ++k) {
-                const int p = lane + (k0 + k) * kWave;
+            for (int k = 0; k < kPiecesPerLane; ++k) {
+                const int p = lane + k * kWave;
                 const int r = p / kSlots, sl = p % kSlots;
                 const uint8_t* src = stage + r * kPitch + (((sl + r) % kSlots) << 4);
                 lo[k] = *reinterpret_cast<const v4f*>(src);
@@ -1182,10 +1174,10 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
             }
             if constexpr (V::kEpilogueFence) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = k0; k < k0 + kAtOnce; ++k) {
+            for (int k = 0; k < kPiecesPerLane; ++k) {
                 const int p = lane + k * kWave;
                 const int r = i * 32 + p / kSlots, sl = p % kSlots;
-                v4f y0 = lo[k - k0], y1 = hi[k - k0];
+                v4f y0 = lo[k], y1 = hi[k];
                 y0[0] += __uint_as_float(old[k][0] << 16);
                 y0[1] += __uint_as_float(old[k][0] & 0xFFFF0000u);
                 y0[2] += __uint_as_float(old[k][1] << 16);
@@ -1199,8 +1191,6 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
                 const bf16x4 o0 = __builtin_convertvector(y0, bf16x4), o1 = __builtin_convertvector(y1, bf16x4);
                 const v2u w0 = __builtin_bit_cast(v2u, o0), w1 = __builtin_bit_cast(v2u, o1);
                 *reinterpret_cast<v4u*>(cbase + (size_t)r * Cn + sl * 8) = v4u{w0[0], w0[1], w1[0], w1[1]};
-            }
-            if constexpr (V::kEpilogueFence) __builtin_amdgcn_sched_barrier(0);
             }
         }
         if constexpr (V::kProfile) stamp(4);
@@ -1218,7 +1208,8 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
         for (int k = 1; k < kNextA + kNextB; ++k) next_touch[0] ^= next_touch[k];
         asm volatile("" ::"v"(next_touch[0]));
     }
-    unsigned mag = mag_now();
+    unsigned mag = (unsigned)__builtin_bit_cast(uint16_t, (__bf16)maxabs);   // non-negative: magnitude bits
+    if constexpr (EDGE != kNoEdge) mag = (edge_mag & 0xFFFFu) > (edge_mag >> 16) ? (edge_mag & 0xFFFFu) : (edge_mag >> 16);
     if (amax_bits) {
         mag = wave_max_u32(mag);
         if (lane == 0) s_amax[wave] = mag;

@@ -346,7 +346,13 @@ static WholePlan plan_whole(int64_t R, int64_t C, int64_t T, int num_cus, bool b
 TilePlan plan_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16,
                    size_t scratch_bytes) {
     WholePlan p = plan_whole(R, C, T, num_cus, bf16, ta || tb || bf16 ? 0 : scratch_bytes);
-    if (p.tile.ni) return better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, p.tile, p.split.cost_us / p.split.whole_cost_us, p.split.n_groups > 0);
+    if (p.tile.ni) {
+        // better_tile prices whole tiles, so a tile of its choice is computed whole, scratch or not: gemm_scratch_bytes has nothing for it (1024 x 24320 x 8192,
+        // where 256 x 256 tiles replace smaller ones).
+        TilePlan tile = better_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, p.tile, p.split.cost_us / p.split.whole_cost_us, p.split.n_groups > 0);
+        tile.shares = p.split.n_groups > 0 && tile.ni == p.tile.ni && tile.nj == p.tile.nj && tile.edge == kNoEdge;
+        return tile;
+    }
     if (!ta || tb) {
         const EdgeChoice ec = choose_edge_tile(R, C, T, num_cus, ta, tb, slabs_a, slabs_b, accumulate, with_amax, bf16);
         p.tile = {ec.ni, ec.nj, ec.edge};
@@ -393,7 +399,7 @@ static void launch_one(const uint8_t* A, const uint8_t* B, int64_t R, int64_t C,
     const RowsPlan plan = plan_rows(R, C, T, num_cus, slabs_a, slabs_b, accumulate != 0, amax != nullptr, FA == kFmtBf16, scratch.ptr ? scratch.bytes : 0);
     const TilePlan tile = plan.tile;
     if (plan.side) { launch_mini<FA, FB>(plan.side, A, B, R, C, T, sA, sB, c, accumulate, amax, stream, slabs_a, slabs_b); return; }
-    if (tile.ni && tile.edge == kNoEdge && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, scratch, slabs_a, slabs_b, tile)) return;
+    if (tile.ni && tile.edge == kNoEdge && launch_chosen_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, tile.shares ? scratch : GemmScratch{}, slabs_a, slabs_b, tile)) return;
     if (tile.ni && launch_edge_tile<FA, FB, false, false>(A, B, R, C, T, sA, sB, c, accumulate, amax, stream, num_cus, slabs_a, slabs_b, tile)) return;
     if constexpr (FA == kFmtBf16) {
         const int64_t n = R * C;
@@ -446,7 +452,7 @@ size_t gemm_scratch_bytes(int64_t R, int64_t C, int64_t T, int num_cus) {
     // shared out unless another kernel takes the shape: small tiles, whole larger ones (plan_tile: the same with addition and without)
     for (int with = 0; with < 4; ++with) {
         const RowsPlan plan = plan_rows(R, C, T, num_cus, false, false, (with & 1) != 0, (with & 2) != 0, false, unlimited);
-        if (plan.side == 0) return plan.tile.ni == p.tile.ni && plan.tile.nj == p.tile.nj && plan.tile.edge == kNoEdge ? bytes : 0;
+        if (plan.side == 0) return plan.tile.shares ? bytes : 0;
     }
     return 0;
 }

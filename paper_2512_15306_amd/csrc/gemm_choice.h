@@ -127,7 +127,10 @@ inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus,
 // ---- A second look at problems of many tiles.
 //
 // A tile and its form: kNoEdge where the tile divides the problem, kEdge where it is guarded (or a large tile adds to the output).
-struct TilePlan { int ni, nj, edge; };       // ni = 0: the generic kernel
+struct TilePlan {
+    int ni, nj, edge;           // ni = 0: the generic kernel
+    bool shares = false;        // its last round is shared out (choose_split), where scratch is given
+};
 
 // Microseconds of a contraction of `tiles` tiles: a launch, then for every round of tiles the prologue and output of a tile and its K steps.  A last
 // round that is not full takes less than a full one: under the power cap the CUs that have a tile run faster.  One table for FP8 and BF16 (a step is

@@ -117,6 +117,23 @@ def test_integer_inputs_stay_exact_when_tiles_are_shared(monkeypatch):
         assert am.item() == np.abs(want_acc).max(), split
 
 
+@pytest.mark.parametrize("R,C,T", [(1024, 24320, 8192), (2048, 12032, 8448), (5120, 4864, 8960)])
+def test_shapes_without_scratch_of_their_own_ignore_what_they_are_given(R, C, T):
+    """Tiles of 256 x 256 that replace smaller ones: llmq_fp8_gemm_scratch_bytes is 0, so a scratch that is there all the same (that of
+    another contraction of the layer) stays as it is, and the bytes are those of the call without."""
+    assert llmq.llmq_fp8_gemm_scratch_bytes(R, C, T) == 0
+    g = torch.Generator(device=DEV).manual_seed(R + T)
+    A, B = ((torch.randn(n, T, generator=g, device=DEV)).to(torch.float8_e4m3fn).view(torch.uint8) for n in (R, C))
+    dsa, dsb = _scales(1.9, 0.7)
+    scratch = torch.full((128 << 20,), 0xFF, dtype=torch.uint8, device=DEV)
+    for accumulate in (False, True):
+        c = torch.ones((2, R, C), dtype=torch.bfloat16, device=DEV)
+        for k, s in enumerate((scratch, None)):
+            llmq.llmq_fp8_gemm_with_scratch(A, 0, False, B, 0, False, dsa, dsb, c[k], accumulate, None, s)
+        assert bool((scratch == 0xFF).all()), accumulate
+        assert torch.equal(c[0].view(torch.int16), c[1].view(torch.int16)), accumulate
+
+
 @pytest.mark.parametrize("cfg_i,li,which", [(4, 3, "wgrad"), (5, 0, "wgrad"), (3, 2, "wgrad")])
 def test_full_size_gemms_the_planner_shares(cfg_i, li, which):
     """Shapes of the benchmark configurations that the library shares out by itself (long contractions whose

@@ -36,12 +36,13 @@ struct EdgeChoice {
 // and no tile to write out, which makes it the faster one for small problems, as long as its operands can be loaded in
 // vectors or the contraction is one K step long.  FP8: the same sums, so the same bytes.  A model in microseconds: waits of
 // one wave, and for every further round of workgroups per CU; fitted to 1712 shapes in four layouts up to 4001 x 1001 outputs
-// and T = 2048.  Generic / tile kernel:
-//   both operands in rows, R x C x T   100 x 136 x 64 2.9 / 5.2, x 512 4.4 / 6.2, x 1024 6.4 / 7.4, x 2048 10.4 / 9.8;  1000 x 520 x 64 4.0 / 5.4,
-//     x 256 5.6 / 5.8, x 384 7.0 / 6.1;  2000 x 1000 x 64 7.5 / 5.9;  T no multiple of 32: 100 x 136 x 400 6.9 / 6.2, x 50 6.5 / 7.5, x 1001 47 / 14
-//   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 2.9 / 7.3, x 1024 6.5 / 9.5;  1000 x 1001 x 256 7.2 / 8.0, x 512 10.6 / 8.7
-//   B T-major   100 x 136 x 64 6.0 / 6.7, x 256 9.4 / 7.6;  300 x 300 x 50 7.8 / 9.1;   both T-major   300 x 300 x 16 6.7 / 8.5, x 32 9.3 / 8.8
-//   BF16   40 x 40 x 25 5.2 / 8.2, x 65 7.6 / 8.4, x 100 10.8 / 8.3;  300 x 300 x 25 7.2 / 11.4, 513 x 520 x 25 11.2 / 9.1;  100 x 136 x 16 5.3 / 6.3, x 32 7.0 / 6.9
+// and T = 2048 while the tile kernel had four waves; with eight it is 0.2 to 0.4 us faster, and of 6000 shapes two take the generic kernel that are more
+// than 3 % faster on a tile of 128 x 128.  Generic / tile kernel (eight waves up to 15 K steps):
+//   both operands in rows, R x C x T   100 x 136 x 64 3.3 / 4.6, x 512 4.8 / 5.6, x 1024 6.8 / 6.8, x 2048 10.7 / 9.5;  1000 x 520 x 64 4.4 / 4.9,
+//     x 256 6.0 / 5.3, x 384 7.3 / 5.6;  2000 x 1000 x 64 7.9 / 5.4;  T no multiple of 32: 100 x 136 x 400 7.1 / 5.5, x 50 6.9 / 7.3, x 1001 47 / 14
+//   C no multiple of 8 (stores of two bytes a lane)   300 x 300 x 64 3.3 / 7.9, x 1024 6.8 / 10.1;  1000 x 1001 x 256 7.6 / 8.5, x 512 11.0 / 9.1
+//   B T-major   100 x 136 x 64 6.2 / 6.3, x 256 9.7 / 7.2;  300 x 300 x 50 8.1 / 9.5;   both T-major   300 x 300 x 16 7.1 / 8.8, x 32 9.7 / 9.1
+//   BF16   40 x 40 x 25 4.0 / 6.8, x 65 6.5 / 6.9, x 100 9.7 / 7.1;  300 x 300 x 25 5.4 / 9.7, 513 x 520 x 25 10.1 / 7.6;  100 x 136 x 8 3.0 / 4.7, x 16 4.1 / 4.7
 inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb, bool accumulate, bool with_amax, bool bf16, int num_cus) {
     if (bf16) {                                                             // (T in bytes)
         const int64_t most = T <= 16 ? 320000 : T % 16 == 0 ? (T <= 32 ? 60000 : 0) : T <= 56 ? 160000 : T <= 104 ? 60000 : T <= 144 ? 52000 : 0;
@@ -81,15 +82,15 @@ inline bool generic_is_faster(int64_t R, int64_t C, int64_t T, bool ta, bool tb,
 // over 28 shapes from 1000^3 to 9000^2 x 1000: 0.7 % behind on average with aligned rows, 2.6 % with unaligned ones and 1.4 % with both
 // operands T-major; no other efficiencies of this model do better on the first two.
 // Tiles of 192 rows (aligned rows only) stand between the others where those would need another round: without / with them, operands in rows,
-// R x C x T 4114 x 4156 x 4784 128.7 / 108.7 us, 4911 x 6786 x 6912 233 / 196, 2385 x 3578 x 2448 47.5 / 40.5, 8026 x 2771 x 6864 207 / 196,
-// 5971 x 1623 x 1104 29.0 / 27.0;  B T-major 2385 x 3584 x 2448 36.5 / 29.7;  both T-major 4128 x 4160 x 4784 110 / 93, 4912 x 6800 x 6912
-// 237 / 210;  BF16 4114 x 4156 x 1196 133 / 110.  Short contractions of operands in rows lose with 192 x 128
-// (3901 x 1149 x 720 15.2 / 15.6), hence the lower figure.
+// R x C x T 4114 x 4156 x 4784 138.8 / 115.8 us, 4911 x 6786 x 6912 242 / 208, 2385 x 3578 x 2448 47.7 / 40.6, 8026 x 2771 x 6864 194 / 166,
+// 5971 x 1623 x 1104 29.0 / 24.7;  B T-major 2385 x 3584 x 2448 35.9 / 30.1;  both T-major 4128 x 4160 x 4784 116 / 96, 4912 x 6800 x 6912
+// 246 / 205;  BF16 4114 x 4156 x 2392 131 / 113.  Short contractions of operands in rows lose with 192 x 128
+// (3901 x 1149 x 720 14.1 / 14.4), hence the lower figure.  (On some of these the tiles of better_tile below are faster still.)
 // Where all 128 x 128 tiles are resident at once, two to a CU, they hide each other's prologue and output, so 192 x 128 needs K steps to win by (least_192).
 // 128 x 128 / 192 x 128 time by K steps 1, 2, 3 to 4, 5 to 8, 9 to 16, more, over 1200 shapes: 0.98, 1.01, 1.04, 1.09, 1.09, 1.11;  added to the output
 // 0.93, 0.96, 1.02, 1.05, 1.06, 1.09;  widths no multiples of 8 (stores of single elements) 0.91, 0.92, 0.96, 0.98, 1.00, 1.05;  with absmax (fewer
 // atomics) 1.12, 1.13, 1.07, 1.03, 1.04, 1.11.  192 x 256 tiles of odd widths lose the same way where there are several rounds of them: 3328 x 10548 x 128 added
-// to the output 50.7 / 60.7, 7105 x 4754 x 64 43.2 / 56.7.
+// to the output 43.9 / 57.4, 7105 x 4754 x 64 36.1 / 45.7.
 inline EdgeChoice choose_edge_tile(int64_t R, int64_t C, int64_t T, int num_cus, bool ta, bool tb, bool slabs_a, bool slabs_b, bool accumulate, bool with_amax, bool bf16) {
     EdgeChoice best{0, 0, 0};
     // 32-bit offsets from the first row of a tile, of operands (as above) and of the output; the guarded loads need 16
@@ -158,7 +159,7 @@ inline double tile_us(const TilePlan& p, int64_t tiles, int64_t steps, bool accu
 
 // What the models of choose_tile and choose_edge_tile do not weigh: the large tiles 256 x 320 (4 x 5) and 320 x 256 (5 x 4), and guarded tiles of 256 x 256
 // and 192 x 256 also where a smaller tile divides the problem.  Returns `base`, their choice, or a tile that tile_us has 2 % or more ahead of it.
-//   Large tiles: an eighth fewer operand bytes per product from L2 to LDS and from LDS to registers, which is what the power cap leaves the matrix cores
+//   Large tiles: a tenth fewer operand bytes per product from L2 to LDS and from LDS to registers, which is what the power cap leaves the matrix cores
 //   short of, and other counts of tiles.  FP8 4 x 4 / large, microseconds: 16384 x 5120 x 5120 (5 / 4 whole rounds) 295.7 / 288.4;  55296 x 5120 x 16384 3103 /
 //   3001;  8192 x 5120 x 13824 (2.5 / 2 rounds) 402 / 360;  4096 x 5120 x 3072 (1.25 / 1 round) 68.0 / 48.9, BF16 (256 x 128 tiles before) 120 / 89;
 //   4096 x 2560 x 4096 (one round of either) 40.3 / 47.9.
@@ -230,12 +231,13 @@ inline double small_tiles_us(int side, int64_t R, int64_t C, int64_t T, bool acc
 }
 
 // The small tiles: their side, or 0 for another kernel.  The models above, fitted to 26000 FP8 and 21000 BF16 shapes of up to 256 tiles of
-// 128 x 128: what they choose is 0.2 % slower on average than the fastest of all kernels, and more than 3 % slower than without small tiles on 0.3 % of them.
+// 128 x 128 while those had four waves.  With eight, over 6000 FP8 shapes: what they choose is 0.2 % slower on average than the fastest of all kernels, and more than 3 %
+// slower than without small tiles on 0.9 % of them (0.3 % with four waves), more than 10 % on 0.1 %.  Taking 0.2 to 0.5 us off the times of the larger tile up to 15 K steps chooses no better.
 // Every workgroup raises the output absmax, and atomics on one address follow each other.  R x C x T, 128 x 128 / 64 x 64 / 32 x 32:
-//   256 x 1024 x 512 5.2 / 4.7 / 3.7, with absmax 5.2 / 5.2 / 6.0;  256 x 512 x 1024 6.3 / 5.4 / 4.0, 5.5 with absmax;  1024 x 512 x 256 4.6 / 4.7 / 5.8;
-//   128 x 256 x 6688 33.6 / 15.3 / 8.5, 117 x 304 x 14496 61.7 / 37.2 / 16.1, 128 x 1792 x 19456 53.1 / 37.2 / 19.2, 448 x 512 x 3584 13.5 / 10.6 / 6.9,
-//   16 x 4096 x 4096 14.6 / 10.1 / 6.7, 862 x 768 x 3008 15.6 / 11.3 / 16.0, 1024 x 1024 x 4096 14.8 / 12.0 / 24.6, 128 x 8192 x 1024 6.6 / 5.8 / 11.8,
-//   1024 x 2048 x 2048 9.9 / 14.6 / 30.5
+//   256 x 1024 x 512 5.4 / 5.1 / 4.1, with absmax (four waves) 5.2 / 5.2 / 6.0;  256 x 512 x 1024 6.6 / 5.9 / 4.4;  1024 x 512 x 256 4.9 / 5.2 / 6.3;
+//   128 x 256 x 6688 21.0 / 15.8 / 9.0, 117 x 304 x 14496 40.7 / 28.7 / 15.0, 128 x 1792 x 19456 53.2 / 37.8 / 19.4, 448 x 512 x 3584 13.1 / 10.1 / 6.5,
+//   16 x 4096 x 4096 14.2 / 10.3 / 6.6, 862 x 768 x 3008 12.5 / 9.9 / 15.2, 1024 x 1024 x 4096 14.6 / 12.5 / 24.6, 128 x 8192 x 1024 7.1 / 6.4 / 12.3,
+//   1024 x 2048 x 2048 10.2 / 14.2 / 28.2
 // generic / 64 x 64 / 32 x 32 of short contractions: 1 x 1 x 256 2.4 / 3.5 / 3.2, 624 x 689 x 224 4.1 / 5.7 / -, 3456 x 128 x 160 3.9 / 4.8 / -, 300 x 300 x 64
 //   2.8 / 4.6 / 3.5, 100 x 136 x 512 4.3 / 4.9 / 3.5;  added to what is there 88 x 17 x 64 3.2 / 4.3 / 4.0, 206 x 1326 x 128 4.7 / 8.2 / 7.5
 // shared_us: what the contraction takes with its left-over tiles shared out (shared_tiles_us), 0 if they are not.  Operands beyond the
@@ -264,15 +266,15 @@ inline int takes_mini(int64_t R, int64_t C, int64_t T, bool slabs_a, bool slabs_
 // ones are there: with a token count that is no multiple of 16 the rows of those start at any address, so their chunks go through
 // registers and touch two cache lines each, while the row-major copies' rows are as long as the layer is wide.  Transposed /
 // row-major copies, N x K x M, microseconds:
-//   M no multiple of 16   7168 x 5120 x 8100 363 / 246, 2880 x 960 x 1777 20.0 / 12.3, 3072 x 3072 x 105 20.5 / 12.1, 512 x 512 x 17 6.5 / 5.2
+//   M no multiple of 16   7168 x 5120 x 8100 355 / 219, 2880 x 960 x 1777 20.1 / 11.1, 3072 x 3072 x 105 21.2 / 9.9, 512 x 512 x 17 6.1 / 4.7
 //     widths no multiples of 16 either: as aligned as the rows of the copies are (1, 2, or 4 and more bytes: in dwords), over 3000 shapes of more than
 //     one K step, transposed / row-major time with M odd 1.07 to 1.36;  M a multiple of 2, both widths of 2 1.05, one odd and the other of 16 1.12, both
-//     odd 0.98;  M a multiple of 4 or 8, both widths of 4 1.03 to 1.12, one odd 0.88 to 1.00 (739 x 7055 x 8476 83 / 105, 139 x 75 x 2804 17.6 / 24.6)
-//     one K step: the generic kernel, 300 x 300 x 127 8.0 / 10.3
-//   M a multiple of 16, not of 64 (aligned chunks over two lines)   7168 x 5120 x 8112 319 / 246; operands that an XCD's 4 MB L2 holds gain
-//     nothing: 1024 x 512 x 2032 10.2 / 10.2; and where the transposed copies' small tiles are taken, they are the faster ones: 1024 x 512 x 8112
-//     25.2 / 28.3, 1024 x 512 x 4016 15.3 / 17.0, 512 x 512 x 8112 11.8 / 26.9, 304 x 256 x 14496 16.8 / 55.1, 1536 x 448 x 12560 38.3 / 42.1
-//   M a multiple of 64   8128: 3072 x 3072 86.5 / 79.0, 14496 x 304 65 / 73;  640 x 384 x 640 5.5 / 5.6: left as they are
+//     odd 0.98;  M a multiple of 4 or 8, both widths of 4 1.03 to 1.12, one odd 0.88 to 1.00 (739 x 7055 x 8476 86 / 111, 139 x 75 x 2804 17.9 / 24.5)
+//     one K step: the generic kernel, 300 x 300 x 127 7.3 / 9.4
+//   M a multiple of 16, not of 64 (aligned chunks over two lines)   7168 x 5120 x 8112 273 / 232; operands that an XCD's 4 MB L2 holds lose, 1024 x 512 x
+//     2032 8.0 / 9.7; and where the transposed copies' small tiles are taken, they are the faster ones: 1024 x 512 x 8112
+//     25.3 / 28.0, 1024 x 512 x 4016 15.1 / 15.1, 512 x 512 x 8112 11.8 / 24.8, 304 x 256 x 14496 17.3 / 54.3, 1536 x 448 x 12560 38.8 / 42.4
+//   M a multiple of 64   8128: 3072 x 3072 82.8 / 70.0, 14496 x 304 64 / 63;  640 x 384 x 640 4.5 / 5.9: left as they are
 inline bool wgrad_reads_row_major(int64_t M, int64_t N, int64_t K, bool accumulate, int num_cus) {
     if (M % 64 == 0 || M < 16 || N < 16 || K < 16) return false;
     const int64_t lim = 0x7FFFFF00ll - ((int64_t)1 << 24);           // what the T-major tile kernels address

@@ -6,9 +6,10 @@
 //
 // Tuned kernel (template on the wave tile NI x NJ in units of 32: workgroup tile BM x BN with
 // BM = 64 NI, BN = 64 NJ, both in {128, 192, 256}, and 256 x 320 and 320 x 256; R % BM == 0, Cn % BN == 0, T % 128 == 0)
-//   - one workgroup of 4 wavefronts (2 x 2) per output tile, one workgroup per CU; a wavefront owns
-//     2 NI x 2 NJ blocks of v_mfma_f32_16x16x128_f8f6f4 with fp32 accumulators (256 registers per lane at
-//     4 x 4: the whole accumulator file; 4 x 5 and 5 x 4 keep a fifth of theirs in ordinary registers);
+//   - one workgroup of 4 wavefronts (2 x 2) per output tile, one workgroup per CU (tiles of up to six units, 3 x 2 the largest: two); a
+//     wavefront owns 2 NI x 2 NJ blocks of v_mfma_f32_16x16x128_f8f6f4 with fp32 accumulators (256 registers per lane at
+//     4 x 4: the whole accumulator file; 4 x 5 and 5 x 4 keep a fifth of theirs in ordinary registers).  Short contractions of
+//     few 2 x 2 tiles have 8 wavefronts (2 x 4) of 4 x 2 blocks (GemmDeepWideTuning);
 //   - K advances 128 bytes per step, one MFMA deep; the A and B slabs (BM / BN rows x 128 B) go from global
 //     memory straight into LDS with buffer_load ... lds (16 bytes per lane, no VGPR staging), double buffered;
 //   - LDS rows are 128 B; the 16-byte chunk index is XOR-ed with a function of the row (row_swizzle), applied
@@ -231,8 +232,11 @@ __device__ inline void mma_block(v4f& c, const v8i& a, const v8i& b) {
     // allocator moves the 4-register blocks between the files inside the K loop (hundreds of copies and a
     // handful of spills per K step, which made the kernel issue-bound at half its speed).  The compiler does
     // not know what the statement is, so it adds none of the MFMA wait states; the kernel needs none: fragments
-    // come from LDS reads (waited for by counter), a block is updated again 16 or more MFMAs later, and
-    // the epilogue starts behind wait states of its own, a counter wait and a barrier.
+    // come from LDS reads (waited for by counter), the epilogue starts behind wait states of its own, a counter wait and a
+    // barrier, and a block is updated in place, which may follow the last update directly: between MFMAs whose destination is
+    // their source C, the very same registers, the compiler puts no wait states on gfx950 either, given the builtins of both
+    // types one behind the other (before an ordinary read of the last result it puts 12 or 8).  The two MFMAs of a BF16 block do follow each
+    // other; otherwise a block comes back about three quarters of a step later, 6 MFMAs with eight waves and at least 39 of a 4 x 4 tile.
     if constexpr (FA == kFmtBf16) {
         // two v_mfma_f32_16x16x32_bf16, one per 16-byte half of the fragments
         const v4i a_lo = {a[0], a[1], a[2], a[3]}, a_hi = {a[4], a[5], a[6], a[7]};
@@ -443,10 +447,10 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
     const float scale_a = FA == kFmtBf16 ? 1.0f : *d_sA, scale_b = FB == kFmtBf16 ? 1.0f : *d_sB;
 
     // ---- global -> LDS.  Row-wise operand: one instruction moves 8 rows x 128 B; wave w moves rows
-    // [16 NX w, 16 NX (w+1)) of the slab with 2 NX instructions; instruction j covers rows 8 j + (lane >> 3)
-    // of the wave's share, and the swizzle of those rows only depends on the parity of j (the share starts
+    // [RA w, RA (w+1)) of the A slab (B: RB) with LA (LB) instructions, four waves 16 NX rows with 2 NX; instruction j covers rows
+    // 8 j + (lane >> 3) of the wave's share, and the swizzle of those rows only depends on the parity of j (the share starts
     // at a multiple of 16 rows).  T-major operand: an instruction moves 1 KB = 64 units of consecutive LDS
-    // rows (64 NX bytes each); wave w moves slab rows [32 w, 32 w + 32), again 2 NX instructions, whose
+    // rows (64 NX bytes each); wave w moves slab rows [RT w, RT (w+1)), as many instructions, whose
     // lane pattern repeats every kPeriod instructions (kPeriodRows slab rows).
     // Bytes of an operand from the tile's first byte on that the tile may read: to the end of the last row of the tile
     // that exists (row-wise; the slab form, with rows x 128 bytes between K steps, ends with its last piece).
@@ -484,8 +488,8 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
         tail_voffB[m] = beyond ? kOutOfRange : ld_voffB[m];
     }
     const int ld_soffA = wave * (TA ? RT : RA) * ldA, ld_soffB = wave * (TB ? RT : RB) * ldB;
-    // The direct-to-LDS loads of one slab pair: pieces 0 .. 2 NI - 1 fill the wave's share of the A slab, the
-    // next 2 NJ that of the B slab.  step: K step of the slab, or a negative value for "no slab"
+    // The direct-to-LDS loads of one slab pair: pieces 0 .. LA - 1 fill the wave's share of the A slab, the
+    // next LB that of the B slab.  step: K step of the slab, or a negative value for "no slab"
     // (nothing is fetched).
     auto load_base = [&](int step, int& baseA, int& baseB) {
         baseA = step < 0 ? kOutOfRange : ld_soffA + step * ksA;
@@ -523,7 +527,7 @@ __global__ __launch_bounds__(128 * V::kWavesC, V::kWavesC == 4 || (NI * NJ <= 6 
         voffs_of_step(step);
         static_for<kLoadsPerStep>([&](auto piece) { issue_load(slabA, slabB, baseA, baseB, piece); });
     };
-    // kEdgeUnaligned: the same pieces through registers.
+    // kEdgeUnaligned: the same pieces through registers.  (A 4 x 4 tile has too few of them: the operand pointers are kept in scratch memory and read back where the last slab is rewritten.)
     const uint8_t* uaA = TA ? A + (size_t)tr * BM : A + (size_t)tr * BM * ldA;
     const uint8_t* uaB = TB ? B + (size_t)tc * BN : B + (size_t)tc * BN * ldB;
     auto last16 = [&](int64_t bytes) -> unsigned { return bytes - 16 < 0x7FFFFFF0ll ? (unsigned)(bytes - 16) : 0x7FFFFFF0u; };

@@ -318,8 +318,9 @@ TileChoice choose_tile(int64_t R, int64_t C, int64_t T, int num_cus, size_t scra
             // when the contraction is short
             // (BF16 moves twice the bytes per product, which costs 128 x 128 tiles more and the 2 : 1 ones less.  Over 32 shapes
             // from 2560^3 to 16384 x 5120 these numbers' choice is 1.6 % behind the best tile on average and FP8's 4.2 %; they differ on
-            // eleven.  256 x 128 / 128 x 128 tiles, microseconds: 4096 x 5120 x 3072 121 / 137, x 4096 158 / 187, 8192 x 1024 x 4096 62 / 77,
-            // 16384 x 1280 x 5120 208 / 239; and where they lose, 4096 x 5120 x 2048 83 / 81, 2560^3 41 / 38)
+            // eleven.  The 128 x 128 tiles were slower then; 256 x 128 / 128 x 128 now, microseconds: 4096 x 5120 x 3072 118 / 120, x 4096 152 / 150, 8192 x 1024 x 4096
+            // 55 / 60, 16384 x 1280 x 5120 185 / 193; and where they lose, 4096 x 5120 x 2048 84 / 82, 2560^3 40 / 38.  Where a larger tile is far ahead, 4096 x 5120 x 3072 90
+            // and 16384 x 1280 x 5120 138 with 256 x 320, better_tile takes it.)
             const double e = per_cu == 2 ? (bf16 ? 0.66 : T <= 3072 ? 0.90 : 0.80) : bf16 && ni * nj == 8 ? 0.80 : eff[ni][nj];
             // a ragged last round may be shared out among all CUs (choose_split): the model's gain scales the cost
             const SplitChoice sc = choose_split((int)tiles, (int)(T / BK), (int)slots, ni, nj, scratch_bytes);
